@@ -29,6 +29,14 @@ bool use_tile(const cce_desc *d) { return d->algo != CCE_ALGO_GATHER && tile_eli
 // The forward call forms the hidden-state gradient as well (fuse_dH), where the matrix-core path runs.
 bool fused_dH(const cce_desc *d) { return d->fuse_dH != 0 && use_tile(d); }
 
+// Shared lists and the full catalogue elsewhere (fp32 inputs, other hidden sizes): the dense kernels in fp32 precision,
+// unless the caller asks for the row-gather kernels.
+bool use_dense(const cce_desc *d)
+{
+    if (d->algo != CCE_ALGO_AUTO || d->neg_mode == CCE_NEG_PER_POSITION || use_tile(d)) return false;
+    return ((d->neg_mode == CCE_NEG_FULL) ? d->V : (int64_t)d->K) >= 1;
+}
+
 // Workspace layout of the matrix-core path.  Split factors depend on the descriptor only, so that the size query and
 // the launches agree.
 struct Layout {
@@ -190,7 +198,7 @@ bool use_inverted(const cce_desc *d)
 // per-position negatives too many for the inverted index (their backward pass gathers the rows anyway, for dE).
 bool fused_gather(const cce_desc *d)
 {
-    return d->fuse_dH != 0 && !use_tile(d) && (d->neg_mode != CCE_NEG_PER_POSITION || use_inverted(d));
+    return d->fuse_dH != 0 && !use_tile(d) && !use_dense(d) && (d->neg_mode != CCE_NEG_PER_POSITION || use_inverted(d));
 }
 // ... and what it keeps in the workspace where there is no inverted index: p+ - 1 per position and the rows U.
 struct PlainLayout {
@@ -217,6 +225,128 @@ void set_fused_gather(const cce_desc *d, void *workspace, Params &p)
         p.coef = reinterpret_cast<float *>(ws + L.coef);
         p.U = reinterpret_cast<float *>(ws + L.U);
     }
+}
+
+// Workspace of the dense family.  Every size grows with N, so that a workspace serves smaller batches too.
+struct DenseLayout {
+    size_t idx, coef, ref, inv, part_ms, part_o, U, part_U, total;
+    int64_t ms_rows, u_rows;  // rows of the partial results: splits * N stays below
+};
+DenseLayout make_dense_layout(const cce_desc *d)
+{
+    DenseLayout L{};
+    const size_t N = (size_t)d->N;
+    L.ms_rows = d->N * 128 < 262144 ? d->N * 128 : 262144;
+    L.u_rows = d->N * 64 < 65536 ? d->N * 64 : 65536;
+    size_t off = kHeaderBytes;
+    L.idx = off;     off += align256(N * 4);
+    L.part_ms = off; off += align256((size_t)L.ms_rows * 8);
+    L.part_o = off;  off += align256(N * 4);
+    L.coef = off;    off += align256(N * 4);  // (a forward-only call touches nothing from here on)
+    L.ref = off;     off += align256(N * 4);
+    L.inv = off;     off += align256(N * 4);
+    L.U = off;       off += d->fuse_dH ? align256(N * (size_t)d->d * 4) : 0;
+    L.part_U = off;  off += align256((size_t)L.u_rows * (size_t)d->d * 4);
+    L.total = off;
+    return L;
+}
+// Padded positions are compacted where that saves more than the launch it takes (about 5 us): a small batch is bound by
+// latencies, and a wavefront without a valid row costs it nothing.
+constexpr int64_t kDenseCompactAbove = 4096;
+// The preparation kernel reads the mask 16 bytes at a time.
+bool dense_compacts(const cce_desc *d, const uint8_t *mask)
+{
+    return d->validate_indices || (mask && d->N > kDenseCompactAbove && (reinterpret_cast<uintptr_t>(mask) & 15u) == 0);
+}
+
+// Ways to split the streamed range of `blocks` blocks so that the chip (two blocks per compute unit) is full, with two
+// tiles per share at least and partial results of at most `rows` rows.
+int dense_splits(int64_t blocks, int64_t tiles, int64_t rows, int64_t N)
+{
+    int64_t s = (512 + blocks - 1) / (blocks > 0 ? blocks : 1);
+    if (blocks > 320) s = 1;
+    if (s > tiles / 2) s = tiles / 2;
+    if (N > 0 && s > rows / N) s = rows / N;
+    return s < 1 ? 1 : (int)s;
+}
+
+DenseArgs make_dense_args(const cce_desc *d, const DenseLayout &L, const void *H, const void *E, const int32_t *tgt,
+                          const int32_t *neg, const uint8_t *mask, void *workspace)
+{
+    char *ws = static_cast<char *>(workspace);
+    const bool shared = d->neg_mode == CCE_NEG_SHARED, compact = dense_compacts(d, mask);
+    DenseArgs a{};
+    a.H = H;
+    a.E = E;
+    a.tgt = tgt;
+    a.neg = shared ? neg : nullptr;
+    a.idx = compact ? reinterpret_cast<const int32_t *>(ws + L.idx) : nullptr;
+    a.n_valid_ptr = compact ? static_cast<const int32_t *>(workspace) + kHdrNValid : nullptr;
+    a.mask = compact ? nullptr : mask;
+    a.pos_mask = mask;
+    a.coef = reinterpret_cast<float *>(ws + L.coef);
+    a.ref = reinterpret_cast<float *>(ws + L.ref);
+    a.inv = reinterpret_cast<float *>(ws + L.inv);
+    a.U = d->fuse_dH ? reinterpret_cast<float *>(ws + L.U) : nullptr;
+    a.part_ms = reinterpret_cast<float2 *>(ws + L.part_ms);
+    a.part_o = reinterpret_cast<float *>(ws + L.part_o);
+    a.part_U = reinterpret_cast<float *>(ws + L.part_U);
+    a.N = a.n_rows = d->N;
+    a.V = d->V;
+    a.n_cols = shared ? d->K : d->V;
+    a.d = d->d;
+    a.splits = 1;
+    a.drop_own = (!shared || d->mask_target_collisions) ? 1 : 0;
+    a.validate = d->validate_indices ? 1 : 0;
+    a.dH_bf16 = (d->dH_dtype == CCE_BF16) ? 1 : 0;
+    return a;
+}
+
+hipError_t dense_prep(const cce_desc *d, const DenseLayout &L, const int32_t *tgt, const int32_t *neg, const uint8_t *mask,
+                      float *loss, float *lse, void *workspace, hipStream_t stream)
+{
+    if (!dense_compacts(d, mask)) return hipSuccess;
+    PrepArgs p{};
+    p.tgt = tgt;
+    p.neg = (d->neg_mode == CCE_NEG_SHARED) ? neg : nullptr;
+    p.mask = mask;
+    p.header = static_cast<int32_t *>(workspace);
+    p.idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + L.idx);
+    p.loss = loss;
+    p.lse = lse;
+    p.N = d->N;
+    p.V = d->V;
+    p.d = d->d;
+    p.K = p.neg ? d->K : 0;
+    p.validate = d->validate_indices ? 1 : 0;
+    return launch_prep(p, stream);
+}
+
+// Position side: lse and loss (DENSE_FWD), with the hidden-state gradient (DENSE_FDH), or dH for a given lse (DENSE_DH).
+hipError_t dense_positions(const cce_desc *d, int pass, const DenseLayout &L, DenseArgs a, hipStream_t stream)
+{
+    if (d->N == 0) return hipSuccess;
+    const DenseShape sh = dense_shape(d->in_dtype == CCE_BF16, pass, d->d);
+    a.x_blocks = (d->N + sh.xpb - 1) / sh.xpb;
+    a.splits = dense_splits(a.x_blocks, (a.n_cols + sh.by - 1) / sh.by, pass == DENSE_FWD ? L.ms_rows : (L.u_rows < L.ms_rows ? L.u_rows : L.ms_rows), d->N);
+    return launch_dense(d->in_dtype == CCE_BF16, pass, a, stream);
+}
+
+// Candidate side: dE of the candidates and of the correct items; with U set also dH = grad_loss U.
+hipError_t dense_candidates(const cce_desc *d, DenseArgs a, hipStream_t stream)
+{
+    if (d->N == 0) return hipSuccess;
+    const DenseShape sh = dense_shape(d->in_dtype == CCE_BF16, DENSE_DE, d->d);
+    a.x_blocks = (a.n_cols + sh.xpb - 1) / sh.xpb;
+    const int64_t tiles = (d->N + sh.by - 1) / sh.by;
+    int64_t s = (512 + a.x_blocks - 1) / a.x_blocks;
+    if (s > tiles / 4) s = tiles / 4;
+    a.splits = s < 1 ? 1 : (int)s;
+    a.tile_blocks = a.x_blocks * a.splits;
+    a.scatter_blocks = (d->N + kDenseScatterPairs - 1) / kDenseScatterPairs;
+    const int64_t per = 256 * kDenseScaleTurns;
+    if (a.U || a.pos_mask || a.validate) a.scale_blocks = (d->N * (d->d / 4) + per - 1) / per;
+    return launch_dense(d->in_dtype == CCE_BF16, DENSE_DE, a, stream);
 }
 
 TileArgs make_tile_args(const cce_desc *d, const Layout &L, const void *H, const void *E, const int32_t *tgt,
@@ -278,6 +408,7 @@ PrepArgs make_prep_args(const cce_desc *d, const Layout &L, const int32_t *tgt, 
 // call's).
 size_t forward_scratch_bytes(const cce_desc *d)
 {
+    if (use_dense(d)) return make_dense_layout(d).coef;
     return use_tile(d) ? make_layout(d).part_dH : kHeaderBytes;
 }
 
@@ -285,6 +416,7 @@ size_t forward_scratch_bytes(const cce_desc *d)
 size_t shared_ids_offset(const cce_desc *d)
 {
     if (use_tile(d)) return make_layout(d).total;
+    if (use_dense(d)) return make_dense_layout(d).total;
     if (use_inverted(d)) return make_pp_layout(d).total;
     return fused_gather(d) ? make_plain_layout(d).total : kHeaderBytes;
 }
@@ -326,7 +458,7 @@ std::vector<ProfRecord> g_prof_records;
 std::vector<hipEvent_t> g_prof_pool;
 const char *const kProfNames[PROF_FAMILIES] = {"gather_fwd", "gather_bwd", "prep",  "tile_fwd", "fwd_merge",  "tile_dh",
                                                "dh_merge",   "tile_de",    "index", "item_de",  "pos_scatter", "bwd_pre", "tile_bwd",
-                                               "tile_fdh",   "fdh_merge",  "dh_scale"};
+                                               "tile_fdh",   "fdh_merge",  "dh_scale", "dense_pos", "dense_merge", "dense_de"};
 hipEvent_t prof_event()
 {
     if (!g_prof_pool.empty()) {
@@ -353,6 +485,16 @@ ProfScope::~ProfScope()
 {
     if (slot >= 0) (void)hipEventRecord(g_prof_records[slot].stop, stream);
 }
+
+hipError_t launch_dense_f32(int pass, const DenseArgs &a, hipStream_t stream);
+hipError_t launch_dense_bf16(int pass, const DenseArgs &a, hipStream_t stream);
+DenseShape dense_shape_f32(int pass, int d);
+DenseShape dense_shape_bf16(int pass, int d);
+hipError_t launch_dense(bool bf16, int pass, const DenseArgs &a, hipStream_t stream)
+{
+    return bf16 ? launch_dense_bf16(pass, a, stream) : launch_dense_f32(pass, a, stream);
+}
+DenseShape dense_shape(bool bf16, int pass, int d) { return bf16 ? dense_shape_bf16(pass, d) : dense_shape_f32(pass, d); }
 
 hipError_t launch_fill_zero(int32_t *dst, size_t words, hipStream_t stream)
 {
@@ -453,6 +595,15 @@ cce_status forward_impl(const cce_desc *desc, const Sampler &smp, const void *H,
         a.splits = L.splits_fwd;
         return cce::launch_tile(cce::TILE_PASS_FWD, a, stream) == hipSuccess ? CCE_OK : CCE_ERR_HIP;
     }
+    if (cce::use_dense(desc)) {
+        const cce::DenseLayout L = cce::make_dense_layout(desc);
+        if (cce::dense_prep(desc, L, tgt, neg, mask, loss, lse, workspace, stream) != hipSuccess) return CCE_ERR_HIP;
+        cce::DenseArgs a = cce::make_dense_args(desc, L, H, E, tgt, neg, mask, workspace);
+        a.loss = loss;
+        a.lse = lse;
+        const int pass = desc->fuse_dH ? cce::DENSE_FDH : cce::DENSE_FWD;
+        return cce::dense_positions(desc, pass, L, a, stream) == hipSuccess ? CCE_OK : CCE_ERR_HIP;
+    }
     cce::Params p = cce::make_params(desc, H, E, tgt, neg, mask, workspace);
     p.loss = loss;
     p.lse = lse;
@@ -509,6 +660,26 @@ cce_status backward_impl(const cce_desc *desc, const Sampler &smp, const void *H
             return cce::launch_tile_backward(a, a_de, stream) == hipSuccess ? CCE_OK : CCE_ERR_HIP;
         if (cce::launch_tile(cce::TILE_PASS_DH, a, stream) != hipSuccess) return CCE_ERR_HIP;
         return cce::launch_tile(cce::TILE_PASS_DE, a_de, stream) == hipSuccess ? CCE_OK : CCE_ERR_HIP;
+    }
+    if (cce::use_dense(desc)) {
+        const cce::DenseLayout L = cce::make_dense_layout(desc);
+        if (!desc->reuse_forward_prep &&
+            cce::dense_prep(desc, L, tgt, neg, mask, nullptr, nullptr, workspace, stream) != hipSuccess)
+            return CCE_ERR_HIP;
+        cce::DenseArgs a = cce::make_dense_args(desc, L, H, E, tgt, neg, mask, workspace);
+        a.lse_in = lse;
+        a.g = grad_loss;
+        a.dH = dH;
+        a.dE = dE;
+        if (desc->fuse_dH && desc->reuse_forward_prep) {  // the forward call left U, the coefficients and the references
+            a.g_separate = 1;
+            return cce::dense_candidates(desc, a, stream) == hipSuccess ? CCE_OK : CCE_ERR_HIP;
+        }
+        a.U = nullptr;
+        a.inv = nullptr;
+        if (cce::dense_positions(desc, cce::DENSE_DH, L, a, stream) != hipSuccess) return CCE_ERR_HIP;
+        a.ref = const_cast<float *>(lse);
+        return cce::dense_candidates(desc, a, stream) == hipSuccess ? CCE_OK : CCE_ERR_HIP;
     }
     cce::Params p = cce::make_params(desc, H, E, tgt, neg, mask, workspace);
     p.lse_in = lse;
@@ -629,6 +800,11 @@ cce_status cce_neg_forward_noalloc(const cce_desc *desc, const void *H, const vo
     if (desc->neg_mode != CCE_NEG_FULL && desc->K > 0 && !neg) return CCE_ERR_NULL;
     if (desc->validate_indices) return CCE_ERR_UNSUPPORTED;  // no status word the caller could read afterwards
     if (desc->fuse_dH) return CCE_ERR_UNSUPPORTED;           // the rows it would keep belong in a caller-owned workspace
+    cce_desc by_rows = *desc;
+    if (cce::use_dense(desc) && cce::forward_scratch_bytes(desc) > cce::kStaticScratchBytes) {
+        by_rows.algo = CCE_ALGO_GATHER;  // more positions than the array compacts: the row-gather kernels need a header only
+        desc = &by_rows;
+    }
     if (cce::forward_scratch_bytes(desc) > cce::kStaticScratchBytes) return CCE_ERR_WORKSPACE;
     void *ws = nullptr;
     st = cce::static_scratch(&ws);

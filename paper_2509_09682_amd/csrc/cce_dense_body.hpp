@@ -1,0 +1,765 @@
+// Matrix-core kernels in fp32 precision for shared candidate lists: fp32 inputs of any hidden size, and bf16 inputs of
+// the hidden sizes the bf16-weight tiles (cce_tile_body.hpp) do not serve.
+//
+// The row-gather kernels recompute a dot product per (position, candidate) pair on the vector units and move every
+// candidate row once per position.  With one list for many positions both are contractions; here they run on the matrix
+// cores without giving up a bit of the arithmetic:
+//   scores   bf16 rows: v_mfma_f32_32x32x16_bf16 (products exact, fp32 sums); fp32 rows: v_mfma_f32_16x16x4_f32.
+//   weights  stay fp32.  For the second product with bf16 rows a weight is cut into three bf16 pieces (8 + 8 + 8
+//            significant bits: the cut is exact), which meet the rows in three matrix instructions.  Three instructions
+//            of the bf16 rate are five times as fast as one of the fp32 rate.
+// One kernel template serves both directions, as in the bf16-weight family: a stationary operand X (one row per lane
+// column, in registers), a streamed operand Y (tiles through LDS), S = Y X^T, W = f(S), acc += Y^T W.
+//   position side (DM_FWD / DM_FDH / DM_DH): X = hidden states, Y = candidate rows.
+//   candidate side (DM_DE):                  X = candidate rows, Y = hidden states.
+// The correct item is never a column: a column that holds it is dropped (collision mask; always in full-catalogue mode)
+// and the item enters by its own score, which also is the first reference of the exponentials, so that a sum of
+// weights is at least one and no empty maximum exists.
+//
+// Above a hidden size of 192 (bf16) the accumulators of a whole row do not fit beside the stationary row: DS wavefronts
+// share the rows, each forms all scores and keeps 1/DS of the output columns (one score product more per wavefront
+// against three products of the second kind).
+#pragma once
+#include <type_traits>
+
+#include "cce_device.hpp"
+#include "cce_kernels.hpp"
+
+namespace cce {
+namespace {
+
+typedef __bf16 dbf16x8 __attribute__((ext_vector_type(8)));
+typedef float df32x16 __attribute__((ext_vector_type(16)));
+typedef float df32x4 __attribute__((ext_vector_type(4)));
+typedef short ds16x4 __attribute__((ext_vector_type(4)));
+typedef ds16x4 __attribute__((address_space(3))) *dlds_v4;
+
+enum { DM_FWD = 0, DM_FDH = 1, DM_DH = 2, DM_DE = 3 };
+
+constexpr int kDenseThreads = 256;
+constexpr int kDenseScatter = kDenseScatterPairs;
+constexpr float kRescaleAbove = 20.f;  // a score this far above the reference moves it (weights stay below e^20)
+
+// KD: hidden size rounded up, in units of 32.
+template <typename T, int KD, int MODE>
+struct DenseGeo {
+    static constexpr bool B16 = sizeof(T) == 2;
+    static constexpr int XR = B16 ? 32 : 16;  // stationary rows per wavefront
+    static constexpr int DS = MODE == DM_FWD ? 1 : B16 ? (KD <= 6 ? 1 : (KD <= 12 ? 2 : 4)) : (KD <= 10 ? 1 : 2);
+    static constexpr int NW = kDenseThreads / 64;
+    static constexpr int XPB = NW / DS * XR;  // stationary rows per block
+    static constexpr int BY = B16 ? 32 : (KD <= 8 ? 32 : 16);  // streamed rows per tile
+    static constexpr int CPR = KD * 2 * (int)sizeof(T);        // 16-byte chunks of a padded row
+    // LDS row pitch in chunks.  Odd: the 128-bit operand reads of 16 consecutive rows fall on 16 different chunk slots.
+    // Not 1 or 15 modulo 16 for bf16: the transpose reads (4 rows x 4 chunks at once) then meet at most two to a slot.
+    static constexpr int PITCH = CPR + ((B16 && KD % 4 == 0) ? 3 : 1);
+    static constexpr int BUF = BY * PITCH;  // chunks per tile buffer
+    static constexpr int NX = 2 * KD;       // 16-byte pieces of the stationary row a lane holds
+    static constexpr int OC = B16 ? 32 : 16;           // output columns per accumulator block
+    static constexpr int OB = KD * 32 / OC / DS;       // accumulator blocks per wavefront
+    static constexpr int LPT = (BY * CPR + kDenseThreads - 1) / kDenseThreads;  // staged chunks per thread and tile
+    static constexpr int NST = (B16 && KD >= 10) ? 2 : 1;  // the staging registers are filled and emptied in NST turns
+    static constexpr int LPS = (LPT + NST - 1) / NST;
+    typedef typename std::conditional<B16, df32x16, df32x4>::type acc_t;
+    static constexpr int AQ = B16 ? 4 : 1;  // groups of four consecutive columns in an accumulator block
+    static constexpr int EPI = NW * XR * 33 / 4 + 1;  // chunks of the transpose buffers of the candidate side
+    static constexpr int KEYS = kDenseScatter / 2;    // chunks of the sort keys of a scatter block
+    static constexpr int LDS_TILES = 2 * BUF > EPI ? 2 * BUF : EPI;
+    static constexpr int LDS = LDS_TILES > KEYS ? LDS_TILES : KEYS;
+};
+
+__device__ __forceinline__ dbf16x8 as_b8(uint4 v)
+{
+    dbf16x8 r;
+    __builtin_memcpy(&r, &v, 16);
+    return r;
+}
+
+// Eight fp32 weights as three bf16x8 operands whose sum they are, exactly (up to weights below 2^-110).
+__device__ __forceinline__ void split3(const float *v, uint4 (&pl)[3])
+{
+    uint32_t a[8], b[8], c[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        a[i] = __float_as_uint(v[i]);
+        const float r = v[i] - __uint_as_float(a[i] & 0xffff0000u);
+        b[i] = __float_as_uint(r);
+        c[i] = __float_as_uint(r - __uint_as_float(b[i] & 0xffff0000u));
+    }
+    auto pack = [](const uint32_t (&w)[8]) {  // the upper halves of eight words
+        return make_uint4(__builtin_amdgcn_perm(w[1], w[0], 0x07060302u), __builtin_amdgcn_perm(w[3], w[2], 0x07060302u),
+                          __builtin_amdgcn_perm(w[5], w[4], 0x07060302u), __builtin_amdgcn_perm(w[7], w[6], 0x07060302u));
+    };
+    pl[0] = pack(a);
+    pl[1] = pack(b);
+    pl[2] = pack(c);
+}
+
+__device__ __forceinline__ void widen4(const float *p, float (&v)[4])
+{
+    const float4 a = *reinterpret_cast<const float4 *>(p);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+}
+__device__ __forceinline__ void widen4(const uint16_t *p, float (&v)[4])
+{
+    const uint2 a = *reinterpret_cast<const uint2 *>(p);
+    v[0] = bf16_lo(a.x); v[1] = bf16_hi(a.x); v[2] = bf16_lo(a.y); v[3] = bf16_hi(a.y);
+}
+
+__device__ __forceinline__ void store_dH4(const DenseArgs &a, int64_t row, int col, const float (&v)[4])
+{
+    if (a.dH_bf16)
+        *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(a.dH) + row * a.d + col) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+    else
+        *reinterpret_cast<float4 *>(static_cast<float *>(a.dH) + row * a.d + col) = make_float4(v[0], v[1], v[2], v[3]);
+}
+
+// Positions a launch works on, before compaction and masks: slots [0, n).
+__device__ __forceinline__ int64_t dense_slots(const DenseArgs &a) { return a.n_valid_ptr ? (int64_t)*a.n_valid_ptr : a.N; }
+// Row of a slot; -1 when the position takes no part.
+__device__ __forceinline__ int32_t dense_row(const DenseArgs &a, int64_t x)
+{
+    if (a.order) {
+        const int64_t r = a.order[x];
+        return (r >= 0 && r < a.n_rows) ? (int32_t)r : -1;
+    }
+    if (a.idx) return a.idx[x];
+    return (a.mask && a.mask[x] == 0) ? -1 : (int32_t)x;
+}
+
+// Bucket a block belongs to: largest b with start[b] <= block (start ascends, start[0] = 0, stride of 3 words).
+__device__ __forceinline__ int dense_bucket(const int32_t *start, int n, int32_t block)
+{
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (start[3 * mid] <= block) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// dE of the correct items: as pos_scatter_block, for any hidden size and either type.  A block sorts 256 (target, slot)
+// pairs in LDS, a wavefront walks 64 of them, sums runs of equal targets and adds one row per run: a hot target then
+// costs one same-address atomic (about 25 ns each) per block instead of one per position.
+template <typename T, int CPL>
+__device__ __forceinline__ void dense_scatter_block(const DenseArgs &a, int64_t chunk, uint64_t *keys)
+{
+    constexpr int BATCH = CPL <= 4 ? 16 : 8;  // rows in flight per wavefront
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t n_pos = dense_slots(a), x = chunk * kDenseScatter + tid;
+    if (chunk * kDenseScatter >= n_pos) return;
+    uint64_t key = ~0ull;
+    if (x < n_pos) {
+        const int32_t row = dense_row(a, x);
+        if (row >= 0) key = ((uint64_t)(uint32_t)a.tgt[row] << 32) | (uint32_t)x;
+    }
+    keys[tid] = key;
+    __syncthreads();
+    for (int k = 2; k <= kDenseScatter; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            const int partner = tid ^ j;
+            if (partner > tid) {
+                const uint64_t ka = keys[tid], kb = keys[partner];
+                if ((ka > kb) == ((tid & k) == 0)) {
+                    keys[tid] = kb;
+                    keys[partner] = ka;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    const uint64_t mine = keys[tid];
+    const uint32_t my_id = (uint32_t)(mine >> 32), my_x = (uint32_t)mine;
+    int32_t my_row = 0;
+    float my_cf = 0.f;
+    if (my_id != 0xffffffffu) {
+        my_row = dense_row(a, my_x);
+        my_cf = a.coef[a.by_slot ? (int64_t)my_x : (int64_t)my_row] * ((a.g_separate && a.g) ? a.g[my_row] : 1.f);
+    }
+    float sum[CPL];
+#pragma unroll
+    for (int t = 0; t < CPL; ++t) sum[t] = 0.f;
+    uint32_t cur = 0xffffffffu;
+    auto flush = [&]() {
+        if (cur == 0xffffffffu) return;
+#pragma unroll
+        for (int t = 0; t < CPL; ++t) {
+            if (t * 64 + lane < a.d) unsafeAtomicAdd(a.dE + (int64_t)cur * a.d + t * 64 + lane, sum[t]);
+            sum[t] = 0.f;
+        }
+    };
+    const T *Hp = static_cast<const T *>(a.H);
+    for (int b = 0; b < 64; b += BATCH) {
+        float hv[BATCH][CPL];
+        uint32_t id[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            id[u] = __builtin_amdgcn_readlane(my_id, b + u);
+            const int32_t row = __builtin_amdgcn_readlane(my_row, b + u);
+#pragma unroll
+            for (int t = 0; t < CPL; ++t) {
+                hv[u][t] = 0.f;
+                if (id[u] != 0xffffffffu && t * 64 + lane < a.d) hv[u][t] = load1(Hp + (int64_t)row * a.d + t * 64 + lane);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            if (id[u] != cur) {
+                flush();
+                cur = id[u];
+            }
+            const float cf = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_cf), b + u));
+#pragma unroll
+            for (int t = 0; t < CPL; ++t) sum[t] = fmaf(cf, hv[u][t], sum[t]);
+        }
+    }
+    flush();
+}
+
+// dH = grad_loss * U of valid positions, zero rows for the others; four columns per thread and turn.  Without U (a dH
+// pass of its own went ahead) the zero rows only.
+__device__ __forceinline__ void dense_scale_block(const DenseArgs &a, int64_t block)
+{
+    const int cpr = a.d / 4;
+    const int64_t total = a.N * (int64_t)cpr;
+#pragma unroll
+    for (int j = 0; j < kDenseScaleTurns; ++j) {
+        const int64_t e = (block * kDenseScaleTurns + j) * kDenseThreads + threadIdx.x;
+        if (e >= total) return;
+        const int64_t i = e / cpr;
+        const int col = (int)(e % cpr) * 4;
+        bool valid = a.pos_mask == nullptr || a.pos_mask[i] != 0;
+        if (valid && a.validate) valid = a.tgt[i] >= 0 && (int64_t)a.tgt[i] < a.V;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        if (valid) {
+            if (!a.U) continue;
+            const float g = a.g ? a.g[i] : 1.f;
+            widen4(a.U + i * a.d + col, v);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] *= g;
+        }
+        store_dH4(a, i, col, v);
+    }
+}
+
+// What a position's sums become: lse, loss, the correct item's coefficient and what the candidate side needs.
+// sn: weights of the negatives relative to exp(ref); op: score of the correct item.
+__device__ __forceinline__ float dense_finish(const DenseArgs &a, int64_t x, int32_t row, float ref, float sn, float op, bool files)
+{
+    const float wp = fast_exp(op - ref), s = sn + wp;
+    const float l2 = fast_log(s);
+    a.lse[row] = ref + l2;
+    a.loss[row] = (ref - op) + l2;
+    const float inv = 1.f / s;
+    if (files) {
+        const int64_t at = a.by_slot ? x : (int64_t)row;
+        a.coef[at] = -sn * inv;  // p+ - 1, without the cancellation
+        a.ref[at] = ref;
+        a.inv[at] = inv;
+    }
+    return inv;
+}
+
+// min two blocks of four wavefronts per compute unit: 256 registers a lane
+template <typename T, int KD, int MODE>
+__global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
+{
+    typedef DenseGeo<T, KD, MODE> G;
+    constexpr bool DE = MODE == DM_DE, B16 = G::B16;
+    constexpr int BY = G::BY, XR = G::XR, OB = G::OB;
+    __shared__ uint4 lds[G::LDS];
+    __shared__ __align__(16) int32_t ids[3][BY];                          // candidate ids / position rows of the tile, -1: no part
+    __shared__ float4 cst[DE ? 3 : 1][DE ? BY / 4 * 3 : 1];  // candidate side: reference, weight factor, target of a row
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lo = lane & (XR - 1), hi = lane / XR;  // column of the stationary operand, share of the reduction index
+    const int sl = wave % G::DS, xg = wave / G::DS;
+    int64_t block = blockIdx.x;
+    if (DE) {
+        if (block < a.scatter_blocks) {
+            dense_scatter_block<T, (KD + 1) / 2>(a, block, reinterpret_cast<uint64_t *>(lds));
+            return;
+        }
+        block -= a.scatter_blocks;
+        if (block >= a.tile_blocks) {
+            dense_scale_block(a, block - a.tile_blocks);
+            return;
+        }
+    }
+    const T *Hp = static_cast<const T *>(a.H), *Ep = static_cast<const T *>(a.E);
+    const int32_t *neg = a.neg;
+
+    // ---- what the block works on: stationary rows [x0, x0 + XPB) of nx, streamed rows [y0, y1)
+    int64_t pos0 = 0, pos1 = dense_slots(a), split, xb;
+    if (a.tab) {  // buckets of positions, each with a list of its own
+        const int b = dense_bucket(a.tab + (DE ? 2 : 1), a.n_buckets, (int32_t)(DE ? block : blockIdx.x));
+        pos0 = a.tab[3 * b];
+        pos1 = a.tab[3 * b + 3];
+        neg += (int64_t)b * a.n_cols;
+        const int64_t in = (DE ? block : (int64_t)blockIdx.x) - a.tab[3 * b + (DE ? 2 : 1)];
+        xb = DE ? in % a.x_blocks : in;
+        split = DE ? in / a.x_blocks : (int64_t)blockIdx.y;
+    } else {
+        xb = DE ? block % a.x_blocks : block;
+        split = DE ? block / a.x_blocks : (int64_t)blockIdx.y;
+    }
+    const int64_t nx = DE ? a.n_cols : pos1 - pos0, ny = DE ? pos1 - pos0 : a.n_cols;
+    const int64_t x0 = xb * G::XPB;
+    int64_t tiles = (ny + BY - 1) / BY, t0, t1;
+    if (DE && a.tab) {
+        t0 = split * a.tiles_per_split;
+        t1 = t0 + a.tiles_per_split < tiles ? t0 + a.tiles_per_split : tiles;
+    } else {
+        const int64_t per = (tiles + a.splits - 1) / a.splits;
+        t0 = split * per;
+        t1 = t0 + per < tiles ? t0 + per : tiles;
+    }
+    if (x0 >= nx) return;
+    if (DE && t0 >= t1) return;  // (the position side still files an empty share)
+
+    // ---- stationary row of this lane
+    const int64_t x = x0 + xg * XR + lo;
+    int32_t xrow = -1;  // row number in H (position side) or E (candidate side)
+    int32_t ti = -1;
+    if (x < nx) {
+        if (DE) {
+            xrow = neg ? neg[x] : (int32_t)x;
+            if (a.validate && (xrow < 0 || (int64_t)xrow >= a.V)) xrow = -1;
+        } else {
+            xrow = dense_row(a, pos0 + x);
+            if (xrow >= 0) ti = a.tgt[xrow];
+        }
+    }
+    const int dch = a.d * (int)sizeof(T) / 16;  // 16-byte chunks of a row
+    uint4 xr[G::NX];
+    {
+        const uint4 *src = reinterpret_cast<const uint4 *>(DE ? Ep + (int64_t)(xrow < 0 ? 0 : xrow) * a.d : Hp + (int64_t)(xrow < 0 ? 0 : xrow) * a.d);
+#pragma unroll
+        for (int k = 0; k < G::NX; ++k) {
+            const int ch = k * (64 / XR) + hi;
+            xr[k] = make_uint4(0, 0, 0, 0);
+            if (xrow >= 0 && ch < dch) xr[k] = src[ch];
+        }
+    }
+    float op = 0.f, ref = 0.f;
+    if (!DE) {  // score of the correct item
+        const uint4 *src = reinterpret_cast<const uint4 *>(Ep + (int64_t)(ti < 0 ? 0 : ti) * a.d);
+#pragma unroll
+        for (int k = 0; k < G::NX; ++k) {
+            const int ch = k * (64 / XR) + hi;
+            uint4 e = make_uint4(0, 0, 0, 0);
+            if (xrow >= 0 && ch < dch) e = src[ch];
+            const uint32_t ew[4] = {e.x, e.y, e.z, e.w}, xw[4] = {xr[k].x, xr[k].y, xr[k].z, xr[k].w};
+            float part = 0.f;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if (B16) {
+                    part = fmaf(bf16_lo(xw[t]), bf16_lo(ew[t]), part);
+                    part = fmaf(bf16_hi(xw[t]), bf16_hi(ew[t]), part);
+                } else {
+                    part = fmaf(__uint_as_float(xw[t]), __uint_as_float(ew[t]), part);
+                }
+            }
+            op += part;
+        }
+#pragma unroll
+        for (int off = XR; off < 64; off <<= 1) op += __shfl_xor(op, off, 64);
+        ref = op;
+        if (MODE == DM_DH) ref = xrow >= 0 ? a.lse_in[xrow] : 0.f;
+    }
+    const bool drop_own = a.drop_own != 0;
+    const int32_t x_drop = drop_own ? (DE ? xrow : ti) : -2;  // a column of the other kind with this number takes no part
+
+    // ---- streaming: ids two tiles ahead, rows one tile ahead
+    auto y_id = [&](int64_t t, int e) -> int32_t {  // id / row of streamed row e of tile t
+        const int64_t y = t * BY + e;
+        if (t >= t1 || y >= ny) return -1;
+        if (DE) return dense_row(a, pos0 + y);
+        if (!neg) return (int32_t)y;
+        const int32_t id = neg[y];
+        return (a.validate && (id < 0 || (int64_t)id >= a.V)) ? -1 : id;
+    };
+    struct Cst { float ref, w; int32_t ti; };
+    auto y_cst = [&](int64_t t, int e, int32_t row) -> Cst {
+        Cst c{INFINITY, 0.f, -1};
+        if (row >= 0) {
+            const int64_t at = a.by_slot ? pos0 + t * BY + e : (int64_t)row;
+            const float g = a.g ? a.g[row] : 1.f;
+            c.w = a.inv ? g * a.inv[at] : g;
+            c.ti = a.tgt[row];
+            if (c.w != 0.f) c.ref = a.ref[at];  // a zero factor keeps exp(-inf) = 0: no 0 * inf
+        }
+        return c;
+    };
+    auto put_cst = [&](int slot, int e, const Cst &c) {
+        float *f = reinterpret_cast<float *>(cst[DE ? slot : 0]);
+        f[e] = c.ref;
+        f[BY + e] = c.w;
+        f[2 * BY + e] = __int_as_float(c.ti);
+    };
+    uint4 stage[G::LPS];
+    const T *Yp = DE ? Hp : Ep;
+    auto issue = [&](int slot, int turn) {
+#pragma unroll
+        for (int i = 0; i < G::LPS; ++i) {
+            const int c = (turn * G::LPS + i) * kDenseThreads + tid;
+            stage[i] = make_uint4(0, 0, 0, 0);
+            if (c < BY * G::CPR) {
+                const int r = c / G::CPR, ch = c % G::CPR;
+                const int32_t id = ids[slot][r];
+                if (id >= 0 && ch < dch) stage[i] = reinterpret_cast<const uint4 *>(Yp + (int64_t)id * a.d)[ch];
+            }
+        }
+    };
+    auto land = [&](uint4 *buf, int turn) {
+#pragma unroll
+        for (int i = 0; i < G::LPS; ++i) {
+            const int c = (turn * G::LPS + i) * kDenseThreads + tid;
+            if (c < BY * G::CPR) buf[(c / G::CPR) * G::PITCH + c % G::CPR] = stage[i];
+        }
+    };
+    int32_t next_row = -1;  // candidate side: row of tile t + 3, fetched a turn before its constants
+    if (tid < BY) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int32_t id = y_id(t0 + q, tid);
+            ids[q][tid] = id;
+            if (DE) put_cst(q, tid, y_cst(t0 + q, tid, id));
+        }
+        if (DE) next_row = y_id(t0 + 2, tid);
+    }
+    __syncthreads();
+    if (t0 < t1) {
+#pragma unroll
+        for (int turn = 0; turn < G::NST; ++turn) {
+            issue(0, turn);
+            land(lds, turn);
+        }
+    }
+
+    typename G::acc_t acc[MODE == DM_FWD ? 1 : OB];
+    if (MODE != DM_FWD) {
+#pragma unroll
+        for (int b = 0; b < OB; ++b)
+#pragma unroll
+            for (int i = 0; i < 4 * G::AQ; ++i) acc[b][i] = 0.f;
+    }
+    float sn = 0.f;
+    // fp32 weights of one score block (4 AQ values a lane: streamed rows row_of(i)), then the second product
+    constexpr int SUB = BY / XR;  // score blocks per tile
+    int slot = 0;
+    for (int64_t t = t0; t < t1; ++t) {
+        const int slot1 = slot == 2 ? 0 : slot + 1, slot2 = slot1 == 2 ? 0 : slot1 + 1;
+        const uint4 *buf = lds + ((t - t0) & 1) * G::BUF;
+        uint4 *const other = lds + ((t - t0 + 1) & 1) * G::BUF;
+        __syncthreads();
+        const bool more = t + 1 < t1;
+        if (more) issue(slot1, 0);
+        int32_t id2 = -1;
+        Cst c2{INFINITY, 0.f, -1};
+        if (tid < BY) {
+            if (DE) {
+                id2 = next_row;
+                c2 = y_cst(t + 2, tid, id2);
+                next_row = y_id(t + 3, tid);
+            } else {
+                id2 = y_id(t + 2, tid);
+            }
+        }
+#pragma unroll
+        for (int sb = 0; sb < SUB; ++sb) {
+            typename G::acc_t s;
+#pragma unroll
+            for (int i = 0; i < 4 * G::AQ; ++i) s[i] = 0.f;
+            const uint4 *arow = buf + (sb * XR + lo) * G::PITCH + hi;
+#pragma unroll
+            for (int k = 0; k < G::NX; ++k) {
+                const uint4 o = arow[k * (64 / XR)];
+                if constexpr (B16) {
+                    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(o), as_b8(xr[k]), s, 0, 0, 0);
+                } else {
+                    s = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(o.x), __uint_as_float(xr[k].x), s, 0, 0, 0);
+                    s = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(o.y), __uint_as_float(xr[k].y), s, 0, 0, 0);
+                    s = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(o.z), __uint_as_float(xr[k].z), s, 0, 0, 0);
+                    s = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(o.w), __uint_as_float(xr[k].w), s, 0, 0, 0);
+                }
+            }
+            if (G::NST == 2 && sb == 0 && more) {
+                land(other, 0);
+                issue(slot1, 1);
+            }
+            // weights: value 4 q + r belongs to streamed row sb XR + 8 q + 4 hi + r (bf16) or sb XR + 4 hi + r (fp32)
+            float v[4 * G::AQ];
+            if (DE) {
+                const float4 *cf = cst[DE ? slot : 0];
+#pragma unroll
+                for (int q = 0; q < G::AQ; ++q) {
+                    const int e4 = sb * (XR / 4) + 2 * q + hi;
+                    const float4 r4 = cf[e4], w4 = cf[BY / 4 + e4], t4 = cf[BY / 2 + e4];
+                    const float rr[4] = {r4.x, r4.y, r4.z, r4.w}, ww[4] = {w4.x, w4.y, w4.z, w4.w}, tt[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float w = ww[r] * fast_exp(s[4 * q + r] - rr[r]);
+                        v[4 * q + r] = (__float_as_int(tt[r]) == x_drop) ? 0.f : w;
+                    }
+                }
+            } else {
+                float top = -INFINITY;
+#pragma unroll
+                for (int q = 0; q < G::AQ; ++q) {
+                    const int4 i4 = *reinterpret_cast<const int4 *>(&ids[slot][sb * XR + 8 * q + 4 * hi]);
+                    const int32_t ii[4] = {i4.x, i4.y, i4.z, i4.w};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        v[4 * q + r] = (ii[r] < 0 || ii[r] == x_drop) ? -INFINITY : s[4 * q + r];
+                        top = fmaxf(top, v[4 * q + r]);
+                    }
+                }
+                if (MODE != DM_DH && __any(top > ref + kRescaleAbove)) {  // rare: move the reference up, rescale the sums
+#pragma unroll
+                    for (int off = XR; off < 64; off <<= 1) top = fmaxf(top, __shfl_xor(top, off, 64));
+                    const float to = fmaxf(ref, top), sc = fast_exp(ref - to);
+                    ref = to;
+                    sn *= sc;
+                    if (MODE != DM_FWD) {
+#pragma unroll
+                        for (int b = 0; b < OB; ++b)
+#pragma unroll
+                            for (int i = 0; i < 4 * G::AQ; ++i) acc[b][i] *= sc;
+                    }
+                }
+                float part[G::AQ];
+#pragma unroll
+                for (int q = 0; q < G::AQ; ++q) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[4 * q + r] = fast_exp(v[4 * q + r] - ref);
+                    part[q] = (v[4 * q] + v[4 * q + 1]) + (v[4 * q + 2] + v[4 * q + 3]);
+                }
+                if constexpr (G::AQ == 4) sn += (part[0] + part[1]) + (part[2] + part[3]);
+                else sn += part[0];
+            }
+            if (MODE == DM_FWD) continue;
+            if constexpr (B16) {
+                const int j16 = lane & 15;
+                // transpose reads: rows hi 4 + j16 / 4 and 8 below, columns of this lane's half of a block of 32
+                const uint16_t *tb = reinterpret_cast<const uint16_t *>(buf) + (hi * 4 + (j16 >> 2)) * (G::PITCH * 8) +
+                                     sl * OB * 32 + ((lane >> 4) & 1) * 16 + (j16 & 3) * 4;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    uint4 pl[3];
+                    split3(v + 8 * c, pl);
+#pragma unroll
+                    for (int b = 0; b < OB; ++b) {
+                        const uint16_t *q0 = tb + c * 16 * (G::PITCH * 8) + b * 32;
+                        const ds16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dlds_v4)q0);
+                        const ds16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dlds_v4)(q0 + 8 * (G::PITCH * 8)));
+                        uint4 av;
+                        __builtin_memcpy(&av.x, &r0, 8);
+                        __builtin_memcpy(&av.z, &r1, 8);
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(av), as_b8(pl[2]), acc[b], 0, 0, 0);
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(av), as_b8(pl[1]), acc[b], 0, 0, 0);
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(av), as_b8(pl[0]), acc[b], 0, 0, 0);
+                    }
+                }
+            } else {
+                const float *tb = reinterpret_cast<const float *>(buf) + (sb * XR + 4 * hi) * (G::PITCH * 4) + sl * OB * 16 + lo;
+#pragma unroll
+                for (int b = 0; b < OB; ++b) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(tb[r * (G::PITCH * 4) + b * 16], v[r], acc[b], 0, 0, 0);
+                }
+            }
+        }
+        if (more) land(other, G::NST - 1);
+        if (tid < BY) {
+            ids[slot2][tid] = id2;
+            if (DE) put_cst(slot2, tid, c2);
+        }
+        slot = slot1;
+    }
+
+    if constexpr (DE) {
+        // rows of the candidates: blocks of 32 columns turned round in LDS, so that an atomic instruction covers 32
+        // consecutive floats of two rows
+        __syncthreads();
+        float *tr = reinterpret_cast<float *>(lds) + wave * (XR * 33);
+        constexpr int PER = 32 / G::OC;  // accumulator blocks per 32 columns
+#pragma unroll
+        for (int b0 = 0; b0 < OB; b0 += PER) {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int b = 0; b < PER; ++b)
+#pragma unroll
+                for (int i = 0; i < 4 * G::AQ; ++i) tr[lo * 33 + b * G::OC + (i >> 2) * 8 + hi * 4 + (i & 3)] = acc[b0 + b][i];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int col = (sl * OB + b0) * G::OC + (lane & 31);
+#pragma unroll
+            for (int i = 0; i < XR / 2; ++i) {
+                const int r = 2 * i + (lane >> 5);
+                const int32_t id = __shfl(xrow, r, 64);
+                const float val = tr[r * 33 + (lane & 31)];
+                if (id >= 0 && col < a.d) unsafeAtomicAdd(a.dE + (int64_t)id * a.d + col, val);
+            }
+        }
+        return;
+    } else {
+#pragma unroll
+        for (int off = XR; off < 64; off <<= 1) sn += __shfl_xor(sn, off, 64);
+        const int64_t xs = pos0 + x;  // slot
+        if (a.splits > 1) {  // partial results, combined by dense_merge_kernel
+            if (x >= nx) return;
+            if (hi == 0 && sl == 0) {
+                a.part_ms[split * a.N + xs] = make_float2(ref, sn);
+                if (split == 0) a.part_o[xs] = op;
+            }
+            if (MODE != DM_FWD && xrow >= 0) {
+#pragma unroll
+                for (int b = 0; b < OB; ++b)
+#pragma unroll
+                    for (int q = 0; q < G::AQ; ++q) {
+                        const int col = (sl * OB + b) * G::OC + q * 8 + hi * 4;
+                        if (col < a.d)
+                            *reinterpret_cast<float4 *>(a.part_U + (split * a.N + xs) * a.d + col) =
+                                make_float4(acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]);
+                    }
+            }
+            return;
+        }
+        if (x >= nx) return;
+        if (xrow < 0) {
+            // padded (only without compaction); the candidate launch writes zero dH rows
+            if (MODE != DM_DH && !a.order && hi == 0 && sl == 0) a.loss[xs] = a.lse[xs] = 0.f;
+            return;
+        }
+        float inv = 1.f, ct;  // U = inv * sum + ct * E_tgt
+        if (MODE == DM_DH) {
+            ct = fast_exp(op - ref) - 1.f;
+            if (hi == 0 && sl == 0) a.coef[xrow] = (a.g ? a.g[xrow] : 1.f) * ct;
+        } else {
+            if (hi == 0 && sl == 0) inv = dense_finish(a, xs, xrow, ref, sn, op, MODE == DM_FDH);
+            else inv = 1.f / (sn + fast_exp(op - ref));
+            ct = -sn * inv;
+        }
+        if (MODE == DM_FWD) return;
+        const float g = (MODE == DM_DH || a.direct_dH) ? (a.g ? a.g[xrow] : 1.f) : 1.f;
+#pragma unroll
+        for (int b = 0; b < OB; ++b)
+#pragma unroll
+            for (int q = 0; q < G::AQ; ++q) {
+                const int col = (sl * OB + b) * G::OC + q * 8 + hi * 4;
+                if (col >= a.d) continue;
+                float et[4], u[4];
+                widen4(Ep + (int64_t)ti * a.d + col, et);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) u[r] = g * fmaf(ct, et[r], acc[b][4 * q + r] * inv);
+                if (MODE == DM_DH || a.direct_dH) store_dH4(a, xrow, col, u);
+                else *reinterpret_cast<float4 *>(a.U + (int64_t)xrow * a.d + col) = make_float4(u[0], u[1], u[2], u[3]);
+            }
+    }
+}
+
+// Combines the shares of a split position side: 16 threads a position, four columns each and turn.
+template <typename T, int MODE>
+__global__ __launch_bounds__(256) void dense_merge_kernel(DenseArgs a)
+{
+    const int64_t x = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    const int c = threadIdx.x & 15;
+    if (x >= dense_slots(a)) return;
+    const int32_t row = dense_row(a, x);
+    if (row < 0) {
+        if (MODE != DM_DH && !a.order && c == 0) a.loss[x] = a.lse[x] = 0.f;
+        return;
+    }
+    float M = -INFINITY, sn = 0.f;
+    for (int k = 0; k < a.splits; ++k) M = fmaxf(M, a.part_ms[k * a.N + x].x);
+    for (int k = 0; k < a.splits; ++k) {
+        const float2 ms = a.part_ms[k * a.N + x];
+        sn += ms.y * fast_exp(ms.x - M);
+    }
+    const float op = a.part_o[x];
+    float inv = 1.f, ct;
+    if (MODE == DM_DH) {
+        ct = fast_exp(op - M) - 1.f;
+        if (c == 0) a.coef[row] = (a.g ? a.g[row] : 1.f) * ct;
+    } else {
+        if (c == 0) inv = dense_finish(a, x, row, M, sn, op, MODE == DM_FDH);
+        else inv = 1.f / (sn + fast_exp(op - M));
+        ct = -sn * inv;
+    }
+    if (MODE == DM_FWD) return;
+    const bool to_dH = MODE == DM_DH || a.direct_dH;
+    const float g = (to_dH && a.g) ? a.g[row] : 1.f;
+    const int32_t ti = a.tgt[row];
+    for (int col = c * 4; col < a.d; col += 64) {
+        float u[4] = {0.f, 0.f, 0.f, 0.f}, et[4];
+        for (int k = 0; k < a.splits; ++k) {
+            const float sc = MODE == DM_DH ? 1.f : fast_exp(a.part_ms[k * a.N + x].x - M);
+            float pv[4];
+            widen4(a.part_U + (k * a.N + x) * a.d + col, pv);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) u[r] = fmaf(pv[r], sc, u[r]);
+        }
+        widen4(static_cast<const T *>(a.E) + (int64_t)ti * a.d + col, et);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) u[r] = g * fmaf(ct, et[r], u[r] * inv);
+        if (to_dH) store_dH4(a, row, col, u);
+        else *reinterpret_cast<float4 *>(a.U + (int64_t)row * a.d + col) = make_float4(u[0], u[1], u[2], u[3]);
+    }
+}
+
+template <typename T, int KD>
+hipError_t launch_dense_kd(int pass, DenseArgs a, hipStream_t stream)
+{
+    const dim3 threads(kDenseThreads);
+    if (pass == DENSE_DE) {
+        const int64_t blocks = a.scatter_blocks + a.tile_blocks + a.scale_blocks;
+        if (blocks == 0) return hipSuccess;
+        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+        ProfScope prof(PROF_DENSE_DE, stream);
+        hipLaunchKernelGGL((dense_kernel<T, KD, DM_DE>), dim3((unsigned)blocks), threads, 0, stream, a);
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)a.x_blocks, (unsigned)a.splits);
+    {
+        ProfScope prof(PROF_DENSE_POS, stream);
+        if (pass == DENSE_FWD) hipLaunchKernelGGL((dense_kernel<T, KD, DM_FWD>), grid, threads, 0, stream, a);
+        else if (pass == DENSE_FDH) hipLaunchKernelGGL((dense_kernel<T, KD, DM_FDH>), grid, threads, 0, stream, a);
+        else hipLaunchKernelGGL((dense_kernel<T, KD, DM_DH>), grid, threads, 0, stream, a);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.splits == 1) return e;
+    ProfScope prof(PROF_DENSE_MERGE, stream);
+    const dim3 mgrid((unsigned)((a.N + 15) / 16));
+    if (pass == DENSE_FWD) hipLaunchKernelGGL((dense_merge_kernel<T, DM_FWD>), mgrid, dim3(256), 0, stream, a);
+    else if (pass == DENSE_FDH) hipLaunchKernelGGL((dense_merge_kernel<T, DM_FDH>), mgrid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((dense_merge_kernel<T, DM_DH>), mgrid, dim3(256), 0, stream, a);
+    return hipGetLastError();
+}
+
+template <typename T, int KD>
+DenseShape dense_shape_kd(int pass)
+{
+    typedef DenseGeo<T, KD, DM_FWD> F;
+    typedef DenseGeo<T, KD, DM_FDH> B;
+    return pass == DENSE_FWD ? DenseShape{F::XPB, F::BY} : DenseShape{B::XPB, B::BY};
+}
+
+template <typename T, typename F>
+auto dense_by_width(int d, F f)
+{
+    const int kd = (d + 31) / 32;
+    if (kd <= 1) return f(std::integral_constant<int, 1>{});
+    if (kd <= 2) return f(std::integral_constant<int, 2>{});
+    if (kd <= 3) return f(std::integral_constant<int, 3>{});
+    if (kd <= 4) return f(std::integral_constant<int, 4>{});
+    if (kd <= 6) return f(std::integral_constant<int, 6>{});
+    if (kd <= 8) return f(std::integral_constant<int, 8>{});
+    if (kd <= 10) return f(std::integral_constant<int, 10>{});
+    return f(std::integral_constant<int, 16>{});
+}
+
+}  // namespace
+}  // namespace cce

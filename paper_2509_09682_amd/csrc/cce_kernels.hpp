@@ -79,6 +79,45 @@ hipError_t launch_dh_scale(const TileArgs &a, bool file_g, hipStream_t stream);
 bool tile_backward_fusable(int d);
 hipError_t launch_tile_backward(const TileArgs &a_dh, const TileArgs &a_de, hipStream_t stream);
 
+// ---- dense family in fp32 precision: shared lists and the full catalogue where the bf16-weight tiles do not run
+struct DenseArgs {
+    const void *H;               // [n_rows, d]
+    const void *E;               // [V, d]
+    const int32_t *tgt;          // [n_rows]
+    const int32_t *neg;          // [n_cols], or [n_buckets, n_cols]; nullptr: column = item
+    const int32_t *idx;          // compacted position -> row; nullptr: no compaction
+    const int32_t *n_valid_ptr;  // device count of compacted positions; nullptr: N
+    const uint8_t *mask;         // padding mask where nothing was compacted (nullable)
+    const uint8_t *pos_mask;     // padding mask for the rows of dH (nullable)
+    const int64_t *order;        // buckets: slot -> row; nullptr: no buckets
+    const int32_t *tab;          // buckets: [n_buckets + 1][3] first slot, first block of the position / candidate launch
+    const float *lse_in, *g;
+    float *loss, *lse;
+    void *dH;
+    float *dE;
+    float *coef, *inv;           // correct item's coefficient; 1 / sum of weights (candidate side: nullptr = 1)
+    float *ref;                  // reference of a position's exponentials (candidate side: reads it)
+    float *U;                    // [N, d] hidden-state gradient short of grad_loss (nullable)
+    float2 *part_ms;             // [splits, N] reference and sum of a share
+    float *part_o;               // [N] score of the correct item
+    float *part_U;               // [splits, N, d]
+    int64_t N, n_rows, V, n_cols;  // N: slots (positions, or entries of order)
+    int64_t x_blocks;            // blocks of stationary rows (per split)
+    int64_t scatter_blocks, tile_blocks, scale_blocks;  // candidate launch: its three roles, in this order
+    int64_t tiles_per_split;     // buckets, candidate launch
+    int32_t d, splits, n_buckets;
+    int32_t drop_own, validate, dH_bf16;
+    int32_t g_separate;          // scatter: coef is short of grad_loss
+    int32_t by_slot;             // coef / ref / inv are filed under the slot, not the row
+    int32_t direct_dH;           // the fused position pass knows grad_loss: it writes dH, not U
+};
+struct DenseShape { int xpb, by; };  // stationary rows per block, streamed rows per tile
+enum { DENSE_FWD = 0, DENSE_FDH = 1, DENSE_DH = 2, DENSE_DE = 3 };
+constexpr int kDenseScaleTurns = 4;
+constexpr int kDenseScatterPairs = 256;
+hipError_t launch_dense(bool bf16, int pass, const DenseArgs &a, hipStream_t stream);
+DenseShape dense_shape(bool bf16, int pass, int d);
+
 // ---- inverted-index dE of per-position negatives
 struct InvertArgs {
     const void *H;
@@ -130,7 +169,7 @@ hipError_t launch_tile(int pass, const TileArgs &a, hipStream_t stream);
 // Event bracket around a kernel launch while profiling is enabled (see cce_neg_profile_enable); otherwise a no-op.
 enum { PROF_GATHER_FWD = 0, PROF_GATHER_BWD, PROF_PREP, PROF_TILE_FWD, PROF_FWD_MERGE, PROF_TILE_DH, PROF_DH_MERGE,
        PROF_TILE_DE, PROF_INDEX, PROF_ITEM_DE, PROF_POS_SCATTER, PROF_BWD_PRE, PROF_TILE_BWD, PROF_TILE_FDH, PROF_FDH_MERGE,
-       PROF_DH_SCALE, PROF_FAMILIES };
+       PROF_DH_SCALE, PROF_DENSE_POS, PROF_DENSE_MERGE, PROF_DENSE_DE, PROF_FAMILIES };
 struct ProfScope {
     ProfScope(int family, hipStream_t stream);
     ~ProfScope();

@@ -1,0 +1,98 @@
+"""The dense kernels in fp32 precision (shared lists and the full catalogue, fp32 inputs or hidden sizes without a
+bf16-weight matrix kernel) against the fp64 oracle, at the sizes where their tiles, splits and column shares change."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import check_against_oracle
+from workloads import NEG_FULL, NEG_SHARED, make_workload
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5   # the contract of the fp32 path; no 16-bit weight enters here whatever the input type
+
+
+def _run(w, **kw):
+    from hip_harness import run_hip
+
+    return run_hip(w, **kw)
+
+
+# hidden sizes: the smallest, one short of and one past a block of 32 columns, every width class, the largest
+WIDTHS = [("f32", d) for d in (8, 40, 64, 72, 128, 192, 256, 320, 512)] + [("bf16", d) for d in (8, 32, 40, 96, 104, 192, 216, 320, 392, 512)]
+
+
+@pytest.mark.parametrize("mode", [NEG_SHARED, NEG_FULL])
+@pytest.mark.parametrize("dtype,d", WIDTHS)
+def test_widths_and_passes(mode, dtype, d):
+    import paper_2509_09682_amd as P
+
+    V = 203 if mode == NEG_FULL else 157     # not a multiple of a tile; shared: repeats and collisions in the list
+    w = make_workload(f"dense_m{mode}_{dtype}_d{d}", 7, 61, d, V, 0 if mode == NEG_FULL else 77, dtype, mode, 300 + d + mode,
+                      pad="bernoulli", pad_p=0.3, g_kind="random", e_sigma=0.1, tgt_dist="zipf")
+    check_against_oracle(w, _run(w, fuse_dH=True, reuse_prep=True), TOL)
+    check_against_oracle(w, _run(w), TOL)
+    check_against_oracle(w, _run(w, fuse_dH=True, validate=1), TOL)            # compacted, dH pass of its own
+    if mode == NEG_SHARED:
+        w.mask_collisions = 0
+        check_against_oracle(w, _run(w, fuse_dH=True, reuse_prep=True, validate=1), TOL)
+    w.mask[:] = 1
+    out = _run(w, fuse_dH=True, reuse_prep=True, use_mask=False, g=None, repeat_backward=2,
+               dH_dtype=P.CCE_BF16 if dtype == "bf16" else P.CCE_F32)
+    out["dE"] = out["dE"] * 0.5
+    check_against_oracle(w, out, TOL, g=None, dH_tol=4e-3 if dtype == "bf16" else None)   # half an ulp of bf16: 2^-9
+
+
+@pytest.mark.parametrize("batch,seq,V,K", [(1, 1, 50, 1), (1, 3, 5000, 1500), (1, 33, 3000, 33), (2, 64, 90, 31), (9, 1000, 3000, 200),
+                                           (30, 1000, 2000, 40)])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 48), ("bf16", 320)])
+def test_shapes_from_one_position_to_unsplit_grids(batch, seq, V, K, dtype, d):
+    """One position, few positions against many candidates (shares of the list), around a block of positions, and
+    enough positions for compaction and for whole lists per block."""
+    w = make_workload(f"dense_{batch}x{seq}_K{K}_{dtype}_d{d}", batch, seq, d, V, K, dtype, NEG_SHARED, 77 + seq, g_kind="random",
+                      pad="none" if batch * seq < 100 else "right", pad_len_lo=seq // 3, e_sigma=0.1, tgt_dist="zipf")
+    for fuse in (True, False):
+        check_against_oracle(w, _run(w, fuse_dH=fuse, reuse_prep=fuse), TOL)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 96)])
+def test_scores_far_above_the_correct_item(dtype, d):
+    """The correct item's score is the first reference; here some candidates score up to 150 nats more, some positions
+    have every candidate far below."""
+    K = 300
+    w = make_workload(f"dense_climb_{dtype}", 3, 40, d, 2000, K, "f32", NEG_SHARED, 77, pad="bernoulli", pad_p=0.1, g_kind="random",
+                      e_sigma=0.05)
+    H = w.H.reshape(w.N, d).copy()
+    E = w.E.reshape(w.V, d).copy()
+    for i, up in ((5, 150.0), (17, 60.0), (41, 21.0), (90, 25.0)):   # <h_i, e_v> = up, late in the list
+        v = int(w.neg[K // 2 + i])
+        E[v] = up * H[i] / float(H[i].astype(np.float64) @ H[i].astype(np.float64))
+    for i in (60, 61):                                                # the correct item towers over the rest
+        E[w.tgt[i]] = 120.0 * H[i] / float(H[i].astype(np.float64) @ H[i].astype(np.float64))
+    w.H, w.E = H.reshape(w.H.shape), E.reshape(w.E.shape)
+    if dtype == "bf16":
+        from workloads import bf16_bits_from_f32
+        import dataclasses
+
+        w = dataclasses.replace(w, H=bf16_bits_from_f32(w.H), E=bf16_bits_from_f32(w.E), in_dtype="bf16")
+    # a score of 150 carries 2^-24 * 150 of absolute error into its exponent, hence 9e-6 relative into the gradients
+    check_against_oracle(w, _run(w, fuse_dH=True, reuse_prep=True), 4e-5)
+    check_against_oracle(w, _run(w), 4e-5)
+
+
+def test_bad_ids_are_skipped():
+    import paper_2509_09682_amd as P
+
+    w = make_workload("dense_bad_ids", 3, 50, 40, 400, 60, "f32", NEG_SHARED, 5, g_kind="random", pad="bernoulli", pad_p=0.2)
+    ok = w.neg.copy()
+    ref = _run(w, algo=P.CCE_ALGO_GATHER, validate=1)
+    assert ref["status"] == P.CCE_OK
+    w.neg = ok.copy()
+    w.neg[[3, 59]] = (-5, w.V)
+    w.tgt = w.tgt.copy()
+    w.tgt[7] = w.V + 3
+    for fuse in (False, True):
+        a = _run(w, algo=P.CCE_ALGO_GATHER, validate=1, fuse_dH=fuse, reuse_prep=fuse)
+        b = _run(w, validate=1, fuse_dH=fuse, reuse_prep=fuse)
+        assert a["status"] == b["status"] == P.CCE_ERR_INDEX
+        for name in ("loss", "lse", "dH", "dE"):
+            assert np.max(np.abs(a[name] - b[name])) <= 1e-5 * np.max(np.abs(a[name])), name
