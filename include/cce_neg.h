@@ -184,6 +184,25 @@ cce_status cce_neg_forward_noalloc(const cce_desc *desc, const void *H, const vo
                                    const int32_t *neg, const uint8_t *mask, float *loss, float *lse, void *hip_stream);
 
 /*
+ * Forward and backward of a step whose candidates are chosen per BUCKET of positions (one list for all positions of a
+ * bucket), every bucket in the same launches.  desc: N rows of H, V, d, K candidates per bucket, dtypes,
+ * CCE_NEG_SHARED, CCE_ALGO_AUTO, validate_indices = 0 (fuse_dH and reuse_forward_prep are ignored); K >= 1.
+ *   order      [n_order] int64   rows of H that take part, sorted by bucket (an entry outside [0, N) is skipped)
+ *   tgt_slot   [n_order] int32   correct item of every entry of order
+ *   bucket_ptr [n_buckets + 1]   HOST int64, ascending from 0 to n_order: bucket b owns order[bucket_ptr[b] .. [b+1])
+ *   neg        [n_buckets, K]    int32
+ *   grad_loss  [N] nullable, loss / lse [N], dH [N,d] dH_dtype: as for the plain calls, but only rows named in order
+ *              are written; dE [V,d] is accumulated into.
+ * Arithmetic is fp32 throughout (bf16 inputs included).  Every other pointer is DEVICE memory, tgt_slot, order and neg
+ * aligned to their element.
+ */
+size_t cce_neg_bucketed_workspace_bytes(const cce_desc *desc, int64_t n_order, int64_t n_buckets);
+cce_status cce_neg_bucketed_step(const cce_desc *desc, const void *H, const void *E, const int32_t *tgt_slot,
+                                 const int64_t *order, int64_t n_order, const int64_t *bucket_ptr, int64_t n_buckets,
+                                 const int32_t *neg, const float *grad_loss, float *loss, float *lse, void *dH, float *dE,
+                                 void *workspace, size_t workspace_bytes, void *hip_stream);
+
+/*
  * Negative sampling inside the kernels.  The paper draws the negatives of a step on the host (global uniform sampling,
  * or popularity-based sampling through a multinomial over the catalogue: Sec. 5, "Comparison Sampling Strategies")
  * and names the stored index matrix as the memory cost of CCE- over CCE (Sec. 5, "What is better").  The *_sampled

@@ -26,6 +26,7 @@ EXPORTS = (
     "cce_neg_workspace_bytes", "cce_neg_workspace_init", "cce_neg_forward", "cce_neg_backward",
     "cce_neg_index_status", "cce_status_string", "cce_neg_profile_enable", "cce_neg_profile_read",
     "cce_neg_sample", "cce_neg_forward_sampled", "cce_neg_backward_sampled", "cce_neg_forward_noalloc",
+    "cce_neg_bucketed_workspace_bytes", "cce_neg_bucketed_step",
 )
 
 
@@ -81,6 +82,11 @@ def lib() -> ctypes.CDLL:
         L.cce_neg_backward_sampled.restype = ctypes.c_int
         L.cce_neg_backward_sampled.argtypes = [ctypes.POINTER(CceDesc), ctypes.POINTER(CceSampler), vp, vp, i32p, vp, vp, vp,
                                                vp, vp, vp, ctypes.c_size_t, vp]
+        L.cce_neg_bucketed_workspace_bytes.restype = ctypes.c_size_t
+        L.cce_neg_bucketed_workspace_bytes.argtypes = [ctypes.POINTER(CceDesc), ctypes.c_int64, ctypes.c_int64]
+        L.cce_neg_bucketed_step.restype = ctypes.c_int
+        L.cce_neg_bucketed_step.argtypes = [ctypes.POINTER(CceDesc), vp, vp, i32p, vp, ctypes.c_int64, vp, ctypes.c_int64,
+                                            i32p, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
         L.cce_neg_index_status.restype = ctypes.c_int
         L.cce_neg_index_status.argtypes = [vp, ctypes.c_size_t, vp]
         L.cce_neg_profile_enable.restype = ctypes.c_int
@@ -131,7 +137,7 @@ def _want(name: str, t: Optional[torch.Tensor], dtypes, numel: int, *, optional:
 
 
 def check_step_args(desc: CceDesc, H, E, tgt, neg, mask, *, sampled: bool = False, loss=None, lse=None, grad_loss=None,
-                    dH=None, dE=None) -> None:
+                    dH=None, dE=None, n_tgt: Optional[int] = None) -> None:
     """Dtype and size checks of the tensors of a forward or backward call against the descriptor.
 
     The C ABI takes plain pointers and trusts the sizes in the descriptor, so a torch.long index tensor, a short mask
@@ -143,7 +149,7 @@ def check_step_args(desc: CceDesc, H, E, tgt, neg, mask, *, sampled: bool = Fals
     N, V, d, K = int(desc.N), int(desc.V), int(desc.d), int(desc.K)
     _want("H", H, elem, N * d)
     _want("E", E, elem, V * d)
-    _want("tgt", tgt, (torch.int32,), N)
+    _want("tgt", tgt, (torch.int32,), N if n_tgt is None else n_tgt)
     if not sampled and desc.neg_mode != CCE_NEG_FULL and K > 0:
         _want("neg", neg, (torch.int32,), K if desc.neg_mode == CCE_NEG_SHARED else N * K)
         if desc.neg_mode == CCE_NEG_PER_POSITION and neg.dim() == 2 and tuple(neg.shape) != (N, K):
@@ -207,6 +213,26 @@ def cce_neg_backward(desc: CceDesc, H, E, tgt, neg, mask, lse, grad_loss, dH, dE
     if check and st != CCE_OK:
         raise CceError(st, "cce_neg_backward")
     return st
+
+
+def cce_neg_bucketed_step(desc: CceDesc, H, E, tgt_slot, order, bucket_ptr, neg, grad_loss, loss, lse, dH, dE) -> None:
+    """Forward + backward with one candidate list per bucket of positions, all buckets in the same launches (see
+    include/cce_neg.h).  bucket_ptr: host integers."""
+    N, V, d, K = int(desc.N), int(desc.V), int(desc.d), int(desc.K)
+    n_order, n_buckets = int(order.numel()), len(bucket_ptr) - 1
+    check_step_args(desc, H, E, tgt_slot, None, None, sampled=True, loss=loss, lse=lse, grad_loss=grad_loss, dH=dH, dE=dE,
+                    n_tgt=n_order)
+    _want("order", order, (torch.int64,), n_order)
+    _want("neg", neg, (torch.int32,), n_buckets * K)
+    ptr = (ctypes.c_int64 * (n_buckets + 1))(*[int(x) for x in bucket_ptr])
+    n = int(lib().cce_neg_bucketed_workspace_bytes(ctypes.byref(desc), n_order, n_buckets))
+    if n == 0:
+        raise CceError(CCE_ERR_SHAPE, "cce_neg_bucketed_workspace_bytes")
+    ws = torch.empty(n, dtype=torch.uint8, device=H.device)
+    st = lib().cce_neg_bucketed_step(ctypes.byref(desc), _ptr(H), _ptr(E), _ptr(tgt_slot), _ptr(order), n_order, ptr, n_buckets,
+                                     _ptr(neg), _ptr(grad_loss), _ptr(loss), _ptr(lse), _ptr(dH), _ptr(dE), _ptr(ws), n, _stream())
+    if st != CCE_OK:
+        raise CceError(st, "cce_neg_bucketed_step")
 
 
 def make_sampler(kind: int, seed: int, stream: int = 0, alias_thresh: Optional[torch.Tensor] = None,

@@ -6,10 +6,11 @@ The paper's Sec. 5 ("Comparison Sampling Strategies") names the Scalable Cross-E
 groups positions into buckets, picks for each bucket the catalogue items with the largest scores under a cheap proxy,
 and takes the cross-entropy of every position over its bucket's items plus its own correct item; the paper notes that
 such a loss could run on kernels that need nothing but the indices of the correct and the selected items.  That is the
-shared-negatives mode of this library applied bucket by bucket: the positions are brought into bucket order once (a
-row gather of H, plain data movement), each bucket is one forward and one backward call on its contiguous slice with its
-own candidate list, the table gradient of all buckets accumulates into the same buffer, and the per-position results
-are put back in batch order.  How the buckets and their candidates are chosen is the caller's business.
+shared-negatives mode of this library with a list per bucket: every bucket in the same launches, positions read and
+results written where they are (cce_neg_bucketed_step).  Buckets so large that each fills the chip by itself go one by
+one through the bf16 matrix tiles instead: the positions are brought into bucket order once, each bucket is one forward
+and one backward call on its slice, and the results are put back in batch order.  How the buckets and their candidates
+are chosen is the caller's business.
 """
 from __future__ import annotations
 
@@ -18,6 +19,20 @@ from typing import Optional, Sequence
 import torch
 
 from . import binding as B
+
+
+# bf16 inputs and a hidden size with bf16 tiles: flops of an average bucket (8 positions candidates d) up to which all
+# buckets in one launch were the faster form wherever measured (2, 8 and 32 buckets; us for one launch / a launch pair per
+# bucket: d = 64, 32 buckets of 0.13 GFLOP 81 / 1294; d = 64, 8 of 17 GFLOP 584 / 696; d = 128, 2 of 34 GFLOP 267 / 295;
+# d = 256, 2 of 34 GFLOP 319 / 423).  Beyond, a bucket fills the chip and the cheaper bf16 weights of the tiles count.
+_TILE_SIZES = (64, 128, 256)
+_BUCKET_FLOPS_FOR_TILES = 3e10
+
+
+def _one_launch(dt: int, d: int, M: int, n_buckets: int, Kb: int) -> bool:
+    if Kb < 1 or M < 1:
+        return False
+    return dt == B.CCE_F32 or d not in _TILE_SIZES or 8.0 * M * Kb * d < _BUCKET_FLOPS_FOR_TILES * n_buckets
 
 
 def bucketed_step(H: torch.Tensor, E: torch.Tensor, tgt: torch.Tensor, order: torch.Tensor, bucket_ptr: Sequence[int],
@@ -40,8 +55,18 @@ def bucketed_step(H: torch.Tensor, E: torch.Tensor, tgt: torch.Tensor, order: to
     if len(bucket_ptr) != n_buckets + 1 or bucket_ptr[0] != 0 or bucket_ptr[-1] != order.numel():
         raise ValueError("bucket_ptr must hold B + 1 offsets covering `order`")
     dt = B.CCE_F32 if H.dtype == torch.float32 else B.CCE_BF16
-    Hs = H.index_select(0, order).contiguous()          # positions in bucket order: slices are contiguous
     ts = tgt.index_select(0, order).contiguous()
+    if _one_launch(dt, d, order.numel(), n_buckets, Kb):
+        if any(bucket_ptr[b + 1] < bucket_ptr[b] for b in range(n_buckets)):
+            raise ValueError("bucket_ptr must ascend")
+        loss = torch.zeros(N, device=H.device, dtype=torch.float32)
+        lse = torch.zeros(N, device=H.device, dtype=torch.float32)
+        dH = torch.zeros((N, d), device=H.device, dtype=H.dtype)
+        desc = B.make_desc(N, V, d, Kb, dt, B.CCE_NEG_SHARED, dH_dtype=dt, mask_target_collisions=int(mask_target_collisions))
+        B.cce_neg_bucketed_step(desc, H.contiguous(), E, ts, order.contiguous(), bucket_ptr, bucket_neg,
+                                None if grad_loss is None else grad_loss.contiguous(), loss, lse, dH, dE)
+        return loss, lse, dH
+    Hs = H.index_select(0, order).contiguous()          # positions in bucket order: slices are contiguous
     gs = None if grad_loss is None else grad_loss.index_select(0, order).contiguous()
     M = order.numel()
     loss_s = torch.empty(M, device=H.device, dtype=torch.float32)

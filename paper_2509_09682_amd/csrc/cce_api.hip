@@ -232,12 +232,20 @@ struct DenseLayout {
     size_t idx, coef, ref, inv, part_ms, part_o, U, part_U, total;
     int64_t ms_rows, u_rows;  // rows of the partial results: splits * N stays below
 };
+constexpr int64_t kDensePartMs = 262144;    // 2 MB of (reference, sum) pairs
+constexpr int64_t kDensePartRows = 65536;   // 256 KB d of partial rows
 DenseLayout make_dense_layout(const cce_desc *d)
 {
     DenseLayout L{};
     const size_t N = (size_t)d->N;
-    L.ms_rows = d->N * 128 < 262144 ? d->N * 128 : 262144;
-    L.u_rows = d->N * 64 < 65536 ? d->N * 64 : 65536;
+    // Shares of two tiles of candidates at least; partial rows up to what fills the chip (see dense_splits).
+    const int by = dense_shape(d->in_dtype == CCE_BF16, DENSE_FDH, d->d).by;
+    const int64_t tiles = (((d->neg_mode == CCE_NEG_FULL) ? d->V : (int64_t)d->K) + by - 1) / by;
+    const int64_t shares = tiles / 2 > 1 ? tiles / 2 : 0;
+    L.ms_rows = d->N * (shares < 128 ? shares : 128);
+    if (L.ms_rows > kDensePartMs) L.ms_rows = kDensePartMs;
+    L.u_rows = d->N * (shares < 64 ? shares : 64);
+    if (L.u_rows > kDensePartRows) L.u_rows = kDensePartRows;
     size_t off = kHeaderBytes;
     L.idx = off;     off += align256(N * 4);
     L.part_ms = off; off += align256((size_t)L.ms_rows * 8);
@@ -419,6 +427,35 @@ size_t shared_ids_offset(const cce_desc *d)
     if (use_dense(d)) return make_dense_layout(d).total;
     if (use_inverted(d)) return make_pp_layout(d).total;
     return fused_gather(d) ? make_plain_layout(d).total : kHeaderBytes;
+}
+
+// ---- candidate lists per bucket of positions, all buckets in one launch of either side
+constexpr int kTabEntries = 256;  // table entries a launch carries in its arguments
+struct TabChunk {
+    int32_t word[3 * kTabEntries];
+};
+__global__ __launch_bounds__(kTabEntries) void store_table_kernel(int32_t *dst, TabChunk c, int n)
+{
+    for (int i = threadIdx.x; i < 3 * n; i += kTabEntries) dst[i] = c.word[i];
+}
+
+// The descriptor of the dense kernels over the slots of a bucketed call.
+cce_desc bucket_desc(const cce_desc *d, int64_t n_order)
+{
+    cce_desc s = *d;
+    s.N = n_order;
+    s.fuse_dH = 0;  // dH is written at once: no U
+    return s;
+}
+size_t bucket_table_bytes(int64_t n_buckets) { return align256((size_t)(n_buckets + 1) * 12); }
+
+cce_status check_bucketed(const cce_desc *d, int64_t n_order, int64_t n_buckets)
+{
+    const cce_status st = check_desc(d);
+    if (st != CCE_OK) return st;
+    if (n_order < 0 || n_order > 0x7fffffffLL || n_buckets < 0 || n_buckets > 0x3fffffffLL) return CCE_ERR_SHAPE;
+    if (d->neg_mode != CCE_NEG_SHARED || d->K < 1 || d->algo != CCE_ALGO_AUTO || d->validate_indices) return CCE_ERR_UNSUPPORTED;
+    return CCE_OK;
 }
 
 cce_status check_sampler(const cce_desc *d, const cce_sampler *s)
@@ -813,6 +850,86 @@ cce_status cce_neg_forward_noalloc(const cce_desc *desc, const void *H, const vo
     // the array keeps what the last call left: the header (status word, counters) starts from zero every time
     if (cce::launch_fill_zero(static_cast<int32_t *>(ws), cce::kHeaderBytes / 4, stream) != hipSuccess) return CCE_ERR_HIP;
     return cce::forward_impl(desc, cce::Sampler{}, H, E, tgt, neg, mask, loss, lse, ws, stream);
+}
+
+size_t cce_neg_bucketed_workspace_bytes(const cce_desc *desc, int64_t n_order, int64_t n_buckets)
+{
+    if (cce::check_bucketed(desc, n_order, n_buckets) != CCE_OK) return 0;
+    const cce_desc s = cce::bucket_desc(desc, n_order);
+    return cce::make_dense_layout(&s).total + cce::bucket_table_bytes(n_buckets);
+}
+
+cce_status cce_neg_bucketed_step(const cce_desc *desc, const void *H, const void *E, const int32_t *tgt_slot,
+                                 const int64_t *order, int64_t n_order, const int64_t *bucket_ptr, int64_t n_buckets,
+                                 const int32_t *neg, const float *grad_loss, float *loss, float *lse, void *dH, float *dE,
+                                 void *workspace, size_t workspace_bytes, void *hip_stream)
+{
+    const cce_status st = cce::check_bucketed(desc, n_order, n_buckets);
+    if (st != CCE_OK) return st;
+    if (!bucket_ptr) return CCE_ERR_NULL;
+    if (bucket_ptr[0] != 0 || bucket_ptr[n_buckets] != n_order) return CCE_ERR_SHAPE;
+    for (int64_t b = 0; b < n_buckets; ++b)
+        if (bucket_ptr[b + 1] < bucket_ptr[b]) return CCE_ERR_SHAPE;
+    if (n_order == 0) return CCE_OK;
+    if (!H || !E || !tgt_slot || !order || !neg || !loss || !lse || !dH || !dE) return CCE_ERR_NULL;
+    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 15u) ||
+        workspace_bytes < cce_neg_bucketed_workspace_bytes(desc, n_order, n_buckets))
+        return CCE_ERR_WORKSPACE;
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const bool bf16 = desc->in_dtype == CCE_BF16;
+    const cce_desc s = cce::bucket_desc(desc, n_order);
+    const cce::DenseLayout L = cce::make_dense_layout(&s);
+    cce::DenseArgs a = cce::make_dense_args(&s, L, H, E, nullptr, neg, nullptr, workspace);
+    a.n_rows = desc->N;
+    a.order = order;
+    a.tgt_slot = tgt_slot;
+    a.n_buckets = (int32_t)n_buckets;
+    a.by_slot = 1;
+    a.direct_dH = 1;
+    a.g_separate = 1;
+    a.g = grad_loss;
+    a.loss = loss;
+    a.lse = lse;
+    a.dH = dH;
+    a.dE = dE;
+    // blocks of either side: whole blocks of positions per bucket, and per bucket (shares of its positions) x (blocks of
+    // its candidates), a share being as long as about two blocks per compute unit allow, four tiles at least
+    const cce::DenseShape fs = cce::dense_shape(bf16, cce::DENSE_FDH, desc->d), ds = cce::dense_shape(bf16, cce::DENSE_DE, desc->d);
+    const int64_t cand = (desc->K + ds.xpb - 1) / ds.xpb;
+    int64_t tiles = 0;
+    for (int64_t b = 0; b < n_buckets; ++b) tiles += (bucket_ptr[b + 1] - bucket_ptr[b] + ds.by - 1) / ds.by;
+    a.tiles_per_split = (tiles * cand + 511) / 512;
+    if (a.tiles_per_split < 4) a.tiles_per_split = 4;
+    int32_t *tab = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + L.total);
+    a.tab = tab;
+    int64_t pos_blocks = 0, de_blocks = 0;
+    cce::TabChunk chunk;
+    int n = 0;
+    for (int64_t b = 0; b <= n_buckets; ++b) {
+        chunk.word[3 * n] = (int32_t)bucket_ptr[b];
+        chunk.word[3 * n + 1] = (int32_t)pos_blocks;
+        chunk.word[3 * n + 2] = (int32_t)de_blocks;
+        if (b < n_buckets) {
+            const int64_t size = bucket_ptr[b + 1] - bucket_ptr[b];
+            pos_blocks += (size + fs.xpb - 1) / fs.xpb;
+            de_blocks += ((size + ds.by - 1) / ds.by + a.tiles_per_split - 1) / a.tiles_per_split * cand;
+            if (de_blocks > 0x3fffffffLL) return CCE_ERR_SHAPE;
+        }
+        if (++n == cce::kTabEntries || b == n_buckets) {
+            hipLaunchKernelGGL(cce::store_table_kernel, dim3(1), dim3(cce::kTabEntries), 0, stream, tab, chunk, n);
+            if (hipGetLastError() != hipSuccess) return CCE_ERR_HIP;
+            tab += 3 * n;
+            n = 0;
+        }
+    }
+    a.x_blocks = pos_blocks;
+    a.splits = cce::dense_splits(pos_blocks, (desc->K + fs.by - 1) / fs.by, L.u_rows < L.ms_rows ? L.u_rows : L.ms_rows, n_order);
+    if (cce::launch_dense(bf16, cce::DENSE_FDH, a, stream) != hipSuccess) return CCE_ERR_HIP;
+    a.x_blocks = cand;
+    a.splits = 1;
+    a.tile_blocks = de_blocks;
+    a.scatter_blocks = (n_order + cce::kDenseScatterPairs - 1) / cce::kDenseScatterPairs;
+    return cce::launch_dense(bf16, cce::DENSE_DE, a, stream) == hipSuccess ? CCE_OK : CCE_ERR_HIP;
 }
 
 cce_status cce_neg_sample(const cce_desc *desc, const cce_sampler *sampler, int32_t *neg_out, void *hip_stream)

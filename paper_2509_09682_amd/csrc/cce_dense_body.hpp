@@ -127,6 +127,9 @@ __device__ __forceinline__ int32_t dense_row(const DenseArgs &a, int64_t x)
     return (a.mask && a.mask[x] == 0) ? -1 : (int32_t)x;
 }
 
+// Target of the position in slot x (row `row`).
+__device__ __forceinline__ int32_t dense_tgt(const DenseArgs &a, int64_t x, int32_t row) { return a.tgt_slot ? a.tgt_slot[x] : a.tgt[row]; }
+
 // Bucket a block belongs to: largest b with start[b] <= block (start ascends, start[0] = 0, stride of 3 words).
 __device__ __forceinline__ int dense_bucket(const int32_t *start, int n, int32_t block)
 {
@@ -146,13 +149,13 @@ template <typename T, int CPL>
 __device__ __forceinline__ void dense_scatter_block(const DenseArgs &a, int64_t chunk, uint64_t *keys)
 {
     constexpr int BATCH = CPL <= 4 ? 16 : 8;  // rows in flight per wavefront
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int64_t n_pos = dense_slots(a), x = chunk * kDenseScatter + tid;
     if (chunk * kDenseScatter >= n_pos) return;
     uint64_t key = ~0ull;
     if (x < n_pos) {
         const int32_t row = dense_row(a, x);
-        if (row >= 0) key = ((uint64_t)(uint32_t)a.tgt[row] << 32) | (uint32_t)x;
+        if (row >= 0) key = ((uint64_t)(uint32_t)dense_tgt(a, x, row) << 32) | (uint32_t)x;
     }
     keys[tid] = key;
     __syncthreads();
@@ -328,7 +331,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
             if (a.validate && (xrow < 0 || (int64_t)xrow >= a.V)) xrow = -1;
         } else {
             xrow = dense_row(a, pos0 + x);
-            if (xrow >= 0) ti = a.tgt[xrow];
+            if (xrow >= 0) ti = dense_tgt(a, pos0 + x, xrow);
         }
     }
     const int dch = a.d * (int)sizeof(T) / 16;  // 16-byte chunks of a row
@@ -387,7 +390,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
             const int64_t at = a.by_slot ? pos0 + t * BY + e : (int64_t)row;
             const float g = a.g ? a.g[row] : 1.f;
             c.w = a.inv ? g * a.inv[at] : g;
-            c.ti = a.tgt[row];
+            c.ti = dense_tgt(a, pos0 + t * BY + e, row);
             if (c.w != 0.f) c.ref = a.ref[at];  // a zero factor keeps exp(-inf) = 0: no 0 * inf
         }
         return c;
@@ -692,7 +695,7 @@ __global__ __launch_bounds__(256) void dense_merge_kernel(DenseArgs a)
     if (MODE == DM_FWD) return;
     const bool to_dH = MODE == DM_DH || a.direct_dH;
     const float g = (to_dH && a.g) ? a.g[row] : 1.f;
-    const int32_t ti = a.tgt[row];
+    const int32_t ti = dense_tgt(a, x, row);
     for (int col = c * 4; col < a.d; col += 64) {
         float u[4] = {0.f, 0.f, 0.f, 0.f}, et[4];
         for (int k = 0; k < a.splits; ++k) {

@@ -90,6 +90,7 @@ struct DenseArgs {
     const uint8_t *mask;         // padding mask where nothing was compacted (nullable)
     const uint8_t *pos_mask;     // padding mask for the rows of dH (nullable)
     const int64_t *order;        // buckets: slot -> row; nullptr: no buckets
+    const int32_t *tgt_slot;     // buckets: target of a slot
     const int32_t *tab;          // buckets: [n_buckets + 1][3] first slot, first block of the position / candidate launch
     const float *lse_in, *g;
     float *loss, *lse;

@@ -96,3 +96,42 @@ def test_bad_ids_are_skipped():
         assert a["status"] == b["status"] == P.CCE_ERR_INDEX
         for name in ("loss", "lse", "dH", "dE"):
             assert np.max(np.abs(a[name] - b[name])) <= 1e-5 * np.max(np.abs(a[name])), name
+
+
+@pytest.mark.parametrize("sizes,K", [((1,), 1), ((0, 70, 0, 1, 33, 0), 31), ((5,) * 300 + (0, 900), 64), ((2000, 3), 700)])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("bf16", 320)])
+def test_buckets_of_any_size_in_one_launch(sizes, K, dtype, d):
+    """Empty, tiny and uneven buckets, more buckets than one table launch carries, lists that are split."""
+    import dataclasses
+
+    import torch
+
+    import paper_2509_09682_amd as P
+    from paper_2509_09682_amd.consumers import _one_launch
+    from paper_2509_09682_amd.runner import to_device
+    from workloads import NEG_PER_POSITION
+
+    M, n = sum(sizes), len(sizes)
+    N = M + 7
+    w = make_workload(f"dense_buckets_{n}_{dtype}_d{d}", 1, N, d, 1500, K, dtype, NEG_PER_POSITION, 31 + d, g_kind="random",
+                      e_sigma=0.1, tgt_dist="zipf")
+    assert _one_launch(P.CCE_F32 if dtype == "f32" else P.CCE_BF16, d, M, n, K)
+    rng = np.random.default_rng(3)
+    order = rng.permutation(N)[:M]
+    bucket_neg = rng.integers(0, w.V, size=(n, K)).astype(np.int32)
+    bucket_neg[:, 0] = w.tgt[rng.integers(0, N, size=n)]
+    ptr = np.concatenate([[0], np.cumsum(sizes)]).tolist()
+    rows = np.zeros((N, K), np.int32)
+    w.mask[:] = 0
+    for b in range(n):
+        rows[order[ptr[b]:ptr[b + 1]]] = bucket_neg[b]
+    w.mask[order] = 1
+    w = dataclasses.replace(w, neg=rows)
+    H, E, tgt, _, _ = to_device(w)
+    if dtype == "bf16":
+        H, E = H.view(torch.bfloat16), E.view(torch.bfloat16)
+    dE = torch.zeros((w.V, d), device="cuda")
+    loss, lse, dH = P.bucketed_step(H, E, tgt, torch.from_numpy(order).cuda(), ptr, torch.from_numpy(bucket_neg).cuda(),
+                                    torch.from_numpy(w.g).cuda(), dE)
+    out = dict(loss=loss.cpu().numpy(), lse=lse.cpu().numpy(), dH=dH.float().cpu().numpy(), dE=dE.cpu().numpy())
+    check_against_oracle(w, out, TOL, dH_tol=4e-3 if dtype == "bf16" else None)   # dH in bf16: half an ulp, 2^-9
