@@ -239,12 +239,12 @@ DenseLayout make_dense_layout(const cce_desc *d)
     DenseLayout L{};
     const size_t N = (size_t)d->N;
     // Shares of two tiles of candidates at least; partial rows up to what fills the chip (see dense_splits).
-    const int by = dense_shape(d->in_dtype == CCE_BF16, DENSE_FDH, d->d).by;
+    const int by = dense_tile_rows(d->in_dtype == CCE_BF16, d->d);
     const int64_t tiles = (((d->neg_mode == CCE_NEG_FULL) ? d->V : (int64_t)d->K) + by - 1) / by;
-    const int64_t shares = tiles / 2 > 1 ? tiles / 2 : 0;
+    const int64_t shares = tiles >= 4 ? tiles / 2 : 0;
     L.ms_rows = d->N * (shares < 128 ? shares : 128);
     if (L.ms_rows > kDensePartMs) L.ms_rows = kDensePartMs;
-    L.u_rows = d->N * (shares < 64 ? shares : 64);
+    L.u_rows = d->N * (shares < 16 ? shares : 16);
     if (L.u_rows > kDensePartRows) L.u_rows = kDensePartRows;
     size_t off = kHeaderBytes;
     L.idx = off;     off += align256(N * 4);
@@ -267,15 +267,33 @@ bool dense_compacts(const cce_desc *d, const uint8_t *mask)
     return d->validate_indices || (mask && d->N > kDenseCompactAbove && (reinterpret_cast<uintptr_t>(mask) & 15u) == 0);
 }
 
-// Ways to split the streamed range of `blocks` blocks so that the chip (two blocks per compute unit) is full, with two
-// tiles per share at least and partial results of at most `rows` rows.
-int dense_splits(int64_t blocks, int64_t tiles, int64_t rows, int64_t N)
+// Ways to split the streamed range of `blocks` blocks of the position side so that the chip's block slots are full, with
+// two tiles per share at least, at most 16 shares where each costs a row of partial sums, and partial results of at most
+// `rows` rows.
+int dense_splits(int64_t blocks, int64_t tiles, int slots, bool sums, int64_t rows, int64_t N)
 {
-    int64_t s = (512 + blocks - 1) / (blocks > 0 ? blocks : 1);
-    if (blocks > 320) s = 1;
+    if (blocks < 1 || blocks * 8 > (int64_t)slots * 5) return 1;
+    int64_t s = (slots + blocks - 1) / blocks;
+    if (sums && s > 16) s = 16;
     if (s > tiles / 2) s = tiles / 2;
     if (N > 0 && s > rows / N) s = rows / N;
     return s < 1 ? 1 : (int)s;
+}
+
+// Shares of the positions on the candidate side.  A share walks tiles / s tiles and adds its rows by atomics, which run
+// at 327 G/s over the chip whoever issues them: tile time tiles / s plus values s / 327 G/s is least at the root below.
+// Two blocks per compute unit at most, or four where a share stays long (measured, candidate launch in us: K = 2000,
+// d = 96, 2560 positions, bf16: 25 shares 46, 16 shares 37; K = 1024, d = 64, 10,240 positions, fp32: 32 shares 49,
+// 16 shares 57; K = 128, d = 256, 160 positions, fp32: one share 47, three 27; 9000 items, d = 192, fp32: 4 shares 466,
+// 8 shares 407).
+int64_t dense_shares(int64_t blocks, int64_t tiles, int64_t values, const DenseShape &sh)
+{
+    int64_t s = (512 + blocks - 1) / blocks;
+    if (tiles / (2 * s) >= 24) s *= 2;
+    const double best = sqrt((double)tiles * sh.tile_ns * 327.0 / (double)(values > 0 ? values : 1));
+    if ((double)s > best) s = (int64_t)best + 1;
+    if (s > tiles / 2) s = tiles / 2;
+    return s < 1 ? 1 : s;
 }
 
 DenseArgs make_dense_args(const cce_desc *d, const DenseLayout &L, const void *H, const void *E, const int32_t *tgt,
@@ -336,7 +354,8 @@ hipError_t dense_positions(const cce_desc *d, int pass, const DenseLayout &L, De
     if (d->N == 0) return hipSuccess;
     const DenseShape sh = dense_shape(d->in_dtype == CCE_BF16, pass, d->d);
     a.x_blocks = (d->N + sh.xpb - 1) / sh.xpb;
-    a.splits = dense_splits(a.x_blocks, (a.n_cols + sh.by - 1) / sh.by, pass == DENSE_FWD ? L.ms_rows : (L.u_rows < L.ms_rows ? L.u_rows : L.ms_rows), d->N);
+    const bool sums = pass != DENSE_FWD;
+    a.splits = dense_splits(a.x_blocks, (a.n_cols + sh.by - 1) / sh.by, sh.slots, sums, sums && L.u_rows < L.ms_rows ? L.u_rows : L.ms_rows, d->N);
     return launch_dense(d->in_dtype == CCE_BF16, pass, a, stream);
 }
 
@@ -347,9 +366,7 @@ hipError_t dense_candidates(const cce_desc *d, DenseArgs a, hipStream_t stream)
     const DenseShape sh = dense_shape(d->in_dtype == CCE_BF16, DENSE_DE, d->d);
     a.x_blocks = (a.n_cols + sh.xpb - 1) / sh.xpb;
     const int64_t tiles = (d->N + sh.by - 1) / sh.by;
-    int64_t s = (512 + a.x_blocks - 1) / a.x_blocks;
-    if (s > tiles / 4) s = tiles / 4;
-    a.splits = s < 1 ? 1 : (int)s;
+    a.splits = (int)dense_shares(a.x_blocks, tiles, a.n_cols * d->d, sh);
     a.tile_blocks = a.x_blocks * a.splits;
     a.scatter_blocks = (d->N + kDenseScatterPairs - 1) / kDenseScatterPairs;
     const int64_t per = 256 * kDenseScaleTurns;
@@ -893,13 +910,14 @@ cce_status cce_neg_bucketed_step(const cce_desc *desc, const void *H, const void
     a.dH = dH;
     a.dE = dE;
     // blocks of either side: whole blocks of positions per bucket, and per bucket (shares of its positions) x (blocks of
-    // its candidates), a share being as long as about two blocks per compute unit allow, four tiles at least
+    // its candidates), a share being as long as suits an average bucket
     const cce::DenseShape fs = cce::dense_shape(bf16, cce::DENSE_FDH, desc->d), ds = cce::dense_shape(bf16, cce::DENSE_DE, desc->d);
     const int64_t cand = (desc->K + ds.xpb - 1) / ds.xpb;
     int64_t tiles = 0;
     for (int64_t b = 0; b < n_buckets; ++b) tiles += (bucket_ptr[b + 1] - bucket_ptr[b] + ds.by - 1) / ds.by;
-    a.tiles_per_split = (tiles * cand + 511) / 512;
-    if (a.tiles_per_split < 4) a.tiles_per_split = 4;
+    const int64_t per_bucket = (tiles + n_buckets - 1) / n_buckets;  // of an average bucket
+    const int64_t shares = cce::dense_shares(cand * n_buckets, per_bucket, (int64_t)desc->K * desc->d * n_buckets, ds);
+    a.tiles_per_split = (per_bucket + shares - 1) / shares;
     int32_t *tab = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + L.total);
     a.tab = tab;
     int64_t pos_blocks = 0, de_blocks = 0;
@@ -923,7 +941,7 @@ cce_status cce_neg_bucketed_step(const cce_desc *desc, const void *H, const void
         }
     }
     a.x_blocks = pos_blocks;
-    a.splits = cce::dense_splits(pos_blocks, (desc->K + fs.by - 1) / fs.by, L.u_rows < L.ms_rows ? L.u_rows : L.ms_rows, n_order);
+    a.splits = cce::dense_splits(pos_blocks, (desc->K + fs.by - 1) / fs.by, fs.slots, true, L.u_rows < L.ms_rows ? L.u_rows : L.ms_rows, n_order);
     if (cce::launch_dense(bf16, cce::DENSE_FDH, a, stream) != hipSuccess) return CCE_ERR_HIP;
     a.x_blocks = cand;
     a.splits = 1;

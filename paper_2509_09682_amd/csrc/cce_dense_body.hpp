@@ -20,6 +20,7 @@
 // share the rows, each forms all scores and keeps 1/DS of the output columns (one score product more per wavefront
 // against three products of the second kind).
 #pragma once
+#include <atomic>
 #include <type_traits>
 
 #include "cce_device.hpp"
@@ -48,7 +49,7 @@ struct DenseGeo {
     static constexpr int DS = MODE == DM_FWD ? 1 : B16 ? (KD <= 6 ? 1 : (KD <= 12 ? 2 : 4)) : (KD <= 10 ? 1 : 2);
     static constexpr int NW = kDenseThreads / 64;
     static constexpr int XPB = NW / DS * XR;  // stationary rows per block
-    static constexpr int BY = B16 ? 32 : (KD <= 8 ? 32 : 16);  // streamed rows per tile
+    static constexpr int BY = dense_tile_rows(B16, KD * 32);    // streamed rows per tile
     static constexpr int CPR = KD * 2 * (int)sizeof(T);        // 16-byte chunks of a padded row
     // LDS row pitch in chunks.  Odd: the 128-bit operand reads of 16 consecutive rows fall on 16 different chunk slots.
     // Not 1 or 15 modulo 16 for bf16: the transpose reads (4 rows x 4 chunks at once) then meet at most two to a slot.
@@ -664,12 +665,15 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
     }
 }
 
-// Combines the shares of a split position side: 16 threads a position, four columns each and turn.
+// Combines the shares of a split position side: one thread per position and four columns, so that a small batch still
+// spreads over the chip (1000 positions, d = 512, 32 shares, sixteen threads a position: 48 us, all of it latency).
 template <typename T, int MODE>
 __global__ __launch_bounds__(256) void dense_merge_kernel(DenseArgs a)
 {
-    const int64_t x = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-    const int c = threadIdx.x & 15;
+    const int cpr = MODE == DM_FWD ? 1 : a.d / 4;
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t x = e / cpr;
+    const int c = (int)(e % cpr);
     if (x >= dense_slots(a)) return;
     const int32_t row = dense_row(a, x);
     if (row < 0) {
@@ -677,10 +681,20 @@ __global__ __launch_bounds__(256) void dense_merge_kernel(DenseArgs a)
         return;
     }
     float M = -INFINITY, sn = 0.f;
+#pragma unroll 4
     for (int k = 0; k < a.splits; ++k) M = fmaxf(M, a.part_ms[k * a.N + x].x);
+    float u[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
     for (int k = 0; k < a.splits; ++k) {
         const float2 ms = a.part_ms[k * a.N + x];
-        sn += ms.y * fast_exp(ms.x - M);
+        const float sc = MODE == DM_DH ? 1.f : fast_exp(ms.x - M);
+        sn += ms.y * sc;
+        if (MODE != DM_FWD) {
+            float pv[4];
+            widen4(a.part_U + (k * a.N + x) * a.d + c * 4, pv);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) u[r] = fmaf(pv[r], sc, u[r]);
+        }
     }
     const float op = a.part_o[x];
     float inv = 1.f, ct;
@@ -695,22 +709,12 @@ __global__ __launch_bounds__(256) void dense_merge_kernel(DenseArgs a)
     if (MODE == DM_FWD) return;
     const bool to_dH = MODE == DM_DH || a.direct_dH;
     const float g = (to_dH && a.g) ? a.g[row] : 1.f;
-    const int32_t ti = dense_tgt(a, x, row);
-    for (int col = c * 4; col < a.d; col += 64) {
-        float u[4] = {0.f, 0.f, 0.f, 0.f}, et[4];
-        for (int k = 0; k < a.splits; ++k) {
-            const float sc = MODE == DM_DH ? 1.f : fast_exp(a.part_ms[k * a.N + x].x - M);
-            float pv[4];
-            widen4(a.part_U + (k * a.N + x) * a.d + col, pv);
+    float et[4];
+    widen4(static_cast<const T *>(a.E) + (int64_t)dense_tgt(a, x, row) * a.d + c * 4, et);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) u[r] = fmaf(pv[r], sc, u[r]);
-        }
-        widen4(static_cast<const T *>(a.E) + (int64_t)ti * a.d + col, et);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) u[r] = g * fmaf(ct, et[r], u[r] * inv);
-        if (to_dH) store_dH4(a, row, col, u);
-        else *reinterpret_cast<float4 *>(a.U + (int64_t)row * a.d + col) = make_float4(u[0], u[1], u[2], u[3]);
-    }
+    for (int r = 0; r < 4; ++r) u[r] = g * fmaf(ct, et[r], u[r] * inv);
+    if (to_dH) store_dH4(a, row, c * 4, u);
+    else *reinterpret_cast<float4 *>(a.U + (int64_t)row * a.d + c * 4) = make_float4(u[0], u[1], u[2], u[3]);
 }
 
 template <typename T, int KD>
@@ -735,19 +739,43 @@ hipError_t launch_dense_kd(int pass, DenseArgs a, hipStream_t stream)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.splits == 1) return e;
     ProfScope prof(PROF_DENSE_MERGE, stream);
-    const dim3 mgrid((unsigned)((a.N + 15) / 16));
+    const int64_t merged = a.N * (pass == DENSE_FWD ? 1 : a.d / 4);
+    const dim3 mgrid((unsigned)((merged + 255) / 256));
     if (pass == DENSE_FWD) hipLaunchKernelGGL((dense_merge_kernel<T, DM_FWD>), mgrid, dim3(256), 0, stream, a);
     else if (pass == DENSE_FDH) hipLaunchKernelGGL((dense_merge_kernel<T, DM_FDH>), mgrid, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL((dense_merge_kernel<T, DM_DH>), mgrid, dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 
+// Shape of a pass and the blocks of it that the current device holds at once, asked once per kernel and device.
+template <typename T, int KD, int MODE>
+DenseShape dense_shape_mode()
+{
+    typedef DenseGeo<T, KD, MODE> G;
+    constexpr int kMaxDevices = 64;
+    static std::atomic<int> cache[kMaxDevices];  // 0 = not asked yet
+    int per_cu = 0, dev = 0, cus = 0, slots = 512;
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) {
+        const int known = cache[dev].load(std::memory_order_relaxed);
+        if (known > 0) {
+            slots = known;
+        } else if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0 &&
+                   hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, dense_kernel<T, KD, MODE>, kDenseThreads, 0) == hipSuccess && per_cu > 0) {
+            slots = per_cu * cus;
+            cache[dev].store(slots, std::memory_order_relaxed);
+        }
+    }
+    // matrix instructions of a tile, 32 cycles each, two wavefronts to a SIMD at 2.4 GHz
+    constexpr int insts = G::B16 ? 2 * KD + 6 * G::OB : G::BY / 16 * (8 * KD + 4 * G::OB);
+    return DenseShape{G::XPB, G::BY, slots, insts * 64 * 10 / 24};
+}
 template <typename T, int KD>
 DenseShape dense_shape_kd(int pass)
 {
-    typedef DenseGeo<T, KD, DM_FWD> F;
-    typedef DenseGeo<T, KD, DM_FDH> B;
-    return pass == DENSE_FWD ? DenseShape{F::XPB, F::BY} : DenseShape{B::XPB, B::BY};
+    if (pass == DENSE_FWD) return dense_shape_mode<T, KD, DM_FWD>();
+    if (pass == DENSE_FDH) return dense_shape_mode<T, KD, DM_FDH>();
+    if (pass == DENSE_DH) return dense_shape_mode<T, KD, DM_DH>();
+    return dense_shape_mode<T, KD, DM_DE>();
 }
 
 template <typename T, typename F>
