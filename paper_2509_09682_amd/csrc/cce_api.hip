@@ -58,7 +58,7 @@ Layout make_layout(const cce_desc *d)
     const int64_t xblocks = (N + 127) / 128;
     int sx = (xblocks > 0 && xblocks <= 320) ? (int)(2048 / xblocks) : 1;  // the launcher never splits above 320 blocks
     const int64_t col_tiles = (n_cols + by - 1) / by;
-    if (sx > 16) sx = 16;
+    if (sx > 64) sx = 64;  // few positions against a catalogue: 64 shares fill the chip
     if (sx > col_tiles / 2) sx = (int)(col_tiles / 2);
     if (sx < 1) sx = 1;
     L.splits_x = sx;

@@ -1441,16 +1441,20 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(TileArgs a)
     op += __shfl_xor(op, 1, 64);
     op += __shfl_xor(op, 2, 64);
     op += __shfl_xor(op, 4, 64);
-    if (ok && c == 0) {
-        float m = -INFINITY, s = 0.f;
-        for (int sp = 0; sp < a.splits; ++sp) {
-            const float m2 = a.part_m[(int64_t)sp * a.N + x], s2 = a.part_s[(int64_t)sp * a.N + x];
-            const float M = fmaxf(m, m2);
-            if (M > -INFINITY) {
-                s = s * __builtin_amdgcn_exp2f(m - M) + s2 * __builtin_amdgcn_exp2f(m2 - M);
-                m = M;
-            }
+    float m = -INFINITY, s = 0.f;
+    auto merge = [&](float m2, float s2) {
+        const float M = fmaxf(m, m2);
+        if (M > -INFINITY) {
+            s = s * __builtin_amdgcn_exp2f(m - M) + s2 * __builtin_amdgcn_exp2f(m2 - M);
+            m = M;
         }
+    };
+    if (ok) {  // the parts are dealt to the eight lanes: with up to 64 of them one lane's walk is a chain of latencies
+        for (int sp = c; sp < a.splits; sp += 8) merge(a.part_m[(int64_t)sp * a.N + x], a.part_s[(int64_t)sp * a.N + x]);
+    }
+#pragma unroll
+    for (int off = 1; off < 8; off <<= 1) merge(__shfl_xor(m, off, 64), __shfl_xor(s, off, 64));
+    if (ok && c == 0) {
         const float w = a.pos_weight_mode == 2 ? 0.f : (a.cnt ? 1.f - (float)a.cnt[row] : 1.f);
         const float o2 = op * kLog2e;
         const float M = (w != 0.f) ? fmaxf(m, o2) : m;
@@ -1495,6 +1499,7 @@ __global__ __launch_bounds__(256) void dh_merge_kernel(TileArgs a)
         load8(a.E + (int64_t)a.tgt[row] * D + c * 8, e);
 #pragma unroll
         for (int t = 0; t < 8; ++t) op = fmaf(h[t], e[t], op);
+#pragma unroll 4
         for (int sp = 0; sp < splits; ++sp) {
             float v[8];
             load8(a.part_dH + ((int64_t)sp * part_rows + (x - part_x0)) * D + c * 8, v);
@@ -1558,15 +1563,22 @@ __global__ __launch_bounds__(256) void fdh_merge_kernel(TileArgs a)
         load8(a.E + (int64_t)a.tgt[row] * D + c * 8, e);
 #pragma unroll
         for (int t = 0; t < 8; ++t) op = fmaf(h[t], e[t], op);
+#pragma unroll 4
         for (int sp = 0; sp < splits; ++sp) M = fmaxf(M, a.part_m[(int64_t)sp * part_rows + (x - part_x0)]);
+#pragma unroll 4
         for (int sp = 0; sp < splits; ++sp) {
             const int64_t slot = (int64_t)sp * part_rows + (x - part_x0);
             const float ms = a.part_m[slot];
-            if (ms == -INFINITY) continue;  // a part without candidates
-            const float sc = __builtin_amdgcn_exp2f(ms - M);
-            l = fmaf(a.part_s[slot], sc, l);
+            const bool empty = ms == -INFINITY;  // a part without candidates: nothing was written there
+            const float sc = empty ? 0.f : __builtin_amdgcn_exp2f(ms - M);
+            const float ls = a.part_s[slot];
+            l = empty ? l : fmaf(ls, sc, l);
             float v[8];
             load8(a.part_dH + slot * D + c * 8, v);
+            if (empty) {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) v[t] = 0.f;
+            }
 #pragma unroll
             for (int t = 0; t < 8; ++t) sum[t] = fmaf(v[t], sc, sum[t]);
         }
@@ -1667,7 +1679,14 @@ int64_t plan_tile_grid(TileArgs &a, int64_t n_x, int xpb, int threads, int slots
     if (MODE == MODE_DE) {
         // every split of the position range pays n_cols * d atomics: keep them below about a quarter of the matrix
         // time of the pass (4 n_cols d N flop at ~1 PFLOP/s against ~300 G atomics/s) => splits <= 3e-4 N
-        const int cap = (int)(a.N * 5e-4) < 8 ? 8 : (int)(a.N * 5e-4);
+        int cap = (int)(a.N * 5e-4) < 8 ? 8 : (int)(a.N * 5e-4);
+        if (a.d > 128) {
+            // hidden size 256, one block of 256 candidates per compute unit: a short list gives few blocks, and the cap
+            // above left the chip idle.  Tile time tiles / s (2.1 us a tile) plus atomics s n_cols d / 327 G/s is least
+            // at the root (511 candidates, 24,576 positions: 16 splits 93 us)
+            const double best = sqrt((double)(a.N / 32) * 2100.0 * 327.0 / ((double)a.n_cols * a.d));
+            if ((double)cap < best) cap = (int)best;
+        }
         if (a.splits > cap) a.splits = cap;
     }
     const int max_splits = a.splits;
