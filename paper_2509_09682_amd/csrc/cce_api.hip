@@ -8,6 +8,7 @@
 
 #include "cce_device.hpp"
 #include "cce_kernels.hpp"
+#include "cce_scatter.hpp"
 #include "cce_tile_shared.hpp"
 
 namespace cce {
@@ -368,7 +369,7 @@ hipError_t dense_candidates(const cce_desc *d, DenseArgs a, hipStream_t stream)
     const int64_t tiles = (d->N + sh.by - 1) / sh.by;
     a.splits = (int)dense_shares(a.x_blocks, tiles, a.n_cols * d->d, sh);
     a.tile_blocks = a.x_blocks * a.splits;
-    a.scatter_blocks = (d->N + kDenseScatterPairs - 1) / kDenseScatterPairs;
+    a.scatter_blocks = pos_scatter_blocks(d->N);
     const int64_t per = 256 * kDenseScaleTurns;
     if (a.U || a.pos_mask || a.validate) a.scale_blocks = (d->N * (d->d / 4) + per - 1) / per;
     return launch_dense(d->in_dtype == CCE_BF16, DENSE_DE, a, stream);
@@ -946,7 +947,7 @@ cce_status cce_neg_bucketed_step(const cce_desc *desc, const void *H, const void
     a.x_blocks = cand;
     a.splits = 1;
     a.tile_blocks = de_blocks;
-    a.scatter_blocks = (n_order + cce::kDenseScatterPairs - 1) / cce::kDenseScatterPairs;
+    a.scatter_blocks = cce::pos_scatter_blocks(n_order);
     return cce::launch_dense(bf16, cce::DENSE_DE, a, stream) == hipSuccess ? CCE_OK : CCE_ERR_HIP;
 }
 

@@ -25,6 +25,7 @@
 
 #include "cce_device.hpp"
 #include "cce_kernels.hpp"
+#include "cce_scatter.hpp"
 
 namespace cce {
 namespace {
@@ -38,7 +39,7 @@ typedef ds16x4 __attribute__((address_space(3))) *dlds_v4;
 enum { DM_FWD = 0, DM_FDH = 1, DM_DH = 2, DM_DE = 3 };
 
 constexpr int kDenseThreads = 256;
-constexpr int kDenseScatter = kDenseScatterPairs;
+constexpr int kDenseScatter = kPosChunk;
 constexpr float kRescaleAbove = 20.f;  // a score this far above the reference moves it (weights stay below e^20)
 
 // KD: hidden size rounded up, in units of 32.
@@ -143,14 +144,14 @@ __device__ __forceinline__ int dense_bucket(const int32_t *start, int n, int32_t
     return lo;
 }
 
-// dE of the correct items: as pos_scatter_block, for any hidden size and either type.  A block sorts 256 (target, slot)
-// pairs in LDS, a wavefront walks 64 of them, sums runs of equal targets and adds one row per run: a hot target then
-// costs one same-address atomic (about 25 ns each) per block instead of one per position.
+// dE of the correct items: as pos_scatter_block (see there), for any hidden size and either type.
 template <typename T, int CPL>
-__device__ __forceinline__ void dense_scatter_block(const DenseArgs &a, int64_t chunk, uint64_t *keys)
+__device__ __forceinline__ void dense_scatter_block(const DenseArgs &a, int64_t block, uint64_t *keys)
 {
     constexpr int BATCH = CPL <= 4 ? 16 : 8;  // rows in flight per wavefront
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int parts = pos_parts(a.N), part = (int)(block % parts), pairs = 64 / parts;
+    const int64_t chunk = block / parts;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t n_pos = dense_slots(a), x = chunk * kDenseScatter + tid;
     if (chunk * kDenseScatter >= n_pos) return;
     uint64_t key = ~0ull;
@@ -173,7 +174,7 @@ __device__ __forceinline__ void dense_scatter_block(const DenseArgs &a, int64_t 
             __syncthreads();
         }
     }
-    const uint64_t mine = keys[tid];
+    const uint64_t mine = keys[(part * (kDenseScatter / 64) + wave) * pairs + (lane & (pairs - 1))];
     const uint32_t my_id = (uint32_t)(mine >> 32), my_x = (uint32_t)mine;
     int32_t my_row = 0;
     float my_cf = 0.f;
@@ -194,7 +195,7 @@ __device__ __forceinline__ void dense_scatter_block(const DenseArgs &a, int64_t 
         }
     };
     const T *Hp = static_cast<const T *>(a.H);
-    for (int b = 0; b < 64; b += BATCH) {
+    for (int b = 0; b < pairs; b += BATCH) {
         float hv[BATCH][CPL];
         uint32_t id[BATCH];
 #pragma unroll

@@ -269,7 +269,7 @@ __global__ __launch_bounds__(kThreads) void part_scatter_kernel(InvertArgs a, Ti
     __shared__ int32_t cur[kMaxBuckets];
     static_assert(kThreads == kPosChunk && kMaxBuckets * 4 >= kPosChunk * 8, "the scatter role sorts 256 keys in this array");
     if (D_SC != 0 && (int64_t)blockIdx.x < sc_blocks) {
-        pos_scatter_block<(D_SC != 0 ? D_SC : 64)>(sc, (int64_t)blockIdx.x, reinterpret_cast<uint64_t *>(cur));
+        pos_scatter_block<(D_SC != 0 ? D_SC : 64)>(sc, (int64_t)blockIdx.x, reinterpret_cast<uint64_t *>(cur), pos_parts(sc.N));
         return;
     }
     // Buckets of this slice: the block's cursor starts at the block's scanned offset inside the bucket, moved to where
@@ -666,7 +666,7 @@ hipError_t launch_inverted_dE(bool bf16, const InvertArgs &a_in, const TileArgs 
         {
             ProfScope prof(PROF_INDEX, stream);
             if (scatter && j == 0) {  // the correct items' rows ride at the head of the first filing launch
-                const int64_t sc_blocks = (scatter->N + kPosChunk - 1) / kPosChunk;
+                const int64_t sc_blocks = pos_scatter_blocks(scatter->N);
                 const dim3 grid((unsigned)(a.n_part_blocks + sc_blocks));
                 switch (scatter->d) {
                 case 64: hipLaunchKernelGGL(part_scatter_kernel<64>, grid, dim3(kThreads), 0, stream, a, *scatter, sc_blocks); break;

@@ -116,7 +116,6 @@ struct DenseShape { int xpb, by, slots, tile_ns; };  // stationary rows per bloc
                                                      // once, about what a tile takes
 enum { DENSE_FWD = 0, DENSE_FDH = 1, DENSE_DH = 2, DENSE_DE = 3 };
 constexpr int kDenseScaleTurns = 4;
-constexpr int kDenseScatterPairs = 256;
 hipError_t launch_dense(bool bf16, int pass, const DenseArgs &a, hipStream_t stream);
 DenseShape dense_shape(bool bf16, int pass, int d);
 constexpr int dense_tile_rows(bool bf16, int d) { return bf16 || d <= 256 ? 32 : 16; }  // streamed rows per tile

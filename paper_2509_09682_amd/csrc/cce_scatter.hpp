@@ -10,17 +10,33 @@ __device__ __forceinline__ int64_t pos_row(const TileArgs &a, int64_t x) { retur
 
 // dE of the correct items: dE[tgt_i] += coef_i * H_i.  Targets follow a power law, so plain atomics would serialise
 // on a few hot rows (an atomic on one address completes every ~25 ns).  A block sorts 256 (target, position) pairs in
-// LDS; every wavefront then walks 64 consecutive sorted pairs with lane = column, sums runs of equal targets in
+// LDS; every wavefront then walks up to 64 consecutive sorted pairs with lane = column, sums runs of equal targets in
 // registers and issues one row of atomics per run.  These blocks ride at the head of another launch (the dE pass of the
 // matrix-core path, the second index pass of the per-position path), so that their latency (sort, dependent gathers)
-// hides under that launch's own work.  Where the scatter is a launch of its own a block sorts 1024 pairs: longer runs
-// of equal targets, fewer rows of atomics (largest workload: 60 k instead of 78 k).
-constexpr int kPosChunk = 256;        // pairs per block riding in another launch
-constexpr int kPosChunkApart = 1024;  // pairs per block of the stand-alone scatter kernels
+// hides under that launch's own work.
+//
+// A block is a chain of latencies: vector-memory operations complete in order, so the rows of a batch wait for the
+// atomics of the batch before (a wavefront with four batches of 16 rows: 31 us at d = 256, whatever else runs).  With
+// few chunks kPosParts blocks therefore sort the same pairs and take a share each, one batch per wavefront (13 us);
+// runs of equal targets are cut more often that way, and the blocks take slots, so many chunks go whole.  Where the
+// scatter is a launch of its own, many chunks are of 1024 pairs: longer runs, fewer rows of atomics (largest workload:
+// 60 k instead of 78 k).  Launch with the dH scaling at d = 256, us, whole 1024 / shared 256: 1000 positions 45 / 13,
+// 3200: 52 / 15, 32,768: 53 / 34, 65,536: 66 / 62, 204,800: 202 / 213.
+constexpr int kPosChunk = 256;        // pairs per chunk
+constexpr int kPosChunkApart = 1024;  // pairs per chunk of the stand-alone scatter kernels with many positions
+constexpr int kPosParts = 4;
+constexpr int64_t kPosApartAbove = 65536;  // stand-alone: positions from which chunks are long and whole
+constexpr int64_t kPosShareBelow = 8192;   // riding in another launch: positions up to which blocks share a chunk (dE launch,
+                                           // whole / shared: 3200 positions, d = 64: 19 / 14 us; 8000, d = 320: 100 / 52;
+                                           // 25,600, d = 128: 56 / 61)
+__host__ __device__ inline int pos_parts(int64_t N) { return N <= kPosShareBelow ? kPosParts : 1; }
+inline int64_t pos_scatter_blocks(int64_t N) { return (N + kPosChunk - 1) / kPosChunk * pos_parts(N); }
 
 template <int D, int CHUNK = kPosChunk>
-__device__ __forceinline__ void pos_scatter_block(const TileArgs &a, int64_t chunk, uint64_t *keys)
+__device__ __forceinline__ void pos_scatter_block(const TileArgs &a, int64_t block, uint64_t *keys, int parts)
 {
+    const int64_t chunk = block / parts;
+    const int part = (int)(block % parts), pairs = 64 / parts;  // pairs per wavefront
     constexpr int CPL = D / 64;         // columns per lane
     constexpr int kPosBatch = 16;        // rows in flight per wavefront
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -69,11 +85,11 @@ __device__ __forceinline__ void pos_scatter_block(const TileArgs &a, int64_t chu
             }
         }
     };
-    // lane l holds pair l of the wavefront's 64 sorted pairs and its coefficient; the walk broadcasts them lane by lane
-    const uint64_t my_key = keys[wave * 64 + lane];
+    // lane l holds pair l of the wavefront's sorted pairs and its coefficient; the walk broadcasts them lane by lane
+    const uint64_t my_key = keys[(part * (CHUNK / 64) + wave) * pairs + (lane & (pairs - 1))];
     const uint32_t my_id = (uint32_t)(my_key >> 32), my_row = (uint32_t)my_key;
     const float my_cf = (my_id != 0xffffffffu) ? a.coef[my_row] * ((a.g_separate && a.g) ? a.g[my_row] : 1.f) : 0.f;
-    for (int b = 0; b < 64; b += kPosBatch) {
+    for (int b = 0; b < pairs; b += kPosBatch) {
         uint32_t id[kPosBatch];
         float hv[kPosBatch][CPL];
 #pragma unroll

@@ -318,7 +318,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
 
     if (MODE == MODE_DE && block_id < a.pos_blocks) {  // leading blocks: scatter of the correct items
         static_assert(NW * 64 >= kPosChunk, "the scatter role needs 256 threads");
-        pos_scatter_block<D>(a, block_id, reinterpret_cast<uint64_t *>(buf0));
+        pos_scatter_block<D>(a, block_id, reinterpret_cast<uint64_t *>(buf0), pos_parts(a.N));
         return;
     }
     if (MODE == MODE_DE && a.scale_blocks > 0 && block_id >= a.scale_block0) {  // trailing blocks: dH = grad_loss * U
@@ -1694,7 +1694,7 @@ int64_t plan_tile_grid(TileArgs &a, int64_t n_x, int xpb, int threads, int slots
     if (fine && a.splits > 1) a.splits = max_splits;
     int64_t blocks = xblocks * a.splits;
     if (MODE == MODE_DE) {  // the latency-bound scatter blocks go first so that they run under the matrix work
-        a.pos_blocks = a.scatter_apart ? 0 : (a.N + kPosChunk - 1) / kPosChunk;
+        a.pos_blocks = a.scatter_apart ? 0 : pos_scatter_blocks(a.N);
         blocks += a.pos_blocks;
     }
     if (MODE == MODE_DH) {
@@ -1909,26 +1909,26 @@ hipError_t launch_bwd_for_d(TileArgs a_dh, TileArgs a_de, hipStream_t stream)
 
 }  // namespace
 
-template <int D>
-__global__ __launch_bounds__(kPosChunkApart) void pos_scatter_kernel(TileArgs a)
+template <int D, int CHUNK>
+__global__ __launch_bounds__(CHUNK) void pos_scatter_kernel(TileArgs a)
 {
-    __shared__ uint64_t keys[kPosChunkApart];
-    pos_scatter_block<D, kPosChunkApart>(a, blockIdx.x, keys);
+    __shared__ uint64_t keys[CHUNK];
+    pos_scatter_block<D, CHUNK>(a, blockIdx.x, keys, CHUNK == kPosChunk ? kPosParts : 1);
 }
 
 // The correct-item scatter and the scaling dH = grad_loss * U in one launch (hidden size 256, where neither rides in
 // the dE launch): the scatter is bound by latencies and atomics, the scaling by memory bandwidth, and they share no
 // data, so side by side they take about as long as the scatter alone.  The scaling blocks also file grad_loss under the
 // compacted index for the dE pass that follows.
-template <int D>
-__global__ __launch_bounds__(kPosChunkApart) void pos_scatter_scale_kernel(TileArgs a, int64_t scatter_blocks)
+template <int D, int CHUNK>
+__global__ __launch_bounds__(CHUNK) void pos_scatter_scale_kernel(TileArgs a, int64_t scatter_blocks)
 {
-    __shared__ uint64_t keys[kPosChunkApart];
+    __shared__ uint64_t keys[CHUNK];
     if ((int64_t)blockIdx.x < scatter_blocks) {
-        pos_scatter_block<D, kPosChunkApart>(a, blockIdx.x, keys);
+        pos_scatter_block<D, CHUNK>(a, blockIdx.x, keys, CHUNK == kPosChunk ? kPosParts : 1);
         return;
     }
-    const int64_t chunk = ((int64_t)blockIdx.x - scatter_blocks) * kPosChunkApart + threadIdx.x;
+    const int64_t chunk = ((int64_t)blockIdx.x - scatter_blocks) * CHUNK + threadIdx.x;
     const int64_t n_pos = a.n_valid_ptr ? (int64_t)*a.n_valid_ptr : a.N;
     if (chunk < n_pos) a.de_const[a.N + chunk] = __float_as_uint(a.g ? a.g[pos_row(a, chunk)] : 1.f);
     dh_scale_chunk<D>(a, chunk);
@@ -1938,11 +1938,14 @@ template <int D>
 hipError_t launch_pos_scatter_scale_d(const TileArgs &a, hipStream_t stream)
 {
     if (a.N == 0) return hipSuccess;
-    const int64_t scatter_blocks = (a.N + kPosChunkApart - 1) / kPosChunkApart;
-    const int64_t scale_blocks = (a.N * (D / 8) + kPosChunkApart - 1) / kPosChunkApart;
+    const bool whole = a.N > kPosApartAbove;
+    const int threads = whole ? kPosChunkApart : kPosChunk;
+    const int64_t scatter_blocks = (a.N + threads - 1) / threads * (whole ? 1 : kPosParts);
+    const int64_t scale_blocks = (a.N * (D / 8) + threads - 1) / threads;
     ProfScope prof(PROF_POS_SCATTER, stream);
-    hipLaunchKernelGGL((pos_scatter_scale_kernel<D>), dim3((unsigned)(scatter_blocks + scale_blocks)), dim3(kPosChunkApart), 0, stream, a,
-                       scatter_blocks);
+    const dim3 grid((unsigned)(scatter_blocks + scale_blocks));
+    if (whole) hipLaunchKernelGGL((pos_scatter_scale_kernel<D, kPosChunkApart>), grid, dim3(kPosChunkApart), 0, stream, a, scatter_blocks);
+    else hipLaunchKernelGGL((pos_scatter_scale_kernel<D, kPosChunk>), grid, dim3(kPosChunk), 0, stream, a, scatter_blocks);
     return hipGetLastError();
 }
 
@@ -1961,9 +1964,12 @@ template <int D>
 hipError_t launch_pos_scatter_d(const TileArgs &a, hipStream_t stream)
 {
     if (a.N == 0) return hipSuccess;
-    const dim3 grid((unsigned)((a.N + kPosChunkApart - 1) / kPosChunkApart)), block(kPosChunkApart);
+    const bool whole = a.N > kPosApartAbove;
+    const int threads = whole ? kPosChunkApart : kPosChunk;
+    const dim3 grid((unsigned)((a.N + threads - 1) / threads * (whole ? 1 : kPosParts)));
     ProfScope prof(PROF_POS_SCATTER, stream);
-    hipLaunchKernelGGL((pos_scatter_kernel<D>), grid, block, 0, stream, a);
+    if (whole) hipLaunchKernelGGL((pos_scatter_kernel<D, kPosChunkApart>), grid, dim3(kPosChunkApart), 0, stream, a);
+    else hipLaunchKernelGGL((pos_scatter_kernel<D, kPosChunk>), grid, dim3(kPosChunk), 0, stream, a);
     return hipGetLastError();
 }
 
