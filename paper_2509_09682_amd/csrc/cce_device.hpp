@@ -138,6 +138,27 @@ __device__ __forceinline__ float load1(const uint16_t *p) { return __uint_as_flo
 __device__ __forceinline__ float fast_exp(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
 __device__ __forceinline__ float fast_log(float x) { return __builtin_amdgcn_logf(x) * kLn2; }
 
+// Sum over groups of LPR consecutive lanes, in every lane of the group; all lanes of the wavefront take part.  Within
+// sixteen lanes the partners come through the data-parallel primitives of the add itself: neighbour, neighbour pair,
+// mirror of eight, mirror of sixteen.  (As LDS permutes, four a score, they were a third of what the row-gather passes
+// wait for.)
+template <int CTRL>
+__device__ __forceinline__ float add_dpp(float v)
+{
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int LPR>
+__device__ __forceinline__ float group_sum(float v)
+{
+    if (LPR >= 2) v = add_dpp<0xb1>(v);    // quad_perm [1,0,3,2]
+    if (LPR >= 4) v = add_dpp<0x4e>(v);    // quad_perm [2,3,0,1]
+    if (LPR >= 8) v = add_dpp<0x141>(v);   // row_half_mirror
+    if (LPR >= 16) v = add_dpp<0x140>(v);  // row_mirror
+#pragma unroll
+    for (int off = 16; off < LPR; off <<= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
 // Merge two (max, sum-of-exp) pairs of an online softmax; either may be the empty pair (-inf, 0).
 __device__ __forceinline__ void lse_merge(float &m, float &s, float m2, float s2)
 {

@@ -56,14 +56,6 @@ __device__ __forceinline__ void refill_window(const Params &p, int64_t i, int64_
     __builtin_amdgcn_wave_barrier();
 }
 
-template <int LPR>
-__device__ __forceinline__ float group_sum(float v)
-{
-#pragma unroll
-    for (int off = 1; off < LPR; off <<= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 // Candidate j of position i: id, whether it is the correct item, whether it takes part.
 struct Cand {
     int64_t id;

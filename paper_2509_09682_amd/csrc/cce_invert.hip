@@ -422,8 +422,7 @@ __device__ __forceinline__ void walk_segment(const InvertArgs &a, const float (&
             float part = 0.f;
 #pragma unroll
             for (int t = 0; t < 8; ++t) part = fmaf(h[t], e[t], part);
-#pragma unroll
-            for (int off = 1; off < LPR; off <<= 1) part += __shfl_xor(part, off, 64);  // partners share the item
+            part = group_sum<LPR>(part);  // the lanes of a group share the item
             const float G = (pos[u] >= 0) ? g[u] * fast_exp(part - lse[u]) : 0.f;
 #pragma unroll
             for (int t = 0; t < 8; ++t) acc[t] = fmaf(G, h[t], acc[t]);
