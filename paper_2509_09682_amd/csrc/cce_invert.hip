@@ -389,14 +389,16 @@ __global__ __launch_bounds__(kScanThreads) void bucket_sort_kernel(InvertArgs a)
     }
 }
 
-// Walks the positions filed in pairs[r, r_end) for the item whose row e the lane group holds, kInFlight at a time:
+// Walks the positions filed in pairs[r, r_end) for the item whose row e the lane group holds, four at a time:
 // recomputes each score against the hidden state (L2-resident), forms g exp(o - lse) and adds G h to acc.
 // Every lane of the wavefront calls it (the loop condition is a wavefront vote, the scalar products use shuffles).
 template <typename T, int LPR>
 __device__ __forceinline__ void walk_segment(const InvertArgs &a, const float (&e)[8], int32_t r, int32_t r_end, bool col_ok,
                                              int c, float (&acc)[8])
 {
-    constexpr int U = RawChunk<T>::kInFlight;
+    // Four rows in flight: segments are short (6.5 pairs on average on the per-position workload) and the lane groups of a
+    // wavefront go in step, so that a batch of eight was half empty (item pass 480 -> 450 us).
+    constexpr int U = 4;
     const T *Hp = static_cast<const T *>(a.H);
     while (__any(r < r_end)) {
         int32_t pos[U];
@@ -433,9 +435,10 @@ __device__ __forceinline__ void walk_segment(const InvertArgs &a, const float (&
 
 // An item sampled by more than kHotPairs positions (popularity-weighted negatives: the head of the law collects
 // percents of all pairs) would keep one lane group walking for milliseconds.  Its segment is cut into chunks of
-// kHotPairs instead, filed in a work list, and hot_item_kernel spreads the chunks over the chip and adds their partial
-// rows with atomics (d atomics per kHotPairs pairs).
+// kHotChunk instead, filed in a work list, and hot_item_kernel spreads the chunks over the chip, one block each, and
+// adds their partial rows with atomics (d atomics per chunk).
 constexpr int kHotPairs = 256;
+constexpr int kHotChunk = 1024;
 constexpr int kItemBlocks = 16384;  // grid of the item pass over a slice
 
 // One group of LPR lanes per item: e_v stays in registers, the positions that sampled it are walked four at a time.
@@ -465,13 +468,13 @@ __global__ __launch_bounds__(kThreads) void item_dE_kernel(InvertArgs a)
     }
     if (!__any(r < r_end)) continue;
     if (r_end - r > kHotPairs) {  // hot item: file its chunks and leave it to hot_item_kernel
-        const int32_t n_chunks = (r_end - r + kHotPairs - 1) / kHotPairs;
+        const int32_t n_chunks = (r_end - r + kHotChunk - 1) / kHotChunk;
         int32_t slot = 0;
         if (c == 0) slot = atomicAdd(a.hot_count, n_chunks);
         slot = __shfl(slot, lane - c, 64);
         for (int32_t k = c; k < n_chunks; k += LPR) {
-            const int32_t b = r + k * kHotPairs;
-            if (slot + k < a.hot_capacity) a.hot_list[slot + k] = make_int4((int32_t)v, b, min(b + kHotPairs, r_end), 0);
+            const int32_t b = r + k * kHotChunk;
+            if (slot + k < a.hot_capacity) a.hot_list[slot + k] = make_int4((int32_t)v, b, min(b + kHotChunk, r_end), 0);
         }
         r = r_end = 0;
     }
@@ -498,37 +501,46 @@ __global__ __launch_bounds__(kThreads) void item_dE_kernel(InvertArgs a)
     }  // item groups of this block
 }
 
-// The chunks item_dE_kernel filed: one lane group per chunk, a fixed grid strides over the list.
-constexpr int kHotBlocks = 1024;
+// The chunks item_dE_kernel filed: one block per chunk, a fixed grid strides over the list.  Every lane group walks a
+// consecutive share; the wavefronts' sums meet in LDS, so that an atomic instruction covers 64 consecutive floats of the
+// row.  What bounds the pass is the hottest item: its chunks add to one row, one instruction after the other (25 ns
+// each).  With 256 pairs a chunk, a lane group per chunk and eight strided floats per lane (eight instructions) a third
+// of the item's time was spent there: 6.5 M pairs drawn with p ~ rank^-0.9 from 1 M items, d = 128: 348 us before.
+constexpr int kHotBlocks = 2048;
 template <typename T, int LPR>
 __global__ __launch_bounds__(kThreads) void hot_item_kernel(InvertArgs a)
 {
-    constexpr int GPW = 64 / LPR;
-    const int lane = threadIdx.x & 63;
-    const int c = lane % LPR;
+    constexpr int GPW = 64 / LPR, WAVES = kThreads / 64;
+    __shared__ float part[WAVES][LPR * 8];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = lane % LPR, grp = lane / LPR;
     const bool col_ok = c * 8 < a.d;
     const int32_t n = min(*a.hot_count, a.hot_capacity);
-    const int32_t stride = (int32_t)gridDim.x * (kThreads / 64) * GPW;
-    for (int32_t e0 = ((int32_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * GPW; e0 < n; e0 += stride) {
-        const int32_t ent = e0 + lane / LPR;  // e0 is the same for the whole wavefront
-        int32_t v = 0, r = 0, r_end = 0;
-        if (ent < n) {
-            const int4 t = a.hot_list[ent];
-            v = t.x;
-            r = t.y;
-            r_end = t.z;
-        }
+    for (int32_t ent = (int32_t)blockIdx.x; ent < n; ent += (int32_t)gridDim.x) {  // uniform over the block
+        const int4 h = a.hot_list[ent];
         float e[8], acc[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) e[t] = acc[t] = 0.f;
-        const bool mine = r < r_end && col_ok;
-        if (mine) load8(static_cast<const T *>(a.E) + v * (int64_t)a.d + c * 8, e);
-        walk_segment<T, LPR>(a, e, r, r_end, col_ok, c, acc);
-        if (mine) {
-            float *row = a.dE + v * (int64_t)a.d + c * 8;
+        if (col_ok) load8(static_cast<const T *>(a.E) + h.x * (int64_t)a.d + c * 8, e);
+        const int32_t share = (h.z - h.y + WAVES * GPW - 1) / (WAVES * GPW), r = h.y + (wave * GPW + grp) * share;
+        walk_segment<T, LPR>(a, e, r, min(r + share, h.z), col_ok, c, acc);
 #pragma unroll
-            for (int t = 0; t < 8; ++t) unsafeAtomicAdd(row + t, acc[t]);
+        for (int off = LPR; off < 64; off <<= 1) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) acc[t] += __shfl_xor(acc[t], off, 64);
         }
+        if (grp == 0) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) part[wave][c * 8 + t] = acc[t];
+        }
+        __syncthreads();
+        for (int col = threadIdx.x; col < a.d; col += kThreads) {
+            float sum = part[0][col];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) sum += part[w][col];
+            unsafeAtomicAdd(a.dE + h.x * (int64_t)a.d + col, sum);
+        }
+        __syncthreads();
     }
 }
 
