@@ -127,12 +127,22 @@ __global__ __launch_bounds__(kThreads) void fill_kernel(InvertArgs a)
 }
 
 // ---- index build by two-level counting sort without global atomics.
-//  Level 1 partitions the pairs into buckets of kBucketIds consecutive item ids: every block histograms its chunk of
+//  Level 1 partitions the pairs into buckets of 2^bucket_shift consecutive item ids: every block histograms its chunk of
 //  pairs in LDS, the (bucket, block) counts are scanned bucket-major, and the block scatters (id, position) into its
 //  reserved ranges.  Level 2 gives each bucket to one block, which counting-sorts it by id inside LDS and writes the
 //  positions item by item together with the end offset of every item.
-constexpr int kBucketShift = 11;
-constexpr int kBucketIds = 1 << kBucketShift;  // LDS histogram of level 2: 8 KiB
+constexpr int kMaxBucketShift = 11;
+constexpr int kMaxBucketIds = 1 << kMaxBucketShift;  // LDS histogram of level 2: 8 KiB
+// Ids per bucket (a power of two): 256 to 512 buckets up to a million items, so that level 2 has blocks for the
+// chip and a bucket of a small catalogue does not outgrow a slice (25,600 positions, K = 256, d = 128: with 2048 ids per
+// bucket always, 20,000 items, every bucket beyond an eighth of the budget: 41.8 ms a step; 50,000 items, 25 blocks in
+// level 2: 1.37 ms; with this rule 0.76 and 0.66 ms; 1 M items: 489 buckets, 3 % faster than 977).
+int bucket_shift(int64_t V)
+{
+    int s = 0;
+    while (s < kMaxBucketShift && (V >> s) >= 512) ++s;
+    return s;
+}
 constexpr int kMaxBuckets = 2048;               // LDS histogram of level 1: 8 KiB
 constexpr int kChunkPairs = 8192;               // pairs per chunk in level 1; a block takes chunks blockIdx.x, + gridDim.x, ...
 constexpr int kMaxPartBlocks = 4096;            // blocks of level 1: bounds the (bucket, block) histogram at 32 MiB
@@ -142,7 +152,7 @@ constexpr int kMaxPartBlocks = 4096;            // blocks of level 1: bounds the
 // written once; a further slice costs one more reading of the ids (4 bytes per pair) and four launches.
 //   B = max(2^22, N K / 8) pairs;  slices = 1 if N K <= B, else ceil(N K / (7/8 B)): the pairs of the ordinary buckets
 //   are cut at the quantiles j / slices of their running count, so a slice holds at most N K / slices + (one bucket)
-//   <= 7/8 B + 1/8 B pairs, PROVIDED no bucket holds more than B / 8 pairs.  Buckets beyond that (2048 consecutive ids
+//   <= 7/8 B + 1/8 B pairs, PROVIDED no bucket holds more than B / 8 pairs.  Buckets beyond that (consecutive ids
 //   drawing more than half a million pairs, an eighth of everything: a popularity law far more skewed than any workload
 //   here) stay out of the index: their pairs are added to dE one by one with atomics (hot_bucket_kernel).
 constexpr int64_t kMinPairBudget = int64_t(1) << 22;
@@ -193,7 +203,7 @@ __global__ __launch_bounds__(kThreads) void part_count_kernel(InvertArgs a)
     for (int b = threadIdx.x; b < a.n_buckets; b += kThreads) hist[b] = 0;
     __syncthreads();
     for (int64_t chunk = blockIdx.x; chunk < a.n_chunks; chunk += gridDim.x)
-        for_live_pairs(a, chunk, [&](int32_t id, int32_t) { atomicAdd(&hist[id >> kBucketShift], 1); });
+        for_live_pairs(a, chunk, [&](int32_t id, int32_t) { atomicAdd(&hist[id >> a.bucket_shift], 1); });
     __syncthreads();
     for (int b = threadIdx.x; b < a.n_buckets; b += kThreads) a.part_hist[(int64_t)b * gridDim.x + blockIdx.x] = hist[b];
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.part_total = 0;  // last entry of the scanned array: receives the grand total
@@ -281,12 +291,12 @@ __global__ __launch_bounds__(kThreads) void part_scatter_kernel(InvertArgs a, Ti
     __syncthreads();
     for (int64_t chunk = blk; chunk < a.n_chunks; chunk += nb)
         for_live_pairs(a, chunk, [&](int32_t id, int32_t pos) {
-            int32_t *c = &cur[id >> kBucketShift];
+            int32_t *c = &cur[id >> a.bucket_shift];
             if (*c >= 0) a.tmp[atomicAdd(c, 1)] = make_int2(id, pos);  // cursors only grow: the sign never changes
         });
 }
 
-// Pairs of the buckets that stay out of the index (more than an eighth of the budget in 2048 consecutive ids): each is
+// Pairs of the buckets that stay out of the index (more than an eighth of the budget): each is
 // scored and added to dE on its own, one thread per pair, d atomics.  A correctness path for extreme skew, not a fast one.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void hot_bucket_kernel(InvertArgs a)
@@ -298,7 +308,7 @@ __global__ __launch_bounds__(kThreads) void hot_bucket_kernel(InvertArgs a)
     const T *Hp = static_cast<const T *>(a.H), *Ep = static_cast<const T *>(a.E);
     for (int64_t chunk = blockIdx.x; chunk < a.n_chunks; chunk += gridDim.x)
         for_live_pairs(a, chunk, [&](int32_t id, int32_t pos) {
-            if (!is_hot[id >> kBucketShift]) return;
+            if (!is_hot[id >> a.bucket_shift]) return;
             const T *h = Hp + (int64_t)pos * a.d, *e = Ep + (int64_t)id * a.d;
             float o = 0.f;
             for (int t = 0; t < a.d; ++t) o = fmaf(load1(h + t), load1(e + t), o);
@@ -310,7 +320,8 @@ __global__ __launch_bounds__(kThreads) void hot_bucket_kernel(InvertArgs a)
 
 __global__ __launch_bounds__(kScanThreads) void bucket_sort_kernel(InvertArgs a)
 {
-    __shared__ int32_t hist[kBucketIds];
+    __shared__ int32_t hist[kMaxBucketIds];
+    const int ids = 1 << a.bucket_shift;
     __shared__ int32_t lds[kScanThreads / 64 + 1];
     const int b = blockIdx.x;
     if (a.slice_of[b] != a.slice) return;  // block-uniform
@@ -321,12 +332,12 @@ __global__ __launch_bounds__(kScanThreads) void bucket_sort_kernel(InvertArgs a)
     const int32_t s1 = (b + 1 < a.n_buckets) ? a.part_hist[(int64_t)(b + 1) * n_blocks1] : a.part_total[0];
     const int32_t rb = a.bucket_start[b];
     const int32_t re = rb + (s1 - s0);
-    const int64_t id0 = (int64_t)b << kBucketShift;
-    for (int k = threadIdx.x; k < kBucketIds; k += kScanThreads) hist[k] = 0;
+    const int64_t id0 = (int64_t)b << a.bucket_shift;
+    for (int k = threadIdx.x; k < kMaxBucketIds; k += kScanThreads) hist[k] = 0;
     __syncthreads();
     // A hot item owns most entries of its bucket, and 64 lanes adding to one LDS word take 64 turns: in a crowded bucket
     // the lanes that hold the same id as the first active lane are counted with one ballot and added by that lane alone.
-    const bool crowded = re - rb > 16 * kBucketIds;  // block-uniform; ordinary buckets take the plain loops
+    const bool crowded = re - rb > 16 * ids;  // block-uniform; ordinary buckets take the plain loops
     if (!crowded)
         for (int32_t e = rb + (int32_t)threadIdx.x; e < re; e += kScanThreads) atomicAdd(&hist[a.tmp[e].x - (int32_t)id0], 1);
     for (int32_t e0 = rb; crowded && e0 < re; e0 += kScanThreads) {
@@ -345,20 +356,20 @@ __global__ __launch_bounds__(kScanThreads) void bucket_sort_kernel(InvertArgs a)
     }
     __syncthreads();
     // exclusive scan over the counts: consecutive ids per thread
-    int32_t v[kBucketIds / kScanThreads], sum = 0;
+    int32_t v[kMaxBucketIds / kScanThreads], sum = 0;
 #pragma unroll
-    for (int t = 0; t < kBucketIds / kScanThreads; ++t) {
-        v[t] = hist[threadIdx.x * (kBucketIds / kScanThreads) + t];
+    for (int t = 0; t < kMaxBucketIds / kScanThreads; ++t) {
+        v[t] = hist[threadIdx.x * (kMaxBucketIds / kScanThreads) + t];
         sum += v[t];
     }
     int32_t total;
     int32_t run = block_exclusive_scan(sum, lds, total);
 #pragma unroll
-    for (int t = 0; t < kBucketIds / kScanThreads; ++t) {
-        const int k = threadIdx.x * (kBucketIds / kScanThreads) + t;
+    for (int t = 0; t < kMaxBucketIds / kScanThreads; ++t) {
+        const int k = threadIdx.x * (kMaxBucketIds / kScanThreads) + t;
         hist[k] = run;  // start of the item's segment inside the bucket; advanced below while filing
         run += v[t];
-        if (id0 + k < a.V) a.cursor[id0 + k] = rb + run;  // END of the item's segment
+        if (k < ids && id0 + k < a.V) a.cursor[id0 + k] = rb + run;  // END of the item's segment
     }
     __syncthreads();
     if (!crowded)
@@ -453,16 +464,16 @@ __global__ __launch_bounds__(kThreads) void item_dE_kernel(InvertArgs a)
     // items of this launch: the whole table, or the buckets of the slice at hand (a fixed grid strides over them)
     int64_t v_lo = 0, v_hi = a.V;
     if (a.slice_of) {
-        v_lo = (int64_t)a.slice_hot[kMaxSlices + a.slice] << kBucketShift;
-        v_hi = min(a.V, ((int64_t)a.slice_hot[2 * kMaxSlices + a.slice] + 1) << kBucketShift);
+        v_lo = (int64_t)a.slice_hot[kMaxSlices + a.slice] << a.bucket_shift;
+        v_hi = min(a.V, ((int64_t)a.slice_hot[2 * kMaxSlices + a.slice] + 1) << a.bucket_shift);
     }
     for (int64_t v0 = v_lo + (int64_t)blockIdx.x * IPB; v0 < v_hi; v0 += (int64_t)gridDim.x * IPB) {
     const int64_t v = v0 + (threadIdx.x >> 6) * GPW + lane / LPR;
     int32_t r = 0, r_end = 0;
-    if (v < v_hi && (a.slice_of == nullptr || a.slice_of[v >> kBucketShift] == a.slice)) {
+    if (v < v_hi && (a.slice_of == nullptr || a.slice_of[v >> a.bucket_shift] == a.slice)) {
         // cursor[v] is the end of item v's segment; it starts where the one before it ends, the first item of a bucket
         // where the bucket starts in the slice's arrays (without slices: one running array over all items)
-        if (a.slice_of) r = ((v & (kBucketIds - 1)) == 0) ? a.bucket_start[v >> kBucketShift] : a.cursor[v - 1];
+        if (a.slice_of) r = ((v & ((1 << a.bucket_shift) - 1)) == 0) ? a.bucket_start[v >> a.bucket_shift] : a.cursor[v - 1];
         else r = (v == 0) ? 0 : a.cursor[v - 1];
         r_end = a.cursor[v];
     }
@@ -625,7 +636,7 @@ int64_t invert_part_blocks(int64_t N, int64_t K)
     const int64_t chunks = (N * K + kChunkPairs - 1) / kChunkPairs;
     return chunks < kMaxPartBlocks ? chunks : kMaxPartBlocks;
 }
-int64_t invert_buckets(int64_t V) { return (V + kBucketIds - 1) / kBucketIds; }
+int64_t invert_buckets(int64_t V) { return (V + (int64_t(1) << bucket_shift(V)) - 1) >> bucket_shift(V); }
 bool invert_partitioned(int64_t V) { return invert_buckets(V) <= kMaxBuckets; }
 int invert_plan_words() { return 3 * kMaxSlices + 8; }  // work-list counters, first and last bucket of every slice, one flag
 
@@ -656,6 +667,7 @@ hipError_t launch_inverted_dE(bool bf16, const InvertArgs &a_in, const TileArgs 
         return bf16 ? launch_item_dE_by_width<uint16_t>(a, stream) : launch_item_dE_by_width<float>(a, stream);
     }
     a.n_buckets = (int32_t)invert_buckets(a.V);
+    a.bucket_shift = bucket_shift(a.V);
     a.n_part_blocks = invert_part_blocks(a.N, a.K);
     a.n_chunks = (pairs + kChunkPairs - 1) / kChunkPairs;
     a.budget = invert_pair_budget(a.N, a.K);

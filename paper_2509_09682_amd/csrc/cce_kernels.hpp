@@ -145,7 +145,7 @@ struct InvertArgs {
     int32_t *hot_count;      // workspace header word: chunks filed
     int32_t hot_capacity;
     int64_t N, V, n_part_blocks;
-    int32_t d, K, collide, validate, n_buckets;
+    int32_t d, K, collide, validate, n_buckets, bucket_shift;  // 2^bucket_shift consecutive ids per bucket
     Sampler smp;             // kind != 0: the negatives are drawn again here instead of being read from neg
 };
 size_t invert_hot_capacity(int64_t N, int64_t K);  // entries of hot_list

@@ -1,0 +1,38 @@
+"""Per-position negatives of small catalogues: the index is built in buckets of one id up to 2048, its pairs in more than
+one slice, segments from empty to thousands of pairs (one lane group, a block per chunk)."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import check_against_oracle
+from workloads import NEG_PER_POSITION, make_workload
+
+pytestmark = pytest.mark.gpu
+
+
+# catalogues at the edges of the bucket widths (512 items: one id each; 1023 / 1024; 300,000: 1024 ids each); the last
+# two file more pairs than a slice holds
+@pytest.mark.parametrize("V,batch,K", [(40, 3, 37), (511, 4, 64), (512, 4, 64), (1023, 4, 300), (1024, 4, 300), (300_000, 4, 64),
+                                       (700, 30, 720), (2500, 30, 720)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 40)])
+def test_small_catalogues(V, batch, K, dtype, d):
+    from hip_harness import run_hip
+
+    w = make_workload(f"small_V{V}_{dtype}", batch, 200, d, V, K, dtype, NEG_PER_POSITION, 5 + V, g_kind="random", e_sigma=0.05,
+                      tgt_dist="zipf", pad="right", pad_len_lo=190)
+    # dE rows sum up to thousands of pairs in fp32, whatever the order: 2e-5, twice the contract of single rows
+    check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), 2e-5)
+
+
+def test_one_item_that_collects_a_quarter_of_all_pairs():
+    """A bucket beyond an eighth of the pair budget stays out of the index; its pairs are added one by one."""
+    from hip_harness import run_hip
+
+    w = make_workload("one_hot_item", 30, 200, 64, 60_000, 720, "bf16", NEG_PER_POSITION, 99, g_kind="random", e_sigma=0.05)
+    rng = np.random.default_rng(1)
+    neg = w.neg.reshape(w.N, w.K)
+    neg[rng.random(neg.shape) < 0.25] = 31_234
+    # Every position adds its term about 180 times in a row to one fp32 sum; equal adds round alike, so the row is off by
+    # up to 180 sqrt(6000) 2^-25 = 4e-4 of the running sum, which may be twice the final one.  Everything else is exact
+    # to the usual figure, which loss, lse and dH show.
+    errs = check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), 1e-3, row_tol=1e-3)
+    assert max(errs[k] for k in ("loss", "lse", "dH")) <= 1e-5, errs
