@@ -54,7 +54,8 @@ typedef enum {
 } cce_neg_mode;
 
 typedef enum {
-    CCE_ALGO_AUTO = 0,   /* library picks: MFMA tiles for bf16 shared/full, row gathers otherwise */
+    CCE_ALGO_AUTO = 0,   /* library picks: MFMA tiles for bf16 shared/full with d in {64,128,256}, dense kernels in fp32
+                            precision for every other shared/full descriptor, row gathers for per-position negatives */
     CCE_ALGO_GATHER = 1, /* one wavefront per position, candidate rows gathered one by one (Alg. 1 / Alg. 2 as printed) */
     CCE_ALGO_TILE = 2    /* dense H x E_neg^T score tiles on the matrix cores; bf16 inputs, shared or full mode only */
 } cce_algo;
@@ -98,7 +99,7 @@ typedef struct {
                                        scores once more for dE only: four products of the size of the score matrix per
                                        step instead of five, two exponentials per score instead of three.  Set it the
                                        same way in the size query, the forward and the backward descriptor.  On the
-                                       row-gather kernels (fp32, other hidden sizes, per-position negatives) the forward
+                                       row-gather kernels (per-position negatives, CCE_ALGO_GATHER) the forward
                                        call sums the weighted candidate rows while it has them in registers for the
                                        score, and the backward call gathers no candidate row for dH (same 4 N d bytes).
                                        Ignored for per-position negatives beyond the inverted index (2^31 pairs and
@@ -120,6 +121,9 @@ typedef struct {
  *                              4 bytes per table row, 4 per position and at most 32 MiB of bucket counts.  Catalogues
  *                              of more than 2^22 items whose pairs exceed B: a 256-byte header (they keep the atomic
  *                              row adds of Alg. 2);
+ *   shared / full mode, fp32 or another hidden size: 20 bytes per position, 4 d more with fuse_dH, plus partial results
+ *                              of split launches (8 bytes per position and share, 2 MB at most; 4 d bytes, 256 KB x d at
+ *                              most); grows with N, so a workspace serves smaller batches too;
  *   otherwise:                 a 256-byte header (with fuse_dH: 4 + 4 d bytes per position more, also in per-position mode);
  *   shared mode, in addition:  4 bytes per negative (where the *_sampled calls write the list they draw).
  * No score, probability or gradient-coefficient matrix is ever stored: the workspace holds indices and per-position
@@ -172,8 +176,9 @@ cce_status cce_neg_backward(const cce_desc *desc, const void *H, const void *E, 
  * keeps whatever the last call left there.
  *   - A descriptor whose forward pass needs more scratch than the array holds is refused with CCE_ERR_WORKSPACE
  *     before anything is launched.  Matrix-core path: 20 bytes per position, plus 8 per position and split where the
- *     candidate range is split (at most 8 ways), so 32 MiB carry between 390,000 and 1,600,000 positions; other
- *     paths need 256 bytes.  validate_indices = 1 is refused with CCE_ERR_UNSUPPORTED (there is no status
+ *     candidate range is split (at most 8 ways, up to 64 for few positions), so 32 MiB carry between 390,000
+ *     and 1,600,000 positions; the dense kernels need 8 bytes per position and 2 MB, and a batch beyond that falls
+ *     back to the row-gather kernels, which need 256 bytes.  validate_indices = 1 is refused with CCE_ERR_UNSUPPORTED (there is no status
  *     word the caller could read).
  *   - Every call on a GPU shares that GPU's array: calls that overlap on one GPU (two streams, two threads) race.
  *     Calls on one stream are ordered and safe.
@@ -249,9 +254,9 @@ cce_status cce_neg_backward_sampled(const cce_desc *desc, const cce_sampler *sam
 /*
  * Synchronises hip_stream and reads the index status word kept in workspace.  Returns CCE_ERR_INDEX if any call on
  * that workspace since the last query found an id outside [0,V) on a valid position (validate_indices = 1 only),
- * CCE_OK otherwise; the word is cleared.  Bad ids are never dereferenced.  Row-gather kernels (per-position mode, fp32
- * inputs, CCE_ALGO_GATHER): a bad negative is skipped and a position with a bad target is treated as padding, so the
- * outputs are those of the sanitised problem.  Matrix-core kernels (bf16 shared / full mode): a position with a bad
+ * CCE_OK otherwise; the word is cleared.  Bad ids are never dereferenced.  Row-gather and dense kernels (per-position mode,
+ * fp32 inputs, other hidden sizes, CCE_ALGO_GATHER): a bad negative is skipped and a position with a bad target is treated as padding, so the
+ * outputs are those of the sanitised problem.  Matrix-core tiles (bf16 shared / full mode, d in {64,128,256}): a position with a bad
  * target is treated as padding, but a bad SHARED negative is scored as item 0 in its place; the outputs of a flagged
  * call are then unspecified (finite, in bounds, and dE row 0 may have received gradient): discard them.
  */
@@ -263,7 +268,8 @@ cce_status cce_neg_index_status(void *workspace, size_t workspace_bytes, void *h
  * adds the elapsed time per kernel family and returns the number of families written (at most max):
  *   names     [max][32] char (HOST)   family name, NUL-terminated: "gather_fwd", "gather_bwd", "prep", "tile_fwd",
  *                                     "fwd_merge", "tile_dh", "dh_merge", "tile_de", "index", "item_de", "pos_scatter",
- *                                     "bwd_pre", "tile_bwd" (dH and dE pass in one launch)
+ *                                     "bwd_pre", "tile_bwd" (dH and dE pass in one launch), "dense_pos", "dense_merge",
+ *                                     "dense_de"
  *   total_ms  [max] float (HOST)      summed duration since the last read
  *   launches  [max] int32 (HOST)      launches since the last read
  * The records are cleared by the read.  Enabling creates HIP events on demand; nothing else in the library allocates.

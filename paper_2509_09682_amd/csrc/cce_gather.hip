@@ -4,7 +4,8 @@
 // candidate columns j of the index matrix, load the indexed item rows, take the scalar product over the whole hidden
 // dimension (never split, Sec. 3.3), and keep the running max / sum of the online softmax on chip.  It serves every
 // mode and dtype; it is the fast path for per-position negatives (a batched GEMV with no operand reuse, bound by the
-// row gathers) and the exact-fp32 path.
+// row gathers).  Lists that all positions share come here only when the caller asks for this family, with an empty list,
+// or without workspace for very large batches (cce_dense_body.hpp serves them otherwise).
 //
 // Lane layout: a row of d elements is covered by LPR lanes, 8 consecutive elements (one 16-byte bf16 load) per lane, so
 // a wavefront scores 64/LPR candidates per load instruction and UNROLL of those are in flight together.  The dot
