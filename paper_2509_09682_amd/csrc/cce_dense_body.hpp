@@ -272,6 +272,13 @@ __device__ __forceinline__ float dense_finish(const DenseArgs &a, int64_t x, int
     return inv;
 }
 
+// A column of U: inv * sum + (p+ - 1) E_tgt.  The item's -1 stays exact while p+ is small (it is most of the row then);
+// near one the difference comes as ct = -negatives / all, without cancellation.
+__device__ __forceinline__ float dense_row_value(float sum, float inv, float pp, float ct, float et)
+{
+    return fmaf(sum, inv, pp <= 0.5f ? fmaf(pp, et, -et) : ct * et);
+}
+
 // min two blocks of four wavefronts per compute unit: 256 registers a lane
 template <typename T, int KD, int MODE>
 __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
@@ -645,7 +652,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
             if (MODE != DM_DH && !a.order && hi == 0 && sl == 0) a.loss[xs] = a.lse[xs] = 0.f;
             return;
         }
-        float inv = 1.f, ct;  // U = inv * sum + ct * E_tgt
+        float inv = 1.f, ct;
         if (MODE == DM_DH) {
             ct = fast_exp(op - ref) - 1.f;
             if (hi == 0 && sl == 0) a.coef[xrow] = (a.g ? a.g[xrow] : 1.f) * ct;
@@ -655,6 +662,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
             ct = -sn * inv;
         }
         if (MODE == DM_FWD) return;
+        const float pp = fast_exp(op - ref) * inv;
         const float g = (MODE == DM_DH || a.direct_dH) ? (a.g ? a.g[xrow] : 1.f) : 1.f;
 #pragma unroll
         for (int b = 0; b < OB; ++b)
@@ -665,7 +673,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
                 float et[4], u[4];
                 widen4(Ep + (int64_t)ti * a.d + col, et);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) u[r] = g * fmaf(ct, et[r], acc[b][4 * q + r] * inv);
+                for (int r = 0; r < 4; ++r) u[r] = g * dense_row_value(acc[b][4 * q + r], inv, pp, ct, et[r]);
                 if (MODE == DM_DH || a.direct_dH) store_dH4(a, xrow, col, u);
                 else *reinterpret_cast<float4 *>(a.U + (int64_t)xrow * a.d + col) = make_float4(u[0], u[1], u[2], u[3]);
             }
@@ -714,12 +722,13 @@ __global__ __launch_bounds__(256) void dense_merge_kernel(DenseArgs a)
         ct = -sn * inv;
     }
     if (MODE == DM_FWD) return;
+    const float pp = fast_exp(op - M) * inv;
     const bool to_dH = MODE == DM_DH || a.direct_dH;
     const float g = (to_dH && a.g) ? a.g[row] : 1.f;
     float et[4];
     widen4(static_cast<const T *>(a.E) + (int64_t)dense_tgt(a, x, row) * a.d + c * 4, et);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) u[r] = g * fmaf(ct, et[r], u[r] * inv);
+    for (int r = 0; r < 4; ++r) u[r] = g * dense_row_value(u[r], inv, pp, ct, et[r]);
     if (to_dH) store_dH4(a, row, c * 4, u);
     else *reinterpret_cast<float4 *>(a.U + (int64_t)row * a.d + c * 4) = make_float4(u[0], u[1], u[2], u[3]);
 }
