@@ -261,11 +261,12 @@ DenseLayout make_dense_layout(const cce_desc *d)
 }
 // Padded positions are compacted where that saves more than the launch it takes (about 5 us): a small batch is bound by
 // latencies, and a wavefront without a valid row costs it nothing.
+// The rule looks at the descriptor and at whether there is a mask, never at its address: a backward call that reuses the
+// forward call's preparation may hand over a copy of the mask.
 constexpr int64_t kDenseCompactAbove = 4096;
-// The preparation kernel reads the mask 16 bytes at a time.
 bool dense_compacts(const cce_desc *d, const uint8_t *mask)
 {
-    return d->validate_indices || (mask && d->N > kDenseCompactAbove && (reinterpret_cast<uintptr_t>(mask) & 15u) == 0);
+    return d->validate_indices || (mask && d->N > kDenseCompactAbove);
 }
 
 // Ways to split the streamed range of `blocks` blocks of the position side so that the chip's block slots are full, with

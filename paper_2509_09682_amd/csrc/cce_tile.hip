@@ -59,9 +59,12 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(PrepArgs p)
                     before += (t >= 0 && (int64_t)t < p.V) ? 1 : 0;
                 }
             }
-        } else if (p.mask) {  // i0 is a multiple of 1024, the mask is 16-byte aligned
-            const uint4 *m16 = reinterpret_cast<const uint4 *>(p.mask);
-            const int64_t n16 = i0 / 16;
+        } else if (p.mask) {  // whole 16-byte words where the mask has them, single bytes in front of the first and behind the last
+            const int64_t to_word = (int64_t)((16u - (reinterpret_cast<uintptr_t>(p.mask) & 15u)) & 15u);
+            const int64_t front = to_word < i0 ? to_word : i0, n16 = (i0 - front) / 16, back = front + 16 * n16;
+            if (tid < front) before += p.mask[tid] != 0;
+            if (back + tid < i0) before += p.mask[back + tid] != 0;
+            const uint4 *m16 = reinterpret_cast<const uint4 *>(p.mask + front);
             int64_t c = tid;
             for (; c + 3 * kPrepThreads < n16; c += 4 * kPrepThreads) {  // four loads in flight: the walk is a chain of latencies
                 const uint4 v0 = m16[c], v1 = m16[c + kPrepThreads], v2 = m16[c + 2 * kPrepThreads], v3 = m16[c + 3 * kPrepThreads];

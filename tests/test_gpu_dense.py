@@ -135,3 +135,34 @@ def test_buckets_of_any_size_in_one_launch(sizes, K, dtype, d):
                                     torch.from_numpy(w.g).cuda(), dE)
     out = dict(loss=loss.cpu().numpy(), lse=lse.cpu().numpy(), dH=dH.float().cpu().numpy(), dE=dE.cpu().numpy())
     check_against_oracle(w, out, TOL, dH_tol=4e-3 if dtype == "bf16" else None)   # dH in bf16: half an ulp, 2^-9
+
+
+@pytest.mark.parametrize("dtype,d,batch,validate", [("f32", 40, 60, 0), ("bf16", 320, 60, 0), ("bf16", 64, 60, 0), ("f32", 40, 60, 1), ("f32", 40, 5, 0)])
+def test_mask_at_any_address_and_a_copy_of_it_in_the_backward_call(dtype, d, batch, validate):
+    """The forward and the backward call get the same mask contents at addresses of different alignment, either way round;
+    the backward call reuses the preparation.  5940 positions are compacted, 495 are not."""
+    import torch
+
+    import paper_2509_09682_amd as P
+    from paper_2509_09682_amd.runner import to_device
+
+    w = make_workload(f"mask_at_{dtype}_d{d}_{batch}", batch, 99, d, 700, 45, dtype, NEG_SHARED, 41 + d, pad="bernoulli",
+                      pad_p=0.35, g_kind="random", e_sigma=0.1, tgt_dist="zipf")
+    tol = 2e-2 if (dtype, d) == ("bf16", 64) else TOL
+    H, E, tgt, neg, mask = to_device(w)
+    dt = P.CCE_F32 if dtype == "f32" else P.CCE_BF16
+    masks = []
+    for shift in (0, 1, 15):
+        store = torch.full((w.N + 64,), 1, dtype=torch.uint8, device="cuda")
+        store[shift:shift + w.N] = mask
+        masks.append(store[shift:shift + w.N])
+        assert masks[-1].data_ptr() % 16 == shift
+    for fwd, bwd in ((1, 0), (0, 1), (2, 1), (1, 2)):
+        desc = P.make_desc(w.N, w.V, d, w.K, dt, NEG_SHARED, validate_indices=validate, fuse_dH=1)
+        again = P.make_desc(w.N, w.V, d, w.K, dt, NEG_SHARED, validate_indices=validate, fuse_dH=1, reuse_forward_prep=1)
+        ws = P.new_workspace(desc)
+        out = {k: torch.full(shape, float("nan"), device="cuda") for k, shape in (("loss", (w.N,)), ("lse", (w.N,)), ("dH", (w.N, d)))}
+        out["dE"] = torch.zeros((w.V, d), device="cuda")
+        P.cce_neg_forward(desc, H, E, tgt, neg, masks[fwd], out["loss"], out["lse"], ws)
+        P.cce_neg_backward(again, H, E, tgt, neg, masks[bwd], out["lse"], torch.from_numpy(w.g).cuda(), out["dH"], out["dE"], ws)
+        check_against_oracle(w, {k: v.cpu().numpy() for k, v in out.items()}, tol)
