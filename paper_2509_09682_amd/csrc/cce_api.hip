@@ -43,7 +43,8 @@ bool use_dense(const cce_desc *d)
 struct Layout {
     size_t idx, cnt, coef, de_const, part_m, part_s, part_dH, U, total;
     int splits_x;   // dH pass: candidate range split over at most this many blocks per position block
-    int splits_fwd; // forward pass: the same, with its own (cheaper) bound
+    int splits_f;   // forward pass that forms the hidden-state gradient as well: the same
+    int splits_fwd; // forward pass alone: the same, with its own (cheaper) bound
     int splits_de;  // dE pass: position range split
 };
 
@@ -57,16 +58,31 @@ Layout make_layout(const cce_desc *d)
     // Splitting only pays when there are few blocks of stationary rows, which bounds splits * rows, hence the
     // partial buffers, by a constant.
     const int64_t xblocks = (N + 127) / 128;
-    int sx = (xblocks > 0 && xblocks <= 320) ? (int)(2048 / xblocks) : 1;  // the launcher never splits above 320 blocks
+    const int most = (xblocks > 0 && xblocks <= 320) ? (int)(2048 / xblocks) : 1;  // the launcher never splits above 320 blocks
     const int64_t col_tiles = (n_cols + by - 1) / by;
-    if (sx > 64) sx = 64;  // few positions against a catalogue: 64 shares fill the chip
+    int sx = most < 16 ? most : 16;
     if (sx > col_tiles / 2) sx = (int)(col_tiles / 2);
     if (sx < 1) sx = 1;
+    L.splits_f = sx;
+    // A dH pass of few positions fills the chip with more shares.  Powers of two: block b takes share b % splits and runs on
+    // XCD b % 8, so each XCD keeps to shares of its own (3000 positions, 30,011 items, d = 128: merge of 21 shares 46 us, of
+    // 16 shares 15).  Steps in us against the full catalogue, 16 shares / this rule: without fuse_dH, 30,011 items, d = 64,
+    // 300 positions 62 / 40, 2000 positions 91 / 81; d = 256, 1000 positions 283 / 176.  The fused forward pass gains only at
+    // d = 256 (1000 positions: 240 / 175); at d = 64 and 128 its merge of more shares costs what the pass gains and more
+    // (d = 64, 30,011 items, 1000 positions: 70 with 16 shares, 88 with 64; 2000 positions: 85 / 109).
+    for (int few = N <= 1024 ? 64 : (N <= 2048 ? 32 : 0); few > 16; few /= 2)
+        if (few <= col_tiles / 2) {
+            sx = few;
+            break;
+        }
     L.splits_x = sx;
+    if (!tile_backward_fusable(d->d)) L.splits_f = sx;
     // The forward partials are two floats per position and split, so the forward pass may always split: with many
-    // blocks it does so only to even out the last round (the launcher decides).
-    int sf = (int)(col_tiles / 4);
-    if (sf > 8) sf = 8;
+    // blocks it does so only to even out the last round (the launcher decides); few positions against a catalogue are cut
+    // into up to 64 shares.
+    int sf = most < 64 ? most : 64;
+    if (sf > col_tiles / 2) sf = (int)(col_tiles / 2);
+    if (sf < 8) sf = (int)(col_tiles / 4 < 8 ? col_tiles / 4 : 8);
     if (sf < sx) sf = sx;
     if (sf < 1) sf = 1;
     L.splits_fwd = sf;
@@ -644,8 +660,8 @@ cce_status forward_impl(const cce_desc *desc, const Sampler &smp, const void *H,
         cce::TileArgs a = cce::make_tile_args(desc, L, H, E, tgt, neg, mask, workspace);
         a.loss = loss;
         a.lse = lse;
-        if (cce::fused_dH(desc)) {  // lse and the hidden-state gradient short of grad_loss in one pass (splits as the dH pass)
-            a.splits = L.splits_x;
+        if (cce::fused_dH(desc)) {  // lse and the hidden-state gradient short of grad_loss in one pass
+            a.splits = L.splits_f;
             return cce::launch_tile(cce::TILE_PASS_FDH, a, stream) == hipSuccess ? CCE_OK : CCE_ERR_HIP;
         }
         a.splits = L.splits_fwd;

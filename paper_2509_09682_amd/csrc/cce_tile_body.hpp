@@ -1653,7 +1653,8 @@ inline int pick_splits(int64_t xblocks, int max_splits, int slots, bool cheap_me
     }
     int best = 1;
     double best_eff = 0.0;
-    for (int s = 1; s <= max_splits; ++s) {
+    // dH-type passes: above 16 powers of two only (block b takes share b % s and runs on XCD b % 8)
+    for (int s = 1; s <= max_splits; s += (cheap_merge || atomic_merge || s < 16) ? 1 : s) {
         const int64_t blocks = xblocks * s;
         const int64_t rounds = (blocks + slots - 1) / slots;
         const double eff = (double)blocks / (double)(rounds * slots);
@@ -1770,11 +1771,12 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
     constexpr int XG_B = (D <= 64) ? 2 : 1;
     hipError_t e = hipSuccess;
     // Two groups want 256 stationary rows per block: worth it when that still gives about two blocks per compute
-    // unit, either directly or because the streamed range is being split anyway.
+    // unit, either directly or because the streamed range is being split anyway: 16 ways at most (forward pass, up to 64
+    // ways counted / 16: 4096 positions, 30,011 items, d = 64 36.6 / 31.8 us; 6000 positions, 3001 items, d = 128 19.7 / 15.6).
     auto wide = [&](int64_t n_x, bool may_split) {
         const int64_t xb = (n_x + NW_L * 64 - 1) / (NW_L * 64);
         if (NW_L == 8) return xb >= 256;  // one block per compute unit: at least one full round of the coarser unit
-        return xb >= 300 || (may_split && xb < 120 && xb * a.splits >= 480);
+        return xb >= 300 || (may_split && xb < 120 && xb * (a.splits < 16 ? a.splits : 16) >= 480);
     };
     switch (pass) {
     case TILE_PASS_FWD:
