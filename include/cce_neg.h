@@ -109,11 +109,12 @@ typedef struct {
 
 /* Bytes of device workspace both calls need for this descriptor.  Returns 0 for an invalid descriptor.
  *   shared / full mode, bf16:  20 bytes per position (compaction, collision counts, coefficients), 4 d more with fuse_dH,
- *                              plus partial
- *                              results of split launches: 8 bytes per position and forward split, and, for batches
- *                              of at most 40,960 positions, 4 d bytes per position and dH split; hidden size 256 and
- *                              more than 65,536 positions: 64 MiB of partial dH rows for the split of the last round
- *                              of blocks;
+ *                              plus partial results of split launches: 8 bytes per position and forward share (8, or up
+ *                              to 64 for few positions), and 4 d bytes per position and dH share (16, or up to 64 for few
+ *                              positions, 1 MB x d at most; none above 40,960 positions); hidden size 256 and more than
+ *                              65,536 positions: 64 MiB of partial dH rows for the split of the last round of blocks.
+ *                              Up to 40,960 positions never less than for a smaller N; a larger batch may need less than
+ *                              one of 40,960 (ask for every size and take the largest);
  *   per-position mode:         the inverted index that turns the dE scatter into a gather (pairs sorted by item) is
  *                              built and used up in slices of the item-id range: 12 1/8 bytes per pair of ONE slice,
  *                              a slice holding at most B = max(2^22, N K / 8) pairs (so at most 51 MB up to

@@ -72,16 +72,16 @@ def bucketed_step(H: torch.Tensor, E: torch.Tensor, tgt: torch.Tensor, order: to
     loss_s = torch.empty(M, device=H.device, dtype=torch.float32)
     lse_s = torch.empty(M, device=H.device, dtype=torch.float32)
     dH_s = torch.empty((M, d), device=H.device, dtype=H.dtype)
-    largest = max((bucket_ptr[b + 1] - bucket_ptr[b] for b in range(n_buckets)), default=0)
+    kw = dict(dH_dtype=dt, mask_target_collisions=int(mask_target_collisions), fuse_dH=1)
+    sizes = {int(bucket_ptr[b + 1]) - int(bucket_ptr[b]) for b in range(n_buckets)} - {0}
     ws = None
-    if largest > 0:
-        ws = B.new_workspace(B.make_desc(largest, V, d, Kb, dt, B.CCE_NEG_SHARED, dH_dtype=dt,
-                                         mask_target_collisions=int(mask_target_collisions), fuse_dH=1), device=H.device)
+    if sizes:   # one workspace for all buckets; the largest bucket is not always the one that needs the most
+        ws = B.new_workspace(max((B.make_desc(n, V, d, Kb, dt, B.CCE_NEG_SHARED, **kw) for n in sizes), key=B.cce_neg_workspace_bytes),
+                             device=H.device)
     for b in range(n_buckets):
         b0, b1 = int(bucket_ptr[b]), int(bucket_ptr[b + 1])
         if b1 == b0:
             continue
-        kw = dict(dH_dtype=dt, mask_target_collisions=int(mask_target_collisions), fuse_dH=1)
         desc = B.make_desc(b1 - b0, V, d, Kb, dt, B.CCE_NEG_SHARED, **kw)
         desc_b = B.make_desc(b1 - b0, V, d, Kb, dt, B.CCE_NEG_SHARED, reuse_forward_prep=1, **kw)
         neg = bucket_neg[b]

@@ -3,6 +3,7 @@
 #include <math.h>
 
 #include <string.h>
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -48,6 +49,9 @@ struct Layout {
     int splits_de;  // dE pass: position range split
 };
 
+constexpr int64_t kSplitBelow = 40960;      // positions up to which dH-type passes are split: 320 blocks of 128
+constexpr int64_t kSplitRows = 2048 * 128;  // partial rows they file at most: splits * blocks <= 2048
+
 Layout make_layout(const cce_desc *d)
 {
     Layout L{};
@@ -58,7 +62,7 @@ Layout make_layout(const cce_desc *d)
     // Splitting only pays when there are few blocks of stationary rows, which bounds splits * rows, hence the
     // partial buffers, by a constant.
     const int64_t xblocks = (N + 127) / 128;
-    const int most = (xblocks > 0 && xblocks <= 320) ? (int)(2048 / xblocks) : 1;  // the launcher never splits above 320 blocks
+    const int most = (xblocks > 0 && N <= kSplitBelow) ? (int)(2048 / xblocks) : 1;  // the launcher never splits above
     const int64_t col_tiles = (n_cols + by - 1) / by;
     int sx = most < 16 ? most : 16;
     if (sx > col_tiles / 2) sx = (int)(col_tiles / 2);
@@ -100,16 +104,24 @@ Layout make_layout(const cce_desc *d)
     L.cnt = off;      off += align256((size_t)N * 4);
     L.coef = off;     off += align256((size_t)N * 4);
     L.de_const = off; off += align256((size_t)N * 8);
+    // The reserved sizes bound what the shares above need in a form that does not fall as N grows, up to kSplitBelow: a
+    // workspace made for a batch serves a smaller last one.  (Partial rows for batches that have none would outweigh the rest.)
+    auto upto = [](int64_t cap, int64_t n, int64_t rows) { return cap > 1 ? (cap * n < rows ? cap * n : rows) : 0; };
+    const int64_t half = col_tiles / 2, cap8 = col_tiles / 4 < 8 ? col_tiles / 4 : 8;
+    const int64_t cap16 = half < 16 ? half : 16, cap64 = half < 64 ? half : 64;
     {
         // partial (max, sum) per position and split; the fused forward pass also files them for the rows of its
         // last-round split (at most kTailRows of them)
-        size_t words = (sf > 1) ? (size_t)sf * N : 0;
+        size_t words = (size_t)upto(cap64, N, kSplitRows);
+        if (cap8 > 1 && words < (size_t)(cap8 * N)) words = (size_t)(cap8 * N);
         if (fused_dH(d) && tile_tail_partial_bytes(N, d->d) > 0 && words < (size_t)kTailRows) words = (size_t)kTailRows;
         L.part_m = off;   off += align256(words * 4);
         L.part_s = off;   off += align256(words * 4);
     }
     {
-        const size_t split_bytes = (sx > 1) ? (size_t)sx * N * d->d * 4 : 0, tail_bytes = tile_tail_partial_bytes(N, d->d);
+        const int64_t rows = N > kSplitBelow ? 0 : std::max(upto(cap16, N, kSplitRows), upto(cap64, N, 65536));
+        const size_t split_bytes = (size_t)rows * d->d * 4;
+        const size_t tail_bytes = tile_tail_partial_bytes(N, d->d);
         L.part_dH = off;
         off += align256(split_bytes > tail_bytes ? split_bytes : tail_bytes);
     }

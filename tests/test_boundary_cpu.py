@@ -196,3 +196,23 @@ def test_binding_refuses_wrong_dtypes_and_shapes_before_any_launch(binding):
 
     with pytest.raises(TypeError, match="tgt"):
         cce_neg_loss(H, E, tgt.long(), neg, mask, neg_mode=B.CCE_NEG_PER_POSITION)
+
+
+@pytest.mark.parametrize("dtype,limit", [("bf16", 40960), ("f32", 1 << 20)])
+def test_workspace_serves_smaller_batches(binding, dtype, limit):
+    """Shared and full mode: the bytes asked for do not fall as N grows (one workspace for a batch and a smaller last one;
+    bf16 tiles: up to 40,960 positions), and what 4096 positions reserve stays at 16 shares of partial rows."""
+    B = binding
+    dt = B.CCE_BF16 if dtype == "bf16" else B.CCE_F32
+    sizes = sorted(set(list(range(1, 3000, 97)) + list(range(3000, 45000, 331)) + [n + o for n in (1024, 2048, 4096, 16384, 40960, 65536)
+                                                                                   for o in (-128, -1, 0, 1, 128)] + [90000, 204800, 600000]))
+    for d in (64, 128, 256):
+        for mode, cols in ((B.CCE_NEG_SHARED, (1, 100, 600, 4096, 60000)), (B.CCE_NEG_FULL, (700, 30011))):
+            for n_cols in cols:
+                for fuse in (0, 1):
+                    V, K = (70000, n_cols) if mode == B.CCE_NEG_SHARED else (n_cols, 0)
+                    need = [B.cce_neg_workspace_bytes(B.make_desc(N, V, d, K, dt, mode, fuse_dH=fuse)) for N in sizes if N <= limit]
+                    assert need[0] > 0 and all(a <= b for a, b in zip(need, need[1:])), (d, mode, n_cols, fuse)
+    if dtype == "bf16":
+        n = B.cce_neg_workspace_bytes(B.make_desc(4096, 5_000_000, 256, 4096, dt, B.CCE_NEG_SHARED, fuse_dH=1))
+        assert n <= 4096 * (16 * 1024 + 1024 + 20 + 64 * 8) + (1 << 16)

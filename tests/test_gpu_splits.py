@@ -17,3 +17,32 @@ def test_shares_of_the_catalogue(d, V, N):
                       pad_len_lo=N - 20, e_sigma=0.1, tgt_dist="zipf")
     for fuse in (True, False):
         check_against_oracle(w, run_hip(w, fuse_dH=fuse, reuse_prep=fuse), TOL_BF16)
+
+
+@pytest.mark.parametrize("sizes,d,K", [((5000, 4096), 256, 4096), ((9000, 8192), 128, 4096), ((16512, 16384), 64, 4096), ((41100, 40960), 64, 512)])
+def test_one_workspace_for_buckets_of_unequal_size(sizes, d, K, monkeypatch):
+    """The loop of bucketed_step over large buckets makes one workspace for the largest.  Against the one-launch form,
+    which the oracle covers elsewhere; bf16 softmax weights differ by 2^-9 a term, 2^-9 of the norm at most."""
+    import torch
+
+    import paper_2509_09682_amd as P
+    from paper_2509_09682_amd import consumers
+
+    g = torch.Generator(device="cuda").manual_seed(5)
+    M, V = sum(sizes), 20000
+    N = M + 3
+    H = torch.randn((N, d), device="cuda", generator=g).to(torch.bfloat16)
+    E = (0.05 * torch.randn((V, d), device="cuda", generator=g)).to(torch.bfloat16)
+    tgt = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    neg = torch.randint(0, V, (len(sizes), K), device="cuda", generator=g, dtype=torch.int32)
+    order = torch.randperm(N, device="cuda", generator=g)[:M]
+    up = torch.rand(N, device="cuda", generator=g)
+    out = []
+    for bound in (0.0, float("inf")):     # a launch pair per bucket, all buckets in one launch
+        monkeypatch.setattr(consumers, "_BUCKET_FLOPS_FOR_TILES", bound)
+        dE = torch.zeros((V, d), device="cuda")
+        loss, lse, dH = P.bucketed_step(H, E, tgt, order, [0, sizes[0], M], neg, up, dE)
+        out.append((loss, lse, dH.float(), dE))
+    for name, a, b in zip(("loss", "lse", "dH", "dE"), *out):
+        err = float((a - b).norm() / b.norm())
+        assert err <= (4e-6 if name in ("loss", "lse") else 2.0 ** -7 if name == "dH" else 2.0 ** -9), (name, err)
