@@ -63,8 +63,11 @@ def bucketed_step(H: torch.Tensor, E: torch.Tensor, tgt: torch.Tensor, order: to
         lse = torch.zeros(N, device=H.device, dtype=torch.float32)
         dH = torch.zeros((N, d), device=H.device, dtype=H.dtype)
         desc = B.make_desc(N, V, d, Kb, dt, B.CCE_NEG_SHARED, dH_dtype=dt, mask_target_collisions=int(mask_target_collisions))
-        B.cce_neg_bucketed_step(desc, H.contiguous(), E, ts, order.contiguous(), bucket_ptr, bucket_neg,
-                                None if grad_loss is None else grad_loss.contiguous(), loss, lse, dH, dE)
+        g = grad_loss
+        if g is not None and g.numel() != N:   # only the entries of `order` are read
+            g = g.new_zeros(N).index_copy_(0, order, g.index_select(0, order).reshape(-1))
+        B.cce_neg_bucketed_step(desc, H.contiguous(), E, ts, order.contiguous(), bucket_ptr, bucket_neg.contiguous(),
+                                None if g is None else g.contiguous(), loss, lse, dH, dE)
         return loss, lse, dH
     Hs = H.index_select(0, order).contiguous()          # positions in bucket order: slices are contiguous
     gs = None if grad_loss is None else grad_loss.index_select(0, order).contiguous()

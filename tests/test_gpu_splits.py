@@ -46,3 +46,36 @@ def test_one_workspace_for_buckets_of_unequal_size(sizes, d, K, monkeypatch):
     for name, a, b in zip(("loss", "lse", "dH", "dE"), *out):
         err = float((a - b).norm() / b.norm())
         assert err <= (4e-6 if name in ("loss", "lse") else 2.0 ** -7 if name == "dH" else 2.0 ** -9), (name, err)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_both_forms_of_bucketed_step_take_the_same_arguments(dtype, monkeypatch):
+    """Columns of a wider candidate matrix, strided hidden states, order and gradient, a gradient vector longer or shorter than
+    the batch (its entries at the positions that take part count)."""
+    import torch
+
+    import paper_2509_09682_amd as P
+    from paper_2509_09682_amd import consumers
+
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(6)
+    N, V, d, K, M = 70, 300, 64, 21, 50
+    H = torch.randn((N, 2, d), device="cuda", generator=g).to(dt)[:, 1]
+    E = (0.1 * torch.randn((V, d), device="cuda", generator=g)).to(dt)
+    tgt = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    neg = torch.randint(0, V, (3, K + 9), device="cuda", generator=g, dtype=torch.int32)[:, :K]
+    order = torch.randperm(N - 5, device="cuda", generator=g)[:M].repeat_interleave(2)[::2]
+    up = torch.rand(2 * N, device="cuda", generator=g)
+    for bound in ((0.0, float("inf")) if dtype == "bf16" else (0.0,)):
+        monkeypatch.setattr(consumers, "_BUCKET_FLOPS_FOR_TILES", bound)
+        want = None
+        for w in (up[:N], up, up[:N - 5], up[:N, None].expand(N, 2)[:, 0]):
+            dE = torch.zeros((V, d), device="cuda")
+            out = [*P.bucketed_step(H, E, tgt, order, [0, 20, 20, M], neg, w, dE), dE]
+            plain = torch.zeros((V, d), device="cuda")
+            ref = [*P.bucketed_step(H.contiguous(), E, tgt, order.contiguous(), [0, 20, 20, M], neg.contiguous(), up[:N], plain), plain]
+            want = ref if want is None else want
+            for a, b in zip(out[:3] + ref[:3], want[:3] + want[:3]):
+                assert torch.equal(a, b)
+            # dE is a sum by atomics: up to 50 positions' terms in any order, 50 * 2^-24 of the magnitudes
+            assert float((dE - want[3]).abs().max()) <= 1e-5 * float(want[3].abs().max())
