@@ -950,7 +950,14 @@ cce_status cce_neg_bucketed_step(const cce_desc *desc, const void *H, const void
     a.tiles_per_split = (per_bucket + shares - 1) / shares;
     int32_t *tab = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + L.total);
     a.tab = tab;
+    auto pos_of = [&](int64_t b) { return (bucket_ptr[b + 1] - bucket_ptr[b] + fs.xpb - 1) / fs.xpb; };
+    auto de_of = [&](int64_t b) { return ((bucket_ptr[b + 1] - bucket_ptr[b] + ds.by - 1) / ds.by + a.tiles_per_split - 1) / a.tiles_per_split * cand; };
     int64_t pos_blocks = 0, de_blocks = 0;
+    for (int64_t b = 0; b < n_buckets; ++b) {  // before anything is launched
+        de_blocks += de_of(b);
+        if (de_blocks > 0x3fffffffLL) return CCE_ERR_SHAPE;
+    }
+    de_blocks = 0;
     cce::TabChunk chunk;
     int n = 0;
     for (int64_t b = 0; b <= n_buckets; ++b) {
@@ -958,10 +965,8 @@ cce_status cce_neg_bucketed_step(const cce_desc *desc, const void *H, const void
         chunk.word[3 * n + 1] = (int32_t)pos_blocks;
         chunk.word[3 * n + 2] = (int32_t)de_blocks;
         if (b < n_buckets) {
-            const int64_t size = bucket_ptr[b + 1] - bucket_ptr[b];
-            pos_blocks += (size + fs.xpb - 1) / fs.xpb;
-            de_blocks += ((size + ds.by - 1) / ds.by + a.tiles_per_split - 1) / a.tiles_per_split * cand;
-            if (de_blocks > 0x3fffffffLL) return CCE_ERR_SHAPE;
+            pos_blocks += pos_of(b);
+            de_blocks += de_of(b);
         }
         if (++n == cce::kTabEntries || b == n_buckets) {
             hipLaunchKernelGGL(cce::store_table_kernel, dim3(1), dim3(cce::kTabEntries), 0, stream, tab, chunk, n);

@@ -216,3 +216,18 @@ def test_workspace_serves_smaller_batches(binding, dtype, limit):
     if dtype == "bf16":
         n = B.cce_neg_workspace_bytes(B.make_desc(4096, 5_000_000, 256, 4096, dt, B.CCE_NEG_SHARED, fuse_dH=1))
         assert n <= 4096 * (16 * 1024 + 1024 + 20 + 64 * 8) + (1 << 16)
+
+
+def test_bucketed_step_refuses_a_grid_that_does_not_fit_before_launch(binding):
+    """Candidate blocks beyond what one launch holds, by buckets behind the first table launch (256 entries).  Nothing may be
+    launched first: without a GPU that would be a HIP error."""
+    B = binding
+    n_empty, n = 300, 200
+    desc = B.make_desc(n, 1000, 8, 1 << 30, B.CCE_F32, B.CCE_NEG_SHARED)
+    ptr = (ctypes.c_int64 * (n_empty + n + 1))(*([0] * n_empty + list(range(n + 1))))
+    fake = ctypes.c_void_p(0x1000)  # never dereferenced
+    need = int(B.lib().cce_neg_bucketed_workspace_bytes(ctypes.byref(desc), n, n_empty + n))
+    assert need > 0
+    st = B.lib().cce_neg_bucketed_step(ctypes.byref(desc), fake, fake, fake, fake, n, ptr, n_empty + n, fake, None, fake, fake, fake,
+                                       fake, fake, need, None)
+    assert st == B.CCE_ERR_SHAPE
