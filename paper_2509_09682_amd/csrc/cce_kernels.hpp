@@ -53,6 +53,7 @@ struct TileArgs {
     float *part_dH;              // [splits, N, d] partial dH of split runs
     int64_t N, V, n_cols;        // n_cols = K, or V in full-catalogue mode
     int64_t pos_blocks;          // dE launch: blocks [0, pos_blocks) scatter the correct items, the rest run the dE pass
+    int32_t pos_parts;           // dE launch up to d = 128: blocks that share a chunk of the scatter (set by the launcher)
     int64_t pad_blocks;          // dH launch: blocks [0, pad_blocks) zero the dH rows of padded positions (set by the launcher)
     int64_t scale_block0;        // dE launch: blocks from this one on write dH = grad_loss * U (set by the launcher; none
                                  // when scale_blocks is 0)

@@ -318,7 +318,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
 
     if (MODE == MODE_DE && block_id < a.pos_blocks) {  // leading blocks: scatter of the correct items
         static_assert(NW * 64 >= kPosChunk, "the scatter role needs 256 threads");
-        pos_scatter_block<D>(a, block_id, reinterpret_cast<uint64_t *>(buf0), pos_parts(a.N));
+        pos_scatter_block<D>(a, block_id, reinterpret_cast<uint64_t *>(buf0), D <= 128 ? a.pos_parts : pos_parts(a.N));
         return;
     }
     if (MODE == MODE_DE && a.scale_blocks > 0 && block_id >= a.scale_block0) {  // trailing blocks: dH = grad_loss * U
@@ -1695,7 +1695,13 @@ int64_t plan_tile_grid(TileArgs &a, int64_t n_x, int xpb, int threads, int slots
     if (fine && a.splits > 1) a.splits = max_splits;
     int64_t blocks = xblocks * a.splits;
     if (MODE == MODE_DE) {  // the latency-bound scatter blocks go first so that they run under the matrix work
-        a.pos_blocks = a.scatter_apart ? 0 : pos_scatter_blocks(a.N);
+        // blocks that share a chunk only where that does not cost the launch a round more (3000 positions, 16,000 candidates,
+        // d = 128: a grid of 518 blocks instead of 482 on 512 slots, 83 / 75 us)
+        const int64_t chunks = a.scatter_apart ? 0 : (a.N + kPosChunk - 1) / kPosChunk;
+        auto rounds = [&](int64_t n) { return (n + slots - 1) / slots; };
+        a.pos_parts = pos_parts(a.N);
+        if (rounds(blocks + chunks * a.pos_parts) > rounds(blocks + chunks)) a.pos_parts = 1;
+        a.pos_blocks = chunks * a.pos_parts;
         blocks += a.pos_blocks;
     }
     if (MODE == MODE_DH) {

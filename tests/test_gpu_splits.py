@@ -79,3 +79,12 @@ def test_both_forms_of_bucketed_step_take_the_same_arguments(dtype, monkeypatch)
                 assert torch.equal(a, b)
             # dE is a sum by atomics: up to 50 positions' terms in any order, 50 * 2^-24 of the magnitudes
             assert float((dE - want[3]).abs().max()) <= 1e-5 * float(want[3].abs().max())
+
+
+def test_scatter_blocks_that_would_cost_another_round():
+    """505 candidate blocks on 512 block slots: two chunks of positions go whole, where four blocks each would not fit."""
+    from hip_harness import run_hip
+
+    w = make_workload("scatter_round", 1, 300, 128, 505 * 128, 0, "bf16", NEG_FULL, 5, g_kind="random", pad="none", e_sigma=0.1,
+                      tgt_dist="zipf")
+    check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), TOL_BF16)
