@@ -173,8 +173,8 @@ cce_status cce_neg_backward(const cce_desc *desc, const void *H, const void *E, 
  * collision counts, partial max / sum of split launches) lives in a fixed array inside the library's code object,
  * CCE_NEG_NOALLOC_SCRATCH_BYTES per GPU, held until the process ends.  Nothing is allocated or freed by the call:
  * the array's device address is looked up once per device (hipGetSymbolAddress, on the first call with that device
- * current; make that first call outside a graph capture) and a small fill kernel clears the array's header, which
- * keeps whatever the last call left there.
+ * current; make that first call outside a graph capture).  The array keeps whatever the last call left there; a small
+ * fill kernel clears its header where the kernels that follow read it.
  *   - A descriptor whose forward pass needs more scratch than the array holds is refused with CCE_ERR_WORKSPACE
  *     before anything is launched.  Matrix-core path: 20 bytes per position, plus 8 per position and split where the
  *     candidate range is split (at most 8 ways, up to 64 for few positions), so 32 MiB carry between 390,000

@@ -299,11 +299,15 @@ bool dense_compacts(const cce_desc *d, const uint8_t *mask)
 
 // Ways to split the streamed range of `blocks` blocks of the position side so that the chip's block slots are full, with
 // two tiles per share at least, at most 16 shares where each costs a row of partial sums, and partial results of at most
-// `rows` rows.
-int dense_splits(int64_t blocks, int64_t tiles, int slots, bool sums, int64_t rows, int64_t N)
+// `rows` rows.  Shares cost a merge launch, 3.5 us of a caller that queues calls back to back: scoring alone is split only
+// where a whole list takes 10 us or more (unsplit / split, us, fp32 d = 32: 256 candidates 12.6 / 16.1, 512: 18.5 / 15.9;
+// d = 64: 256: 14.5 / 16.1, 512: 24.6 / 15.9; d = 128: 128: 12.9 / 16.0, 256: 20.7 / 15.8; bf16 d = 320: 128: 13.4 / 15.7, 256:
+// 19.8 / 15.9).
+int dense_splits(int64_t blocks, int64_t tiles, const DenseShape &sh, bool sums, int64_t rows, int64_t N)
 {
-    if (blocks < 1 || blocks * 8 > (int64_t)slots * 5) return 1;
-    int64_t s = (slots + blocks - 1) / blocks;
+    if (blocks < 1 || blocks * 8 > (int64_t)sh.slots * 5) return 1;
+    if (!sums && tiles * sh.tile_ns < 10000) return 1;
+    int64_t s = (sh.slots + blocks - 1) / blocks;
     if (sums && s > 16) s = 16;
     if (s > tiles / 2) s = tiles / 2;
     if (N > 0 && s > rows / N) s = rows / N;
@@ -385,7 +389,7 @@ hipError_t dense_positions(const cce_desc *d, int pass, const DenseLayout &L, De
     const DenseShape sh = dense_shape(d->in_dtype == CCE_BF16, pass, d->d);
     a.x_blocks = (d->N + sh.xpb - 1) / sh.xpb;
     const bool sums = pass != DENSE_FWD;
-    a.splits = dense_splits(a.x_blocks, (a.n_cols + sh.by - 1) / sh.by, sh.slots, sums, sums && L.u_rows < L.ms_rows ? L.u_rows : L.ms_rows, d->N);
+    a.splits = dense_splits(a.x_blocks, (a.n_cols + sh.by - 1) / sh.by, sh, sums, sums && L.u_rows < L.ms_rows ? L.u_rows : L.ms_rows, d->N);
     return launch_dense(d->in_dtype == CCE_BF16, pass, a, stream);
 }
 
@@ -894,8 +898,10 @@ cce_status cce_neg_forward_noalloc(const cce_desc *desc, const void *H, const vo
     st = cce::static_scratch(&ws);
     if (st != CCE_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    // the array keeps what the last call left: the header (status word, counters) starts from zero every time
-    if (cce::launch_fill_zero(static_cast<int32_t *>(ws), cce::kHeaderBytes / 4, stream) != hipSuccess) return CCE_ERR_HIP;
+    // the array keeps what the last call left: the header (status word, counters) starts from zero every time.  The dense kernels
+    // read nothing of it but the count that their own preparation has written: no launch for that (it is a quarter of what a
+    // caller with a small batch waits for).
+    if (!cce::use_dense(desc) && cce::launch_fill_zero(static_cast<int32_t *>(ws), cce::kHeaderBytes / 4, stream) != hipSuccess) return CCE_ERR_HIP;
     return cce::forward_impl(desc, cce::Sampler{}, H, E, tgt, neg, mask, loss, lse, ws, stream);
 }
 
@@ -976,7 +982,7 @@ cce_status cce_neg_bucketed_step(const cce_desc *desc, const void *H, const void
         }
     }
     a.x_blocks = pos_blocks;
-    a.splits = cce::dense_splits(pos_blocks, (desc->K + fs.by - 1) / fs.by, fs.slots, true, L.u_rows < L.ms_rows ? L.u_rows : L.ms_rows, n_order);
+    a.splits = cce::dense_splits(pos_blocks, (desc->K + fs.by - 1) / fs.by, fs, true, L.u_rows < L.ms_rows ? L.u_rows : L.ms_rows, n_order);
     if (cce::launch_dense(bf16, cce::DENSE_FDH, a, stream) != hipSuccess) return CCE_ERR_HIP;
     a.x_blocks = cand;
     a.splits = 1;

@@ -781,9 +781,12 @@ DenseShape dense_shape_mode()
             cache[dev].store(slots, std::memory_order_relaxed);
         }
     }
-    // matrix instructions of a tile, 32 cycles each, two wavefronts to a SIMD at 2.4 GHz
+    // matrix instructions of a tile, 32 cycles each, two wavefronts to a SIMD at 2.4 GHz; scoring alone, where a few blocks
+    // have the chip to themselves, as measured (64 positions; fp32, d = 32 / 64 / 128 / 256: 0.87, 1.22, 1.87, 3.15 us; bf16,
+    // d = 48 / 320: 0.79, 1.56)
     constexpr int insts = G::B16 ? 2 * KD + 6 * G::OB : G::BY / 16 * (8 * KD + 4 * G::OB);
-    return DenseShape{G::XPB, G::BY, slots, insts * 64 * 10 / 24};
+    constexpr int alone = G::B16 ? 600 + 96 * KD : 550 + 163 * KD * (G::BY / 16);
+    return DenseShape{G::XPB, G::BY, slots, MODE == DM_FWD ? alone : insts * 64 * 10 / 24};
 }
 template <typename T, int KD>
 DenseShape dense_shape_kd(int pass)

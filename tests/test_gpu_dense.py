@@ -166,3 +166,26 @@ def test_mask_at_any_address_and_a_copy_of_it_in_the_backward_call(dtype, d, bat
         P.cce_neg_forward(desc, H, E, tgt, neg, masks[fwd], out["loss"], out["lse"], ws)
         P.cce_neg_backward(again, H, E, tgt, neg, masks[bwd], out["lse"], torch.from_numpy(w.g).cuda(), out["dH"], out["dE"], ws)
         check_against_oracle(w, {k: v.cpu().numpy() for k, v in out.items()}, tol)
+
+
+@pytest.mark.parametrize("K", [256, 288, 320])
+@pytest.mark.parametrize("batch", [3, 100])
+def test_forward_calls_around_the_shortest_list_that_is_split(K, batch):
+    """d = 64 in fp32: up to 256 candidates a forward call walks the list whole, from 257 on in shares and a merge launch.  The
+    call without a workspace goes first over a larger batch: its scratch memory is used again without being cleared."""
+    import torch
+
+    import paper_2509_09682_amd as P
+    from paper_2509_09682_amd.runner import to_device
+
+    w = make_workload(f"dense_fwd_{K}_{batch}", batch, 60, 64, 900, K, "f32", NEG_SHARED, K + batch, pad="bernoulli", pad_p=0.3,
+                      g_kind="random", e_sigma=0.1, tgt_dist="zipf")
+    out = _run(w)
+    check_against_oracle(w, out, TOL)
+    big = make_workload("dense_fwd_big", 100, 60, 64, 900, 33, "f32", NEG_SHARED, 7, pad="none", g_kind="random")
+    for v in (big, w):
+        desc = P.make_desc(v.N, v.V, v.d, v.K, P.CCE_F32, NEG_SHARED)
+        loss, lse = (torch.full((v.N,), float("nan"), device="cuda") for _ in range(2))
+        P.cce_neg_forward_noalloc(desc, *to_device(v), loss, lse)
+    for name, t in (("loss", loss), ("lse", lse)):
+        assert np.array_equal(t.cpu().numpy().view(np.uint32), out[name].view(np.uint32)), name    # the same kernels, no atomics
