@@ -300,7 +300,7 @@ bool dense_compacts(const cce_desc *d, const uint8_t *mask)
 // Ways to split the streamed range of `blocks` blocks of the position side so that the chip's block slots are full, with
 // two tiles per share at least, at most 16 shares where each costs a row of partial sums, and partial results of at most
 // `rows` rows.  Shares cost a merge launch, 3.5 us of a caller that queues calls back to back: scoring alone is split only
-// where a whole list takes 10 us or more (unsplit / split, us, fp32 d = 32: 256 candidates 12.6 / 16.1, 512: 18.5 / 15.9;
+// where a whole list takes 10 us or more (unsplit / split, us, a fill launch ahead: fp32 d = 32: 256 candidates 12.6 / 16.1, 512: 18.5 / 15.9;
 // d = 64: 256: 14.5 / 16.1, 512: 24.6 / 15.9; d = 128: 128: 12.9 / 16.0, 256: 20.7 / 15.8; bf16 d = 320: 128: 13.4 / 15.7, 256:
 // 19.8 / 15.9).
 int dense_splits(int64_t blocks, int64_t tiles, const DenseShape &sh, bool sums, int64_t rows, int64_t N)
@@ -319,14 +319,15 @@ int dense_splits(int64_t blocks, int64_t tiles, const DenseShape &sh, bool sums,
 // Two blocks per compute unit at most, or four where a share stays long (measured, candidate launch in us: K = 2000,
 // d = 96, 2560 positions, bf16: 25 shares 46, 16 shares 37; K = 1024, d = 64, 10,240 positions, fp32: 32 shares 49,
 // 16 shares 57; K = 128, d = 256, 160 positions, fp32: one share 47, three 27; 9000 items, d = 192, fp32: 4 shares 466,
-// 8 shares 407).
+// 8 shares 407).  Two tiles per share at least, one where there are fewer than eight: a block's chain of tiles is all that a tiny
+// step waits for (160 positions, K = 32, d = 256, fp32: two shares of three tiles 41 us a step, five of one tile 31).
 int64_t dense_shares(int64_t blocks, int64_t tiles, int64_t values, const DenseShape &sh)
 {
     int64_t s = (512 + blocks - 1) / blocks;
     if (tiles / (2 * s) >= 24) s *= 2;
     const double best = sqrt((double)tiles * sh.tile_ns * 327.0 / (double)(values > 0 ? values : 1));
     if ((double)s > best) s = (int64_t)best + 1;
-    if (s > tiles / 2) s = tiles / 2;
+    if (s > tiles / 2) s = tiles < 8 ? std::min(s, tiles) : tiles / 2;
     return s < 1 ? 1 : s;
 }
 

@@ -189,3 +189,12 @@ def test_forward_calls_around_the_shortest_list_that_is_split(K, batch):
         P.cce_neg_forward_noalloc(desc, *to_device(v), loss, lse)
     for name, t in (("loss", loss), ("lse", lse)):
         assert np.array_equal(t.cpu().numpy().view(np.uint32), out[name].view(np.uint32)), name    # the same kernels, no atomics
+
+
+@pytest.mark.parametrize("N", [32, 33, 64, 97, 224, 225])
+@pytest.mark.parametrize("dtype,d", [("f32", 256), ("f32", 512), ("bf16", 96)])
+def test_tiny_steps_in_shares_of_one_tile(N, dtype, d):
+    """One to eight tiles of positions: up to seven are walked by a block each, more in shares of two."""
+    w = make_workload(f"dense_tiny_{N}_{dtype}_d{d}", 1, N, d, 300, 40, dtype, NEG_SHARED, N + d, pad="none" if N % 2 else "right",
+                      pad_len_lo=N - 9, g_kind="random", e_sigma=0.1, tgt_dist="zipf")
+    check_against_oracle(w, _run(w, fuse_dH=True, reuse_prep=True), TOL)
