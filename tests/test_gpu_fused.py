@@ -158,7 +158,7 @@ def test_fused_full_size_c2_against_full_oracle():
     assert errs["dH"] <= b[0] and errs["dE"] <= b[1] and errs["dH_row"] <= b[2] and errs["dE_row"] <= b[3], (errs, b)
 
 
-# ---- the same flag on the row-gather kernels (fp32 inputs, other hidden sizes, per-position negatives): the forward
+# ---- the same flag on the row-gather kernels (per-position negatives, any list with CCE_ALGO_GATHER): the forward
 #      call sums the weighted candidate rows while it has them for the score; the backward call gathers none for dH
 
 def _run_gather(w, **kw):

@@ -14,7 +14,7 @@ TOL_BF16 = 2e-2   # bf16 path
 # contract breaks.  Per tensor: max|x - ref| / max|ref|.  Per row (oracle.compare.row_rel): every dH row and every
 # touched dE row against its own largest entry, floor 1e-3 of the tensor's.
 #   loss / lse, matrix-core path: fp32 accumulation of exact bf16 products, hardware exp2 / log2; worst seen 3.7e-7.
-#   gradients, fp32 arithmetic (row-gather path, fp32 inputs): worst seen 2e-6 per tensor, 3.2e-5 per row.
+#   gradients, fp32 arithmetic (row-gather and dense kernels): worst seen 2e-6 per tensor, 3.2e-5 per row.
 #   gradients, matrix-core path: the probabilities are rounded to bf16 before the second product, half an ulp = 2^-9 =
 #   2e-3 relative per term.  Small cases with few candidates sit right at that figure (worst seen 3.4e-3 per tensor,
 #   4.6e-3 per row), so their bar cannot be ten times the observation without passing the contract; it is about twice.
@@ -678,13 +678,14 @@ def test_random_medium_shapes_on_the_matrix_core_path(seed):
     check_against_oracle(w, _run(w, algo=P.CCE_ALGO_TILE, reuse_prep=reuse), TOL_BF16)
 
 
-@pytest.mark.parametrize("case", ["ordinary_buckets", "one_crowded_bucket", "power_law"])
+@pytest.mark.parametrize("case", ["ordinary_buckets", "small_catalogue", "one_crowded_bucket", "power_law"])
 def test_per_position_index_built_in_slices(case):
     """More (position, negative) pairs than one slice of the inverted index holds (2^22): the index is built and used
-    up slice by slice over the item-id range.  ordinary_buckets: uniform ids over 147 buckets, two slices.
-    one_crowded_bucket: a catalogue of 1000 items, so all 8.4 M pairs fall into one bucket of 2048 ids, more than a
-    eighth of the budget: the bucket stays out of the index and its pairs are added with atomics.  power_law: the
-    head item's bucket is crowded, the others are sliced."""
+    up slice by slice over the item-id range, in buckets of 2^s ids, s the smallest that leaves less than 512 of them.
+    ordinary_buckets: uniform ids over 293 buckets of 1024 ids, two slices.  small_catalogue: 1000 items in 500 buckets of two
+    ids, 8.4 M pairs.  one_crowded_bucket: a tenth of these pairs falls on the two ids of one bucket, more than an eighth of
+    the budget: it stays out of the index and its pairs are added with atomics.  power_law: the head item's bucket of 128 ids
+    is crowded, the others are sliced."""
     import dataclasses
 
     from workloads import zipf_ids
@@ -692,20 +693,30 @@ def test_per_position_index_built_in_slices(case):
     if case == "ordinary_buckets":
         w = make_workload("slices", 100, 200, 64, 300_000, 300, "bf16", NEG_PER_POSITION, 77, g_kind="random", pad="bernoulli",
                           pad_p=0.1, tgt_dist="zipf")
-    elif case == "one_crowded_bucket":
+    elif case in ("small_catalogue", "one_crowded_bucket"):
         w = make_workload("slices_hot", 128, 128, 64, 1000, 512, "bf16", NEG_PER_POSITION, 78, g_kind="random", pad="none")
-    else:
+    if case == "one_crowded_bucket":
+        rng = np.random.default_rng(8)
+        neg = w.neg.copy()
+        hot = rng.random(neg.shape) < 0.1
+        neg[hot] = rng.integers(500, 502, size=int(hot.sum()))
+        w = dataclasses.replace(w, neg=neg)
+    if case == "power_law":
         w = make_workload("slices_zipf", 100, 200, 64, 50_000, 300, "bf16", NEG_PER_POSITION, 79, g_kind="random", pad="right",
                           pad_len_lo=150)
         rng = np.random.default_rng(6)
         ids, _ = zipf_ids(rng, rng, w.N * w.K, w.V, 1.3)
         w = dataclasses.replace(w, neg=ids.reshape(w.N, w.K))
     assert w.N * w.K > (1 << 22)
-    counts = np.bincount((w.neg[w.mask != 0].ravel() >> 11), minlength=(w.V + 2047) >> 11)
+    shift = next(s for s in range(12) if w.V >> s < 512 or s == 11)      # as the library cuts the catalogue
+    counts = np.bincount(w.neg[w.mask != 0].ravel() >> shift)
     print(case, "pairs", w.N * w.K, "buckets", counts.size, "largest bucket", int(counts.max()))
-    if case != "ordinary_buckets":
-        assert counts.max() > (1 << 19)      # beyond an eighth of the budget
-    if case == "power_law":
+    assert (counts.max() > (1 << 19)) == (case in ("one_crowded_bucket", "power_law"))      # beyond an eighth of the budget
+    if case == "one_crowded_bucket":
+        # every position adds its term about 25 times in a row to each of two fp32 sums, one atomic each; equal adds round
+        # alike: 25 sqrt(16384) 2^-25 = 1e-4 of the running sum, which may be several times the final one
+        check_against_oracle(w, _run(w), 5e-4, row_tol=5e-4)
+    elif case == "power_law":
         # the head item's dE row is a sum of over a million terms of both signs, taken by fp32 atomics in arrival order:
         # its rounding error is that of the summation (about sqrt(n) * 2^-24 of the sum of magnitudes), not of the terms
         check_against_oracle(w, _run(w), 2e-3, row_tol=2e-3)

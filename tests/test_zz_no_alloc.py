@@ -70,3 +70,28 @@ def test_noalloc_forward_refuses_what_does_not_fit_and_what_it_cannot_report():
     desc = P.make_desc(1000, 1000, 64, 256, P.CCE_BF16, P.CCE_NEG_SHARED, validate_indices=1)
     assert L.cce_neg_forward_noalloc(ctypes.byref(desc), p, p, p, p, None, p, p, None) == P.CCE_ERR_UNSUPPORTED
     assert L.cce_neg_forward_noalloc(ctypes.byref(desc), None, p, p, p, None, p, p, None) == P.CCE_ERR_NULL
+
+
+def test_noalloc_forward_falls_back_to_the_row_gather_kernels_beyond_the_scratch():
+    """fp32 lists on the dense kernels need 8 bytes of scratch per position: beyond 4,194,272 of them the call runs the
+    row-gather kernels, which need a header only.  One candidate, d = 8: both sides of the limit against the formula."""
+    import torch
+
+    import paper_2509_09682_amd as P
+
+    V, d = 50, 8
+    g = torch.Generator(device="cuda").manual_seed(3)
+    E = torch.randn((V, d), device="cuda", generator=g)
+    neg = torch.tensor([7], dtype=torch.int32, device="cuda")
+    for N in (4_194_240, 4_194_304):
+        H = torch.randn((N, d), device="cuda", generator=g)
+        tgt = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+        mask = (torch.rand(N, device="cuda", generator=g) < 0.7).to(torch.uint8)
+        loss, lse = (torch.full((N,), float("nan"), device="cuda") for _ in range(2))
+        P.cce_neg_forward_noalloc(P.make_desc(N, V, d, 1, P.CCE_F32, NEG_SHARED), H, E, tgt, neg, mask, loss, lse)
+        pos = (H.double() * E[tgt.long()].double()).sum(1)
+        one = torch.where(tgt == 7, -float("inf"), H.double() @ E[7].double())
+        want = torch.logaddexp(pos, one) * mask
+        # scores of eight products of N(0, 1) values reach 30: 2^-24 * 30 * a few roundings in fp32
+        assert float((lse - want).abs().max()) <= 1e-5
+        assert float((loss - (want - pos * mask)).abs().max()) <= 1e-5
