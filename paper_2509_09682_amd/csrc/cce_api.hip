@@ -112,7 +112,7 @@ Layout make_layout(const cce_desc *d)
     {
         // partial (max, sum) per position and split; the fused forward pass also files them for the rows of its
         // last-round split (at most kTailRows of them)
-        size_t words = (size_t)upto(cap64, N, kSplitRows);
+        size_t words = N > kSplitBelow ? 0 : (size_t)upto(cap64, N, kSplitRows);
         if (cap8 > 1 && words < (size_t)(cap8 * N)) words = (size_t)(cap8 * N);
         if (fused_dH(d) && tile_tail_partial_bytes(N, d->d) > 0 && words < (size_t)kTailRows) words = (size_t)kTailRows;
         L.part_m = off;   off += align256(words * 4);

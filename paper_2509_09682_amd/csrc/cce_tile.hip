@@ -59,23 +59,29 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(PrepArgs p)
                     before += (t >= 0 && (int64_t)t < p.V) ? 1 : 0;
                 }
             }
-        } else if (p.mask) {  // whole 16-byte words where the mask has them, single bytes in front of the first and behind the last
-            const int64_t to_word = (int64_t)((16u - (reinterpret_cast<uintptr_t>(p.mask) & 15u)) & 15u);
-            const int64_t front = to_word < i0 ? to_word : i0, n16 = (i0 - front) / 16, back = front + 16 * n16;
-            if (tid < front) before += p.mask[tid] != 0;
-            if (back + tid < i0) before += p.mask[back + tid] != 0;
-            const uint4 *m16 = reinterpret_cast<const uint4 *>(p.mask + front);
-            int64_t c = tid;
-            for (; c + 3 * kPrepThreads < n16; c += 4 * kPrepThreads) {  // four loads in flight: the walk is a chain of latencies
-                const uint4 v0 = m16[c], v1 = m16[c + kPrepThreads], v2 = m16[c + 2 * kPrepThreads], v3 = m16[c + 3 * kPrepThreads];
-                before += nonzero_bytes(v0.x) + nonzero_bytes(v0.y) + nonzero_bytes(v0.z) + nonzero_bytes(v0.w);
-                before += nonzero_bytes(v1.x) + nonzero_bytes(v1.y) + nonzero_bytes(v1.z) + nonzero_bytes(v1.w);
-                before += nonzero_bytes(v2.x) + nonzero_bytes(v2.y) + nonzero_bytes(v2.z) + nonzero_bytes(v2.w);
-                before += nonzero_bytes(v3.x) + nonzero_bytes(v3.y) + nonzero_bytes(v3.z) + nonzero_bytes(v3.w);
-            }
-            for (; c < n16; c += kPrepThreads) {
-                const uint4 v = m16[c];
-                before += nonzero_bytes(v.x) + nonzero_bytes(v.y) + nonzero_bytes(v.z) + nonzero_bytes(v.w);
+        } else if (p.mask) {
+            auto words = [&](const uint4 *m16, int64_t n16) {
+                int64_t c = tid;
+                for (; c + 3 * kPrepThreads < n16; c += 4 * kPrepThreads) {  // four loads in flight: the walk is a chain of latencies
+                    const uint4 v0 = m16[c], v1 = m16[c + kPrepThreads], v2 = m16[c + 2 * kPrepThreads], v3 = m16[c + 3 * kPrepThreads];
+                    before += nonzero_bytes(v0.x) + nonzero_bytes(v0.y) + nonzero_bytes(v0.z) + nonzero_bytes(v0.w);
+                    before += nonzero_bytes(v1.x) + nonzero_bytes(v1.y) + nonzero_bytes(v1.z) + nonzero_bytes(v1.w);
+                    before += nonzero_bytes(v2.x) + nonzero_bytes(v2.y) + nonzero_bytes(v2.z) + nonzero_bytes(v2.w);
+                    before += nonzero_bytes(v3.x) + nonzero_bytes(v3.y) + nonzero_bytes(v3.z) + nonzero_bytes(v3.w);
+                }
+                for (; c < n16; c += kPrepThreads) {
+                    const uint4 v = m16[c];
+                    before += nonzero_bytes(v.x) + nonzero_bytes(v.y) + nonzero_bytes(v.z) + nonzero_bytes(v.w);
+                }
+            };
+            const int off = (int)(reinterpret_cast<uintptr_t>(p.mask) & 15u);
+            if (off == 0) {  // i0 is a multiple of 1024: whole words
+                words(reinterpret_cast<const uint4 *>(p.mask), i0 / 16);
+            } else if (i0 > 0) {  // single bytes in front of the first whole word and behind the last
+                const int64_t front = 16 - off, n16 = (i0 - front) / 16, back = front + 16 * n16;
+                if (tid < front) before += p.mask[tid] != 0;
+                if (back + tid < i0) before += p.mask[back + tid] != 0;
+                words(reinterpret_cast<const uint4 *>(p.mask + front), n16);
             }
         }
 #pragma unroll
