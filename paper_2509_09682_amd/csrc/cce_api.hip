@@ -287,8 +287,11 @@ DenseLayout make_dense_layout(const cce_desc *d)
     L.total = off;
     return L;
 }
-// Padded positions are compacted where that saves more than the launch it takes (about 5 us): a small batch is bound by
-// latencies, and a wavefront without a valid row costs it nothing.
+// Padded positions are compacted where that saves more than the launch it takes: a small batch is bound by latencies, and a
+// wavefront without a valid row costs it nothing.  Steps in us, never / always, fp32, d = 64, K = 1024, 60 % valid: 1000
+// positions 27.0 / 28.3, 4000: 51.6 / 49.7, 12,800: 95.1 / 82.4; 90 % valid: 29.9 / 32.0, 54.5 / 57.2, 104.1 / 101.4; d = 256,
+// K = 256, 60 % valid: 44.7 / 47.7, 61.7 / 59.6, 145 / 115; bf16, d = 96, K = 1024, 90 % valid: 33.7 / 36.7, 53.1 / 54.7, 76.5 /
+// 80.5.
 // The rule looks at the descriptor and at whether there is a mask, never at its address: a backward call that reuses the
 // forward call's preparation may hand over a copy of the mask.
 constexpr int64_t kDenseCompactAbove = 4096;

@@ -166,7 +166,7 @@ constexpr int kPairBatch = 8;
 static_assert(kChunkPairs % (kThreads * kPairBatch) == 0, "whole batches per chunk");
 
 // SAMPLED is a compile-time choice: with the generator in the same loop, stored ids waited behind its branches
-// (part_count_kernel 26 -> 19 us, the filing passes 63 + 37 -> 62 + 32 us on the per-position workload).
+// (part_count_kernel 26 -> 17 us, the filing passes 63 + 37 -> 61 + 30 us on the per-position workload).
 template <bool SAMPLED, typename F>
 __device__ __forceinline__ void for_live_pairs_of(const InvertArgs &a, int64_t chunk, F &&visit)
 {
@@ -417,7 +417,7 @@ __device__ __forceinline__ void walk_segment(const InvertArgs &a, const float (&
                                              int c, float (&acc)[8])
 {
     // Four rows in flight: segments are short (6.5 pairs on average on the per-position workload) and the lane groups of a
-    // wavefront go in step, so that a batch of eight was half empty (item pass 480 -> 450 us).
+    // wavefront go in step, so that a batch of eight was half empty (item pass 480 -> 465 us).
     constexpr int U = 4;
     const T *Hp = static_cast<const T *>(a.H);
     while (__any(r < r_end)) {

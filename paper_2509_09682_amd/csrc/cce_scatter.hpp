@@ -26,9 +26,12 @@ constexpr int kPosChunk = 256;        // pairs per chunk
 constexpr int kPosChunkApart = 1024;  // pairs per chunk of the stand-alone scatter kernels with many positions
 constexpr int kPosParts = 4;
 constexpr int64_t kPosApartAbove = 65536;  // stand-alone: positions from which chunks are long and whole
-constexpr int64_t kPosShareBelow = 8192;   // riding in another launch: positions up to which blocks share a chunk (dE launch,
-                                           // whole / shared: 3200 positions, d = 64: 19 / 14 us; 8000, d = 320: 100 / 52;
-                                           // 25,600, d = 128: 56 / 61)
+// Riding in another launch: positions up to which blocks share a chunk.  dE launch, us, whole / shared: 3200 positions, d = 64:
+// 19 / 14; 8000, d = 320: 100 / 52.  Steps above the line, K = 1024, bf16: tiles, d = 64, 10,880 positions 50.1 / 50.2, 12,800
+// 55.5 / 55.5, 25,600 63.4 / 66.2; d = 128 72.0 / 72.1, 76.2 / 77.6, 97.9 / 101.9.  The line is that of the tiles; the dense
+// kernels and the index passes differ: d = 320, 10,880: 199 / 160, 25,600: 275 / 249, 51,200: 436 / 467; fp32 d = 64, 25,600:
+// 148 / 150; buckets of fp32 d = 128, 25,600: 117 / 136; per position, d = 128, K = 128, 25,600: 403 / 395.
+constexpr int64_t kPosShareBelow = 8192;
 __host__ __device__ inline int pos_parts(int64_t N) { return N <= kPosShareBelow ? kPosParts : 1; }
 inline int64_t pos_scatter_blocks(int64_t N) { return (N + kPosChunk - 1) / kPosChunk * pos_parts(N); }
 
