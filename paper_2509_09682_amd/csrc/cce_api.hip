@@ -317,21 +317,36 @@ int dense_splits(int64_t blocks, int64_t tiles, const DenseShape &sh, bool sums,
     return s < 1 ? 1 : (int)s;
 }
 
-// Shares of the positions on the candidate side.  A share walks tiles / s tiles and adds its rows by atomics, which run
-// at 327 G/s over the chip whoever issues them: tile time tiles / s plus values s / 327 G/s is least at the root below.
-// Two blocks per compute unit at most, or four where a share stays long (measured, candidate launch in us: K = 2000,
-// d = 96, 2560 positions, bf16: 25 shares 46, 16 shares 37; K = 1024, d = 64, 10,240 positions, fp32: 32 shares 49,
-// 16 shares 57; K = 128, d = 256, 160 positions, fp32: one share 47, three 27; 9000 items, d = 192, fp32: 4 shares 466,
-// 8 shares 407).  Two tiles per share at least, one where there are fewer than eight: a block's chain of tiles is all that a tiny
-// step waits for (160 positions, K = 32, d = 256, fp32: two shares of three tiles 41 us a step, five of one tile 31).
+// Shares of the positions on the candidate side.  A share walks tiles / s tiles and adds its rows by atomics, which run at
+// 327 G/s over the chip whoever issues them.  The blocks run in rounds of sh.slots, and a last round that fills at most half
+// of them takes about two thirds of a full one, so the shares that matter are those that end a half or a whole round,
+// and the one where tile time tiles / s and atomics values s / 327 G/s would balance.  Two tiles per share at least, one
+// where there are fewer than eight: a block's chain of tiles is all that a tiny step waits for (160 positions, K = 32,
+// d = 256, fp32: two shares of three tiles 41 us a step, five of one tile 31).  Candidate launch in us, shares that fill the
+// chip about twice / this rule: 3000 positions, 9000 items, d = 256, fp32 413 / 290; 46,080 positions, K = 1024, d = 320, bf16
+// 230 / 216; 5120 positions, K = 1024, d = 192, fp32 66 / 62; 50,000 positions, K = 256, d = 64, fp32 63 / 58.
 int64_t dense_shares(int64_t blocks, int64_t tiles, int64_t values, const DenseShape &sh)
 {
-    int64_t s = (512 + blocks - 1) / blocks;
-    if (tiles / (2 * s) >= 24) s *= 2;
-    const double best = sqrt((double)tiles * sh.tile_ns * 327.0 / (double)(values > 0 ? values : 1));
-    if ((double)s > best) s = (int64_t)best + 1;
-    if (s > tiles / 2) s = tiles < 8 ? std::min(s, tiles) : tiles / 2;
-    return s < 1 ? 1 : s;
+    const int64_t most = tiles < 8 ? tiles : tiles / 2;
+    auto cost = [&](int64_t s) {
+        const int64_t n = blocks * s, full = n / sh.slots, rest = n % sh.slots;
+        const double rounds = (double)full + (rest == 0 ? 0. : (rest * 2 <= sh.slots ? 0.65 : 1.));
+        return rounds * (double)((tiles + s - 1) / s) * sh.tile_ns + (double)values * s / 327.;
+    };
+    int64_t best = 1;
+    double least = cost(1);
+    auto look = [&](int64_t s) {
+        if (s > most) s = most;
+        if (s < 2) return;
+        const double c = cost(s);
+        if (c < least) {
+            least = c;
+            best = s;
+        }
+    };
+    for (int half = 1; half <= 8; ++half) look((int64_t)sh.slots * half / (2 * blocks));
+    look((int64_t)sqrt((double)tiles * sh.tile_ns * 327. / (double)(values > 0 ? values : 1)) + 1);
+    return best;
 }
 
 DenseArgs make_dense_args(const cce_desc *d, const DenseLayout &L, const void *H, const void *E, const int32_t *tgt,
