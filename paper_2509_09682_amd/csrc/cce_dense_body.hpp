@@ -17,13 +17,15 @@
 // weights is at least one and no empty maximum exists.
 //
 // Above a hidden size of 192 (bf16) the accumulators of a whole row do not fit beside the stationary row: DS wavefronts
-// share the rows, each forms all scores and keeps 1/DS of the output columns (one score product more per wavefront
-// against three products of the second kind).
+// share the rows and keep 1/DS of the output columns each.  A score is formed once: a wavefront takes its share of a score
+// block (quads of 16 x 16), cuts the weights into pieces and files them in LDS, where the others read them (12,800 positions,
+// K = 1024, d = 512: position side 158 -> 95 us, candidate side 254 -> 172).
 //
 // Bound: the matrix pipe on large problems (fp32, 5120 positions, 9000 items, d = 192: position side 347 us, 102 of 157
-// TFLOP/s; bf16, 40,960 positions, K = 1024, d = 320: 215 us a side, a quarter of the pipe's peak counting each of the
-// three pieces), the atomics of the candidate side for short lists, chains of first loads below about 2000 positions.
-// Steps, row-gather kernels against these: 51,200 positions, K = 1024, d = 320, bf16 8.01 / 0.44 ms; 12,800 positions,
+// TFLOP/s; bf16, 46,080 positions, K = 1024, d = 320: 166 us a side, 30 % of the pipe's peak counting each of the three
+// pieces; with every score formed twice and rows staged in registers 199 and 230 us), the atomics of the candidate side for
+// short lists, chains of first loads below about 2000 positions.
+// Steps, row-gather kernels against these: 51,200 positions, K = 1024, d = 320, bf16 8.01 / 0.33 ms; 12,800 positions,
 // K = 1024, d = 64, fp32 407 / 92 us; 512 positions, K = 128, d = 64, fp32 32 / 25 us.
 #pragma once
 #include <atomic>
@@ -41,6 +43,20 @@ typedef float df32x16 __attribute__((ext_vector_type(16)));
 typedef float df32x4 __attribute__((ext_vector_type(4)));
 typedef short ds16x4 __attribute__((ext_vector_type(4)));
 typedef ds16x4 __attribute__((address_space(3))) *dlds_v4;
+typedef void __attribute__((address_space(3))) *dlds_ptr;
+typedef const void __attribute__((address_space(1))) *dglobal_cptr;
+
+// Four rows by sixteen columns of a tile, turned round.  The restrict qualifier gives the read an alias scope of its own;
+// without one the compiler guards it with a wait for every load into LDS in flight.
+__device__ __forceinline__ ds16x4 read_tr(dlds_v4 __restrict__ p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16(p); }
+
+typedef uint64_t __attribute__((address_space(3))) *dlds_u64;
+__device__ __forceinline__ void write_half(dlds_u64 __restrict__ p, uint2 v) { *p = (uint64_t)v.y << 32 | v.x; }  // (restrict: as above)
+
+__device__ uint4 no_row;  // sixteen bytes of zeros: what a row that takes no part is loaded from
+
+template <int K>
+__device__ __forceinline__ void dwait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(K) : "memory"); }
 
 enum { DM_FWD = 0, DM_FDH = 1, DM_DH = 2, DM_DE = 3 };
 
@@ -61,18 +77,30 @@ struct DenseGeo {
     // LDS row pitch in chunks.  Odd: the 128-bit operand reads of 16 consecutive rows fall on 16 different chunk slots.
     // Not 1 or 15 modulo 16 for bf16: the transpose reads (4 rows x 4 chunks at once) then meet at most two to a slot.
     static constexpr int PITCH = CPR + ((B16 && KD % 4 == 0) ? 3 : 1);
-    static constexpr int BUF = BY * PITCH;  // chunks per tile buffer
-    static constexpr int NX = 2 * KD;       // 16-byte pieces of the stationary row a lane holds
+    static constexpr int BUF = (BY * PITCH + 63) / 64 * 64;  // chunks per tile buffer, in whole load instructions
+    // EX: the DS wavefronts of a group of stationary rows form a quarter (DS = 4) or half (DS = 2) of a score block each, in
+    // quads of 16 x 16, and exchange the weights through LDS.
+    static constexpr bool EX = B16 && DS > 1;
+    static constexpr int NG = DS == 2 ? 2 : 1;  // EX: quads of a wavefront, side by side (16 stationary rows each)
+    static constexpr int NX = EX ? NG * KD : 2 * KD;  // 16-byte pieces of stationary rows a lane holds
+    static constexpr int EXQ = NW / DS * 3 * 4 * 32;  // EX: chunks of the exchange, (piece, eight streamed rows, stationary row)
     static constexpr int OC = B16 ? 32 : 16;           // output columns per accumulator block
     static constexpr int OB = KD * 32 / OC / DS;       // accumulator blocks per wavefront
-    static constexpr int LPT = (BY * CPR + kDenseThreads - 1) / kDenseThreads;  // staged chunks per thread and tile
-    static constexpr int NST = (B16 && KD >= 10) ? 2 : 1;  // the staging registers are filled and emptied in NST turns
-    static constexpr int LPS = (LPT + NST - 1) / NST;
+    // DIRECT: the streamed rows go straight into LDS, short rows through registers.  A direct load is cheap to wait for and
+    // holds no register, but its address takes three times the arithmetic (a chunk of padding after every row).  Position side,
+    // us, through registers / direct: 1000 positions, 9000 items, d = 48, bf16 26.8 / 29.7; scoring 2000 positions, 20,000
+    // items, d = 128, fp32 109 / 117; 5120 positions, K = 1024, d = 192, fp32 57.1 / 57.4; 3000 positions, 9000 items, d = 256,
+    // fp32 358 / 348; 3000 positions, 20,000 items, d = 320, bf16 289 / 265.
+    static constexpr bool DIRECT = KD >= 8;
+    static constexpr int LPT = DIRECT ? BUF / 64 : (BY * CPR + kDenseThreads - 1) / kDenseThreads;  // load instructions per tile / per thread
+    // Tiles requested ahead: two where three buffers leave room for two blocks per compute unit.
+    static constexpr int PF = !DIRECT ? 1 : 3 * BUF * 16 + (EX ? EXQ * 16 : 0) + 3072 <= 80 * 1024 ? 2 : 1;
+    static constexpr int IDS = PF + 2;                       // tiles whose row numbers (and constants) are at hand
     typedef typename std::conditional<B16, df32x16, df32x4>::type acc_t;
     static constexpr int AQ = B16 ? 4 : 1;  // groups of four consecutive columns in an accumulator block
     static constexpr int EPI = NW * XR * 33 / 4 + 1;  // chunks of the transpose buffers of the candidate side
     static constexpr int KEYS = kDenseScatter / 2;    // chunks of the sort keys of a scatter block
-    static constexpr int LDS_TILES = 2 * BUF > EPI ? 2 * BUF : EPI;
+    static constexpr int LDS_TILES = (PF + 1) * BUF > EPI ? (PF + 1) * BUF : EPI;
     static constexpr int LDS = LDS_TILES > KEYS ? LDS_TILES : KEYS;
 };
 
@@ -83,7 +111,24 @@ __device__ __forceinline__ dbf16x8 as_b8(uint4 v)
     return r;
 }
 
-// Eight fp32 weights as three bf16x8 operands whose sum they are, exactly (up to weights below 2^-110).
+// A barrier of the block that orders LDS accesses and does not wait for global loads in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Fp32 weights as three bf16 operands whose sum they are, exactly (up to weights below 2^-110).
+__device__ __forceinline__ void split3(const float (&v)[4], uint2 (&pl)[3])
+{
+    uint32_t w[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        w[0][i] = __float_as_uint(v[i]);
+        const float r = v[i] - __uint_as_float(w[0][i] & 0xffff0000u);
+        w[1][i] = __float_as_uint(r);
+        w[2][i] = __float_as_uint(r - __uint_as_float(w[1][i] & 0xffff0000u));
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+        pl[p] = make_uint2(__builtin_amdgcn_perm(w[p][1], w[p][0], 0x07060302u), __builtin_amdgcn_perm(w[p][3], w[p][2], 0x07060302u));
+}
 __device__ __forceinline__ void split3(const float *v, uint4 (&pl)[3])
 {
     uint32_t a[8], b[8], c[8];
@@ -284,15 +329,22 @@ template <typename T, int KD, int MODE>
 __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
 {
     typedef DenseGeo<T, KD, MODE> G;
-    constexpr bool DE = MODE == DM_DE, B16 = G::B16;
+    constexpr bool DE = MODE == DM_DE, B16 = G::B16, EX = G::EX;
+    constexpr int NG = G::NG;
     constexpr int BY = G::BY, XR = G::XR, OB = G::OB;
     __shared__ uint4 lds[G::LDS];
-    __shared__ __align__(16) int32_t ids[3][BY];                          // candidate ids / position rows of the tile, -1: no part
-    __shared__ float4 cst[DE ? 3 : 1][DE ? BY / 4 * 3 : 1];  // candidate side: reference, weight factor, target of a row
+    __shared__ __align__(16) int32_t ids[G::IDS][BY];                     // candidate ids / position rows of the tile, -1: no part
+    __shared__ float4 cst[DE ? G::IDS : 1][DE ? BY / 4 * 3 : 1];  // candidate side: reference, weight factor, target of a row
+    __shared__ uint4 xch[EX ? G::EXQ : 1];                   // EX: weights of the score blocks at hand
+    __shared__ float xsum[EX && !DE ? G::NW / G::DS * 2 * 32 : 1];  // EX: a number per stationary row and half of the streamed rows
+    __shared__ int32_t xflag[EX && !DE ? 2 : 1];             // EX: a score has outgrown its reference (by parity of the tile)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lo = lane & (XR - 1), hi = lane / XR;  // column of the stationary operand, share of the reduction index
+    const int swave = __builtin_amdgcn_readfirstlane(wave);
     const int sl = wave % G::DS, xg = wave / G::DS;
+    const int l16 = lane & 15, h16 = lane >> 4;                               // EX: stationary row of a quad, its four streamed rows
+    const int xhalf = sl & 1, xcol = (G::DS == 4 ? sl >> 1 : 0) * 16 + l16;  // EX: streamed half, first stationary row of this lane
     int64_t block = blockIdx.x;
     if (DE) {
         if (block < a.scatter_blocks) {
@@ -351,7 +403,19 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
     }
     const int dch = a.d * (int)sizeof(T) / 16;  // 16-byte chunks of a row
     uint4 xr[G::NX];
-    {
+    if constexpr (EX) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int32_t row = __shfl(xrow, xcol + 16 * g, 64);
+            const uint4 *src = reinterpret_cast<const uint4 *>((DE ? Ep : Hp) + (int64_t)(row < 0 ? 0 : row) * a.d);
+#pragma unroll
+            for (int k = 0; k < KD; ++k) {
+                const int ch = k * 4 + h16;
+                xr[g * KD + k] = make_uint4(0, 0, 0, 0);
+                if (row >= 0 && ch < dch) xr[g * KD + k] = src[ch];
+            }
+        }
+    } else {
         const uint4 *src = reinterpret_cast<const uint4 *>(DE ? Ep + (int64_t)(xrow < 0 ? 0 : xrow) * a.d : Hp + (int64_t)(xrow < 0 ? 0 : xrow) * a.d);
 #pragma unroll
         for (int k = 0; k < G::NX; ++k) {
@@ -361,100 +425,213 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
         }
     }
     float op = 0.f, ref = 0.f;
-    if (!DE) {  // score of the correct item
+    auto dot16 = [](uint4 e, uint4 x) {  // 16 bytes of two rows
+        const uint32_t ew[4] = {e.x, e.y, e.z, e.w}, xw[4] = {x.x, x.y, x.z, x.w};
+        float part = 0.f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (B16) {
+                part = fmaf(bf16_lo(xw[t]), bf16_lo(ew[t]), part);
+                part = fmaf(bf16_hi(xw[t]), bf16_hi(ew[t]), part);
+            } else {
+                part = fmaf(__uint_as_float(xw[t]), __uint_as_float(ew[t]), part);
+            }
+        }
+        return part;
+    };
+    const bool drop_own = a.drop_own != 0;
+    const int32_t x_drop = drop_own ? (DE ? xrow : ti) : -2;  // a column of the other kind with this number takes no part
+    float qref[EX ? NG : 1], qsn[EX ? NG : 1];                // EX: reference and sum of the stationary rows of this wavefront's quads
+    int32_t qdrop[EX ? NG : 1];
+    if constexpr (EX) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            qsn[g] = qref[g] = 0.f;
+            qdrop[g] = __shfl(x_drop, xcol + 16 * g, 64);
+            if (DE) continue;
+            const int32_t own = __shfl(ti, xcol + 16 * g, 64);
+            const bool on = __shfl(xrow, xcol + 16 * g, 64) >= 0;
+            const uint4 *src = reinterpret_cast<const uint4 *>(Ep + (int64_t)(own < 0 ? 0 : own) * a.d);
+#pragma unroll
+            for (int k = 0; k < KD; ++k) {
+                uint4 e = make_uint4(0, 0, 0, 0);
+                if (on && k * 4 + h16 < dch) e = src[k * 4 + h16];
+                qref[g] += dot16(e, xr[g * KD + k]);
+            }
+#pragma unroll
+            for (int off = 16; off < 64; off <<= 1) qref[g] += __shfl_xor(qref[g], off, 64);
+            if (xhalf == 0 && h16 == 0) xsum[xg * 64 + xcol + 16 * g] = qref[g];
+        }
+        if (!DE && tid < 2) xflag[tid] = 0;
+    } else if (!DE) {  // score of the correct item
         const uint4 *src = reinterpret_cast<const uint4 *>(Ep + (int64_t)(ti < 0 ? 0 : ti) * a.d);
 #pragma unroll
         for (int k = 0; k < G::NX; ++k) {
             const int ch = k * (64 / XR) + hi;
             uint4 e = make_uint4(0, 0, 0, 0);
             if (xrow >= 0 && ch < dch) e = src[ch];
-            const uint32_t ew[4] = {e.x, e.y, e.z, e.w}, xw[4] = {xr[k].x, xr[k].y, xr[k].z, xr[k].w};
-            float part = 0.f;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                if (B16) {
-                    part = fmaf(bf16_lo(xw[t]), bf16_lo(ew[t]), part);
-                    part = fmaf(bf16_hi(xw[t]), bf16_hi(ew[t]), part);
-                } else {
-                    part = fmaf(__uint_as_float(xw[t]), __uint_as_float(ew[t]), part);
-                }
-            }
-            op += part;
+            op += dot16(e, xr[k]);
         }
 #pragma unroll
         for (int off = XR; off < 64; off <<= 1) op += __shfl_xor(op, off, 64);
         ref = op;
-        if (MODE == DM_DH) ref = xrow >= 0 ? a.lse_in[xrow] : 0.f;
     }
-    const bool drop_own = a.drop_own != 0;
-    const int32_t x_drop = drop_own ? (DE ? xrow : ti) : -2;  // a column of the other kind with this number takes no part
+    if (MODE == DM_DH) ref = xrow >= 0 ? a.lse_in[xrow] : 0.f;
 
-    // ---- streaming: ids two tiles ahead, rows one tile ahead
-    auto y_id = [&](int64_t t, int e) -> int32_t {  // id / row of streamed row e of tile t
-        const int64_t y = t * BY + e;
-        if (t >= t1 || y >= ny) return -1;
-        if (DE) return dense_row(a, pos0 + y);
-        if (!neg) return (int32_t)y;
-        const int32_t id = neg[y];
-        return (a.validate && (id < 0 || (int64_t)id >= a.V)) ? -1 : id;
+    // ---- streaming: rows PF tiles ahead, their numbers one more
+    // Lane e of the first wavefront fetches the number of streamed row e, and on the candidate side its constants, in two
+    // steps: loads at an address that always exists, whose results nothing looks at until they are filed a tile later (a
+    // check in between would wait for the load with the whole block behind it).
+    const int ye = tid & (BY - 1);
+    struct Raw { uint32_t lo, hi, on; };
+    auto y_clamped = [&](int64_t t) -> int64_t {
+        const int64_t y = t * BY + ye;
+        return y < ny ? y : ny - 1;  // ny > 0
     };
-    struct Cst { float ref, w; int32_t ti; };
-    auto y_cst = [&](int64_t t, int e, int32_t row) -> Cst {
-        Cst c{INFINITY, 0.f, -1};
-        if (row >= 0) {
-            const int64_t at = a.by_slot ? pos0 + t * BY + e : (int64_t)row;
-            const float g = a.g ? a.g[row] : 1.f;
-            c.w = a.inv ? g * a.inv[at] : g;
-            c.ti = dense_tgt(a, pos0 + t * BY + e, row);
-            if (c.w != 0.f) c.ref = a.ref[at];  // a zero factor keeps exp(-inf) = 0: no 0 * inf
+    const char *none = reinterpret_cast<const char *>(&no_row);  // read in the place of a row or an array that is not there
+    asm volatile("" : "+s"(none));                              // (its address is looked up once)
+    auto word = [&](const void *base, int64_t at) {
+        return *(const uint32_t __attribute__((address_space(1))) *)(base ? static_cast<const char *>(base) + at : none);
+    };
+    auto fetch_id = [&](int64_t t) -> Raw {
+        const int64_t y = y_clamped(t), at = pos0 + y;
+        Raw r{0u, 0u, 1u};
+        if (DE) {
+            r.lo = word(a.order ? static_cast<const void *>(a.order) : a.idx, at * (a.order ? 8 : 4));
+            r.hi = word(a.order, at * 8 + 4);
+            r.on = *(const uint8_t __attribute__((address_space(1))) *)(a.mask ? reinterpret_cast<const char *>(a.mask) + at : none);
+        } else {
+            r.lo = word(neg, y * 4);
         }
+        return r;
+    };
+    auto id_of = [&](int64_t t, Raw r) -> int32_t {  // -1: takes no part
+        const int64_t y = t * BY + ye;
+        int32_t id;
+        if (DE) {
+            id = (a.order || a.idx) ? (int32_t)r.lo : (int32_t)(pos0 + y);
+            if (a.order && (r.hi != 0 || (int64_t)r.lo >= a.n_rows)) id = -1;
+            if (a.mask && !a.order && !a.idx && r.on == 0) id = -1;
+        } else {
+            id = neg ? (int32_t)r.lo : (int32_t)y;
+            if (a.validate && (uint32_t)id >= (uint32_t)a.V) id = -1;
+        }
+        return (t < t1 && y < ny) ? id : -1;
+    };
+    struct Cst { uint32_t ref, g, inv, ti; };
+    auto fetch_cst = [&](int64_t t, int32_t row) -> Cst {
+        Cst c{0u, 0u, 0u, 0u};
+        if (!DE) return c;
+        const int64_t slot = pos0 + y_clamped(t), r = row < 0 ? 0 : row, at = a.by_slot ? slot : r;
+        c.g = word(a.g, r * 4);
+        c.inv = word(a.inv, at * 4);
+        c.ti = a.tgt_slot ? word(a.tgt_slot, slot * 4) : word(a.tgt, r * 4);
+        c.ref = word(a.ref, at * 4);
         return c;
     };
-    auto put_cst = [&](int slot, int e, const Cst &c) {
+    auto file = [&](int slot, int32_t id, const Cst &c) {
+        if (tid >= BY) return;
+        ids[slot][tid] = id;
+        if (!DE) return;
         float *f = reinterpret_cast<float *>(cst[DE ? slot : 0]);
-        f[e] = c.ref;
-        f[BY + e] = c.w;
-        f[2 * BY + e] = __int_as_float(c.ti);
+        const float g = a.g ? __uint_as_float(c.g) : 1.f;
+        const float w = id < 0 ? 0.f : (a.inv ? g * __uint_as_float(c.inv) : g);
+        f[tid] = w != 0.f ? __uint_as_float(c.ref) : INFINITY;  // a zero factor keeps exp(-inf) = 0: no 0 * inf
+        f[BY + tid] = w;
+        f[2 * BY + tid] = __int_as_float(id >= 0 ? (int32_t)c.ti : -1);
     };
-    uint4 stage[G::LPS];
+    // One load group: the rows of a tile.  DIRECT: the buffer is a row of chunks in the order of its pitch; an instruction
+    // fills 64 of them, lane l the l-th.  Rows that take no part, columns beyond d and the chunks between rows come from a
+    // chunk of zeros.  The destination is handed over as a bare offset, so that the compiler does not guard every operand read
+    // with a wait for all loads in flight (landed() and the barrier behind it see to that).
     const T *Yp = DE ? Hp : Ep;
-    auto issue = [&](int slot, int turn) {
+    const int32_t row_bytes = a.d * (int)sizeof(T);
+    uint4 stage[G::DIRECT ? 1 : G::LPT];
+    auto issue = [&](int buffer, int slot) {
+        if constexpr (!G::DIRECT) {
 #pragma unroll
-        for (int i = 0; i < G::LPS; ++i) {
-            const int c = (turn * G::LPS + i) * kDenseThreads + tid;
-            stage[i] = make_uint4(0, 0, 0, 0);
-            if (c < BY * G::CPR) {
-                const int r = c / G::CPR, ch = c % G::CPR;
-                const int32_t id = ids[slot][r];
-                if (id >= 0 && ch < dch) stage[i] = reinterpret_cast<const uint4 *>(Yp + (int64_t)id * a.d)[ch];
+            for (int i = 0; i < G::LPT; ++i) {
+                const int c = i * kDenseThreads + tid;
+                stage[i] = make_uint4(0, 0, 0, 0);
+                if (c < BY * G::CPR) {
+                    const int r = c / G::CPR, ch = c % G::CPR;
+                    const int32_t id = ids[slot][r];
+                    if (id >= 0 && ch < dch) stage[i] = reinterpret_cast<const uint4 *>(Yp + (int64_t)id * a.d)[ch];
+                }
             }
+            return;
+        }
+        uint32_t dst = (uint32_t)(uintptr_t)(dlds_ptr)(lds + buffer * G::BUF);
+        asm volatile("" : "+s"(dst));
+        uint32_t me = (uint32_t)tid;
+        asm volatile("" : "+v"(me));  // recomputed at every tile: carried, the chunk numbers would cost a register each
+        // the last wavefronts take what does not divide: the first, which also fetches the numbers, has the fewest loads in flight
+        constexpr int WHOLE = G::LPT / G::NW, REST = G::LPT % G::NW, MOST = WHOLE + (REST ? 1 : 0);
+        auto inst = [&](int i) { return i < WHOLE ? swave + i * G::NW : WHOLE * G::NW + swave - (G::NW - REST); };
+        constexpr int AT_ONCE = MOST <= 6 ? MOST : 3;  // row numbers held at a time
+#pragma unroll
+        for (int i0 = 0; i0 < MOST; i0 += AT_ONCE) {
+            int32_t id[AT_ONCE];
+            uint32_t ofs[AT_ONCE];
+#pragma unroll
+            for (int j = 0; j < AT_ONCE; ++j) {
+                const uint32_t c = (me & 63) + (uint32_t)(inst(i0 + j) * 64), r = c / G::PITCH, ch = c - r * G::PITCH;
+                id[j] = ids[slot][r < BY ? r : BY - 1];
+                if ((int)ch >= dch || r >= BY) id[j] = -1;
+                ofs[j] = ch * 16;
+            }
+#pragma unroll
+            for (int j = 0; j < AT_ONCE; ++j) {
+                const int i = i0 + j;
+                if (i >= MOST || (i >= WHOLE && swave < G::NW - REST)) continue;
+                const char *src = reinterpret_cast<const char *>(Yp) + ((int64_t)id[j] * row_bytes + ofs[j]);
+                if (id[j] < 0) src = none;
+                __builtin_amdgcn_global_load_lds((dglobal_cptr)src, (dlds_ptr)(uintptr_t)(dst + (uint32_t)inst(i) * 1024u), 16, 0, 0);
+            }
+            if (AT_ONCE < MOST) __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto land = [&](uint4 *buf, int turn) {
+    // Waits until at most the youngest PF - 1 load groups are in flight.  A group is requested at every tile, beyond the last
+    // one of zeros, so that the counts are the same on every path.
+    auto landed = [&](int buffer) {
+        if constexpr (!G::DIRECT) {
+            uint4 *const buf = lds + buffer * G::BUF;
 #pragma unroll
-        for (int i = 0; i < G::LPS; ++i) {
-            const int c = (turn * G::LPS + i) * kDenseThreads + tid;
-            if (c < BY * G::CPR) buf[(c / G::CPR) * G::PITCH + c % G::CPR] = stage[i];
+            for (int i = 0; i < G::LPT; ++i) {
+                const int c = i * kDenseThreads + tid;
+                if (c < BY * G::CPR) buf[(c / G::CPR) * G::PITCH + c % G::CPR] = stage[i];
+            }
+        } else if constexpr (G::PF == 1) {
+            dwait_vm<0>();
+        } else {
+            if (G::LPT % G::NW != 0 && swave >= G::NW - G::LPT % G::NW) dwait_vm<G::LPT / G::NW + 1>();
+            else dwait_vm<G::LPT / G::NW>();
         }
     };
-    int32_t next_row = -1;  // candidate side: row of tile t + 3, fetched a turn before its constants
-    if (tid < BY) {
+    Raw raw{0u, 0u, 0u};  // number of row ye of the tile after those at hand
+    if (swave == 0 && ny > 0) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int32_t id = y_id(t0 + q, tid);
-            ids[q][tid] = id;
-            if (DE) put_cst(q, tid, y_cst(t0 + q, tid, id));
+        for (int q = 0; q < G::PF + 1; ++q) {
+            const int32_t id = id_of(t0 + q, fetch_id(t0 + q));
+            file(q, id, fetch_cst(t0 + q, id));
         }
-        if (DE) next_row = y_id(t0 + 2, tid);
+        if (DE) raw = fetch_id(t0 + G::PF + 1);
     }
     __syncthreads();
-    if (t0 < t1) {
+    if constexpr (EX && !DE) {
+        op = xsum[xg * 64 + lo];
+        if (MODE != DM_DH) ref = op;
+        if (MODE == DM_DH) {
 #pragma unroll
-        for (int turn = 0; turn < G::NST; ++turn) {
-            issue(0, turn);
-            land(lds, turn);
+            for (int g = 0; g < NG; ++g) qref[g] = __shfl(ref, xcol + 16 * g, 64);
         }
     }
+    // The stationary rows are waited for here: a load that may be in flight at the head of the loop would have the compiler
+    // wait for all loads at its first use in every turn.
+#pragma unroll
+    for (int k = 0; k < G::NX; ++k) asm volatile("" : "+v"(xr[k].x), "+v"(xr[k].y), "+v"(xr[k].z), "+v"(xr[k].w));
+#pragma unroll
+    for (int q = 0; q < G::PF; ++q) issue(q, q);
 
     typename G::acc_t acc[MODE == DM_FWD ? 1 : OB];
     if (MODE != DM_FWD) {
@@ -466,27 +643,158 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
     float sn = 0.f;
     // fp32 weights of one score block (4 AQ values a lane: streamed rows row_of(i)), then the second product
     constexpr int SUB = BY / XR;  // score blocks per tile
-    int slot = 0;
+    int slot = 0, at = 0;  // of tile t: entry of ids and cst, buffer
+    landed(0);
     for (int64_t t = t0; t < t1; ++t) {
-        const int slot1 = slot == 2 ? 0 : slot + 1, slot2 = slot1 == 2 ? 0 : slot1 + 1;
-        const uint4 *buf = lds + ((t - t0) & 1) * G::BUF;
-        uint4 *const other = lds + ((t - t0 + 1) & 1) * G::BUF;
-        __syncthreads();
-        const bool more = t + 1 < t1;
-        if (more) issue(slot1, 0);
+        const uint4 *buf = lds + at * G::BUF;
+        lds_barrier();
+        // rows of tile t + PF, into the buffer that tile t - 1 has left; position side: numbers of tile t + PF + 1; candidate side:
+        // constants of that tile and numbers of the next
         int32_t id2 = -1;
-        Cst c2{INFINITY, 0.f, -1};
-        if (tid < BY) {
+        Cst c2{0u, 0u, 0u, 0u};
+        if (swave == 0) {
             if (DE) {
-                id2 = next_row;
-                c2 = y_cst(t + 2, tid, id2);
-                next_row = y_id(t + 3, tid);
-            } else {
-                id2 = y_id(t + 2, tid);
+                id2 = id_of(t + G::PF + 1, raw);
+                c2 = fetch_cst(t + G::PF + 1, id2);
             }
+            raw = fetch_id(t + G::PF + (DE ? 2 : 1));
         }
+        issue(at == 0 ? G::PF : at - 1, (slot + G::PF) % G::IDS);
 #pragma unroll
         for (int sb = 0; sb < SUB; ++sb) {
+            uint4 *const xq = xch + xg * (3 * 4 * 32);
+            float v[4 * G::AQ];
+            // operands of the second product for half c of the streamed rows, one per block of output columns: rows hi 4 + j / 4
+            // and 8 below (j: lane of sixteen; EX, odd hi: the other way round), columns of this lane's half of a block of 32
+            uint4 ya[EX ? 2 : 1][OB];
+            auto read_half = [&](int c, uint4 (&y)[OB]) {
+                const uint16_t *tb = reinterpret_cast<const uint16_t *>(buf) + (c * 16 + hi * 4 + (l16 >> 2)) * (G::PITCH * 8) +
+                                     sl * OB * 32 + (h16 & 1) * 16 + (l16 & 3) * 4;
+                const int turn = EX ? hi * 8 * (G::PITCH * 8) : 0;
+#pragma unroll
+                for (int b = 0; b < OB; ++b) {
+                    const ds16x4 r0 = read_tr((dlds_v4)(tb + b * 32 + turn)), r1 = read_tr((dlds_v4)(tb + b * 32 + 8 * (G::PITCH * 8) - turn));
+                    __builtin_memcpy(&y[b].x, &r0, 8);
+                    __builtin_memcpy(&y[b].z, &r1, 8);
+                }
+            };
+            if constexpr (EX) {
+                // quads of the score block: streamed rows 16 xhalf + 4 h16 + r, stationary rows xcol + 16 g
+                df32x4 s[NG];
+#pragma unroll
+                for (int g = 0; g < NG; ++g) s[g] = df32x4{0.f, 0.f, 0.f, 0.f};
+                const uint4 *arow = buf + (xhalf * 16 + l16) * G::PITCH + h16;
+                // Operands well ahead of their use: left to itself the compiler reads two at a time and waits for each pair.  All
+                // of them at once, or two batches in flight where that would spill.
+                constexpr int OPS = (!DE && KD == 10) ? 4 : KD, BATCHES = (KD + OPS - 1) / OPS;
+                uint4 o[BATCHES > 1 ? 2 : 1][OPS];
+                auto read_ops = [&](int n) {
+#pragma unroll
+                    for (int k = 0; k < OPS; ++k)
+                        if (n * OPS + k < KD) o[n & 1][k] = arow[(n * OPS + k) * 4];
+                };
+                read_ops(0);
+#pragma unroll
+                for (int n = 0; n < BATCHES; ++n) {
+                    if (n + 1 < BATCHES) read_ops(n + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int k = 0; k < OPS; ++k)
+#pragma unroll
+                        for (int g = 0; g < NG; ++g)
+                            if (n * OPS + k < KD)
+                                s[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_b8(o[n & 1][k]), as_b8(xr[g * KD + n * OPS + k]), s[g], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                read_half(0, ya[0]);  // the first operands of the second product land under the weights
+                __builtin_amdgcn_sched_barrier(0);
+                const int e4 = xhalf * 4 + h16;  // four streamed rows
+                // weights of a quad.  A chunk of the exchange is what one lane of the second product takes: rows hi 4 .. + 3 of a
+                // half and those 8 below, for odd hi the other way round, so that a store instruction meets every bank once
+                auto put = [&](int g, const float (&w)[4]) {
+                    uint2 pc[3];
+                    split3(w, pc);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+                    {
+                        write_half((dlds_u64)(reinterpret_cast<uint2 *>(xq + (p * 4 + xhalf * 2 + (h16 & 1)) * 32 + xcol + 16 * g) + ((h16 >> 1) ^ (h16 & 1))), pc[p]);
+                        asm volatile("" ::: "memory");  // two stores made into one would lose their alias scope
+                    }
+                };
+                if constexpr (DE) {
+                    const float4 *cf = cst[slot];
+                    const float4 r4 = cf[e4], w4 = cf[BY / 4 + e4], t4 = cf[BY / 2 + e4];
+                    const float rr[4] = {r4.x, r4.y, r4.z, r4.w}, ww[4] = {w4.x, w4.y, w4.z, w4.w}, tt[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) {
+                        float w[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            w[r] = ww[r] * fast_exp(s[g][r] - rr[r]);
+                            if (__float_as_int(tt[r]) == qdrop[g]) w[r] = 0.f;
+                        }
+                        put(g, w);
+                    }
+                    lds_barrier();
+                } else {
+                    const int4 i4 = *reinterpret_cast<const int4 *>(&ids[slot][4 * e4]);
+                    const int32_t ii[4] = {i4.x, i4.y, i4.z, i4.w};
+                    float top[NG], part[NG];
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (ii[r] < 0 || ii[r] == qdrop[g]) s[g][r] = -INFINITY;
+                        top[g] = fmaxf(fmaxf(s[g][0], s[g][1]), fmaxf(s[g][2], s[g][3]));
+                    }
+                    auto weigh = [&](int g) {
+                        float w[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) w[r] = fast_exp(s[g][r] - qref[g]);
+                        put(g, w);
+                        part[g] = (w[0] + w[1]) + (w[2] + w[3]);
+                    };
+                    const int par = (int)(t - t0) & 1;
+                    if (MODE != DM_DH) {
+                        bool high = top[0] > qref[0] + kRescaleAbove;
+                        if (NG == 2) high = high || top[NG - 1] > qref[NG - 1] + kRescaleAbove;
+                        if (__any(high) && lane == 0) xflag[par] = 1;
+                    }
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) weigh(g);
+                    lds_barrier();
+                    if (MODE != DM_DH && __builtin_amdgcn_readfirstlane(xflag[par]) != 0) {
+                        // rare, and the same decision in every wavefront of the block: the references move up to the largest
+                        // score of the tile, the sums are rescaled and the weights formed again
+#pragma unroll
+                        for (int g = 0; g < NG; ++g) {
+                            float m = top[g];
+#pragma unroll
+                            for (int off = 16; off < 64; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+                            if (h16 == 0) xsum[(xg * 2 + xhalf) * 32 + xcol + 16 * g] = m;
+                        }
+                        lds_barrier();
+#pragma unroll
+                        for (int g = 0; g < NG; ++g) {
+                            const float *m = xsum + xg * 64 + xcol + 16 * g;
+                            const float to = fmaxf(qref[g], fmaxf(m[0], m[32]));
+                            qsn[g] *= fast_exp(qref[g] - to);
+                            qref[g] = to;
+                            weigh(g);
+                        }
+                        const float to = fmaxf(ref, fmaxf(xsum[xg * 64 + lo], xsum[xg * 64 + 32 + lo])), sc = fast_exp(ref - to);
+                        ref = to;
+#pragma unroll
+                        for (int b = 0; b < (MODE == DM_FWD ? 0 : OB); ++b)
+#pragma unroll
+                            for (int i = 0; i < 4 * G::AQ; ++i) acc[b][i] *= sc;
+                        lds_barrier();
+                        if (tid == 0) xflag[par] = 0;
+                    }
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) qsn[g] += part[g];
+                }
+            } else {
             typename G::acc_t s;
 #pragma unroll
             for (int i = 0; i < 4 * G::AQ; ++i) s[i] = 0.f;
@@ -503,12 +811,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
                     s = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(o.w), __uint_as_float(xr[k].w), s, 0, 0, 0);
                 }
             }
-            if (G::NST == 2 && sb == 0 && more) {
-                land(other, 0);
-                issue(slot1, 1);
-            }
             // weights: value 4 q + r belongs to streamed row sb XR + 8 q + 4 hi + r (bf16) or sb XR + 4 hi + r (fp32)
-            float v[4 * G::AQ];
             if (DE) {
                 const float4 *cf = cst[DE ? slot : 0];
 #pragma unroll
@@ -557,27 +860,55 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
                 if constexpr (G::AQ == 4) sn += (part[0] + part[1]) + (part[2] + part[3]);
                 else sn += part[0];
             }
+            }
             if (MODE == DM_FWD) continue;
             if constexpr (B16) {
-                const int j16 = lane & 15;
-                // transpose reads: rows hi 4 + j16 / 4 and 8 below, columns of this lane's half of a block of 32
-                const uint16_t *tb = reinterpret_cast<const uint16_t *>(buf) + (hi * 4 + (j16 >> 2)) * (G::PITCH * 8) +
-                                     sl * OB * 32 + ((lane >> 4) & 1) * 16 + (j16 & 3) * 4;
+                if constexpr (EX) {
+                    auto read_weights = [&](int c, uint4 (&pl)[3]) {
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    uint4 pl[3];
-                    split3(v + 8 * c, pl);
+                        for (int p = 0; p < 3; ++p) pl[p] = xq[(p * 4 + c * 2 + hi) * 32 + lo];
+                    };
+                    auto product = [&](int c, uint4 w) {
 #pragma unroll
-                    for (int b = 0; b < OB; ++b) {
-                        const uint16_t *q0 = tb + c * 16 * (G::PITCH * 8) + b * 32;
-                        const ds16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dlds_v4)q0);
-                        const ds16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dlds_v4)(q0 + 8 * (G::PITCH * 8)));
-                        uint4 av;
-                        __builtin_memcpy(&av.x, &r0, 8);
-                        __builtin_memcpy(&av.z, &r1, 8);
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(av), as_b8(pl[2]), acc[b], 0, 0, 0);
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(av), as_b8(pl[1]), acc[b], 0, 0, 0);
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(av), as_b8(pl[0]), acc[b], 0, 0, 0);
+                        for (int b = 0; b < OB; ++b)
+                            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(ya[c][b]), as_b8(w), acc[b], 0, 0, 0);
+                    };
+                    uint4 p0[3], p1[3];
+                    constexpr bool EARLY = DE || KD != 10;  // registers for all operands at once
+                    read_weights(0, p0);
+                    if (EARLY) read_half(1, ya[1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    product(0, p0[2]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (EARLY) read_weights(1, p1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    product(0, p0[1]);
+                    if (!EARLY) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        read_weights(1, p1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    product(0, p0[0]);
+                    if (!EARLY) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        read_half(1, ya[0]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    product(EARLY ? 1 : 0, p1[2]);
+                    product(EARLY ? 1 : 0, p1[1]);
+                    product(EARLY ? 1 : 0, p1[0]);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        uint4 pl[3];
+                        split3(v + 8 * c, pl);
+                        uint4 y[OB];
+                        read_half(c, y);
+#pragma unroll
+                        for (int b = 0; b < OB; ++b)
+#pragma unroll
+                            for (int p = 2; p >= 0; --p)
+                                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(y[b]), as_b8(pl[p]), acc[b], 0, 0, 0);
                     }
                 }
             } else {
@@ -590,13 +921,12 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
                 }
             }
         }
-        if (more) land(other, G::NST - 1);
-        if (tid < BY) {
-            ids[slot2][tid] = id2;
-            if (DE) put_cst(slot2, tid, c2);
-        }
-        slot = slot1;
+        if (swave == 0) file((slot + G::PF + 1) % G::IDS, DE ? id2 : id_of(t + G::PF + 1, raw), c2);
+        slot = slot == G::IDS - 1 ? 0 : slot + 1;
+        at = at == G::PF ? 0 : at + 1;
+        landed(at);
     }
+    if (G::DIRECT) dwait_vm<0>();  // the groups beyond the last tile, before their buffers are used again or given back
 
     if constexpr (DE) {
         // rows of the candidates: blocks of 32 columns turned round in LDS, so that an atomic instruction covers 32
@@ -624,8 +954,20 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
         }
         return;
     } else {
+        if constexpr (EX) {
+            lds_barrier();  // (a rescaling of the last tile may still be reading xsum)
 #pragma unroll
-        for (int off = XR; off < 64; off <<= 1) sn += __shfl_xor(sn, off, 64);
+            for (int g = 0; g < NG; ++g) {
+#pragma unroll
+                for (int off = 16; off < 64; off <<= 1) qsn[g] += __shfl_xor(qsn[g], off, 64);
+                if (h16 == 0) xsum[(xg * 2 + xhalf) * 32 + xcol + 16 * g] = qsn[g];
+            }
+            lds_barrier();
+            sn = xsum[xg * 64 + lo] + xsum[xg * 64 + 32 + lo];
+        } else {
+#pragma unroll
+            for (int off = XR; off < 64; off <<= 1) sn += __shfl_xor(sn, off, 64);
+        }
         const int64_t xs = pos0 + x;  // slot
         if (a.splits > 1) {  // partial results, combined by dense_merge_kernel
             if (x >= nx) return;
@@ -784,7 +1126,7 @@ DenseShape dense_shape_mode()
     // matrix instructions of a tile, 32 cycles each, two wavefronts to a SIMD at 2.4 GHz; scoring alone, where a few blocks
     // have the chip to themselves, as measured (64 positions; fp32, d = 32 / 64 / 128 / 256: 0.87, 1.22, 1.87, 3.15 us; bf16,
     // d = 48 / 320: 0.79, 1.56)
-    constexpr int insts = G::B16 ? 2 * KD + 6 * G::OB : G::BY / 16 * (8 * KD + 4 * G::OB);
+    constexpr int insts = G::B16 ? 2 * KD / G::DS + 6 * G::OB : G::BY / 16 * (8 * KD + 4 * G::OB);
     constexpr int alone = G::B16 ? 600 + 96 * KD : 550 + 163 * KD * (G::BY / 16);
     return DenseShape{G::XPB, G::BY, slots, MODE == DM_FWD ? alone : insts * 64 * 10 / 24};
 }

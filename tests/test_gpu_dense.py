@@ -198,3 +198,24 @@ def test_tiny_steps_in_shares_of_one_tile(N, dtype, d):
     w = make_workload(f"dense_tiny_{N}_{dtype}_d{d}", 1, N, d, 300, 40, dtype, NEG_SHARED, N + d, pad="none" if N % 2 else "right",
                       pad_len_lo=N - 9, g_kind="random", e_sigma=0.1, tgt_dist="zipf")
     check_against_oracle(w, _run(w, fuse_dH=True, reuse_prep=True), TOL)
+
+
+@pytest.mark.parametrize("K", [300, 33, 16])
+@pytest.mark.parametrize("d", [216, 320, 392])
+def test_long_rows_share_scores_and_their_references(d, K):
+    """Above 192 columns several wavefronts form parts of a score block and exchange the weights; a score far above its
+    reference, in either half of a tile, in the first, a later or the short last one, moves the references of the whole block."""
+    import dataclasses
+
+    from workloads import bf16_bits_from_f32
+
+    w = make_workload(f"dense_exchange_{d}_{K}", 3, 45, d, 2000, K, "f32", NEG_SHARED, d + K, pad="bernoulli", pad_p=0.1,
+                      g_kind="random", e_sigma=0.05)
+    H, E = w.H.reshape(w.N, d).copy(), w.E.reshape(w.V, d).copy()
+    for i, at, up in ((5, 3, 150.0), (17, 20, 60.0), (70, 40, 21.0), (90, 170, 25.0), (33, K - 1, 110.0)):   # <h_i, e> = up
+        if at < K:
+            E[int(w.neg[at])] = up * H[i] / float(H[i].astype(np.float64) @ H[i].astype(np.float64))
+    w = dataclasses.replace(w, H=bf16_bits_from_f32(H.reshape(w.H.shape)), E=bf16_bits_from_f32(E.reshape(w.E.shape)), in_dtype="bf16")
+    # a score of 150 carries 2^-24 * 150 of absolute error into its exponent, hence 9e-6 relative into the gradients
+    check_against_oracle(w, _run(w, fuse_dH=True, reuse_prep=True), 4e-5)
+    check_against_oracle(w, _run(w), 4e-5)
