@@ -23,7 +23,9 @@ constexpr int kWavesPerBlock = 4;
 // load instructions in flight per wavefront: bf16 rows stay packed in registers until they are used, so eight fit where
 // four widened ones would
 template <typename T> constexpr int unroll_of() { return RawChunk<T>::kInFlight; }
-constexpr int kWindow = 256;  // per-position negatives: candidate ids a wavefront stages per refill of its LDS window
+// Per-position negatives: candidate ids a wavefront stages per refill of its LDS window.  512: with the correct item in front, a
+// list of 256 ids is 257 candidates, and a second refill for the last of them held up every wavefront.
+constexpr int kWindow = 512;
 
 // Where the ids of the negatives come from.
 enum { IDS_DIRECT = 0,   // shared list (or none): read where needed, every wavefront reads the same cached words
@@ -40,18 +42,27 @@ __device__ __forceinline__ void refill_window(const Params &p, int64_t i, int64_
     const int lane = threadIdx.x & 63;
     __builtin_amdgcn_wave_barrier();
     if (IDS == IDS_SAMPLED) {
-        int32_t id[4];
-        sample4(p.smp, (uint64_t)i, (uint32_t)(j0 >> 2) + lane, id);
-        *reinterpret_cast<int4 *>(win + 4 * lane) = make_int4(id[0], id[1], id[2], id[3]);
-    } else {
-        int32_t id[4];
+        constexpr int G = kWindow / 256;  // groups of four draws per lane
+        Draws d[G];
+        int32_t id[G][4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int g = 0; g < G; ++g) {  // past the list: column 0 (a draw costs more than its look-up, and most lists end here)
+            const uint32_t q = (uint32_t)(j0 >> 2) + g * 64 + lane;
+            d[g] = Draws{};
+            if (4 * (int64_t)q <= p.K) draw4(p.smp, (uint64_t)i, q, d[g]);
+        }
+        resolve4(p.smp, d, id);
+#pragma unroll
+        for (int g = 0; g < G; ++g) *reinterpret_cast<int4 *>(win + 4 * (g * 64 + lane)) = make_int4(id[g][0], id[g][1], id[g][2], id[g][3]);
+    } else {
+        int32_t id[kWindow / 64];
+#pragma unroll
+        for (int t = 0; t < kWindow / 64; ++t) {
             const int64_t j = j0 + t * 64 + lane;
             id[t] = (j >= 1 && j <= p.K) ? p.neg[i * (int64_t)p.K + (j - 1)] : 0;
         }
 #pragma unroll
-        for (int t = 0; t < 4; ++t) win[t * 64 + lane] = id[t];
+        for (int t = 0; t < kWindow / 64; ++t) win[t * 64 + lane] = id[t];
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();

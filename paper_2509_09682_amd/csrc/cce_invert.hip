@@ -161,14 +161,14 @@ constexpr int kSliceHot = -1;                   // slice_of[] of a bucket that s
 
 // The pairs of a block's chunk, kPairBatch per thread at a time: all mask bytes are requested first, then ids and
 // targets of the valid positions only (entries of padded positions are never read), so a thread waits for two round
-// trips per batch instead of three per pair.  Sampled negatives are drawn again here instead of being read.  Fewer than 2^31 pairs on this path: 32-bit pair arithmetic.
+// trips per batch instead of three per pair.  Fewer than 2^31 pairs on this path: 32-bit pair arithmetic.
 constexpr int kPairBatch = 8;
 static_assert(kChunkPairs % (kThreads * kPairBatch) == 0, "whole batches per chunk");
 
 // SAMPLED is a compile-time choice: with the generator in the same loop, stored ids waited behind its branches
 // (part_count_kernel 26 -> 17 us, the filing passes 63 + 37 -> 61 + 30 us on the per-position workload).
-template <bool SAMPLED, typename F>
-__device__ __forceinline__ void for_live_pairs_of(const InvertArgs &a, int64_t chunk, F &&visit)
+template <typename F>
+__device__ __forceinline__ void for_stored_pairs(const InvertArgs &a, int64_t chunk, F &&visit)
 {
     const uint32_t p0 = (uint32_t)chunk * kChunkPairs, total = (uint32_t)(a.N * a.K), K = (uint32_t)a.K;
     for (int u0 = threadIdx.x; u0 < kChunkPairs; u0 += kThreads * kPairBatch) {
@@ -185,8 +185,7 @@ __device__ __forceinline__ void for_live_pairs_of(const InvertArgs &a, int64_t c
         for (int j = 0; j < kPairBatch; ++j) {
             id[j] = ti[j] = 0;
             if (live[j]) {
-                const uint32_t pair = p0 + u0 + j * kThreads;
-                id[j] = SAMPLED ? sample1(a.smp, pos[j], pair - pos[j] * K + 1u) : a.neg[pair];  // slot s is draw s + 1
+                id[j] = a.neg[p0 + u0 + j * kThreads];
                 ti[j] = a.tgt[pos[j]];
             }
         }
@@ -199,11 +198,63 @@ __device__ __forceinline__ void for_live_pairs_of(const InvertArgs &a, int64_t c
     }
 }
 
+// Sampled negatives are drawn again instead of being read, in groups of four draws (a generator call yields two or four), two
+// groups per thread at a time (one draw a thread, eight at a time, each with a generator call of its own: the index of 2.4 M
+// uniform draws from 20,000 items 84 us, so 68).  Draw 0 of a position is its correct item: K / 4 + 1 groups a position, kChunkPairs / 4 to a chunk.
+constexpr int kDrawGroups = 2;
+__host__ __device__ inline int64_t draw_groups(int64_t K) { return K / 4 + 1; }
+template <typename F>
+__device__ __forceinline__ void for_drawn_pairs(const InvertArgs &a, int64_t chunk, F &&visit)
+{
+    const uint32_t per = (uint32_t)draw_groups(a.K), total = (uint32_t)a.N * per, g0 = (uint32_t)chunk * (kChunkPairs / 4);
+    for (int u0 = threadIdx.x; u0 < kChunkPairs / 4; u0 += kThreads * kDrawGroups) {
+        uint32_t pos[kDrawGroups], q[kDrawGroups];
+        bool live[kDrawGroups];
+        int32_t ti[kDrawGroups], id[kDrawGroups][4];
+        Draws d[kDrawGroups];
+#pragma unroll
+        for (int j = 0; j < kDrawGroups; ++j) {
+            const uint32_t grp = g0 + u0 + j * kThreads;
+            pos[j] = grp / per;
+            q[j] = grp - pos[j] * per;
+            live[j] = grp < total && (a.mask == nullptr || a.mask[pos[j]] != 0);
+        }
+#pragma unroll
+        for (int j = 0; j < kDrawGroups; ++j) {
+            d[j] = Draws{};
+            ti[j] = 0;
+            if (live[j]) {
+                ti[j] = a.tgt[pos[j]];
+                draw4(a.smp, pos[j], q[j], d[j]);
+            }
+        }
+        resolve4(a.smp, d, id);
+#pragma unroll
+        for (int j = 0; j < kDrawGroups; ++j) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const uint32_t draw = 4 * q[j] + t;
+                bool on = live[j] && draw >= 1 && draw <= (uint32_t)a.K;
+                if (a.validate && (ti[j] < 0 || (int64_t)ti[j] >= a.V || id[j][t] < 0 || (int64_t)id[j][t] >= a.V)) on = false;  // flagged elsewhere
+                if (a.collide && id[j][t] == ti[j]) on = false;
+                if (on) visit(id[j][t], (int32_t)pos[j]);
+            }
+        }
+    }
+}
+
 template <typename F>
 __device__ __forceinline__ void for_live_pairs(const InvertArgs &a, int64_t chunk, F &&visit)
 {
-    if (a.smp.kind) for_live_pairs_of<true>(a, chunk, visit);
-    else for_live_pairs_of<false>(a, chunk, visit);
+    if (a.smp.kind) for_drawn_pairs(a, chunk, visit);
+    else for_stored_pairs(a, chunk, visit);
+}
+
+// The alias table with both words of an entry side by side.
+__global__ __launch_bounds__(kThreads) void pack_alias_kernel(Sampler s, uint2 *out)
+{
+    const int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (c < s.V) out[c] = make_uint2(s.thresh[c], (uint32_t)s.alias[c]);
 }
 
 __global__ __launch_bounds__(kThreads) void part_count_kernel(InvertArgs a)
@@ -639,6 +690,13 @@ hipError_t launch_sample(const Sampler &smp, int64_t n_pos, int32_t K, int32_t *
     return hipGetLastError();
 }
 
+hipError_t launch_pack_alias(const Sampler &smp, hipStream_t stream)
+{
+    hipLaunchKernelGGL(pack_alias_kernel, dim3((unsigned)(((int64_t)smp.V + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, smp,
+                       const_cast<uint2 *>(smp.packed));
+    return hipGetLastError();
+}
+
 int64_t invert_pair_budget(int64_t N, int64_t K)
 {
     const int64_t pairs = N * K, eighth = (pairs + 7) / 8;
@@ -695,6 +753,7 @@ hipError_t launch_inverted_dE(bool bf16, const InvertArgs &a_in, const TileArgs 
     a.bucket_shift = bucket_shift(a.V);
     a.n_part_blocks = invert_part_blocks(a.N, a.K);
     a.n_chunks = (pairs + kChunkPairs - 1) / kChunkPairs;
+    if (a.smp.kind) a.n_chunks = (a.N * draw_groups(a.K) + kChunkPairs / 4 - 1) / (kChunkPairs / 4);
     a.budget = invert_pair_budget(a.N, a.K);
     a.n_slices = invert_slices(a.N, a.K);
     if (a.n_slices > kMaxSlices) return hipErrorInvalidValue;  // cannot happen: at most 11 by construction
@@ -709,6 +768,7 @@ hipError_t launch_inverted_dE(bool bf16, const InvertArgs &a_in, const TileArgs 
         if (!check()) return e;
     }
     for (int32_t j = 0; j < a.n_slices; ++j) {
+        if (j > 0 && a.smp.packed && (e = launch_pack_alias(a.smp, stream)) != hipSuccess) return e;  // it lies where the pairs are filed
         a.slice = j;
         a.hot_count = a.slice_hot + j;
         {
@@ -734,6 +794,7 @@ hipError_t launch_inverted_dE(bool bf16, const InvertArgs &a_in, const TileArgs 
     }
     if (a.n_slices > 1) {  // buckets too crowded for any slice, if there are any
         ProfScope prof(PROF_ITEM_DE, stream);
+        a.smp.packed = nullptr;  // under the pairs of the last slice
         if (bf16) hipLaunchKernelGGL(hot_bucket_kernel<uint16_t>, dim3((unsigned)a.n_part_blocks), dim3(kThreads), 0, stream, a);
         else hipLaunchKernelGGL(hot_bucket_kernel<float>, dim3((unsigned)a.n_part_blocks), dim3(kThreads), 0, stream, a);
         if (!check()) return e;

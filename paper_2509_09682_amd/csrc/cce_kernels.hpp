@@ -182,6 +182,8 @@ struct ProfScope {
 
 // Writes the ids a sampler denotes: out[n_pos, K], row i = draws 1..K of position i (n_pos = 1: the shared list).
 hipError_t launch_sample(const Sampler &smp, int64_t n_pos, int32_t K, int32_t *out, hipStream_t stream);
+// Fills smp.packed from the caller's table.
+hipError_t launch_pack_alias(const Sampler &smp, hipStream_t stream);
 
 // Clears `words` 32-bit words at dst with a fill kernel (no memset node).
 hipError_t launch_fill_zero(int32_t *dst, size_t words, hipStream_t stream);

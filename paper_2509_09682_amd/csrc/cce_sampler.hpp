@@ -24,6 +24,9 @@ struct Sampler {
     uint32_t V;
     const uint32_t *thresh;   // alias method: [V] keep thresholds in units of 2^-32
     const int32_t *alias;     // alias method: [V]
+    // Alias method, per-position lists of a call with room for it: both words of an entry side by side, so that a draw costs
+    // one access to a random line instead of two, one after the other.
+    const uint2 *packed;      // [V] or nullptr
 };
 
 enum { kSamplerUniform = 1, kSamplerAlias = 2 };
@@ -46,42 +49,76 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
-// Ids of the four consecutive draws j = 4 q4 .. 4 q4 + 3 of a position (both laws).
-__device__ __forceinline__ void sample4(const Sampler &s, uint64_t pos, uint32_t q4, int32_t (&id)[4])
+// The four consecutive draws j = 4 q4 .. 4 q4 + 3 of a position (both laws), in two steps, so that the table look-ups of
+// several groups can be in flight together: the columns, then the ids.
+struct Draws {
+    uint32_t col[4], keep[4];  // column of the table (uniform: the id itself) and the word compared with its threshold
+};
+__device__ __forceinline__ void draw4(const Sampler &s, uint64_t pos, uint32_t q4, Draws &d)
 {
     const uint32_t p_lo = (uint32_t)pos, p_hi = (uint32_t)(pos >> 32);
     uint32_t w[4];
     if (s.kind == kSamplerUniform) {
         philox4x32_10(q4, p_lo, p_hi, s.stream, s.k0, s.k1, w);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) id[t] = (int32_t)__umulhi(w[t], s.V);
+        for (int t = 0; t < 4; ++t) {
+            d.col[t] = __umulhi(w[t], s.V);
+            d.keep[t] = 0;
+        }
     } else {
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             philox4x32_10(2 * q4 + half, p_lo, p_hi, s.stream, s.k0, s.k1, w);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const uint32_t col = __umulhi(w[2 * t], s.V);
-                id[2 * half + t] = (w[2 * t + 1] < s.thresh[col]) ? (int32_t)col : s.alias[col];
+                d.col[2 * half + t] = __umulhi(w[2 * t], s.V);
+                d.keep[2 * half + t] = w[2 * t + 1];
             }
         }
     }
+}
+// Table entries of the draws: one load each from the interleaved table, two dependent ones from the caller's.
+template <int G>
+__device__ __forceinline__ void resolve4(const Sampler &s, const Draws (&d)[G], int32_t (&id)[G][4])
+{
+    if (s.kind == kSamplerUniform) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) id[g][t] = (int32_t)d[g].col[t];
+    } else if (s.packed) {
+        uint2 e[G][4];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) e[g][t] = s.packed[d[g].col[t]];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) id[g][t] = (int32_t)(d[g].keep[t] < e[g][t].x ? d[g].col[t] : e[g][t].y);
+    } else {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) id[g][t] = (d[g].keep[t] < s.thresh[d[g].col[t]]) ? (int32_t)d[g].col[t] : s.alias[d[g].col[t]];
+    }
+}
+__device__ __forceinline__ void sample4(const Sampler &s, uint64_t pos, uint32_t q4, int32_t (&id)[4])
+{
+    Draws d[1];
+    int32_t ids[1][4];
+    draw4(s, pos, q4, d[0]);
+    resolve4(s, d, ids);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) id[t] = ids[0][t];
 }
 
 // Id of a single draw.
 __device__ __forceinline__ int32_t sample1(const Sampler &s, uint64_t pos, uint32_t j)
 {
-    const uint32_t p_lo = (uint32_t)pos, p_hi = (uint32_t)(pos >> 32);
-    uint32_t w[4];
-    if (s.kind == kSamplerUniform) {
-        philox4x32_10(j >> 2, p_lo, p_hi, s.stream, s.k0, s.k1, w);
-        const uint32_t r = (j & 2) ? ((j & 1) ? w[3] : w[2]) : ((j & 1) ? w[1] : w[0]);
-        return (int32_t)__umulhi(r, s.V);
-    }
-    philox4x32_10(j >> 1, p_lo, p_hi, s.stream, s.k0, s.k1, w);
-    const uint32_t r0 = (j & 1) ? w[2] : w[0], r1 = (j & 1) ? w[3] : w[1];
-    const uint32_t col = __umulhi(r0, s.V);
-    return (r1 < s.thresh[col]) ? (int32_t)col : s.alias[col];
+    int32_t id[4];
+    sample4(s, pos, j >> 2, id);
+    return (j & 2) ? ((j & 1) ? id[3] : id[2]) : ((j & 1) ? id[1] : id[0]);
 }
 
 }  // namespace cce

@@ -131,3 +131,18 @@ def test_sampled_calls_edge_cases():
         w = _shape(1, 19, 500, mode, d=128, dtype="bf16")
         w_ref = dataclasses.replace(w, neg=_reference_ids(w, S.UNIFORM, 5, 0, None))
         _check(w_ref, run_hip_sampled(w, smp), TOL_BF16)
+
+
+@pytest.mark.parametrize("N,K,V,d", [(40, 512, 5120, 40), (40, 511, 5121, 40), (61, 255, 700, 64), (33, 256, 900, 128), (90, 3, 60, 16),
+                                     (16500, 256, 30_000, 8)])
+def test_alias_draws_around_their_groups_windows_and_slices(N, K, V, d):
+    """The last group of four draws and the last window of a list, the fewest draws for which the table is copied (4 V) and one
+    less, and more pairs than a slice of the index holds, where it is copied again for the second slice."""
+    from hip_harness import device_sampler, run_hip_sampled
+
+    w = _shape(N, K, V, NEG_PER_POSITION, d=d, pad="bernoulli", pad_p=0.2, tgt_dist="zipf")
+    table = _table(V)
+    smp, keep = device_sampler(S.ALIAS, 31, 2, *table)
+    w_ref = dataclasses.replace(w, neg=_reference_ids(w, S.ALIAS, 31, 2, table))
+    _check(w_ref, run_hip_sampled(w, smp), 2e-5)
+    _check(w_ref, run_hip_sampled(w, smp, fuse_dH=True), 2e-5)
