@@ -24,6 +24,7 @@
 // file of its own (cce_tile_d64.hip, cce_tile_d128.hip, cce_tile_d256.hip), which keeps the build parallel; everything
 // here sits in an unnamed namespace, so each of those files gets its own copy.
 #pragma once
+#include <algorithm>
 #include <atomic>
 
 #include "cce_device.hpp"
@@ -1672,26 +1673,34 @@ inline int pick_splits(int64_t xblocks, int max_splits, int slots, bool cheap_me
 // Split factor and leading blocks of one pass; returns the number of blocks of its grid (0: nothing to do).
 // fine: the pass shares its launch with another role that fills most block slots; if it splits at all, it splits as
 // finely as allowed, so that its blocks fill the gaps (c4: the fused backward launch 704 -> 671 us with 16 instead of 10).
+// as_given: a.splits is the caller's choice.
+// Ways to split the position range of a dE pass at most.
+inline int de_split_cap(const TileArgs &a)
+{
+    // every split of the position range pays n_cols * d atomics: keep them below about a quarter of the matrix
+    // time of the pass (4 n_cols d N flop at ~1 PFLOP/s against ~300 G atomics/s) => splits <= 3e-4 N
+    int cap = (int)(a.N * 5e-4) < 8 ? 8 : (int)(a.N * 5e-4);
+    if (a.d > 128) {
+        // hidden size 256, one block of 256 candidates per compute unit: a short list gives few blocks, and the cap
+        // above left the chip idle.  Tile time tiles / s (2.1 us a tile) plus atomics s n_cols d / 327 G/s is least
+        // at the root (511 candidates, 24,576 positions: 16 splits 93 us)
+        const double best = sqrt((double)(a.N / 32) * 2100.0 * 327.0 / ((double)a.n_cols * a.d));
+        if ((double)cap < best) cap = (int)best;
+    }
+    return cap;
+}
+
 template <int MODE>
-int64_t plan_tile_grid(TileArgs &a, int64_t n_x, int xpb, int threads, int slots, bool fine = false)
+int64_t plan_tile_grid(TileArgs &a, int64_t n_x, int xpb, int threads, int slots, bool fine = false, bool as_given = false)
 {
     const int64_t xblocks = (n_x + xpb - 1) / xpb;
     if (xblocks == 0) return 0;
     if (MODE == MODE_DE) {
-        // every split of the position range pays n_cols * d atomics: keep them below about a quarter of the matrix
-        // time of the pass (4 n_cols d N flop at ~1 PFLOP/s against ~300 G atomics/s) => splits <= 3e-4 N
-        int cap = (int)(a.N * 5e-4) < 8 ? 8 : (int)(a.N * 5e-4);
-        if (a.d > 128) {
-            // hidden size 256, one block of 256 candidates per compute unit: a short list gives few blocks, and the cap
-            // above left the chip idle.  Tile time tiles / s (2.1 us a tile) plus atomics s n_cols d / 327 G/s is least
-            // at the root (511 candidates, 24,576 positions: 16 splits 93 us)
-            const double best = sqrt((double)(a.N / 32) * 2100.0 * 327.0 / ((double)a.n_cols * a.d));
-            if ((double)cap < best) cap = (int)best;
-        }
+        const int cap = de_split_cap(a);
         if (a.splits > cap) a.splits = cap;
     }
     const int max_splits = a.splits;
-    a.splits = pick_splits(xblocks, a.splits, slots, MODE == MODE_FWD, MODE == MODE_DE);
+    if (!as_given) a.splits = pick_splits(xblocks, a.splits, slots, MODE == MODE_FWD, MODE == MODE_DE);
     if (fine && a.splits > 1) a.splits = max_splits;
     int64_t blocks = xblocks * a.splits;
     if (MODE == MODE_DE) {  // the latency-bound scatter blocks go first so that they run under the matrix work
@@ -1717,11 +1726,11 @@ int64_t plan_tile_grid(TileArgs &a, int64_t n_x, int xpb, int threads, int slots
 }
 
 template <int D, int MODE, int BY, int NW, int XG, int MINB, int NBUF, int DS = 1, bool FILTER = false>
-hipError_t launch_tile_kernel(TileArgs &a, int64_t n_x, hipStream_t stream)
+hipError_t launch_tile_kernel(TileArgs &a, int64_t n_x, hipStream_t stream, bool as_given = false)
 {
     const int slots = resident_blocks(tile_kernel<D, MODE, BY, NW, XG, MINB, NBUF, DS, FILTER>, NW * 64);
     constexpr int XPB = (NW / DS) * XG * 32;
-    int64_t blocks = plan_tile_grid<MODE>(a, n_x, XPB, NW * 64, slots);
+    int64_t blocks = plan_tile_grid<MODE>(a, n_x, XPB, NW * 64, slots, false, as_given);
     if (blocks == 0) return hipSuccess;
     a.tail_slots = 0;
     if ((MODE == MODE_DH || MODE == MODE_FDH) && D > 128 && a.splits == 1 && n_x > kTailRows && (int64_t)slots * XPB <= kTailRows) {
@@ -1746,6 +1755,12 @@ hipError_t launch_bwd_kernel(TileArgs &a_dh, TileArgs &a_de, hipStream_t stream)
                        a_dh, a_de, de_blocks);
     return hipGetLastError();
 }
+
+// Hidden size 256: microseconds of a tile in a block of eight wavefronts, and what a tile takes a block of four that has a
+// compute unit to itself, in those (one wavefront to a SIMD: nobody waits for the matrix pipe).  24,576 positions, us, blocks
+// of 256 / of 128: forward + dH against 511 candidates 56 / 42, 2048 candidates 130 / 93; 20,000 positions, 9000 items 453 / 308;
+// dE, 60,000 positions, 511 candidates 105 / 87, 8000 positions 48 / 42.
+constexpr double kTileUs = 2.07, kNarrowTile = 0.65;
 
 template <int D>
 hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
@@ -1835,6 +1850,25 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
                 done = true;
             }
         }
+        if constexpr (D > 128) {
+            // Blocks of 128 rows, one to a compute unit, where that is the faster way to fill the chip: tiles of a share, and the
+            // partial rows of the shares (written and read, at 5 TB/s), which need half the shares.
+            const int cus = resident_blocks(tile_kernel<D, MODE_FDH, BY_B, NW_L, 1, MINB, NBUF_FDH, DS_B, false>, NW_L * 64);
+            const int64_t xb = (a.N + 127) / 128;
+            if (xb > 0 && xb <= cus) {
+                TileArgs w = a;
+                (void)plan_tile_grid<MODE_FDH>(w, a.N, NW_L * 32, NW_L * 64, cus);
+                int64_t s = std::min<int64_t>(cus / xb, a.splits);
+                while (s > 16 && (s & (s - 1)) != 0) s &= s - 1;  // as in pick_splits
+                const double tiles = (double)((a.n_cols + BY_B - 1) / BY_B), rows_us = a.splits > 1 ? (double)a.N * D * 8 / 5e6 : 0.;
+                auto cost = [&](int64_t n, double tile_us) { return tiles / n * tile_us + (n > 1 ? n * rows_us : 0.); };
+                if (cost(s, kTileUs * kNarrowTile) < cost(w.splits, kTileUs)) {
+                    a.splits = (int)s;
+                    e = launch_tile_kernel<D, MODE_FDH, BY_B, 4, 1, 2, NBUF_FDH, DS_B>(a, a.N, stream, true);
+                    done = true;
+                }
+            }
+        }
         if (!done) e = launch_tile_kernel<D, MODE_FDH, BY_B, NW_L, 1, MINB, NBUF_FDH, DS_B>(a, a.N, stream);
         if constexpr (D > 128) {
             if (e == hipSuccess && a.tail_slots > 0) {
@@ -1870,6 +1904,19 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
         if (a.filter_log2 > -INFINITY) {
             if constexpr (D > 128) return launch_tile_kernel<D, MODE_DE, BY_B, NW_L, 1, MINB, NBUF_B, DS_B, true>(a, a.n_cols, stream);
             else return hipErrorInvalidValue;
+        }
+        if constexpr (D > 128) {
+            const int cus = resident_blocks(tile_kernel<D, MODE_DE, BY_B, NW_L, 1, MINB, NBUF_B, DS_B, false>, NW_L * 64);
+            TileArgs w = a;
+            const int64_t wide_blocks = plan_tile_grid<MODE_DE>(w, a.n_cols, NW_L * 32, NW_L * 64, cus);
+            const int64_t xb = (a.n_cols + 127) / 128, tiles = (a.N + BY_B - 1) / BY_B;
+            int64_t s = cus / xb;
+            const int cap = std::min(de_split_cap(a), a.splits);
+            if (s > cap) s = cap;
+            if (s >= 1 && (double)((tiles + s - 1) / s) * kNarrowTile < (double)((wide_blocks + cus - 1) / cus) * ((tiles + w.splits - 1) / w.splits)) {
+                a.splits = (int)s;
+                return launch_tile_kernel<D, MODE_DE, BY_B, 4, 1, 2, NBUF_B, DS_B>(a, a.n_cols, stream, true);
+            }
         }
         return launch_tile_kernel<D, MODE_DE, BY_B, NW_L, 1, MINB, NBUF_B, DS_B>(a, a.n_cols, stream);
     default:

@@ -88,3 +88,22 @@ def test_scatter_blocks_that_would_cost_another_round():
     w = make_workload("scatter_round", 1, 300, 128, 505 * 128, 0, "bf16", NEG_FULL, 5, g_kind="random", pad="none", e_sigma=0.1,
                       tgt_dist="zipf")
     check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), TOL_BF16)
+
+
+@pytest.mark.parametrize("N,K", [(127, 33), (129, 32), (300, 511), (8001, 70), (20000, 41), (33000, 64)])
+def test_blocks_of_either_width_at_d256(N, K):
+    """d = 256: blocks of 128 positions with and without shares, blocks of 256 (the last case); candidates late in the list whose
+    scores outgrow the reference by 90 nats send a block of either kind into the exact form."""
+    import dataclasses
+
+    import numpy as np
+    from hip_harness import run_hip
+    from workloads import NEG_SHARED, bf16_bits_from_f32
+
+    w = make_workload(f"width_{N}_{K}", 1, N, 256, 3000, K, "f32", NEG_SHARED, N + K, g_kind="random", pad="bernoulli", pad_p=0.2,
+                      e_sigma=0.05, tgt_dist="zipf")
+    H, E = w.H.reshape(w.N, 256).copy(), w.E.reshape(w.V, 256).copy()
+    for i in (N // 3, N - 2):
+        E[int(w.neg[K - 1 if i > N // 2 else K - 2])] = 90.0 * H[i] / float(H[i].astype(np.float64) @ H[i].astype(np.float64))
+    w = dataclasses.replace(w, H=bf16_bits_from_f32(H.reshape(w.H.shape)), E=bf16_bits_from_f32(E.reshape(w.E.shape)), in_dtype="bf16")
+    check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), TOL_BF16)
