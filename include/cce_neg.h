@@ -116,9 +116,10 @@ typedef struct {
  *                              Up to 40,960 positions never less than for a smaller N; a larger batch may need less than
  *                              one of 40,960 (ask for every size and take the largest);
  *   per-position mode:         the inverted index that turns the dE scatter into a gather (pairs sorted by item) is
- *                              built and used up in slices of the item-id range: 12 1/8 bytes per pair of ONE slice,
- *                              a slice holding at most B = max(2^22, N K / 8) pairs (so at most 51 MB up to
- *                              N K = 2^25 pairs, and 3/8 of the bytes of the [N,K] id matrix itself beyond), plus
+ *                              built and used up in slices of the item-id range: 6 1/8 bytes per pair of ONE slice up to
+ *                              2^16 positions (12 1/4 above, and beyond 2^22 items), a slice holding at most
+ *                              B = max(2^23, N K / 8) pairs (2^22 for 2^23; so at most 52 MB up to N K = 2^25 pairs,
+ *                              and 3/8 of the bytes of the [N,K] id matrix itself beyond), plus
  *                              4 bytes per table row, 4 per position and at most 32 MiB of bucket counts.  Catalogues
  *                              of more than 2^22 items whose pairs exceed B: a 256-byte header (they keep the atomic
  *                              row adds of Alg. 2);

@@ -189,15 +189,16 @@ Params make_params(const cce_desc *d, const void *H, const void *E, const int32_
 }
 
 // Workspace of the per-position mode: the correct-item coefficients and the inverted index of the negatives, which is
-// built and used up in slices of the item-id range: 12 bytes per pair of ONE slice (at most max(2^22, N K / 8) pairs),
-// one word per item, one per position, and the (bucket, block) counts of the first sort level (32 MiB at most).
+// built and used up in slices of the item-id range: 12 bytes per pair of ONE slice (at most max(2^22, N K / 8) pairs; 6 bytes
+// and 2^23 for 2^22 up to 2^16 positions), one word per item, one per position, and the (bucket, block) counts of the first
+// sort level (32 MiB at most).
 struct PpLayout {
     size_t coef, cursor, block_sums, pairs, tmp, part_hist, hot_list, plan, U, total;
 };
 PpLayout make_pp_layout(const cce_desc *d)
 {
     PpLayout L{};
-    const size_t n_pairs = (size_t)invert_index_pairs(d->N, d->K);
+    const size_t n_pairs = (size_t)invert_index_pairs(d->N, d->K, d->V), pos_bytes = invert_narrow(d->N, d->V) ? 2 : 4;
     const bool part = invert_partitioned(d->V);
     const size_t n_buckets = part ? (size_t)invert_buckets(d->V) : 0;
     const size_t n_hist = part ? n_buckets * (size_t)invert_part_blocks(d->N, d->K) + 1 : 0;
@@ -206,8 +207,8 @@ PpLayout make_pp_layout(const cce_desc *d)
     L.coef = off;        off += align256((size_t)d->N * 4);
     L.cursor = off;      off += align256((size_t)d->V * 4);
     L.block_sums = off;  off += align256(invert_scan_blocks((int64_t)scan_n) * 4);
-    L.pairs = off;       off += align256(n_pairs * 4);
-    L.tmp = off;         off += part ? align256(n_pairs * 8) : 0;
+    L.pairs = off;       off += align256(n_pairs * pos_bytes);
+    L.tmp = off;         off += part ? align256(n_pairs * 2 * pos_bytes) : 0;
     L.part_hist = off;   off += align256(n_hist * 4);
     L.hot_list = off;    off += align256(invert_hot_capacity(d->N, d->K) * 16);
     L.plan = off;        off += align256((2 * n_buckets + (size_t)invert_plan_words()) * 4);
@@ -220,7 +221,7 @@ bool use_inverted(const cce_desc *d)
     // The index holds 32-bit offsets: larger problems keep the atomic row adds of the row-gather pass, and so do
     // catalogues beyond the sliced build (more than 2048 * 2048 items) whose pairs do not fit one slice.
     if (d->neg_mode != CCE_NEG_PER_POSITION || d->K <= 0 || d->N * (int64_t)d->K >= 0x7fffffffLL) return false;
-    return invert_partitioned(d->V) || invert_slices(d->N, d->K) == 1;
+    return invert_partitioned(d->V) || invert_slices(d->N, d->K, d->V) == 1;
 }
 
 // The forward call of the row-gather family forms the hidden-state gradient as well (fuse_dH): every mode but
@@ -682,7 +683,7 @@ cce_status stage_sampler(const cce_desc *desc, const cce_sampler *sampler, void 
     } else {
         smp = s;
         if (s.kind == kSamplerAlias && use_inverted(desc) && invert_partitioned(desc->V) && desc->N * (int64_t)desc->K >= kPackDraws * desc->V &&
-            2 * desc->V <= invert_index_pairs(desc->N, desc->K)) {
+            8 * desc->V <= invert_index_pairs(desc->N, desc->K, desc->V) * (invert_narrow(desc->N, desc->V) ? 2 : 4)) {
             smp.packed = reinterpret_cast<const uint2 *>(static_cast<char *>(workspace) + make_pp_layout(desc).pairs);
             if (launch_pack_alias(smp, stream) != hipSuccess) return CCE_ERR_HIP;
         }
@@ -861,8 +862,8 @@ cce_status backward_impl(const cce_desc *desc, const Sampler &smp, const void *H
     ia.dE = dE;
     ia.cursor = reinterpret_cast<int32_t *>(ws + L.cursor);
     ia.block_sums = reinterpret_cast<int32_t *>(ws + L.block_sums);
-    ia.pairs = reinterpret_cast<int32_t *>(ws + L.pairs);
-    ia.tmp = reinterpret_cast<int2 *>(ws + L.tmp);
+    ia.pairs = ws + L.pairs;
+    ia.tmp = ws + L.tmp;
     ia.part_hist = reinterpret_cast<int32_t *>(ws + L.part_hist);
     ia.hot_list = reinterpret_cast<int4 *>(ws + L.hot_list);
     ia.bucket_start = reinterpret_cast<int32_t *>(ws + L.plan);

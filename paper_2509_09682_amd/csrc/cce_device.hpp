@@ -116,6 +116,7 @@ __device__ __forceinline__ void stream_store(float4 *p, float4 v)
     __builtin_nontemporal_store(w, reinterpret_cast<f32x4_nt *>(p));
 }
 __device__ __forceinline__ int32_t stream_load(const int32_t *p) { return __builtin_nontemporal_load(p); }
+__device__ __forceinline__ uint16_t stream_load(const uint16_t *p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void stream_load8(const float *p, float (&v)[8])
 {
     const float4 a = stream_load(reinterpret_cast<const float4 *>(p)), b = stream_load(reinterpret_cast<const float4 *>(p) + 1);

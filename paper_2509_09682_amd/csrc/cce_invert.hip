@@ -7,6 +7,8 @@
 // V-word table), then let one lane group per item recompute its few scores against hidden states that sit in L2 and
 // add the finished row to dE once, without atomics.  Table rows are read once and written once; no score is stored.
 // The correct items (power-law hot rows) are not part of the index: the aggregated scatter adds them.
+#include <algorithm>
+
 #include "cce_device.hpp"
 #include "cce_kernels.hpp"
 #include "cce_scatter.hpp"
@@ -122,7 +124,7 @@ __global__ __launch_bounds__(kThreads) void fill_kernel(InvertArgs a)
     int32_t id;
     if (pair_live(a, pair, id)) {
         const int32_t slot = atomicAdd(a.cursor + id, 1);
-        a.pairs[slot] = (int32_t)(pair / a.K);  // only the position is needed downstream
+        static_cast<int32_t *>(a.pairs)[slot] = (int32_t)(pair / a.K);  // only the position is needed downstream
     }
 }
 
@@ -150,12 +152,33 @@ constexpr int kMaxPartBlocks = 4096;            // blocks of level 1: bounds the
 // of growing with N * K: every slice is a run of consecutive buckets that holds at most B pairs, gets filed into the same
 // B-entry arrays, and is consumed by the item pass before the next one is filed.  Every table row is still read and
 // written once; a further slice costs one more reading of the ids (4 bytes per pair) and four launches.
-//   B = max(2^22, N K / 8) pairs;  slices = 1 if N K <= B, else ceil(N K / (7/8 B)): the pairs of the ordinary buckets
-//   are cut at the quantiles j / slices of their running count, so a slice holds at most N K / slices + (one bucket)
+//   B = max(2^22, N K / 8) pairs, 2^23 for 2^22 where pairs are narrow (below);  slices = 1 if N K <= B, else
+//   ceil(N K / (7/8 B)): the pairs of the ordinary buckets are cut at the quantiles j / slices of their running count, so a slice holds at most N K / slices + (one bucket)
 //   <= 7/8 B + 1/8 B pairs, PROVIDED no bucket holds more than B / 8 pairs.  Buckets beyond that (consecutive ids
 //   drawing more than half a million pairs, an eighth of everything: a popularity law far more skewed than any workload
 //   here) stay out of the index: their pairs are added to dE one by one with atomics (hot_bucket_kernel).
 constexpr int64_t kMinPairBudget = int64_t(1) << 22;
+// A pair on its way to its item: the id and the position, 8 bytes, and the position alone once it is filed, 4.  Up to 2^16
+// positions both fit half of that, because the bucket is known where an entry is read: the id's offset in it (kMaxBucketShift
+// bits at most) and 16 bits of position.  The same memory then holds twice the pairs, and every index pass moves half the bytes.
+// 25,600 positions, K = 256, 1 M items: one slice instead of two, filing 62 + 30 -> 82 us, sort 2 x 27 -> 39, step 887 -> 853; drawn by
+// popularity: filing 111 + 113 -> 141, step 1476 -> 1257.
+constexpr int64_t kNarrowPositions = int64_t(1) << 16;
+static_assert(kMaxBucketShift <= 16, "an id's offset in its bucket and 16 bits of position fit a word");
+struct WidePair {
+    using Entry = int2;
+    using Pos = int32_t;
+    static __device__ __forceinline__ Entry make(int32_t k, int32_t pos) { return make_int2(k, pos); }
+    static __device__ __forceinline__ int32_t item(Entry e) { return e.x; }
+    static __device__ __forceinline__ Pos pos(Entry e) { return e.y; }
+};
+struct NarrowPair {
+    using Entry = uint32_t;
+    using Pos = uint16_t;
+    static __device__ __forceinline__ Entry make(int32_t k, int32_t pos) { return (uint32_t)k << 16 | (uint32_t)pos; }
+    static __device__ __forceinline__ int32_t item(Entry e) { return (int32_t)(e >> 16); }
+    static __device__ __forceinline__ Pos pos(Entry e) { return (Pos)(e & 0xffffu); }
+};
 constexpr int kMaxSlices = 32;
 constexpr int kSliceHot = -1;                   // slice_of[] of a bucket that stays out of the index
 
@@ -333,7 +356,7 @@ __global__ __launch_bounds__(kScanThreads) void plan_slices_kernel(InvertArgs a)
 
 // D_SC != 0: the first sc_blocks blocks scatter the gradient rows of the correct items (hidden size D_SC) instead;
 // nothing in this launch or the next reads or writes dE, and their latency hides under the filing of the pairs.
-template <int D_SC>
+template <typename P, int D_SC>
 __global__ __launch_bounds__(kThreads) void part_scatter_kernel(InvertArgs a, TileArgs sc, int64_t sc_blocks)
 {
     __shared__ int32_t cur[kMaxBuckets];
@@ -352,7 +375,8 @@ __global__ __launch_bounds__(kThreads) void part_scatter_kernel(InvertArgs a, Ti
     for (int64_t chunk = blk; chunk < a.n_chunks; chunk += nb)
         for_live_pairs(a, chunk, [&](int32_t id, int32_t pos) {
             int32_t *c = &cur[id >> a.bucket_shift];
-            if (*c >= 0) a.tmp[atomicAdd(c, 1)] = make_int2(id, pos);  // cursors only grow: the sign never changes
+            if (*c >= 0)  // cursors only grow: the sign never changes
+                static_cast<typename P::Entry *>(a.tmp)[atomicAdd(c, 1)] = P::make(id & ((1 << a.bucket_shift) - 1), pos);
         });
 }
 
@@ -378,6 +402,78 @@ __global__ __launch_bounds__(kThreads) void hot_bucket_kernel(InvertArgs a)
         });
 }
 
+// Level 2 reads a bucket's entries BATCH a thread at a time.  A hot item owns most entries of its bucket, and 64 lanes adding to
+// one LDS word take 64 turns: in a crowded bucket a wavefront counts the entries that hold the same id as its first lane by
+// ballots over the batch, and one lane adds them at once.  The block of the most crowded bucket is what the launch waits for
+// (6.5 M pairs drawn with p ~ rank^-0.9 from 1 M items, a slice: one add for every 64 entries 157 us, for 512, the next entries on
+// their way meanwhile, 75 us).
+template <typename P, int BATCH>
+struct CrowdedBucket {
+    const typename P::Entry *tmp;
+    int32_t rb, re;
+    int32_t k[BATCH];  // id's offset in the bucket, -1 past its end
+    typename P::Entry t[BATCH], t_next[BATCH];
+
+    __device__ __forceinline__ void fetch(int32_t e0, typename P::Entry (&to)[BATCH]) const
+    {
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const int32_t e = e0 + j * kScanThreads + (int32_t)threadIdx.x;
+            to[j] = typename P::Entry{};
+            if (e < re) to[j] = tmp[e];
+        }
+    }
+    // visit(lead, the lanes that hold it): every batch of the bucket, the next one on its way meanwhile
+    template <typename F>
+    __device__ __forceinline__ void walk(F &&visit)
+    {
+        fetch(rb, t);
+        for (int32_t e0 = rb; e0 < re; e0 += BATCH * kScanThreads) {
+            fetch(e0 + BATCH * kScanThreads, t_next);
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) k[j] = (e0 + j * kScanThreads + (int32_t)threadIdx.x < re) ? P::item(t[j]) : -1;
+            visit(__builtin_amdgcn_readfirstlane(k[0]));
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) t[j] = t_next[j];
+        }
+    }
+    __device__ __forceinline__ void count(int32_t *hist)
+    {
+        walk([&](int32_t lead) {
+            int32_t same = 0;
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) {
+                same += (int32_t)__popcll(__ballot(k[j] == lead));
+                if (k[j] >= 0 && k[j] != lead) atomicAdd(&hist[k[j]], 1);
+            }
+            if ((threadIdx.x & 63) == 0 && lead >= 0) atomicAdd(&hist[lead], same);
+        });
+    }
+    __device__ __forceinline__ void file(int32_t *hist, typename P::Pos *pairs)
+    {
+        const int lane = threadIdx.x & 63;
+        walk([&](int32_t lead) {
+            int32_t before[BATCH], same = 0;
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) {  // ranks among the entries of the first lane's id
+                const uint64_t m = __ballot(k[j] == lead);
+                before[j] = same + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+                same += (int32_t)__popcll(m);
+            }
+            int32_t base = 0;
+            if (lane == 0 && lead >= 0) base = atomicAdd(&hist[lead], same);
+            base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) {
+                if (k[j] < 0) continue;
+                const int32_t slot = k[j] == lead ? base + before[j] : atomicAdd(&hist[k[j]], 1);
+                pairs[rb + slot] = P::pos(t[j]);
+            }
+        });
+    }
+};
+
+template <typename P>
 __global__ __launch_bounds__(kScanThreads) void bucket_sort_kernel(InvertArgs a)
 {
     __shared__ int32_t hist[kMaxBucketIds];
@@ -393,41 +489,23 @@ __global__ __launch_bounds__(kScanThreads) void bucket_sort_kernel(InvertArgs a)
     const int32_t rb = a.bucket_start[b];
     const int32_t re = rb + (s1 - s0);
     const int64_t id0 = (int64_t)b << a.bucket_shift;
+    const typename P::Entry *tmp = static_cast<const typename P::Entry *>(a.tmp);
+    typename P::Pos *pairs = static_cast<typename P::Pos *>(a.pairs);
     for (int k = threadIdx.x; k < kMaxBucketIds; k += kScanThreads) hist[k] = 0;
     __syncthreads();
-    // A hot item owns most entries of its bucket, and 64 lanes adding to one LDS word take 64 turns: in a crowded bucket a
-    // wavefront counts the entries that hold the same id as its first lane by ballots over kSortBatch entries a lane, and one
-    // lane adds them at once.  The block of the most crowded bucket is what the launch waits for (6.5 M pairs drawn with
-    // p ~ rank^-0.9 from 1 M items, a slice: one add for every 64 entries 157 us, for 512, the next entries on their way meanwhile, 75 us).
+    // Block-uniform; ordinary buckets take the plain loops, crowded ones of a few batches an entry a thread at a time (3748
+    // items, 60,000 pairs: eight 7.2 us, one 4.7).
     constexpr int kSortBatch = 8;
-    const bool crowded = re - rb > 16 * ids;  // block-uniform; ordinary buckets take the plain loops
-    const int lane = threadIdx.x & 63;
-    auto fetch = [&](int32_t e0, int2 (&t)[kSortBatch]) {
-#pragma unroll
-        for (int j = 0; j < kSortBatch; ++j) {
-            const int32_t e = e0 + j * kScanThreads + (int32_t)threadIdx.x;
-            t[j] = make_int2((int32_t)id0 - 1, 0);
-            if (e < re) t[j] = a.tmp[e];
-        }
-    };
-    int2 t[kSortBatch], t_next[kSortBatch];  // entries at hand and the ones after them, on their way meanwhile
+    const bool crowded = re - rb > 16 * ids, batches = re - rb > 2 * kSortBatch * kScanThreads;
+    CrowdedBucket<P, kSortBatch> many;
+    CrowdedBucket<P, 1> few;
+    many.tmp = few.tmp = tmp;
+    many.rb = few.rb = rb;
+    many.re = few.re = re;
     if (!crowded)
-        for (int32_t e = rb + (int32_t)threadIdx.x; e < re; e += kScanThreads) atomicAdd(&hist[a.tmp[e].x - (int32_t)id0], 1);
-    if (crowded) fetch(rb, t);
-    for (int32_t e0 = rb; crowded && e0 < re; e0 += kSortBatch * kScanThreads) {
-        fetch(e0 + kSortBatch * kScanThreads, t_next);
-        const int32_t lead = __builtin_amdgcn_readfirstlane(t[0].x);
-        int32_t same = 0;
-#pragma unroll
-        for (int j = 0; j < kSortBatch; ++j) {
-            same += (int32_t)__popcll(__ballot(t[j].x == lead));
-            if (t[j].x >= (int32_t)id0 && t[j].x != lead) atomicAdd(&hist[t[j].x - (int32_t)id0], 1);
-        }
-        if (lane == 0 && lead >= (int32_t)id0) atomicAdd(&hist[lead - (int32_t)id0], same);
-#pragma unroll
-        for (int j = 0; j < kSortBatch; ++j) t[j] = t_next[j];
-    }
-    if (crowded) fetch(rb, t);  // again, for the filing
+        for (int32_t e = rb + (int32_t)threadIdx.x; e < re; e += kScanThreads) atomicAdd(&hist[P::item(tmp[e])], 1);
+    else if (batches) many.count(hist);
+    else few.count(hist);
     __syncthreads();
     // exclusive scan over the counts: consecutive ids per thread
     int32_t v[kMaxBucketIds / kScanThreads], sum = 0;
@@ -448,38 +526,18 @@ __global__ __launch_bounds__(kScanThreads) void bucket_sort_kernel(InvertArgs a)
     __syncthreads();
     if (!crowded)
         for (int32_t e = rb + (int32_t)threadIdx.x; e < re; e += kScanThreads) {
-            const int2 t = a.tmp[e];
-            const int32_t slot = atomicAdd(&hist[t.x - (int32_t)id0], 1);
-            a.pairs[rb + slot] = t.y;
+            const typename P::Entry t = tmp[e];
+            const int32_t slot = atomicAdd(&hist[P::item(t)], 1);
+            pairs[rb + slot] = P::pos(t);
         }
-    for (int32_t e0 = rb; crowded && e0 < re; e0 += kSortBatch * kScanThreads) {
-        fetch(e0 + kSortBatch * kScanThreads, t_next);
-        int32_t before[kSortBatch], same = 0;
-        const int32_t lead = __builtin_amdgcn_readfirstlane(t[0].x);
-#pragma unroll
-        for (int j = 0; j < kSortBatch; ++j) {  // ranks among the entries of the first lane's id
-            const uint64_t m = __ballot(t[j].x == lead);
-            before[j] = same + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
-            same += (int32_t)__popcll(m);
-        }
-        int32_t base = 0;
-        if (lane == 0 && lead >= (int32_t)id0) base = atomicAdd(&hist[lead - (int32_t)id0], same);
-        base = __builtin_amdgcn_readfirstlane(base);
-#pragma unroll
-        for (int j = 0; j < kSortBatch; ++j) {
-            if (t[j].x < (int32_t)id0) continue;
-            const int32_t slot = t[j].x == lead ? base + before[j] : atomicAdd(&hist[t[j].x - (int32_t)id0], 1);
-            a.pairs[rb + slot] = t[j].y;
-        }
-#pragma unroll
-        for (int j = 0; j < kSortBatch; ++j) t[j] = t_next[j];
-    }
+    else if (batches) many.file(hist, pairs);
+    else few.file(hist, pairs);
 }
 
 // Walks the positions filed in pairs[r, r_end) for the item whose row e the lane group holds, four at a time:
 // recomputes each score against the hidden state (L2-resident), forms g exp(o - lse) and adds G h to acc.
 // Every lane of the wavefront calls it (the loop condition is a wavefront vote, the scalar products use shuffles).
-template <typename T, int LPR>
+template <typename T, typename P, int LPR>
 __device__ __forceinline__ void walk_segment(const InvertArgs &a, const float (&e)[8], int32_t r, int32_t r_end, bool col_ok,
                                              int c, float (&acc)[8])
 {
@@ -492,7 +550,7 @@ __device__ __forceinline__ void walk_segment(const InvertArgs &a, const float (&
         RawChunk<T> raw[U];
         float lse[U], g[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) pos[u] = (r + u < r_end) ? stream_load(a.pairs + r + u) : -1;
+        for (int u = 0; u < U; ++u) pos[u] = (r + u < r_end) ? (int32_t)stream_load(static_cast<const typename P::Pos *>(a.pairs) + r + u) : -1;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             raw[u].clear();
@@ -529,7 +587,7 @@ constexpr int kHotChunk = 1024;
 constexpr int kItemBlocks = 16384;  // grid of the item pass over a slice
 
 // One group of LPR lanes per item: e_v stays in registers, the positions that sampled it are walked four at a time.
-template <typename T, int LPR>
+template <typename T, typename P, int LPR>
 __global__ __launch_bounds__(kThreads) void item_dE_kernel(InvertArgs a)
 {
     constexpr int GPW = 64 / LPR;  // items per wavefront
@@ -577,7 +635,7 @@ __global__ __launch_bounds__(kThreads) void item_dE_kernel(InvertArgs a)
         dx = stream_load(row);
         dy = stream_load(row + 1);
     }
-    walk_segment<T, LPR>(a, e, r, r_end, col_ok, c, acc);
+    walk_segment<T, P, LPR>(a, e, r, r_end, col_ok, c, acc);
     // the row belongs to this lane group alone: plain read-modify-write
     if (mine) {
         dx.x += acc[0]; dx.y += acc[1]; dx.z += acc[2]; dx.w += acc[3];
@@ -594,7 +652,7 @@ __global__ __launch_bounds__(kThreads) void item_dE_kernel(InvertArgs a)
 // each).  With 256 pairs a chunk, a lane group per chunk and eight strided floats per lane (eight instructions) a third
 // of the item's time was spent there: 6.5 M pairs drawn with p ~ rank^-0.9 from 1 M items, d = 128: 348 us before.
 constexpr int kHotBlocks = 2048;
-template <typename T, int LPR>
+template <typename T, typename P, int LPR>
 __global__ __launch_bounds__(kThreads) void hot_item_kernel(InvertArgs a)
 {
     constexpr int GPW = 64 / LPR, WAVES = kThreads / 64;
@@ -610,7 +668,7 @@ __global__ __launch_bounds__(kThreads) void hot_item_kernel(InvertArgs a)
         for (int t = 0; t < 8; ++t) e[t] = acc[t] = 0.f;
         if (col_ok) load8(static_cast<const T *>(a.E) + h.x * (int64_t)a.d + c * 8, e);
         const int32_t share = (h.z - h.y + WAVES * GPW - 1) / (WAVES * GPW), r = h.y + (wave * GPW + grp) * share;
-        walk_segment<T, LPR>(a, e, r, min(r + share, h.z), col_ok, c, acc);
+        walk_segment<T, P, LPR>(a, e, r, min(r + share, h.z), col_ok, c, acc);
 #pragma unroll
         for (int off = LPR; off < 64; off <<= 1) {
 #pragma unroll
@@ -631,7 +689,7 @@ __global__ __launch_bounds__(kThreads) void hot_item_kernel(InvertArgs a)
     }
 }
 
-template <typename T, int LPR>
+template <typename T, typename P, int LPR>
 hipError_t launch_item_dE(const InvertArgs &a, hipStream_t stream)
 {
     constexpr int items_per_block = (kThreads / 64) * (64 / LPR);
@@ -644,23 +702,23 @@ hipError_t launch_item_dE(const InvertArgs &a, hipStream_t stream)
     // kItemBlocks strides over it
     int64_t item_blocks = (a.V + items_per_block - 1) / items_per_block;
     if (a.slice_of && item_blocks > kItemBlocks) item_blocks = kItemBlocks;
-    hipLaunchKernelGGL((item_dE_kernel<T, LPR>), dim3((unsigned)item_blocks), dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL((item_dE_kernel<T, P, LPR>), dim3((unsigned)item_blocks), dim3(kThreads), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((hot_item_kernel<T, LPR>), dim3(kHotBlocks), dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL((hot_item_kernel<T, P, LPR>), dim3(kHotBlocks), dim3(kThreads), 0, stream, a);
     return hipGetLastError();
 }
 
-template <typename T>
+template <typename T, typename P>
 hipError_t launch_item_dE_by_width(const InvertArgs &a, hipStream_t stream)
 {
     const int chunks = (a.d + 7) / 8;
-    if (chunks <= 2) return launch_item_dE<T, 2>(a, stream);
-    if (chunks <= 4) return launch_item_dE<T, 4>(a, stream);
-    if (chunks <= 8) return launch_item_dE<T, 8>(a, stream);
-    if (chunks <= 16) return launch_item_dE<T, 16>(a, stream);
-    if (chunks <= 32) return launch_item_dE<T, 32>(a, stream);
-    return launch_item_dE<T, 64>(a, stream);
+    if (chunks <= 2) return launch_item_dE<T, P, 2>(a, stream);
+    if (chunks <= 4) return launch_item_dE<T, P, 4>(a, stream);
+    if (chunks <= 8) return launch_item_dE<T, P, 8>(a, stream);
+    if (chunks <= 16) return launch_item_dE<T, P, 16>(a, stream);
+    if (chunks <= 32) return launch_item_dE<T, P, 32>(a, stream);
+    return launch_item_dE<T, P, 64>(a, stream);
 }
 
 // One thread per four consecutive draws of a position.
@@ -697,22 +755,28 @@ hipError_t launch_pack_alias(const Sampler &smp, hipStream_t stream)
     return hipGetLastError();
 }
 
-int64_t invert_pair_budget(int64_t N, int64_t K)
+bool invert_narrow(int64_t N, int64_t V) { return N <= kNarrowPositions && invert_partitioned(V); }
+int64_t invert_pair_budget(int64_t N, int64_t K, int64_t V)
 {
-    const int64_t pairs = N * K, eighth = (pairs + 7) / 8;
-    return eighth > kMinPairBudget ? eighth : kMinPairBudget;
+    const int64_t least = kMinPairBudget * (invert_narrow(N, V) ? 2 : 1), eighth = (N * K + 7) / 8;
+    return eighth > least ? eighth : least;
 }
-int invert_slices(int64_t N, int64_t K)
+int invert_slices(int64_t N, int64_t K, int64_t V)
 {
-    const int64_t pairs = N * K, B = invert_pair_budget(N, K), room = B - B / 8;
+    const int64_t pairs = N * K, B = invert_pair_budget(N, K, V), room = B - B / 8;
     return pairs <= B ? 1 : (int)((pairs + room - 1) / room);
 }
-int64_t invert_index_pairs(int64_t N, int64_t K)   // entries of the arrays the index is filed into
+int64_t invert_index_pairs(int64_t N, int64_t K, int64_t V)   // entries of the arrays the index is filed into
 {
-    const int64_t pairs = N * K, B = invert_pair_budget(N, K);
+    const int64_t pairs = N * K, B = invert_pair_budget(N, K, V);
     return pairs < B ? pairs : B;
 }
-size_t invert_hot_capacity(int64_t N, int64_t K) { return (size_t)(2 * (invert_index_pairs(N, K) / kHotPairs) + 16); }
+// (with the narrow budget also where pairs are wide: a workspace made for many positions serves fewer)
+size_t invert_hot_capacity(int64_t N, int64_t K)
+{
+    const int64_t pairs = N * K, most = std::max(2 * kMinPairBudget, (pairs + 7) / 8);
+    return (size_t)(2 * (std::min(pairs, most) / kHotPairs) + 16);
+}
 size_t invert_scan_blocks(int64_t n) { return (size_t)((n + kScanChunk - 1) / kScanChunk); }
 int64_t invert_part_blocks(int64_t N, int64_t K)
 {
@@ -722,6 +786,67 @@ int64_t invert_part_blocks(int64_t N, int64_t K)
 int64_t invert_buckets(int64_t V) { return (V + (int64_t(1) << bucket_shift(V)) - 1) >> bucket_shift(V); }
 bool invert_partitioned(int64_t V) { return invert_buckets(V) <= kMaxBuckets; }
 int invert_plan_words() { return 3 * kMaxSlices + 8; }  // work-list counters, first and last bucket of every slice, one flag
+
+namespace {
+// Catalogues cut into buckets: count, scan, plan, then slice by slice file, sort and consume.
+template <typename P>
+hipError_t launch_sliced_dE(bool bf16, InvertArgs a, const TileArgs *scatter, hipStream_t stream)
+{
+    hipError_t e;
+    auto check = [&]() { return (e = hipGetLastError()) == hipSuccess; };
+    a.n_buckets = (int32_t)invert_buckets(a.V);
+    a.bucket_shift = bucket_shift(a.V);
+    a.n_part_blocks = invert_part_blocks(a.N, a.K);
+    a.n_chunks = (a.N * a.K + kChunkPairs - 1) / kChunkPairs;
+    if (a.smp.kind) a.n_chunks = (a.N * draw_groups(a.K) + kChunkPairs / 4 - 1) / (kChunkPairs / 4);
+    a.budget = invert_pair_budget(a.N, a.K, a.V);
+    a.n_slices = invert_slices(a.N, a.K, a.V);
+    if (a.n_slices > kMaxSlices) return hipErrorInvalidValue;  // cannot happen: at most 11 by construction
+    const int64_t n_hist = (int64_t)a.n_buckets * a.n_part_blocks;
+    a.part_total = a.part_hist + n_hist;  // one extra word: scanning n_hist + 1 entries leaves the grand total there
+    {
+        ProfScope prof(PROF_INDEX, stream);
+        hipLaunchKernelGGL(part_count_kernel, dim3((unsigned)a.n_part_blocks), dim3(kThreads), 0, stream, a);
+        if (!check()) return e;
+        if ((e = launch_scan(a.part_hist, n_hist + 1, a.block_sums, stream)) != hipSuccess) return e;
+        hipLaunchKernelGGL(plan_slices_kernel, dim3(1), dim3(kScanThreads), 0, stream, a);
+        if (!check()) return e;
+    }
+    for (int32_t j = 0; j < a.n_slices; ++j) {
+        if (j > 0 && a.smp.packed && (e = launch_pack_alias(a.smp, stream)) != hipSuccess) return e;  // it lies where the pairs are filed
+        a.slice = j;
+        a.hot_count = a.slice_hot + j;
+        {
+            ProfScope prof(PROF_INDEX, stream);
+            if (scatter && j == 0) {  // the correct items' rows ride at the head of the first filing launch
+                const int64_t sc_blocks = pos_scatter_blocks(scatter->N);
+                const dim3 grid((unsigned)(a.n_part_blocks + sc_blocks));
+                switch (scatter->d) {
+                case 64: hipLaunchKernelGGL((part_scatter_kernel<P, 64>), grid, dim3(kThreads), 0, stream, a, *scatter, sc_blocks); break;
+                case 128: hipLaunchKernelGGL((part_scatter_kernel<P, 128>), grid, dim3(kThreads), 0, stream, a, *scatter, sc_blocks); break;
+                case 256: hipLaunchKernelGGL((part_scatter_kernel<P, 256>), grid, dim3(kThreads), 0, stream, a, *scatter, sc_blocks); break;
+                default: return hipErrorInvalidValue;
+                }
+            } else {
+                hipLaunchKernelGGL((part_scatter_kernel<P, 0>), dim3((unsigned)a.n_part_blocks), dim3(kThreads), 0, stream, a, TileArgs{}, 0);
+            }
+            if (!check()) return e;
+            hipLaunchKernelGGL((bucket_sort_kernel<P>), dim3((unsigned)a.n_buckets), dim3(kScanThreads), 0, stream, a);
+            if (!check()) return e;
+        }
+        e = bf16 ? launch_item_dE_by_width<uint16_t, P>(a, stream) : launch_item_dE_by_width<float, P>(a, stream);
+        if (e != hipSuccess) return e;
+    }
+    if (a.n_slices > 1) {  // buckets too crowded for any slice, if there are any
+        ProfScope prof(PROF_ITEM_DE, stream);
+        a.smp.packed = nullptr;  // under the pairs of the last slice
+        if (bf16) hipLaunchKernelGGL(hot_bucket_kernel<uint16_t>, dim3((unsigned)a.n_part_blocks), dim3(kThreads), 0, stream, a);
+        else hipLaunchKernelGGL(hot_bucket_kernel<float>, dim3((unsigned)a.n_part_blocks), dim3(kThreads), 0, stream, a);
+        if (!check()) return e;
+    }
+    return hipSuccess;
+}
+}  // namespace
 
 hipError_t launch_inverted_dE(bool bf16, const InvertArgs &a_in, const TileArgs *scatter, hipStream_t stream)
 {
@@ -747,59 +872,9 @@ hipError_t launch_inverted_dE(bool bf16, const InvertArgs &a_in, const TileArgs 
             hipLaunchKernelGGL(fill_kernel, dim3(pair_blocks), dim3(kThreads), 0, stream, a);
             if (!check()) return e;
         }
-        return bf16 ? launch_item_dE_by_width<uint16_t>(a, stream) : launch_item_dE_by_width<float>(a, stream);
+        return bf16 ? launch_item_dE_by_width<uint16_t, WidePair>(a, stream) : launch_item_dE_by_width<float, WidePair>(a, stream);
     }
-    a.n_buckets = (int32_t)invert_buckets(a.V);
-    a.bucket_shift = bucket_shift(a.V);
-    a.n_part_blocks = invert_part_blocks(a.N, a.K);
-    a.n_chunks = (pairs + kChunkPairs - 1) / kChunkPairs;
-    if (a.smp.kind) a.n_chunks = (a.N * draw_groups(a.K) + kChunkPairs / 4 - 1) / (kChunkPairs / 4);
-    a.budget = invert_pair_budget(a.N, a.K);
-    a.n_slices = invert_slices(a.N, a.K);
-    if (a.n_slices > kMaxSlices) return hipErrorInvalidValue;  // cannot happen: at most 11 by construction
-    const int64_t n_hist = (int64_t)a.n_buckets * a.n_part_blocks;
-    a.part_total = a.part_hist + n_hist;  // one extra word: scanning n_hist + 1 entries leaves the grand total there
-    {
-        ProfScope prof(PROF_INDEX, stream);
-        hipLaunchKernelGGL(part_count_kernel, dim3((unsigned)a.n_part_blocks), dim3(kThreads), 0, stream, a);
-        if (!check()) return e;
-        if ((e = launch_scan(a.part_hist, n_hist + 1, a.block_sums, stream)) != hipSuccess) return e;
-        hipLaunchKernelGGL(plan_slices_kernel, dim3(1), dim3(kScanThreads), 0, stream, a);
-        if (!check()) return e;
-    }
-    for (int32_t j = 0; j < a.n_slices; ++j) {
-        if (j > 0 && a.smp.packed && (e = launch_pack_alias(a.smp, stream)) != hipSuccess) return e;  // it lies where the pairs are filed
-        a.slice = j;
-        a.hot_count = a.slice_hot + j;
-        {
-            ProfScope prof(PROF_INDEX, stream);
-            if (scatter && j == 0) {  // the correct items' rows ride at the head of the first filing launch
-                const int64_t sc_blocks = pos_scatter_blocks(scatter->N);
-                const dim3 grid((unsigned)(a.n_part_blocks + sc_blocks));
-                switch (scatter->d) {
-                case 64: hipLaunchKernelGGL(part_scatter_kernel<64>, grid, dim3(kThreads), 0, stream, a, *scatter, sc_blocks); break;
-                case 128: hipLaunchKernelGGL(part_scatter_kernel<128>, grid, dim3(kThreads), 0, stream, a, *scatter, sc_blocks); break;
-                case 256: hipLaunchKernelGGL(part_scatter_kernel<256>, grid, dim3(kThreads), 0, stream, a, *scatter, sc_blocks); break;
-                default: return hipErrorInvalidValue;
-                }
-            } else {
-                hipLaunchKernelGGL(part_scatter_kernel<0>, dim3((unsigned)a.n_part_blocks), dim3(kThreads), 0, stream, a, TileArgs{}, 0);
-            }
-            if (!check()) return e;
-            hipLaunchKernelGGL(bucket_sort_kernel, dim3((unsigned)a.n_buckets), dim3(kScanThreads), 0, stream, a);
-            if (!check()) return e;
-        }
-        e = bf16 ? launch_item_dE_by_width<uint16_t>(a, stream) : launch_item_dE_by_width<float>(a, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (a.n_slices > 1) {  // buckets too crowded for any slice, if there are any
-        ProfScope prof(PROF_ITEM_DE, stream);
-        a.smp.packed = nullptr;  // under the pairs of the last slice
-        if (bf16) hipLaunchKernelGGL(hot_bucket_kernel<uint16_t>, dim3((unsigned)a.n_part_blocks), dim3(kThreads), 0, stream, a);
-        else hipLaunchKernelGGL(hot_bucket_kernel<float>, dim3((unsigned)a.n_part_blocks), dim3(kThreads), 0, stream, a);
-        if (!check()) return e;
-    }
-    return hipSuccess;
+    return invert_narrow(a.N, a.V) ? launch_sliced_dE<NarrowPair>(bf16, a, scatter, stream) : launch_sliced_dE<WidePair>(bf16, a, scatter, stream);
 }
 
 }  // namespace cce

@@ -36,3 +36,19 @@ def test_one_item_that_collects_a_quarter_of_all_pairs():
     # to the usual figure, which loss, lse and dH show.
     errs = check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), 1e-3, row_tol=1e-3)
     assert max(errs[k] for k in ("loss", "lse", "dH")) <= 1e-5, errs
+
+
+@pytest.mark.parametrize("N,K,V,d,hot", [(65536, 65, 3000, 8, 0.0), (65537, 65, 3000, 8, 0.0), (65537, 65, 3000, 8, 0.15),
+                                         (16384, 640, 3000, 8, 0.0), (16384, 640, 3000, 8, 0.2)])
+def test_slices_of_narrow_and_wide_pairs(N, K, V, d, hot):
+    """Up to 65,536 positions a slice holds 2^23 pairs of half the width, above 2^22: one slice of 4.3 M pairs and two; 10.5 M narrow
+    pairs in two.  hot: a bucket beyond an eighth of the budget, which stays out of the index in either width."""
+    from hip_harness import run_hip
+
+    w = make_workload(f"pairs_{N}_{K}", N, 1, d, V, K, "bf16", NEG_PER_POSITION, 3, g_kind="random", e_sigma=0.05, tgt_dist="zipf")
+    if hot:
+        neg = w.neg.reshape(w.N, w.K)
+        neg[np.random.default_rng(2).random(neg.shape) < hot] = V - 3
+    # as above: 2e-5 for sums of thousands of pairs; the hot row is off by hot K sqrt(N) 2^-25 <= 5e-4 of its running sum
+    tol = 1e-3 if hot else 2e-5
+    check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), tol, row_tol=tol)
