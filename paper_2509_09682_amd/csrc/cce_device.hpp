@@ -68,38 +68,6 @@ __device__ __forceinline__ void load8(const uint16_t *p, float (&v)[8])
     v[4] = bf16_lo(r.z); v[5] = bf16_hi(r.z);
     v[6] = bf16_lo(r.w); v[7] = bf16_hi(r.w);
 }
-// A row chunk of 8 elements as it comes from memory; bf16 rows stay packed (4 registers) until they are used, so that
-// twice as many rows can be in flight per wavefront as with widened copies.
-template <typename T> struct RawChunk;
-template <> struct RawChunk<uint16_t> {
-    uint4 v;
-    static constexpr int kInFlight = 8;
-    __device__ __forceinline__ void load(const uint16_t *p) { v = *reinterpret_cast<const uint4 *>(p); }
-    __device__ __forceinline__ void clear() { v = make_uint4(0, 0, 0, 0); }
-    __device__ __forceinline__ void widen(float (&h)[8]) const
-    {
-        h[0] = bf16_lo(v.x); h[1] = bf16_hi(v.x);
-        h[2] = bf16_lo(v.y); h[3] = bf16_hi(v.y);
-        h[4] = bf16_lo(v.z); h[5] = bf16_hi(v.z);
-        h[6] = bf16_lo(v.w); h[7] = bf16_hi(v.w);
-    }
-};
-template <> struct RawChunk<float> {
-    float4 a, b;
-    static constexpr int kInFlight = 4;
-    __device__ __forceinline__ void load(const float *p)
-    {
-        a = reinterpret_cast<const float4 *>(p)[0];
-        b = reinterpret_cast<const float4 *>(p)[1];
-    }
-    __device__ __forceinline__ void clear() { a = b = make_float4(0.f, 0.f, 0.f, 0.f); }
-    __device__ __forceinline__ void widen(float (&h)[8]) const
-    {
-        h[0] = a.x; h[1] = a.y; h[2] = a.z; h[3] = a.w;
-        h[4] = b.x; h[5] = b.y; h[6] = b.z; h[7] = b.w;
-    }
-};
-
 // Streaming accesses (data used once): loads and stores marked non-temporal leave the L2 lines they touch first in
 // line for eviction, so that a small operand that IS reused (the hidden states in the item pass) stays resident.
 typedef float f32x4_nt __attribute__((ext_vector_type(4)));
@@ -117,20 +85,48 @@ __device__ __forceinline__ void stream_store(float4 *p, float4 v)
 }
 __device__ __forceinline__ int32_t stream_load(const int32_t *p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ uint16_t stream_load(const uint16_t *p) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ void stream_load8(const float *p, float (&v)[8])
-{
-    const float4 a = stream_load(reinterpret_cast<const float4 *>(p)), b = stream_load(reinterpret_cast<const float4 *>(p) + 1);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-}
-__device__ __forceinline__ void stream_load8(const uint16_t *p, float (&v)[8])
-{
-    const u32x4_nt r = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt *>(p));
-    v[0] = bf16_lo(r.x); v[1] = bf16_hi(r.x);
-    v[2] = bf16_lo(r.y); v[3] = bf16_hi(r.y);
-    v[4] = bf16_lo(r.z); v[5] = bf16_hi(r.z);
-    v[6] = bf16_lo(r.w); v[7] = bf16_hi(r.w);
-}
+
+// A row chunk of 8 elements as it comes from memory; bf16 rows stay packed (4 registers) until they are used, so that
+// twice as many rows can be in flight per wavefront as with widened copies.
+template <typename T> struct RawChunk;
+template <> struct RawChunk<uint16_t> {
+    uint4 v;
+    static constexpr int kInFlight = 8;
+    __device__ __forceinline__ void load(const uint16_t *p) { v = *reinterpret_cast<const uint4 *>(p); }
+    __device__ __forceinline__ void load_stream(const uint16_t *p)
+    {
+        const u32x4_nt r = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt *>(p));
+        v = make_uint4(r.x, r.y, r.z, r.w);
+    }
+    __device__ __forceinline__ void clear() { v = make_uint4(0, 0, 0, 0); }
+    __device__ __forceinline__ void widen(float (&h)[8]) const
+    {
+        h[0] = bf16_lo(v.x); h[1] = bf16_hi(v.x);
+        h[2] = bf16_lo(v.y); h[3] = bf16_hi(v.y);
+        h[4] = bf16_lo(v.z); h[5] = bf16_hi(v.z);
+        h[6] = bf16_lo(v.w); h[7] = bf16_hi(v.w);
+    }
+};
+template <> struct RawChunk<float> {
+    float4 a, b;
+    static constexpr int kInFlight = 4;
+    __device__ __forceinline__ void load(const float *p)
+    {
+        a = reinterpret_cast<const float4 *>(p)[0];
+        b = reinterpret_cast<const float4 *>(p)[1];
+    }
+    __device__ __forceinline__ void load_stream(const float *p)
+    {
+        a = stream_load(reinterpret_cast<const float4 *>(p));
+        b = stream_load(reinterpret_cast<const float4 *>(p) + 1);
+    }
+    __device__ __forceinline__ void clear() { a = b = make_float4(0.f, 0.f, 0.f, 0.f); }
+    __device__ __forceinline__ void widen(float (&h)[8]) const
+    {
+        h[0] = a.x; h[1] = a.y; h[2] = a.z; h[3] = a.w;
+        h[4] = b.x; h[5] = b.y; h[6] = b.z; h[7] = b.w;
+    }
+};
 
 __device__ __forceinline__ float load1(const float *p) { return *p; }
 __device__ __forceinline__ float load1(const uint16_t *p) { return __uint_as_float(static_cast<uint32_t>(*p) << 16); }

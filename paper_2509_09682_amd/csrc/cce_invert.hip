@@ -534,34 +534,82 @@ __global__ __launch_bounds__(kScanThreads) void bucket_sort_kernel(InvertArgs a)
     else few.file(hist, pairs);
 }
 
+// Rows of a table below 4 GiB by 32-bit offsets; a load beyond its end brings zeros.
+struct RowBuffer {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ RowBuffer(const void *base, uint32_t bytes)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00027000)) {}
+    __device__ __forceinline__ void load(uint32_t off, RawChunk<uint16_t> &to) const
+    {
+        const u32x4_nt v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
+        to.v = make_uint4(v.x, v.y, v.z, v.w);
+    }
+    __device__ __forceinline__ void load(uint32_t off, RawChunk<float> &to) const
+    {
+        const u32x4_nt v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
+        const u32x4_nt w = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 16, 0);
+        to.a = make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+        to.b = make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w));
+    }
+};
+
 // Walks the positions filed in pairs[r, r_end) for the item whose row e the lane group holds, four at a time:
 // recomputes each score against the hidden state (L2-resident), forms g exp(o - lse) and adds G h to acc.
-// Every lane of the wavefront calls it (the loop condition is a wavefront vote, the scalar products use shuffles).
+// The lanes of a group enter together; groups of a wavefront leave when their own segment ends.  What bounds the walk is a mix
+// of vector issue (60 %) and waiting for rows, so both were cut: past the end of a segment its last position is walked again with
+// weight 0 (nothing to clear, no lane masks), rows are addressed by 32-bit offsets where positions have 16 bits, and the next
+// four positions are on their way before the rows at hand are used.
+// 25,600 positions, K = 256, 1 M items: item pass 470 -> 460 us; drawn by popularity 568 -> 543, crowded items 93 -> 82.  Six
+// wavefronts a SIMD for five: 471 (the hidden states, 6.5 MB, share 4 MB of L2 with what is streamed).
 template <typename T, typename P, int LPR>
-__device__ __forceinline__ void walk_segment(const InvertArgs &a, const float (&e)[8], int32_t r, int32_t r_end, bool col_ok,
+__device__ __forceinline__ void walk_segment(const InvertArgs &a, const RawChunk<T> &e_raw, int32_t r, int32_t r_end, bool col_ok,
                                              int c, float (&acc)[8])
 {
     // Four rows in flight: segments are short (6.5 pairs on average on the per-position workload) and the lane groups of a
     // wavefront go in step, so that a batch of eight was half empty (item pass 480 -> 465 us).
     constexpr int U = 4;
-    const T *Hp = static_cast<const T *>(a.H);
-    while (__any(r < r_end)) {
-        int32_t pos[U];
-        RawChunk<T> raw[U];
+    constexpr bool kNarrow = sizeof(typename P::Pos) == 2;
+    const char *lse_base = reinterpret_cast<const char *>(a.lse_in), *g_base = a.g ? reinterpret_cast<const char *>(a.g) : lse_base;
+    const uint32_t row_bytes = (uint32_t)a.d * (uint32_t)sizeof(T), col_bytes = (uint32_t)c * 8u * (uint32_t)sizeof(T);
+    // narrow: 2^16 rows of at most 512 elements, 2^27 bytes; a lane beyond the row reads beyond the buffer, that is zeros
+    const RowBuffer rows(a.H, kNarrow ? (uint32_t)a.N * row_bytes : 0u);
+    const uint32_t col_off = col_ok ? col_bytes : 0x80000000u;
+    uint32_t pos[U];
+    RawChunk<T> raw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) raw[u].clear();
+    auto positions = [&](int32_t at) {  // at most 2^28 pairs a slice
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            pos[u] = (uint32_t)stream_load(reinterpret_cast<const typename P::Pos *>(
+                static_cast<const char *>(a.pairs) + (uint32_t)max(min(at + u, r_end - 1), 0) * (uint32_t)sizeof(typename P::Pos)));
+    };
+    // The fences keep the loads where they stand: the compiler moves the two calls into one at the head of the loop otherwise,
+    // where nothing runs ahead of the rows.
+    positions(r);
+    asm volatile("" ::: "memory");
+    float e[8];
+    e_raw.widen(e);
+    while (r < r_end) {
         float lse[U], g[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) pos[u] = (r + u < r_end) ? (int32_t)stream_load(static_cast<const typename P::Pos *>(a.pairs) + r + u) : -1;
-#pragma unroll
         for (int u = 0; u < U; ++u) {
-            raw[u].clear();
-            lse[u] = 0.f;
-            g[u] = 0.f;
-            if (pos[u] >= 0) {
-                if (col_ok) raw[u].load(Hp + pos[u] * (int64_t)a.d + c * 8);
-                lse[u] = a.lse_in[pos[u]];
-                g[u] = a.g ? a.g[pos[u]] : 1.f;
-            }
+            const size_t at = kNarrow ? (size_t)(pos[u] * 4u) : (size_t)pos[u] * 4;
+            lse[u] = *reinterpret_cast<const float *>(lse_base + at);
+            g[u] = *reinterpret_cast<const float *>(g_base + at);
         }
+        if (kNarrow) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) rows.load(__umul24(pos[u], row_bytes) + col_off, raw[u]);
+        } else if (col_ok) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                raw[u].load(reinterpret_cast<const T *>(static_cast<const char *>(a.H) + (uint64_t)pos[u] * row_bytes + col_bytes));
+        }
+        const int32_t left = r_end - r;
+        r += U;
+        positions(r);  // whatever is left: a load in a branch of its own would make the rows wait for it
+        asm volatile("" ::: "memory");
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             float h[8];
@@ -570,11 +618,10 @@ __device__ __forceinline__ void walk_segment(const InvertArgs &a, const float (&
 #pragma unroll
             for (int t = 0; t < 8; ++t) part = fmaf(h[t], e[t], part);
             part = group_sum<LPR>(part);  // the lanes of a group share the item
-            const float G = (pos[u] >= 0) ? g[u] * fast_exp(part - lse[u]) : 0.f;
+            const float G = (u < left ? (a.g ? g[u] : 1.f) : 0.f) * fast_exp(part - lse[u]);
 #pragma unroll
             for (int t = 0; t < 8; ++t) acc[t] = fmaf(G, h[t], acc[t]);
         }
-        r += U;
     }
 }
 
@@ -601,16 +648,28 @@ __global__ __launch_bounds__(kThreads) void item_dE_kernel(InvertArgs a)
         v_lo = (int64_t)a.slice_hot[kMaxSlices + a.slice] << a.bucket_shift;
         v_hi = min(a.V, ((int64_t)a.slice_hot[2 * kMaxSlices + a.slice] + 1) << a.bucket_shift);
     }
-    for (int64_t v0 = v_lo + (int64_t)blockIdx.x * IPB; v0 < v_hi; v0 += (int64_t)gridDim.x * IPB) {
-    const int64_t v = v0 + (threadIdx.x >> 6) * GPW + lane / LPR;
-    int32_t r = 0, r_end = 0;
-    if (v < v_hi && (a.slice_of == nullptr || a.slice_of[v >> a.bucket_shift] == a.slice)) {
-        // cursor[v] is the end of item v's segment; it starts where the one before it ends, the first item of a bucket
-        // where the bucket starts in the slice's arrays (without slices: one running array over all items)
-        if (a.slice_of) r = ((v & ((1 << a.bucket_shift) - 1)) == 0) ? a.bucket_start[v >> a.bucket_shift] : a.cursor[v - 1];
-        else r = (v == 0) ? 0 : a.cursor[v - 1];
-        r_end = a.cursor[v];
-    }
+    // cursor[v] is the end of item v's segment; it starts where the one before it ends, the first item of a bucket
+    // where the bucket starts in the slice's arrays (without slices: one running array over all items).  The segments of the next
+    // trip are looked up before the walk of this one; every load is issued whatever the others bring.
+    const int32_t *slice_of = a.slice_of ? a.slice_of : a.cursor, *start_of = a.slice_of ? a.bucket_start : a.cursor;
+    const int shift = a.slice_of ? a.bucket_shift : 0;
+    struct Segment {
+        int32_t slice, start, before, end;
+    };
+    auto look_up = [&](int64_t v) {
+        const int64_t w = v < v_hi ? v : v_hi - 1;  // (an empty slice has v_hi <= v_lo and takes no trip: any item)
+        const int64_t x = w > 0 ? w : 0;
+        return Segment{slice_of[x >> shift], start_of[x >> shift], a.cursor[x > 0 ? x - 1 : 0], a.cursor[x]};
+    };
+    const int64_t step = (int64_t)gridDim.x * IPB, own = (threadIdx.x >> 6) * GPW + lane / LPR;
+    Segment next = look_up(v_lo + (int64_t)blockIdx.x * IPB + own);
+    for (int64_t v0 = v_lo + (int64_t)blockIdx.x * IPB; v0 < v_hi; v0 += step) {
+    const int64_t v = v0 + own;
+    const Segment at = next;
+    next = look_up(v + step);
+    const bool first = a.slice_of ? (v & ((1 << a.bucket_shift) - 1)) == 0 : v == 0;
+    int32_t r = first ? (a.slice_of ? at.start : 0) : at.before, r_end = at.end;
+    if (v >= v_hi || (a.slice_of && at.slice != a.slice)) r = r_end = 0;
     if (!__any(r < r_end)) continue;
     if (r_end - r > kHotPairs) {  // hot item: file its chunks and leave it to hot_item_kernel
         const int32_t n_chunks = (r_end - r + kHotChunk - 1) / kHotChunk;
@@ -623,15 +682,17 @@ __global__ __launch_bounds__(kThreads) void item_dE_kernel(InvertArgs a)
         }
         r = r_end = 0;
     }
-    float e[8], acc[8];
+    RawChunk<T> e;
+    e.clear();
+    float acc[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) e[t] = acc[t] = 0.f;
+    for (int t = 0; t < 8; ++t) acc[t] = 0.f;
     // the item row and the dE row it will be added to are requested together, before the walk over the positions
     const bool mine = r < r_end && col_ok;
     float4 *row = reinterpret_cast<float4 *>(a.dE + (mine ? v : 0) * (int64_t)a.d + c * 8);
     float4 dx = make_float4(0.f, 0.f, 0.f, 0.f), dy = dx;
     if (mine) {  // used once each: they must not push the hidden states out of L2
-        stream_load8(static_cast<const T *>(a.E) + v * (int64_t)a.d + c * 8, e);
+        e.load_stream(static_cast<const T *>(a.E) + v * (int64_t)a.d + c * 8);
         dx = stream_load(row);
         dy = stream_load(row + 1);
     }
@@ -663,10 +724,12 @@ __global__ __launch_bounds__(kThreads) void hot_item_kernel(InvertArgs a)
     const int32_t n = min(*a.hot_count, a.hot_capacity);
     for (int32_t ent = (int32_t)blockIdx.x; ent < n; ent += (int32_t)gridDim.x) {  // uniform over the block
         const int4 h = a.hot_list[ent];
-        float e[8], acc[8];
+        RawChunk<T> e;
+        e.clear();
+        float acc[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) e[t] = acc[t] = 0.f;
-        if (col_ok) load8(static_cast<const T *>(a.E) + h.x * (int64_t)a.d + c * 8, e);
+        for (int t = 0; t < 8; ++t) acc[t] = 0.f;
+        if (col_ok) e.load(static_cast<const T *>(a.E) + h.x * (int64_t)a.d + c * 8);
         const int32_t share = (h.z - h.y + WAVES * GPW - 1) / (WAVES * GPW), r = h.y + (wave * GPW + grp) * share;
         walk_segment<T, P, LPR>(a, e, r, min(r + share, h.z), col_ok, c, acc);
 #pragma unroll
