@@ -147,6 +147,9 @@ int bucket_shift(int64_t V)
 }
 constexpr int kMaxBuckets = 2048;               // LDS histogram of level 1: 8 KiB
 constexpr int kChunkPairs = 8192;               // pairs per chunk in level 1; a block takes chunks blockIdx.x, + gridDim.x, ...
+// Chunks are smaller, 2048 pairs at least, where there would be fewer than 256 of them: the passes over few pairs wait for the chain
+// of a block's batches (60,000 pairs: counting 8.7 -> 4.5 us, filing 18 -> 11).
+constexpr int kMinChunkPairs = 2048, kFewChunks = 256;
 constexpr int kMaxPartBlocks = 4096;            // blocks of level 1: bounds the (bucket, block) histogram at 32 MiB
 // The index is built and used up in SLICES of the item-id range, so that its memory is bounded by a pair budget B instead
 // of growing with N * K: every slice is a run of consecutive buckets that holds at most B pairs, gets filed into the same
@@ -186,15 +189,15 @@ constexpr int kSliceHot = -1;                   // slice_of[] of a bucket that s
 // targets of the valid positions only (entries of padded positions are never read), so a thread waits for two round
 // trips per batch instead of three per pair.  Fewer than 2^31 pairs on this path: 32-bit pair arithmetic.
 constexpr int kPairBatch = 8;
-static_assert(kChunkPairs % (kThreads * kPairBatch) == 0, "whole batches per chunk");
+static_assert(kMinChunkPairs % (kThreads * kPairBatch) == 0, "whole batches per chunk");
 
 // SAMPLED is a compile-time choice: with the generator in the same loop, stored ids waited behind its branches
 // (part_count_kernel 26 -> 17 us, the filing passes 63 + 37 -> 61 + 30 us on the per-position workload).
 template <typename F>
 __device__ __forceinline__ void for_stored_pairs(const InvertArgs &a, int64_t chunk, F &&visit)
 {
-    const uint32_t p0 = (uint32_t)chunk * kChunkPairs, total = (uint32_t)(a.N * a.K), K = (uint32_t)a.K;
-    for (int u0 = threadIdx.x; u0 < kChunkPairs; u0 += kThreads * kPairBatch) {
+    const uint32_t p0 = (uint32_t)chunk * (uint32_t)a.chunk_pairs, total = (uint32_t)(a.N * a.K), K = (uint32_t)a.K;
+    for (int u0 = threadIdx.x; u0 < a.chunk_pairs; u0 += kThreads * kPairBatch) {
         uint32_t pos[kPairBatch];
         bool live[kPairBatch];
         int32_t id[kPairBatch], ti[kPairBatch];
@@ -223,14 +226,14 @@ __device__ __forceinline__ void for_stored_pairs(const InvertArgs &a, int64_t ch
 
 // Sampled negatives are drawn again instead of being read, in groups of four draws (a generator call yields two or four), two
 // groups per thread at a time (one draw a thread, eight at a time, each with a generator call of its own: the index of 2.4 M
-// uniform draws from 20,000 items 84 us, so 68).  Draw 0 of a position is its correct item: K / 4 + 1 groups a position, kChunkPairs / 4 to a chunk.
+// uniform draws from 20,000 items 84 us, so 68).  Draw 0 of a position is its correct item: K / 4 + 1 groups a position, chunk_pairs / 4 to a chunk.
 constexpr int kDrawGroups = 2;
 __host__ __device__ inline int64_t draw_groups(int64_t K) { return K / 4 + 1; }
 template <typename F>
 __device__ __forceinline__ void for_drawn_pairs(const InvertArgs &a, int64_t chunk, F &&visit)
 {
-    const uint32_t per = (uint32_t)draw_groups(a.K), total = (uint32_t)a.N * per, g0 = (uint32_t)chunk * (kChunkPairs / 4);
-    for (int u0 = threadIdx.x; u0 < kChunkPairs / 4; u0 += kThreads * kDrawGroups) {
+    const uint32_t per = (uint32_t)draw_groups(a.K), total = (uint32_t)a.N * per, g0 = (uint32_t)chunk * (uint32_t)(a.chunk_pairs / 4);
+    for (int u0 = threadIdx.x; u0 < a.chunk_pairs / 4; u0 += kThreads * kDrawGroups) {
         uint32_t pos[kDrawGroups], q[kDrawGroups];
         bool live[kDrawGroups];
         int32_t ti[kDrawGroups], id[kDrawGroups][4];
@@ -359,7 +362,13 @@ __global__ __launch_bounds__(kScanThreads) void plan_slices_kernel(InvertArgs a)
 template <typename P, int D_SC>
 __global__ __launch_bounds__(kThreads) void part_scatter_kernel(InvertArgs a, TileArgs sc, int64_t sc_blocks)
 {
-    __shared__ int32_t cur[kMaxBuckets];
+    // Narrow pairs of one chunk a block are put in order of their buckets in LDS first and leave as runs: written one by one, 64
+    // lines an instruction, the launch waited for its stores.  (Wide ones would take 64 KB of staging, two blocks a CU.)
+    // 6.5 M pairs in 489 buckets: 82 -> 53 us, drawn by popularity 141 -> 90.
+    constexpr bool kStaged = sizeof(typename P::Entry) == 4;
+    // 40 KB, four blocks a CU.
+    __shared__ __align__(16) int32_t cur[kMaxBuckets];
+    __shared__ typename P::Entry stage[kStaged ? kChunkPairs : 1];
     static_assert(kThreads == kPosChunk && kMaxBuckets * 4 >= kPosChunk * 8, "the scatter role sorts 256 keys in this array");
     if (D_SC != 0 && (int64_t)blockIdx.x < sc_blocks) {
         pos_scatter_block<(D_SC != 0 ? D_SC : 64)>(sc, (int64_t)blockIdx.x, reinterpret_cast<uint64_t *>(cur), pos_parts(sc.N));
@@ -369,6 +378,70 @@ __global__ __launch_bounds__(kThreads) void part_scatter_kernel(InvertArgs a, Ti
     // the bucket starts in the slice's arrays.  Buckets of other slices get a negative cursor and are skipped.
     const int64_t blk = (int64_t)blockIdx.x - (D_SC != 0 ? sc_blocks : 0);
     const int64_t nb = a.n_part_blocks;
+    if (kStaged && a.n_chunks <= nb) {
+        // where each bucket's run starts in the block's chunk: the block's scanned counts of one bucket and the next block's
+        // are apart by what this block brings
+        constexpr int PER = kMaxBuckets / kThreads;
+        const int per = (a.n_buckets + kThreads - 1) / kThreads;  // consecutive buckets a thread
+        int32_t n[PER], sl[PER], sum = 0;
+#pragma unroll
+        for (int t = 0; t < PER; ++t) {  // all loads before the first use
+            n[t] = 0;
+            sl[t] = -2;
+            if (t < per) {
+                const int b = min((int)threadIdx.x * per + t, a.n_buckets - 1);
+                const int32_t *h = a.part_hist + (int64_t)b * nb + blk;
+                n[t] = h[1] - h[0];
+                sl[t] = a.slice_of[b];
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < PER; ++t) {
+            if (t >= per || (int)threadIdx.x * per + t >= a.n_buckets || sl[t] != a.slice) n[t] = -1;
+            else sum += n[t];
+        }
+        int32_t incl = sum, *wave_sums = reinterpret_cast<int32_t *>(stage);
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t o = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        if (lane == 63) wave_sums[wave] = incl;
+        __syncthreads();
+        int32_t run = incl - sum;
+        for (int w = 0; w < wave; ++w) run += wave_sums[w];
+#pragma unroll
+        for (int t = 0; t < PER; ++t) {
+            const int b = threadIdx.x * per + t;
+            if (t < per && b < a.n_buckets) cur[b] = n[t] < 0 ? ~run : run;  // other slices' buckets: negative, skipped
+            if (n[t] > 0) run += n[t];
+        }
+        __syncthreads();
+        for_live_pairs(a, blk, [&](int32_t id, int32_t pos) {
+            int32_t *c = &cur[id >> a.bucket_shift];
+            if (*c >= 0) stage[atomicAdd(c, 1)] = P::make(id & ((1 << a.bucket_shift) - 1), pos);
+        });
+        __syncthreads();
+        // sixteen lanes a bucket, kRuns buckets at a time; a run starts where the one before it ended
+        constexpr int kRuns = 8, kStep = kThreads / 16;
+        typename P::Entry *out = static_cast<typename P::Entry *>(a.tmp);
+        for (int b0 = threadIdx.x / 16; b0 < a.n_buckets; b0 += kRuns * kStep) {
+            int32_t begin[kRuns], end[kRuns], to[kRuns];
+#pragma unroll
+            for (int t = 0; t < kRuns; ++t) {
+                const int b = min(b0 + t * kStep, a.n_buckets - 1);
+                const int32_t before = b ? cur[b - 1] : 0;
+                begin[t] = before < 0 ? ~before : before;
+                end[t] = b0 + t * kStep < a.n_buckets ? cur[b] : -1;
+                to[t] = a.part_hist[(int64_t)b * nb + blk] - a.part_hist[(int64_t)b * nb] + a.bucket_start[b];
+            }
+#pragma unroll
+            for (int t = 0; t < kRuns; ++t)
+                for (int32_t k = begin[t] + threadIdx.x % 16; k < end[t]; k += 16) out[to[t] + k - begin[t]] = stage[k];
+        }
+        return;
+    }
     for (int b = threadIdx.x; b < a.n_buckets; b += kThreads)
         cur[b] = (a.slice_of[b] == a.slice) ? a.part_hist[(int64_t)b * nb + blk] - a.part_hist[(int64_t)b * nb] + a.bucket_start[b] : -1;
     __syncthreads();
@@ -841,9 +914,19 @@ size_t invert_hot_capacity(int64_t N, int64_t K)
     return (size_t)(2 * (std::min(pairs, most) / kHotPairs) + 16);
 }
 size_t invert_scan_blocks(int64_t n) { return (size_t)((n + kScanChunk - 1) / kScanChunk); }
+// Chunks of level 1: pairs a chunk and how many, for `pairs` stored ids or draws (whose groups of four hold the correct item and
+// the rest of the last group as well).
+int32_t chunk_pairs_of(int64_t pairs)
+{
+    int32_t c = kChunkPairs;
+    while (c > kMinChunkPairs && pairs < (int64_t)c * kFewChunks) c /= 2;
+    return c;
+}
+// Blocks of level 1 at most, stored or drawn; does not fall as N grows.
 int64_t invert_part_blocks(int64_t N, int64_t K)
 {
-    const int64_t chunks = (N * K + kChunkPairs - 1) / kChunkPairs;
+    const int64_t pairs = N * draw_groups(K) * 4, few = (pairs + kMinChunkPairs - 1) / kMinChunkPairs;
+    const int64_t chunks = std::max(std::min<int64_t>(few, 2 * kFewChunks), (pairs + kChunkPairs - 1) / kChunkPairs);
     return chunks < kMaxPartBlocks ? chunks : kMaxPartBlocks;
 }
 int64_t invert_buckets(int64_t V) { return (V + (int64_t(1) << bucket_shift(V)) - 1) >> bucket_shift(V); }
@@ -859,9 +942,10 @@ hipError_t launch_sliced_dE(bool bf16, InvertArgs a, const TileArgs *scatter, hi
     auto check = [&]() { return (e = hipGetLastError()) == hipSuccess; };
     a.n_buckets = (int32_t)invert_buckets(a.V);
     a.bucket_shift = bucket_shift(a.V);
-    a.n_part_blocks = invert_part_blocks(a.N, a.K);
-    a.n_chunks = (a.N * a.K + kChunkPairs - 1) / kChunkPairs;
-    if (a.smp.kind) a.n_chunks = (a.N * draw_groups(a.K) + kChunkPairs / 4 - 1) / (kChunkPairs / 4);
+    const int64_t level1 = a.smp.kind ? a.N * draw_groups(a.K) * 4 : a.N * a.K;
+    a.chunk_pairs = chunk_pairs_of(level1);
+    a.n_chunks = (level1 + a.chunk_pairs - 1) / a.chunk_pairs;
+    a.n_part_blocks = std::min<int64_t>(a.n_chunks, kMaxPartBlocks);  // a chunk each: 13 blocks of 800 with two held up the rest
     a.budget = invert_pair_budget(a.N, a.K, a.V);
     a.n_slices = invert_slices(a.N, a.K, a.V);
     if (a.n_slices > kMaxSlices) return hipErrorInvalidValue;  // cannot happen: at most 11 by construction

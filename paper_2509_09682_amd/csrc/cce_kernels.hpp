@@ -138,7 +138,8 @@ struct InvertArgs {
     int32_t *bucket_start;   // [n_buckets] workspace: where a bucket starts in the arrays of its slice (nullptr: unsliced)
     int32_t *slice_of;       // [n_buckets] workspace: slice of every bucket, -1 = out of the index (nullptr: unsliced)
     int32_t *slice_hot;      // [invert_plan_words] workspace: per slice the work-list counter, first and last bucket; a flag
-    int64_t budget, n_chunks;  // pairs per slice at most; chunks of 8192 pairs in all
+    int64_t budget, n_chunks;  // pairs per slice at most; chunks of chunk_pairs pairs in all
+    int32_t chunk_pairs;
     int32_t n_slices, slice;   // slices of this call; the one this launch works on
     int32_t *part_hist;      // [n_buckets * n_part_blocks + 1] workspace: (bucket, block) counts -> offsets
     int32_t *part_total;     // = part_hist + n_buckets * n_part_blocks (set by the launcher)

@@ -52,3 +52,26 @@ def test_slices_of_narrow_and_wide_pairs(N, K, V, d, hot):
     # as above: 2e-5 for sums of thousands of pairs; the hot row is off by hot K sqrt(N) 2^-25 <= 5e-4 of its running sum
     tol = 1e-3 if hot else 2e-5
     check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), tol, row_tol=tol)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("N,K,V,d", [(1, 1, 5, 24), (64, 32, 600, 264), (683, 3, 2000, 24), (8192, 64, 900, 8), (4095, 128, 70_000, 40),
+                                     (8191, 256, 70_000, 16), (8192, 257, 1_100_000, 8)])
+def test_chunks_of_the_index(N, K, V, d, dtype):
+    """A chunk of the index is 2048 pairs and doubles up to 8192 with 256 chunks of it: a pair, 2048 and one more, each side of
+    2^19 and 2^21 pairs; one to 538 buckets, rows that leave lanes of their group idle; masks that leave a block nothing to file."""
+    from hip_harness import run_hip
+
+    w = make_workload(f"chunks_{N}_{K}_{dtype}", N, 1, d, V, K, dtype, NEG_PER_POSITION, 11, g_kind="random", e_sigma=0.05, tgt_dist="zipf",
+                      pad="bernoulli" if N > 1 else "none", pad_p=0.4)
+    if N > 4000:
+        w.mask[100:3000] = 0
+    check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), 2e-5)
+
+
+def test_more_chunks_than_blocks():
+    """33.6 M pairs: a block takes several chunks and files its pairs one by one."""
+    from hip_harness import run_hip
+
+    w = make_workload("chunks_many", 65536, 1, 8, 30_000, 513, "bf16", NEG_PER_POSITION, 12, g_kind="random", e_sigma=0.05)
+    check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), 2e-5)
