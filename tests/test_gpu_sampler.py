@@ -146,3 +146,17 @@ def test_alias_draws_around_their_groups_windows_and_slices(N, K, V, d):
     w_ref = dataclasses.replace(w, neg=_reference_ids(w, S.ALIAS, 31, 2, table))
     _check(w_ref, run_hip_sampled(w, smp), 2e-5)
     _check(w_ref, run_hip_sampled(w, smp, fuse_dH=True), 2e-5)
+
+
+@pytest.mark.parametrize("kind", [S.UNIFORM, S.ALIAS])
+def test_draws_from_more_items_than_the_buckets_of_the_index_cover(kind):
+    """Beyond 2^22 items the index is counted and filed pair by pair, a draw at a time."""
+    from hip_harness import device_sampler, run_hip_sampled
+
+    w = _shape(150, 33, (1 << 22) + 5, NEG_PER_POSITION, d=8, pad="bernoulli", pad_p=0.2, tgt_dist="zipf")
+    rng = np.random.default_rng(4)
+    table = (rng.integers(0, 1 << 32, w.V, dtype=np.uint32), rng.integers(0, w.V, w.V, dtype=np.int32)) if kind == S.ALIAS else None
+    smp, keep = device_sampler(kind, 5, 6, *(table or ()))
+    w_ref = dataclasses.replace(w, neg=_reference_ids(w, kind, 5, 6, table))
+    for fuse in (False, True):
+        _check(w_ref, run_hip_sampled(w, smp, fuse_dH=fuse), TOL_F32)
