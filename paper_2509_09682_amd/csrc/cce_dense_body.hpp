@@ -635,9 +635,10 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
         }
     }
     // The stationary rows are waited for here: a load that may be in flight at the head of the loop would have the compiler
-    // wait for all loads at its first use in every turn.
-#pragma unroll
-    for (int k = 0; k < G::NX; ++k) asm volatile("" : "+v"(xr[k].x), "+v"(xr[k].y), "+v"(xr[k].z), "+v"(xr[k].w));
+    // wait for all loads at its first use in every turn (51,200 positions, K = 1024, d = 320, bf16: candidate side 191 us, so
+    // 183).  By a wait that the compiler counts in: an empty asm block that takes them tied their registers as well (52 lists of
+    // 3171 candidates for 24 positions each, d = 256: candidate side 175 us, so 161).  Rows staged in registers need no such wait.
+    if (G::DIRECT) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 #pragma unroll
     for (int q = 0; q < G::PF; ++q) issue(q, q);
 
