@@ -591,8 +591,8 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
             if (AT_ONCE < MOST) __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // Waits until at most the youngest PF - 1 load groups are in flight.  A group is requested at every tile, beyond the last
-    // one of zeros, so that the counts are the same on every path.
+    // DIRECT: waits until at most the youngest PF - 1 load groups are in flight.  A group is requested at every tile, beyond the
+    // last one of zeros, so that the counts are the same on every path.
     auto landed = [&](int buffer) {
         if constexpr (!G::DIRECT) {
             uint4 *const buf = lds + buffer * G::BUF;
@@ -609,21 +609,20 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
         }
     };
     Raw raw{0u, 0u, 0u};  // number of row ye of the tile after those at hand
-    if (swave == 0 && ny > 0) {
-        if constexpr (DE) {
+    if (swave == 0 && ny > 0) {  // numbers of the first tiles in one round trip, their constants in another
+        Raw first[G::PF + 1];
+        int32_t id[G::PF + 1];
+        Cst c[G::PF + 1];
 #pragma unroll
-            for (int q = 0; q < G::PF + 1; ++q) {
-                const int32_t id = id_of(t0 + q, fetch_id(t0 + q));
-                file(q, id, fetch_cst(t0 + q, id));
-            }
-            raw = fetch_id(t0 + G::PF + 1);
-        } else {  // one round trip for all of them (scoring 1302 positions, 300 candidates, d = 48, bf16: 11.5 us, so 11.4)
-            Raw first[G::PF + 1];
+        for (int q = 0; q < G::PF + 1; ++q) first[q] = fetch_id(t0 + q);
+        if (DE) raw = fetch_id(t0 + G::PF + 1);
 #pragma unroll
-            for (int q = 0; q < G::PF + 1; ++q) first[q] = fetch_id(t0 + q);
-#pragma unroll
-            for (int q = 0; q < G::PF + 1; ++q) file(q, id_of(t0 + q, first[q]), Cst{0u, 0u, 0u, 0u});
+        for (int q = 0; q < G::PF + 1; ++q) {
+            id[q] = id_of(t0 + q, first[q]);
+            c[q] = fetch_cst(t0 + q, id[q]);
         }
+#pragma unroll
+        for (int q = 0; q < G::PF + 1; ++q) file(q, id[q], c[q]);
     }
     __syncthreads();
     if constexpr (EX && !DE) {
@@ -653,22 +652,29 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
     // fp32 weights of one score block (4 AQ values a lane: streamed rows row_of(i)), then the second product
     constexpr int SUB = BY / XR;  // score blocks per tile
     int slot = 0, at = 0;  // of tile t: entry of ids and cst, buffer
+    // Rows staged in registers are asked for before the numbers of a later tile, and not beyond the last one: the next tile waits
+    // for them.  Numbers first / rows first, us: steps of 108 positions, K = 182, d = 192, bf16 33.0 / 32.2, d = 128, fp32
+    // 26.8 / 25.9; scoring 1302 positions, 299 candidates, d = 48, bf16 11.7 / 11.2; 5000 positions, K = 1024, d = 128, fp32
+    // 89.8 / 91.6.  Short fp32 rows keep the numbers first on the candidate side (12,800 positions, K = 1024, d = 64: 89.5 / 91.0).
+    constexpr bool kRowsFirst = !G::DIRECT && (!DE || B16 || KD >= 4);
     landed(0);
     for (int64_t t = t0; t < t1; ++t) {
         const uint4 *buf = lds + at * G::BUF;
         lds_barrier();
         // rows of tile t + PF, into the buffer that tile t - 1 has left; position side: numbers of tile t + PF + 1; candidate side:
         // constants of that tile and numbers of the next
+        const bool more = t + 1 < t1;
         int32_t id2 = -1;
         Cst c2{0u, 0u, 0u, 0u};
-        if (swave == 0) {
+        if (kRowsFirst && more) issue(at == 0 ? G::PF : at - 1, (slot + G::PF) % G::IDS);
+        if (swave == 0 && (MODE != DM_FWD || more)) {
             if (DE) {
                 id2 = id_of(t + G::PF + 1, raw);
                 c2 = fetch_cst(t + G::PF + 1, id2);
             }
             raw = fetch_id(t + G::PF + (DE ? 2 : 1));
         }
-        issue(at == 0 ? G::PF : at - 1, (slot + G::PF) % G::IDS);
+        if (!kRowsFirst) issue(at == 0 ? G::PF : at - 1, (slot + G::PF) % G::IDS);
 #pragma unroll
         for (int sb = 0; sb < SUB; ++sb) {
             uint4 *const xq = xch + xg * (3 * 4 * 32);
@@ -676,16 +682,19 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
             // operands of the second product for half c of the streamed rows, one per block of output columns: rows hi 4 + j / 4
             // and 8 below (j: lane of sixteen; EX, odd hi: the other way round), columns of this lane's half of a block of 32
             uint4 ya[EX ? 2 : 1][OB];
-            auto read_half = [&](int c, uint4 (&y)[OB]) {
+            auto read_operand = [&](int c, int b) {
                 const uint16_t *tb = reinterpret_cast<const uint16_t *>(buf) + (c * 16 + hi * 4 + (l16 >> 2)) * (G::PITCH * 8) +
                                      sl * OB * 32 + (h16 & 1) * 16 + (l16 & 3) * 4;
                 const int turn = EX ? hi * 8 * (G::PITCH * 8) : 0;
+                const ds16x4 r0 = read_tr((dlds_v4)(tb + b * 32 + turn)), r1 = read_tr((dlds_v4)(tb + b * 32 + 8 * (G::PITCH * 8) - turn));
+                uint4 y;
+                __builtin_memcpy(&y.x, &r0, 8);
+                __builtin_memcpy(&y.z, &r1, 8);
+                return y;
+            };
+            auto read_half = [&](int c, uint4 (&y)[OB]) {
 #pragma unroll
-                for (int b = 0; b < OB; ++b) {
-                    const ds16x4 r0 = read_tr((dlds_v4)(tb + b * 32 + turn)), r1 = read_tr((dlds_v4)(tb + b * 32 + 8 * (G::PITCH * 8) - turn));
-                    __builtin_memcpy(&y[b].x, &r0, 8);
-                    __builtin_memcpy(&y[b].z, &r1, 8);
-                }
+                for (int b = 0; b < OB; ++b) y[b] = read_operand(c, b);
             };
             if constexpr (EX) {
                 // quads of the score block: streamed rows 16 xhalf + 4 h16 + r, stationary rows xcol + 16 g
@@ -911,13 +920,15 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
                     for (int c = 0; c < 2; ++c) {
                         uint4 pl[3];
                         split3(v + 8 * c, pl);
-                        uint4 y[OB];
-                        read_half(c, y);
+                        // an operand at a time: all of them at once take 24 registers at d = 192 (12,800 positions, K = 1024:
+                        // candidate side 86 us, so 82)
 #pragma unroll
-                        for (int b = 0; b < OB; ++b)
+                        for (int b = 0; b < OB; ++b) {
+                            const uint4 y = read_operand(c, b);
 #pragma unroll
                             for (int p = 2; p >= 0; --p)
-                                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(y[b]), as_b8(pl[p]), acc[b], 0, 0, 0);
+                                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_b8(y), as_b8(pl[p]), acc[b], 0, 0, 0);
+                        }
                     }
                 }
             } else {
@@ -930,10 +941,11 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
                 }
             }
         }
-        if (swave == 0) file((slot + G::PF + 1) % G::IDS, DE ? id2 : id_of(t + G::PF + 1, raw), c2);
+        if (kRowsFirst && more) landed(at == G::PF ? 0 : at + 1);
+        if (swave == 0 && (!kRowsFirst || more)) file((slot + G::PF + 1) % G::IDS, DE ? id2 : id_of(t + G::PF + 1, raw), c2);
         slot = slot == G::IDS - 1 ? 0 : slot + 1;
         at = at == G::PF ? 0 : at + 1;
-        landed(at);
+        if (!kRowsFirst) landed(at);
     }
     if (G::DIRECT) dwait_vm<0>();  // the groups beyond the last tile, before their buffers are used again or given back
 
