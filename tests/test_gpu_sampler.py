@@ -134,11 +134,14 @@ def test_sampled_calls_edge_cases():
 
 
 @pytest.mark.parametrize("N,K,V,d", [(40, 512, 5120, 40), (40, 511, 5121, 40), (61, 255, 700, 64), (33, 256, 900, 128), (90, 3, 60, 16),
-                                     (16500, 256, 30_000, 8)])
+                                     (16500, 256, 30_000, 8), (16500, 520, 30_000, 8), (65600, 66, 30_000, 8)])
 def test_alias_draws_around_their_groups_windows_and_slices(N, K, V, d):
     """The last group of four draws and the last window of a list, the fewest draws for which the table is copied (4 V) and one
-    less, and more pairs than a slice of the index holds, where it is copied again for the second slice."""
+    less, and more pairs than a slice of the index holds (the last two), where it is copied again for the second slice."""
     from hip_harness import device_sampler, run_hip_sampled
+    from test_gpu_parity import pair_budget
+
+    assert (N * K > pair_budget(N, K)) == (K in (520, 66))
 
     w = _shape(N, K, V, NEG_PER_POSITION, d=d, pad="bernoulli", pad_p=0.2, tgt_dist="zipf")
     table = _table(V)
@@ -146,6 +149,26 @@ def test_alias_draws_around_their_groups_windows_and_slices(N, K, V, d):
     w_ref = dataclasses.replace(w, neg=_reference_ids(w, S.ALIAS, 31, 2, table))
     _check(w_ref, run_hip_sampled(w, smp), 2e-5)
     _check(w_ref, run_hip_sampled(w, smp, fuse_dH=True), 2e-5)
+
+
+@pytest.mark.parametrize("N,K,dtype", [(16500, 520, "f32"), (65600, 66, "bf16")])
+def test_alias_law_whose_crowded_bucket_stays_out_of_the_index(N, K, dtype):
+    """An item of 15 % of the draws: the pairs of its bucket are added one by one, drawn from the caller's table, because those of
+    the last slice lie where its copy was."""
+    from hip_harness import device_sampler, run_hip_sampled
+    from test_gpu_parity import check_against_oracle, pair_budget
+
+    w = _shape(N, K, 30_000, NEG_PER_POSITION, d=64, dtype=dtype, tgt_dist="zipf", e_sigma=0.05)
+    weights = np.ones(w.V)
+    weights[777] = 0.15 / 0.85 * (w.V - 1)
+    table = alias_table(weights)
+    smp, keep = device_sampler(S.ALIAS, 8, 1, *table)
+    w_ref = dataclasses.replace(w, neg=_reference_ids(w, S.ALIAS, 8, 1, table))
+    assert N * K > pair_budget(N, K) and (w_ref.neg == 777).sum() > pair_budget(N, K) // 8
+    for fuse in (False, True):
+        # the hot row: a position adds its term 0.15 K times in a row to one fp32 sum, 78 sqrt(16500) 2^-25 = 3e-4 of the running sum
+        errs = check_against_oracle(w_ref, run_hip_sampled(w, smp, fuse_dH=fuse), 1e-3, row_tol=1e-3)
+        assert max(errs[k] for k in ("loss", "lse", "dH")) <= 1e-5, errs
 
 
 @pytest.mark.parametrize("kind", [S.UNIFORM, S.ALIAS])
