@@ -54,7 +54,11 @@ def test_workspace_bytes_rejects_bad_descriptors(binding):
     def pp(N, V, K, d=128):
         return B.cce_neg_workspace_bytes(B.make_desc(N, V, d, K, B.CCE_BF16, B.CCE_NEG_PER_POSITION))
     c3 = pp(25600, 1_000_000, 256)
-    assert c3 <= 12.2 * (1 << 22) + 4 * 1_000_000 + 4 * 25600 + (4 << 20)       # one slice of 2^22 pairs, not 12 N K = 79 MB
+    assert c3 <= 6.125 * 25600 * 256 + 4 * 1_000_000 + 4 * 25600 + (2 << 20)    # one slice of narrow pairs, not 12 N K = 79 MB
+    for V in (40, 3000, 1_000_000, 1 << 22):
+        for K in (1, 16, 63, 64, 65, 127, 128, 129, 256, 1024, 4096):
+            need = [pp(N, V, K) for N in (65_535, 65_536, 65_537, 65_600)]
+            assert need[0] > 256 and need == sorted(need), (V, K)               # does not fall where pairs get wide
     assert pp(25600, 1_000_000, 2560) <= 2.1 * c3
     big = pp(204800, 1_000_000, 2560)                                           # 524 M pairs
     assert big <= 0.375 * 4 * 204800 * 2560 * 1.05 + 4 * 1_000_000 + 4 * 204800 + (34 << 20)
