@@ -857,8 +857,9 @@ hipError_t launch_item_dE_by_width(const InvertArgs &a, hipStream_t stream)
     return launch_item_dE<T, P, 64>(a, stream);
 }
 
-// One thread per four consecutive draws of a position.
-__global__ __launch_bounds__(kThreads) void sample_kernel(Sampler smp, int64_t n_pos, int32_t K, int32_t *out)
+// One thread per four consecutive draws of a position.  (Arguments in this order: what it reads of them is 64 bytes; the
+// output behind the sampler lay beyond: 2.20 us, so 2.07.)
+__global__ __launch_bounds__(kThreads) void sample_kernel(int32_t *out, int64_t n_pos, int32_t K, Sampler smp)
 {
     const int64_t quads = ((int64_t)K + 4) / 4;  // draws 0..K cover K/4 + 1 groups of four
     const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -880,7 +881,7 @@ hipError_t launch_sample(const Sampler &smp, int64_t n_pos, int32_t K, int32_t *
 {
     const int64_t threads = n_pos * (((int64_t)K + 4) / 4);
     if (n_pos <= 0 || K <= 0) return hipSuccess;
-    hipLaunchKernelGGL(sample_kernel, dim3((unsigned)((threads + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, smp, n_pos, K, out);
+    hipLaunchKernelGGL(sample_kernel, dim3((unsigned)((threads + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, out, n_pos, K, smp);
     return hipGetLastError();
 }
 

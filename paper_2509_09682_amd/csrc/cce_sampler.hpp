@@ -103,14 +103,27 @@ __device__ __forceinline__ void resolve4(const Sampler &s, const Draws (&d)[G], 
             for (int t = 0; t < 4; ++t) id[g][t] = (d[g].keep[t] < s.thresh[d[g].col[t]]) ? (int32_t)d[g].col[t] : s.alias[d[g].col[t]];
     }
 }
+// The same ids from the caller's table alone, half a group at a time: what a launch that only draws takes (through the two steps
+// above its code is longer: at most 1025 threads, either law, 2.27 us, so 2.20).
 __device__ __forceinline__ void sample4(const Sampler &s, uint64_t pos, uint32_t q4, int32_t (&id)[4])
 {
-    Draws d[1];
-    int32_t ids[1][4];
-    draw4(s, pos, q4, d[0]);
-    resolve4(s, d, ids);
+    const uint32_t p_lo = (uint32_t)pos, p_hi = (uint32_t)(pos >> 32);
+    uint32_t w[4];
+    if (s.kind == kSamplerUniform) {
+        philox4x32_10(q4, p_lo, p_hi, s.stream, s.k0, s.k1, w);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) id[t] = ids[0][t];
+        for (int t = 0; t < 4; ++t) id[t] = (int32_t)__umulhi(w[t], s.V);
+    } else {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            philox4x32_10(2 * q4 + half, p_lo, p_hi, s.stream, s.k0, s.k1, w);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const uint32_t col = __umulhi(w[2 * t], s.V);
+                id[2 * half + t] = (w[2 * t + 1] < s.thresh[col]) ? (int32_t)col : s.alias[col];
+            }
+        }
+    }
 }
 
 // Id of a single draw: one generator call and one column, whatever the law.  (A group of four for one of its draws takes two calls

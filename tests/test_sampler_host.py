@@ -33,10 +33,13 @@ extern "C" long draw_one_by_one(int kind, uint64_t seed, uint32_t stream, uint32
     const long cost = products;
     for (int i = 0; i < N; ++i)
         for (int q = 0; q <= K / 4; ++q) {
-            int32_t id[4];
+            cce::Draws d[1];
+            int32_t id[4], looked_up[1][4];
             cce::sample4(s, (uint64_t)i, (uint32_t)q, id);
+            cce::draw4(s, (uint64_t)i, (uint32_t)q, d[0]);
+            cce::resolve4(s, d, looked_up);
             for (int t = 0; t < 4; ++t)
-                if (4 * q + t >= 1 && 4 * q + t <= K) four[(long)i * K + 4 * q + t - 1] = id[t];
+                if (4 * q + t >= 1 && 4 * q + t <= K) four[(long)i * K + 4 * q + t - 1] = id[t] == looked_up[0][t] ? id[t] : -1;
         }
     return cost;
 }
