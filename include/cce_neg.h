@@ -117,7 +117,7 @@ typedef struct {
  *                              one of 40,960 (ask for every size and take the largest);
  *   per-position mode:         the inverted index that turns the dE scatter into a gather (pairs sorted by item) is
  *                              built and used up in slices of the item-id range: 6 1/8 bytes per pair of ONE slice up to
- *                              2^16 positions (12 1/4 above, and beyond 2^22 items), a slice holding at most
+ *                              2^16 positions (12 1/4 above; 4 1/8 beyond 2^22 items), a slice holding at most
  *                              B = max(2^23, N K / 8) pairs (2^22 for 2^23; so at most 52 MB up to N K = 2^25 pairs,
  *                              and 3/8 of the bytes of the [N,K] id matrix itself beyond), plus
  *                              4 bytes per table row, 4 per position and at most 32 MiB of bucket counts.  Catalogues

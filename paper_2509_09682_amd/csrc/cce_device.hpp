@@ -135,10 +135,10 @@ __device__ __forceinline__ float load1(const uint16_t *p) { return __uint_as_flo
 __device__ __forceinline__ float fast_exp(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
 __device__ __forceinline__ float fast_log(float x) { return __builtin_amdgcn_logf(x) * kLn2; }
 
-// Sum over groups of LPR consecutive lanes, in every lane of the group; all lanes of the wavefront take part.  Within
-// sixteen lanes the partners come through the data-parallel primitives of the add itself: neighbour, neighbour pair,
-// mirror of eight, mirror of sixteen.  (As LDS permutes, four a score, they were a third of what the row-gather passes
-// wait for.)
+// Sum over groups of LPR consecutive lanes, in every lane of the group.  The lanes of a group call it together, all
+// partners being of the group; other groups of the wavefront may be elsewhere.  Within sixteen lanes the partners come
+// through the data-parallel primitives of the add itself: neighbour, neighbour pair, mirror of eight, mirror of sixteen.
+// (As LDS permutes, four a score, they were a third of what the row-gather passes wait for.)
 template <int CTRL>
 __device__ __forceinline__ float add_dpp(float v)
 {

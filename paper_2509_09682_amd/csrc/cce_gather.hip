@@ -29,13 +29,13 @@ constexpr int kWindow = 512;
 
 // Where the ids of the negatives come from.
 enum { IDS_DIRECT = 0,   // shared list (or none): read where needed, every wavefront reads the same cached words
-       IDS_STORED = 1,   // per-position list in memory: staged a window at a time with four coalesced loads
+       IDS_STORED = 1,   // per-position list in memory: staged a window at a time with kWindow / 64 coalesced loads
        IDS_SAMPLED = 2 };  // per-position draws of the counter-based sampler: generated a window at a time
 
 // Per-position negatives: the wavefront fills its LDS window with the ids of candidates [j0, j0 + kWindow) of its
 // position (candidate j >= 1 is slot j - 1 of the list, draw j of the sampler); candidate() reads them from there,
-// so the row gathers never wait for a scattered 4-byte load first.  Sampled: four consecutive draws per lane from one
-// or two generator calls.  LDS operations of one wavefront complete in order, so the reads that follow see the writes.
+// so the row gathers never wait for a scattered 4-byte load first.  Sampled: kWindow / 256 groups of four
+// consecutive draws per lane, one or two generator calls a group.  LDS operations of one wavefront complete in order, so the reads that follow see the writes.
 template <int IDS>
 __device__ __forceinline__ void refill_window(const Params &p, int64_t i, int64_t j0, int32_t *win)
 {

@@ -156,10 +156,11 @@ constexpr int kMaxPartBlocks = 4096;            // blocks of level 1: bounds the
 // B-entry arrays, and is consumed by the item pass before the next one is filed.  Every table row is still read and
 // written once; a further slice costs one more reading of the ids (4 bytes per pair) and four launches.
 //   B = max(2^22, N K / 8) pairs, 2^23 for 2^22 where pairs are narrow (below);  slices = 1 if N K <= B, else
-//   ceil(N K / (7/8 B)): the pairs of the ordinary buckets are cut at the quantiles j / slices of their running count, so a slice holds at most N K / slices + (one bucket)
-//   <= 7/8 B + 1/8 B pairs, PROVIDED no bucket holds more than B / 8 pairs.  Buckets beyond that (consecutive ids
-//   drawing more than half a million pairs, an eighth of everything: a popularity law far more skewed than any workload
-//   here) stay out of the index: their pairs are added to dE one by one with atomics (hot_bucket_kernel).
+//   ceil(N K / (7/8 B)): the pairs of the ordinary buckets are cut at the quantiles j / slices of their running count, so a
+//   slice holds at most N K / slices + (one bucket) <= 7/8 B + 1/8 B pairs, PROVIDED no bucket holds more than B / 8 pairs.
+//   Buckets beyond that (consecutive ids drawing more than half a million pairs, a million narrow ones, an eighth of everything:
+//   a popularity law far more skewed than any workload here) stay out of the index: their pairs are added to dE one by one with
+//   atomics (hot_bucket_kernel).
 constexpr int64_t kMinPairBudget = int64_t(1) << 22;
 // A pair on its way to its item: the id and the position, 8 bytes, and the position alone once it is filed, 4.  Up to 2^16
 // positions both fit half of that, because the bucket is known where an entry is read: the id's offset in it (kMaxBucketShift
@@ -191,8 +192,9 @@ constexpr int kSliceHot = -1;                   // slice_of[] of a bucket that s
 constexpr int kPairBatch = 8;
 static_assert(kMinChunkPairs % (kThreads * kPairBatch) == 0, "whole batches per chunk");
 
-// SAMPLED is a compile-time choice: with the generator in the same loop, stored ids waited behind its branches
-// (part_count_kernel 26 -> 17 us, the filing passes 63 + 37 -> 61 + 30 us on the per-position workload).
+// Stored and drawn ids have loops of their own, chosen once per launch (for_live_pairs): with the generator in the same loop,
+// stored ids waited behind its branches (part_count_kernel 26 -> 17 us, the filing passes 63 + 37 -> 61 + 30 us on the
+// per-position workload).
 template <typename F>
 __device__ __forceinline__ void for_stored_pairs(const InvertArgs &a, int64_t chunk, F &&visit)
 {

@@ -1670,10 +1670,6 @@ inline int pick_splits(int64_t xblocks, int max_splits, int slots, bool cheap_me
     return best;
 }
 
-// Split factor and leading blocks of one pass; returns the number of blocks of its grid (0: nothing to do).
-// fine: the pass shares its launch with another role that fills most block slots; if it splits at all, it splits as
-// finely as allowed, so that its blocks fill the gaps (c4: the fused backward launch 704 -> 671 us with 16 instead of 10).
-// as_given: a.splits is the caller's choice.
 // Ways to split the position range of a dE pass at most.
 inline int de_split_cap(const TileArgs &a)
 {
@@ -1690,6 +1686,10 @@ inline int de_split_cap(const TileArgs &a)
     return cap;
 }
 
+// Split factor and leading blocks of one pass; returns the number of blocks of its grid (0: nothing to do).
+// fine: the pass shares its launch with another role that fills most block slots; if it splits at all, it splits as
+// finely as allowed, so that its blocks fill the gaps (c4: the fused backward launch 704 -> 671 us with 16 instead of 10).
+// as_given: a.splits is the caller's choice.
 template <int MODE>
 int64_t plan_tile_grid(TileArgs &a, int64_t n_x, int xpb, int threads, int slots, bool fine = false, bool as_given = false)
 {
