@@ -27,20 +27,36 @@ PEAK_HBM_GBS = 8000.0            # MI355X HBM3E peak
 PEAK_F32_VALU_TFLOPS = 157.3
 
 
-def algorithmic_work(w):
+def index_pair_bytes(w):
+    """Bytes of a pair of the inverted index on its way to its item; half of them once it is filed."""
+    return 4 if w.N <= 1 << 16 and w.V <= 1 << 22 else 8
+
+
+def touched_rows(w):
+    """Expected number of distinct ids among the negatives of all valid positions (uniform draws)."""
+    return w.V * (1.0 - math.exp(-float(w.n_valid) * w.K / w.V))
+
+
+def algorithmic_work(w, fused=False):
     """Algorithmic flops and minimum HBM bytes of one forward+backward, counted on valid positions only.
 
     flops: four GEMM-equivalents (scores forward, scores recomputed, dH, dE), 2 flop per multiply-add:
            8 * n_cand * d per valid position, n_cand = K+1 (or V for the full catalogue).
     bytes: every operand the method must move once: H read in both passes, the gathered candidate rows in both passes,
-           dH written, dE rows written once (write-once accounting), ids, per-position vectors.
+           dH written, dE rows written once (write-once accounting), ids, per-position vectors.  Per-position negatives with
+           fuse_dH gather the candidate rows once; each touched table row is then read once more, its dE row read and written
+           once, the ids read by the two index passes as well, and the pairs of the index written and read per sort level.
     """
     nv = w.n_valid
     esz = 4 if w.in_dtype == "f32" else 2
     n_cand = w.V if w.neg_mode == 2 else w.K + 1
     flops = 8.0 * n_cand * w.d * nv
     row = w.d * esz
-    if w.neg_mode == 1:      # per-position: every candidate row is fetched per position, twice; dE rows written once each
+    if w.neg_mode == 1 and fused:
+        gathered = float(nv) * n_cand * row
+        dE_bytes = touched_rows(w) * (row + 2 * w.d * 4)
+        ids = float(nv) * w.K * (3 * 4 + 3 * index_pair_bytes(w))
+    elif w.neg_mode == 1:    # per-position: every candidate row is fetched per position, twice; dE rows written once each
         gathered = 2.0 * nv * n_cand * row
         dE_bytes = float(nv) * n_cand * w.d * 4
         ids = 2.0 * nv * w.K * 4
@@ -94,14 +110,13 @@ def kernel_work(w, family, fused=False):
         return "hbm", rows + ids + nv * w.d * esz + float(nv) * n_cand * w.d * 4 + nv * w.d * 4 + w.N * 13
     pairs = float(nv) * w.K
     if family == "item_de":
-        # per (position, negative) pair: the position's H row and the pair's id; per touched table row: E read once,
-        # dE read and written once.  Touched rows: expected number of distinct ids among nv*K uniform draws.
-        touched = w.V * (1.0 - math.exp(-pairs / w.V))
-        return "hbm", pairs * (w.d * esz + 4) + touched * (w.d * esz + 2 * w.d * 4)
+        # per (position, negative) pair: the position's H row (half of them come from L2) and its number; per touched table
+        # row: E read once, dE read and written once
+        return "hbm", pairs * (w.d * esz + index_pair_bytes(w) // 2) + touched_rows(w) * (w.d * esz + 2 * w.d * 4)
     if family == "index":
-        # inverted index: ids read by the counting and by the filing pass, (id, position) pairs written and read once
-        # by each of the two sort levels, positions filed under their item
-        return "hbm", pairs * (2 * 4 + 2 * 8 + 2 * 8 + 4)
+        # inverted index: ids read by the counting and by the filing pass, (id, position) pairs written by the first sort
+        # level and read twice by the second, positions filed under their item
+        return "hbm", pairs * (2 * 4 + 3 * index_pair_bytes(w) + index_pair_bytes(w) // 2)
     if family == "pos_scatter":
         return "hbm", float(nv) * (w.d * esz + 2 * w.d * 4 + 8)
     return "hbm", 0.0
@@ -242,7 +257,7 @@ def measure(w, args, *, headline: bool) -> dict:
     dominant = max(fam, key=lambda k: fam[k][0])
     dom_ms = fam[dominant][0] / steps
 
-    flops, bytes_min = algorithmic_work(w)
+    flops, bytes_min = algorithmic_work(w, fused=bool(fuse))
     bound, work = kernel_work(w, dominant, fused=bool(fuse))
     if bound == "mfma":
         peak = PEAK_MFMA_BF16_TFLOPS if w.in_dtype == "bf16" else PEAK_F32_VALU_TFLOPS
