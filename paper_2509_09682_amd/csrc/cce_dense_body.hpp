@@ -656,7 +656,10 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
     // for them.  Numbers first / rows first, us: steps of 108 positions, K = 182, d = 192, bf16 33.0 / 32.2, d = 128, fp32
     // 26.8 / 25.9; scoring 1302 positions, 299 candidates, d = 48, bf16 11.7 / 11.2; 5000 positions, K = 1024, d = 128, fp32
     // 89.8 / 91.6.  Short fp32 rows keep the numbers first on the candidate side (12,800 positions, K = 1024, d = 64: 89.5 / 91.0).
-    constexpr bool kRowsFirst = !G::DIRECT && (!DE || B16 || KD >= 4);
+    // So do rows of 65 to 96 columns on either side, us: step of 657 positions, 25,508 items, d = 96, bf16 113.6 / 118.6; 588
+    // positions, 70,369 items, fp32 525 / 535; 2560 positions, K = 2000, bf16 50.9 / 52.9; scoring 8000 positions, 17,000 items
+    // 63.1 / 64.9 bf16, 282.0 / 285.6 fp32; 1302 positions, 299 candidates 12.44 / 12.51.
+    constexpr bool kRowsFirst = !G::DIRECT && KD != 3 && (!DE || B16 || KD >= 4);
     landed(0);
     for (int64_t t = t0; t < t1; ++t) {
         const uint4 *buf = lds + at * G::BUF;
@@ -667,7 +670,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs a)
         int32_t id2 = -1;
         Cst c2{0u, 0u, 0u, 0u};
         if (kRowsFirst && more) issue(at == 0 ? G::PF : at - 1, (slot + G::PF) % G::IDS);
-        if (swave == 0 && (MODE != DM_FWD || more)) {
+        if (swave == 0 && (MODE != DM_FWD || more || KD == 3)) {
             if (DE) {
                 id2 = id_of(t + G::PF + 1, raw);
                 c2 = fetch_cst(t + G::PF + 1, id2);
