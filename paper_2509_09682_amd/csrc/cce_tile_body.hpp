@@ -26,6 +26,7 @@
 #pragma once
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "cce_device.hpp"
 #include "cce_kernels.hpp"
@@ -217,8 +218,14 @@ __device__ __forceinline__ void dh_scale_chunk(const TileArgs &a, int64_t chunk)
 // DS: wavefronts that share a group of stationary rows in the backward passes; each of them forms the full score tile
 // and keeps 1/DS of the output columns, which divides the accumulator registers by DS at the price of DS score products.
 // LDS needs of one tile-kernel configuration (the kernel wrappers declare the arrays, the body gets pointers).
-template <int D, int MODE, int BY, int NW, int XG, int NBUF, int DS>
+// STREAM: the unbroken pipeline of the passes with a second product (run_stream in tile_body), whose ring is one array.
+constexpr bool streams(int d, int mode, int by, int nbuf, int ds, bool filter)
+{
+    return d <= 128 && by % 64 == 0 && mode != MODE_FWD && nbuf == 4 && ds == 1 && !filter;
+}
+template <int D, int MODE, int BY, int NW, int XG, int NBUF, int DS, bool FILTER>
 struct TileGeom {
+    static constexpr bool STREAM = streams(D, MODE, BY, NBUF, DS, FILTER);
     static constexpr int TILE = BY * D;
     static constexpr int IDS = (BY < 64) ? 64 : BY;
     static constexpr int CONSTS = (MODE == MODE_DE) ? 2 * BY : 0;
@@ -226,11 +233,14 @@ struct TileGeom {
     static constexpr int XPB = (NW / DS) * XG * 32;
     static constexpr int EPI_BYTES = NW * 32 * 33 * 4 + XPB * 8;
     static constexpr bool EPI_IN_TILES = (MODE == MODE_DE) && (NW == 4) && (TILE * 2 >= 2 * 32 * 33 * 4 + XPB * 8);
-    static constexpr int BUF0 = (NBUF == 0) ? 2 * BUF : BUF;
-    static constexpr int BUF1 = (NBUF >= 2) ? BUF : 8;
-    static constexpr int BUF2 = (NBUF >= 3) ? BUF : 8;
-    static constexpr int BUF3 = (NBUF >= 4) ? BUF : 8;
-    static constexpr int EPI_OWN = (MODE == MODE_DE && !EPI_IN_TILES) ? EPI_BYTES / 4 : 4;  // floats
+    static constexpr int BUF0 = (NBUF == 0) ? 2 * BUF : (STREAM ? 4 * BUF : BUF);
+    static constexpr int BUF1 = (NBUF >= 2 && !STREAM) ? BUF : 8;
+    static constexpr int BUF2 = (NBUF >= 3 && !STREAM) ? BUF : 8;
+    static constexpr int BUF3 = (NBUF >= 4 && !STREAM) ? BUF : 8;
+    static constexpr bool FOLD = STREAM && MODE == MODE_DE && XG == 2;  // per wavefront: offsets of a tile, sign words of two
+    static_assert(!FOLD || BY == 128, "a lane folds two rows of a tile");
+    static constexpr int FOLD_FLOATS = FOLD ? 2 * BY : 0;
+    static constexpr int EPI_OWN = (MODE == MODE_DE && !EPI_IN_TILES) ? EPI_BYTES / 4 : (FOLD ? NW * FOLD_FLOATS : 4);  // floats
 };
 
 // ---------------------------------------------------------------------------------------------------------------------
@@ -270,6 +280,8 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     // The pipelined sub-tile loop alternates between two register sets; above d = 128 only the forward pass with one
     // group of stationary rows has the registers for it (the operands of a whole sub-tile are d/4 registers).
     constexpr bool SWP = (BY % 64 == 0) && (D <= 128 || (MODE == MODE_FWD && XG == 1));
+    typedef TileGeom<D, MODE, BY, NW, XG, NBUF, DS, FILTER> G;
+    constexpr bool STREAM = G::STREAM;
     constexpr int KK = D / 16;             // k-steps of the score product
     constexpr int MB = D / 32;             // 32-row output blocks of the second product
     constexpr int CPR = D / 8;             // 16-byte chunks per row
@@ -306,6 +318,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     // (NBUF = 0) keeps one copy of the loop body where registers are short.
     auto buf_at = [&](int i) -> uint16_t * {
         if (NBUF == 0) return buf0 + (i & 1) * BUF;
+        if (STREAM) return buf0 + (i & 3) * BUF;
         return i == 0 ? buf0 : (i == 1 ? buf1 : (i == 2 ? buf2 : buf3));
     };
 
@@ -497,7 +510,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     // was then exposed in full.  That a tile has landed before it is read is the business of wait_for_next() and the
     // barrier behind it, for every buffer alike.
     auto issue_group = [&](int64_t t, const int32_t (&rows)[NR], uint16_t *dst_generic) {
-        uint32_t dst_lds = (uint32_t)(uintptr_t)(lds_ptr)dst_generic;
+        uint32_t dst_lds = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uintptr_t)(lds_ptr)dst_generic);
         asm volatile("" : "+s"(dst_lds));
         uint16_t __attribute__((address_space(3))) *dst = (uint16_t __attribute__((address_space(3))) *)(uintptr_t)dst_lds;
         if (small_table) {
@@ -1109,7 +1122,13 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
 #pragma unroll
             for (int g = 0; g < XG; ++g) run_m[g] = tmax[g];
         }
-        if (NBUF == 4) {
+        if constexpr (STREAM) {  // the exact form, off the common path
+#pragma unroll 1
+            for (int64_t t = t_begin; t < t_stop && !overflow; ++t) {
+                const int s = (int)((t - t_begin) & 3);
+                step(t, buf_at(s), buf_at(s + 3));
+            }
+        } else if (NBUF == 4) {
             for (int64_t t = t_begin; t < t_stop; t += 4) {
                 step(t, buf0, buf3);
                 if (t + 1 >= t_stop || overflow) break;
@@ -1159,7 +1178,266 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         }
         return overflow != 0;
     };
-    if (run_attempt(FastTag{})) {
+    // ---- STREAM: the tiles of the range as one unbroken sequence of sub-tiles (hidden sizes up to 128, passes with a second
+    // product).  A phase is one sub-tile: its softmax arithmetic runs between the matrix instructions of the second product of
+    // the sub-tile before it and, behind those, of the score product of the one after it, across tile borders.  LDS operands
+    // are asked for half a phase ahead of their use.  Every matrix instruction and the vector instructions behind it are fenced
+    // off as a slice: the scheduler, given the same work as a group pattern, put the operand reads directly ahead of their
+    // use, so that every phase began with the LDS latency and the latency of the score product in full.
+    auto run_stream = [&]() -> bool {
+        constexpr int NS = NM_P + NM_S;         // slices of a phase, one matrix instruction each
+        constexpr int NPAIR = 8 * XG;           // pairs of scores of a lane
+        constexpr int FIRST = (XG == 1) ? 1 : 0;  // one row group: the scores come off the matrix pipe as the phase begins
+        constexpr bool WATCH = (MODE == MODE_FDH);
+        f32x16 sv[2][XG];
+        gp_t gp[2];
+        s16x8 tr[2][MBH];
+        float4 cy[4], gy[4];   // DE: exponent offsets and upstream gradients of the streamed rows
+        float part[XG][4];     // FDH: running sums
+        // FOLD (dE with two row groups, where the registers of the gradients are short and their products an eighth of the
+        // vector instructions): g 2^x = +-2^(x + log2 |g|).  A wavefront folds the gradients of a tile into the offsets once,
+        // in LDS of its own.  From the first tile with a negative gradient on, signs are put on the packed coefficients, two at a time.
+        constexpr bool FOLD = G::FOLD;
+        bool negative = false;  // wave-uniform, and the same in every wavefront of the block
+        float *const folded = epi_own + wave * G::FOLD_FLOATS;
+        auto fold_tile = [&](const uint16_t *tile, int parity) {  // the signs of two tiles: those of one are read while the next one is folded
+            const float2 c = reinterpret_cast<const float2 *>(tile + OFF_C)[lane];  // rows 2 lane, 2 lane + 1
+            const float2 g = reinterpret_cast<const float2 *>(tile + OFF_C)[BY / 2 + lane];
+            reinterpret_cast<float2 *>(folded)[lane] = make_float2(c.x + __builtin_amdgcn_logf(fabsf(g.x)), c.y + __builtin_amdgcn_logf(fabsf(g.y)));
+            // in the order a lane of the streaming loop wants them: sub-tile, half, eight words
+            const int at = (lane >> 4) * 16 + ((lane >> 1) & 1) * 8 + ((lane >> 2) & 3) * 2 + (lane & 1);
+            const uint32_t signs = (__float_as_uint(g.x) >> 31 << 15) | (__float_as_uint(g.y) & 0x80000000u);
+            reinterpret_cast<uint32_t *>(folded + BY)[parity * (BY / 2) + at] = signs;
+            negative |= __any(signs != 0u);
+        };
+        auto load_consts = [&](const uint16_t *tile, int sb, int qq) {
+            if constexpr (FOLD) {
+                cy[qq] = *reinterpret_cast<const float4 *>(&folded[sb * 32 + qq * 8 + hi * 4]);
+                return;
+            }
+            const float *yc = reinterpret_cast<const float *>(tile + OFF_C);
+            cy[qq] = *reinterpret_cast<const float4 *>(&yc[sb * 32 + qq * 8 + hi * 4]);
+            gy[qq] = *reinterpret_cast<const float4 *>(&yc[BY + sb * 32 + qq * 8 + hi * 4]);
+        };
+        auto load_op = [&](const uint16_t *tile, int sb, int kk) -> uint4 {
+            return *reinterpret_cast<const uint4 *>(lds_at(tile + sb * 32 * D, a_base, ((kk * 2) & SM) * 8, (kk / NA) * (NA * 16)));
+        };
+        auto load_tr1 = [&](const uint16_t *tile, int sb, int j) {  // j: k2 * MBH + mb
+            const int k2 = j / MBH, mb = j % MBH;
+            const uint16_t *tbase = tile + (sb * 32 + k2 * 16) * D;
+            const int col = (mb / NT) * (NT * 32);
+            const s16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(lds_at(tbase, t_base0, ((mb * 4) & SM) * 8, col)));
+            const s16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(lds_at(tbase, t_base1, ((mb * 4) & SM) * 8, col)));
+            tr[k2][mb] = __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+        auto mfma_second = [&](int i, const gp_t &p) {  // piece by piece of the transposed operand, the row groups inside
+            const int g = i % XG, k2 = i / XG / MBH, mb = (i / XG) % MBH;
+            bf16x8 av;
+            __builtin_memcpy(&av, &tr[k2][mb], 16);
+            const uint4 bv = make_uint4(p[g][k2 * 4 + 0], p[g][k2 * 4 + 1], p[g][k2 * 4 + 2], p[g][k2 * 4 + 3]);
+            acc[g][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, as_bf16x8(bv), acc[g][mb], 0, 0, 0);
+        };
+        constexpr int TR_AHEAD = 4;  // slices from the read of a transposed piece to its use
+        auto zero = [&](f32x16 &v) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = 0.f;
+        };
+        auto phase = [&](const uint16_t *ptile, int pk, const uint16_t *tile, int k, const uint16_t *ntile, int nk, auto parity, auto with_signs, int tile_parity) {
+            constexpr int c = decltype(parity)::value ? 1 : 0, n = c ^ 1;
+            constexpr bool SIGNS = decltype(with_signs)::value;
+            uint4 op[KK], sy[2];
+            if (SIGNS) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) sy[h] = *reinterpret_cast<const uint4 *>(&folded[BY + tile_parity * (BY / 2) + k * 16 + hi * 8 + h * 4]);
+            }
+            float w[2 * NPAIR];
+            auto begin_pair = [&](int p) {
+                const int g = p / 8, q = 2 * (p % 8);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float ofs;
+                    if (MODE == MODE_FDH) ofs = -run_m[g];
+                    else if (MODE == MODE_DH) ofs = cx[g];
+                    else ofs = (q % 4 == 0) ? (h ? cy[q / 4].y : cy[q / 4].x) : (h ? cy[q / 4].w : cy[q / 4].z);
+                    w[2 * p + h] = __builtin_amdgcn_exp2f(fmaf(sv[c][g][q + h], kLog2e, ofs));
+                }
+            };
+            auto end_pair = [&](int p) {
+                const int g = p / 8, q = 2 * (p % 8);
+                float v0 = w[2 * p], v1 = w[2 * p + 1];
+                if (MODE == MODE_FDH) {
+                    part[g][q % 4] += v0;
+                    part[g][q % 4 + 1] += v1;
+                }
+                if (MODE == MODE_DE && !FOLD) {
+                    v0 *= (q % 4 == 0) ? gy[q / 4].x : gy[q / 4].z;
+                    v1 *= (q % 4 == 0) ? gy[q / 4].y : gy[q / 4].w;
+                }
+                gp[c][g][q / 2] = pack2(v0, v1);
+                if (SIGNS) {
+                    const uint4 sg = sy[q / 8];
+                    gp[c][g][q / 2] ^= (q % 8 == 0) ? sg.x : (q % 8 == 2) ? sg.y : (q % 8 == 4) ? sg.z : sg.w;
+                }
+                if (MODE == MODE_DE && g == XG - 1 && q % 4 == 2) load_consts(ntile, nk, q / 4);  // of the next sub-tile
+            };
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (i < NM_P) {
+                    mfma_second(i, gp[n]);
+                } else {
+                    const int g = (i - NM_P) / KK, kk = (i - NM_P) % KK;
+                    if (kk == 0) zero(sv[n][g]);
+                    sv[n][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(op[kk]), as_bf16x8(xr[g][kk]), sv[n][g], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (i < KK) op[i] = load_op(ntile, nk, i);
+#pragma unroll
+                for (int j = 0; j < 2 * MBH; ++j) {  // pieces late in the list are read at the head of the phase that uses them
+                    if (j * XG < TR_AHEAD && i == NS + j * XG - TR_AHEAD) load_tr1(tile, k, j);
+                    if (j * XG >= TR_AHEAD && i == j * XG - TR_AHEAD) load_tr1(ptile, pk, j);
+                }
+#pragma unroll
+                for (int p = 0; p < NPAIR; ++p)
+                    if (FIRST + p * (NS - FIRST) / NPAIR == i) begin_pair(p);
+#pragma unroll
+                for (int p = 0; p < NPAIR; ++p)
+                    if (FIRST + p * (NS - FIRST) / NPAIR + 1 == i) end_pair(p);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int p = 0; p < NPAIR; ++p)
+                if (FIRST + p * (NS - FIRST) / NPAIR + 1 >= NS) end_pair(p);
+        };
+        int overflow = 0;
+        auto note_parts = [&](int parity) {
+            bool over = false;
+#pragma unroll
+            for (int g = 0; g < XG; ++g) over |= !((part[g][0] + part[g][1]) + (part[g][2] + part[g][3]) < 1.0e30f);  // or NaN
+            if (__any(over)) {
+                if (lane == 0) over_flag[parity] = 1;
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the barrier below does not wait for it
+            }
+        };
+        // Tile t.  Ahead of its last phase, which reads the first operands of tile t + 1: wait for that tile, and start the loads
+        // of tile t + 3 into the buffer of tile t - 1, whose last operands every wavefront has used in the first phase of t.
+        auto step = [&](int64_t t, int at, auto signs) {
+            // the first tile's predecessor has coefficients of zero: any finite rows do
+            const uint16_t *const cur = buf_at(at), *const prev = t == t_begin ? cur : buf_at((at + 3) % 4), *const next = buf_at((at + 1) % 4);
+            const int tile_parity = at & 1;
+            int seen = 0;
+#pragma unroll
+            for (int k = 0; k + 1 < NSB; ++k) {
+                if (k == 0) phase(prev, NSB - 1, cur, 0, cur, 1, std::false_type{}, signs, tile_parity);
+                else if (k % 2 == 0) phase(cur, k - 1, cur, k, cur, k + 1, std::false_type{}, signs, tile_parity);
+                else phase(cur, k - 1, cur, k, cur, k + 1, std::true_type{}, signs, tile_parity);
+            }
+            if (t + 1 < t_end) {
+                wait_all_but<LPW>(t + 2 < t_end ? 1 : 0, group_extras);
+                if (WATCH) note_parts((int)((t - t_begin) & 1));
+                asm volatile("s_barrier" ::: "memory");
+                if (t + PF < t_end) {
+                    int32_t rows[NR];
+                    rows_from_lds(t + PF, cur, rows);
+                    issue_group(t + PF, rows, buf_at((at + 3) % 4));
+                }
+                if (WATCH) seen = over_flag[(int)((t - t_begin) & 1)];
+            }
+            if constexpr (FOLD) fold_tile(next, tile_parity ^ 1);  // the offsets of tile t are in registers to the last one
+            phase(cur, NSB - 2, cur, NSB - 1, next, 0, std::true_type{}, signs, tile_parity);
+            if (WATCH) overflow |= __builtin_amdgcn_readfirstlane(seen);
+        };
+        if (WATCH && tid < 2) over_flag[tid] = 0;  // visible behind the barrier that follows the first loads
+        if (t_begin < t_end) {
+            int32_t rows[PF][NR];
+#pragma unroll
+            for (int j = 0; j < PF; ++j)
+                if (t_begin + j < t_end) rows_from_global(t_begin + j, rows[j]);
+#pragma unroll
+            for (int j = 0; j < PF; ++j)
+                if (t_begin + j < t_end) issue_group(t_begin + j, rows[j], buf_at(j));
+        }
+        wait_for_next(t_begin - 1);
+        barrier_keep_loads();
+        if (WATCH && t_begin < t_end) {  // reference: the largest score among the first 32 candidates
+            const int64_t left = n_y - t_begin * BY;
+            float tmax[XG];
+            tile_max(buf0, 1, left < BY ? (int)left : BY, tmax);
+#pragma unroll
+            for (int g = 0; g < XG; ++g) run_m[g] = tmax[g];
+        }
+        if (t_begin < t_stop) {
+            // first scores; the sub-tile before the first one has coefficients of zero
+#pragma unroll
+            for (int g = 0; g < XG; ++g) {
+                zero(sv[0][g]);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) gp[1][g][q] = 0u;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) part[g][q] = 0.f;
+            }
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                const uint4 o = load_op(buf0, 0, kk);
+#pragma unroll
+                for (int g = 0; g < XG; ++g)
+                    sv[0][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(o), as_bf16x8(xr[g][kk]), sv[0][g], 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 2 * MBH; ++j)
+                if (j * XG < TR_AHEAD) load_tr1(buf0, 0, j);
+            if (MODE == MODE_DE) {
+                if constexpr (FOLD) fold_tile(buf0, 0);
+#pragma unroll
+                for (int qq = 0; qq < 4; ++qq) load_consts(buf0, 0, qq);
+            }
+            int at = 0;
+            int64_t t = t_begin;
+            // one copy of the tile and one way out: the state carried round is most of the register file
+            if (!negative) {
+#pragma unroll 1
+                do {
+                    step(t, __builtin_amdgcn_readfirstlane(at), std::false_type{});
+                    at = (at + 1) % 4;
+                    ++t;
+                } while (t < t_stop && !overflow && !negative);
+            }
+            if constexpr (FOLD) {
+#pragma unroll 1
+                for (; t < t_stop; ++t) {
+                    step(t, __builtin_amdgcn_readfirstlane(at), std::true_type{});
+                    at = (at + 1) % 4;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 2 * MBH; ++j)
+                if (j * XG >= TR_AHEAD) load_tr1(buf_at(at + 3), NSB - 1, j);
+#pragma unroll
+            for (int i = 0; i < NM_P; ++i) mfma_second(i, gp[1]);
+            if (WATCH) {
+#pragma unroll
+                for (int g = 0; g < XG; ++g) run_s[g] = (part[g][0] + part[g][1]) + (part[g][2] + part[g][3]);
+                note_overflow(0);
+            }
+        }
+        if (tail_ragged && !overflow) {
+            process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{}, Exact{});
+            if (WATCH) note_overflow(1);
+        }
+        __syncthreads();  // the tile buffers are free, the flags in place
+        if (WATCH) {
+            if (!overflow) overflow = __builtin_amdgcn_readfirstlane(over_flag[0] | over_flag[1]);
+            if (overflow) {  // loads of later tiles may still be in flight into the ring: let them land
+                wait_vm<0>();
+                __syncthreads();
+            }
+        }
+        return overflow != 0;
+    };
+    bool again;
+    if constexpr (STREAM) again = run_stream();
+    else again = run_attempt(FastTag{});
+    if (again) {
         if constexpr (MODE == MODE_FDH) {  // start over in the exact form
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
@@ -1349,7 +1627,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
 template <int D, int MODE, int BY, int NW, int XG, int MINB, int NBUF, int DS, bool FILTER>
 __global__ __launch_bounds__(NW * 64, MINB) void tile_kernel(TileArgs a)
 {
-    typedef TileGeom<D, MODE, BY, NW, XG, NBUF, DS> G;
+    typedef TileGeom<D, MODE, BY, NW, XG, NBUF, DS, FILTER> G;
     __shared__ __attribute__((aligned(1024))) uint16_t buf0[G::BUF0];
     __shared__ __attribute__((aligned(1024))) uint16_t buf1[G::BUF1];
     __shared__ __attribute__((aligned(1024))) uint16_t buf2[G::BUF2];
@@ -1366,8 +1644,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void tile_kernel(TileArgs a)
 template <int D, int BY, int XG_DH, int XG_DE, int NBUF, bool FILTER>
 __global__ __launch_bounds__(256, 2) void tile_bwd_kernel(TileArgs a_dh, TileArgs a_de, int64_t de_blocks)
 {
-    typedef TileGeom<D, MODE_DH, BY, 4, XG_DH, NBUF, 1> GH;
-    typedef TileGeom<D, MODE_DE, BY, 4, XG_DE, NBUF, 1> GE;
+    typedef TileGeom<D, MODE_DH, BY, 4, XG_DH, NBUF, 1, FILTER> GH;
+    typedef TileGeom<D, MODE_DE, BY, 4, XG_DE, NBUF, 1, FILTER> GE;
     constexpr int B0 = GH::BUF0 > GE::BUF0 ? GH::BUF0 : GE::BUF0, B1 = GH::BUF1 > GE::BUF1 ? GH::BUF1 : GE::BUF1;
     constexpr int B2 = GH::BUF2 > GE::BUF2 ? GH::BUF2 : GE::BUF2, B3 = GH::BUF3 > GE::BUF3 ? GH::BUF3 : GE::BUF3;
     __shared__ __attribute__((aligned(1024))) uint16_t buf0[B0];

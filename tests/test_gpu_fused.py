@@ -244,3 +244,32 @@ def test_fused_sampled_calls(mode, dtype, d):
     out = run_hip_sampled(w, smp, fuse_dH=True)
     assert out["status"] == 0
     check_against_oracle(w_ref, out, TOL_BF16 if (dtype == "bf16" and mode == NEG_SHARED) else 2e-5)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("tiles,rest", [(0, 1), (0, 33), (1, 0), (1, 1), (2, 0), (3, 31), (4, 0), (5, 1), (6, 0), (7, 17)])
+def test_streamed_ranges_of_few_tiles(d, tiles, rest):
+    """The streaming passes carry a sub-tile across the borders of their tiles (8192 / d rows each): ranges that end with a
+    tile, one row behind it, before the ring of buffers is full and after it has gone round, on either streamed side."""
+    from hip_harness import run_hip
+    import paper_2509_09682_amd as P
+
+    n = tiles * (8192 // d) + rest
+    for N, K in ((97, n), (n, 97)):
+        w = make_workload(f"few_tiles_{d}_{n}_{N}", N, 1, d, max(4 * K, 300), K, "bf16", NEG_SHARED, 31 + n, g_kind="random",
+                          e_sigma=0.1, tgt_dist="zipf")
+        check_against_oracle(w, _run(w), TOL_BF16)
+        check_against_oracle(w, run_hip(w, algo=P.CCE_ALGO_TILE, reuse_prep=True), TOL_BF16)
+
+
+@pytest.mark.parametrize("first_negative", [None, 0, 700, 1910])
+def test_signs_and_zeros_of_the_upstream_gradient(first_negative):
+    """Full catalogue at d = 64, long enough for two row groups to a wavefront: the dE pass folds log2 |g| into the exponent
+    offsets and looks at signs from the first tile on that holds a negative gradient."""
+    w = make_workload("signs", 1920, 1, 64, 77_003, 0, "bf16", NEG_FULL, 77, g_kind="random", e_sigma=0.1, tgt_dist="zipf")
+    w.g[:] = np.abs(w.g) * np.exp2(np.random.default_rng(3).integers(-20, 20, w.N)).astype(np.float32)
+    w.g[::7] = 0
+    if first_negative is not None:
+        w.g[first_negative::3] *= -1
+    # rows of dE are sums over positions whose gradients span 2^40: the largest ones decide, as in any sum of few terms
+    check_against_oracle(w, _run(w), TOL_BF16, row_tol=TOL_BF16)
