@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "cce_device.hpp"
 #include "cce_kernels.hpp"
@@ -43,6 +44,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -174,6 +176,31 @@ __device__ __forceinline__ float max3_after(float after, float x, float y, float
     return r;
 }
 
+// Direct-to-LDS loads that the compiler does not see as such: 16 or 4 bytes a lane from src to lds + 16 (4) * lane.  Shown one, it
+// protects the next transpose read with a wait for all loads in flight.  Waits and barriers are the caller's, as everywhere here;
+// there is no result register that could be written late.  m0 is the compiler's for its own loads of this kind only, and a kernel
+// uses one sort or the other.
+__device__ __forceinline__ void load_to_lds_16(const void *src, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory");
+}
+__device__ __forceinline__ void load_to_lds_4(const void *src, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(src) : "memory");
+}
+
+// f(0), f(1), ... with compile-time arguments, for bodies beyond what the unroller takes.
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_each(std::integer_sequence<int, I...>, F &&f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_each(std::make_integer_sequence<int, N>{}, f);
+}
+
 constexpr int kScaleChunks = 4;  // 32-byte pieces of dH per thread of a scaling block
 
 // dH = grad_loss * U for the valid positions, zero rows for the padded ones: one lane per 8 columns, positions in their
@@ -223,9 +250,15 @@ constexpr bool streams(int d, int mode, int by, int nbuf, int ds, bool filter)
 {
     return d <= 128 && by % 64 == 0 && mode != MODE_FWD && nbuf == 4 && ds == 1 && !filter;
 }
+// The same for hidden size 256, a wavefront to a SIMD and all of its registers (run_stream_wide).
+constexpr bool streams_wide(int d, int mode, int by, int nw, int ds, bool filter)
+{
+    return d == 256 && by == 32 && nw == 4 && mode != MODE_FWD && ds == 1 && !filter;
+}
 template <int D, int MODE, int BY, int NW, int XG, int NBUF, int DS, bool FILTER>
 struct TileGeom {
-    static constexpr bool STREAM = streams(D, MODE, BY, NBUF, DS, FILTER);
+    static constexpr bool WIDE = streams_wide(D, MODE, BY, NW, DS, FILTER);
+    static constexpr bool STREAM = streams(D, MODE, BY, NBUF, DS, FILTER) || WIDE;
     static constexpr int TILE = BY * D;
     static constexpr int IDS = (BY < 64) ? 64 : BY;
     static constexpr int CONSTS = (MODE == MODE_DE) ? 2 * BY : 0;
@@ -233,11 +266,11 @@ struct TileGeom {
     static constexpr int XPB = (NW / DS) * XG * 32;
     static constexpr int EPI_BYTES = NW * 32 * 33 * 4 + XPB * 8;
     static constexpr bool EPI_IN_TILES = (MODE == MODE_DE) && (NW == 4) && (TILE * 2 >= 2 * 32 * 33 * 4 + XPB * 8);
-    static constexpr int BUF0 = (NBUF == 0) ? 2 * BUF : (STREAM ? 4 * BUF : BUF);
+    static constexpr int BUF0 = (NBUF == 0) ? 2 * BUF : (STREAM ? NBUF * BUF : BUF);
     static constexpr int BUF1 = (NBUF >= 2 && !STREAM) ? BUF : 8;
     static constexpr int BUF2 = (NBUF >= 3 && !STREAM) ? BUF : 8;
     static constexpr int BUF3 = (NBUF >= 4 && !STREAM) ? BUF : 8;
-    static constexpr bool FOLD = STREAM && MODE == MODE_DE && XG == 2;  // per wavefront: offsets of a tile, sign words of two
+    static constexpr bool FOLD = STREAM && !WIDE && MODE == MODE_DE && XG == 2;  // per wavefront: offsets of a tile, sign words of two
     static_assert(!FOLD || BY == 128, "a lane folds two rows of a tile");
     static constexpr int FOLD_FLOATS = FOLD ? 2 * BY : 0;
     static constexpr int EPI_OWN = (MODE == MODE_DE && !EPI_IN_TILES) ? EPI_BYTES / 4 : (FOLD ? NW * FOLD_FLOATS : 4);  // floats
@@ -281,7 +314,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     // group of stationary rows has the registers for it (the operands of a whole sub-tile are d/4 registers).
     constexpr bool SWP = (BY % 64 == 0) && (D <= 128 || (MODE == MODE_FWD && XG == 1));
     typedef TileGeom<D, MODE, BY, NW, XG, NBUF, DS, FILTER> G;
-    constexpr bool STREAM = G::STREAM;
+    constexpr bool STREAM = G::STREAM, WIDE = G::WIDE;
     constexpr int KK = D / 16;             // k-steps of the score product
     constexpr int MB = D / 32;             // 32-row output blocks of the second product
     constexpr int CPR = D / 8;             // 16-byte chunks per row
@@ -295,8 +328,8 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     constexpr int LOADS = BY * CPR / 64;   // 1-KiB direct-to-LDS load instructions per tile
     static_assert(LOADS % NW == 0, "tile loads must split evenly over the wavefronts");
     constexpr int LPW = LOADS / NW;
-    static_assert(NBUF == 0 || (NBUF >= 2 && NBUF <= 4), "ring of 2 to 4 buffers, or 0 for the rolled form");
-    constexpr int PF = (NBUF == 0) ? 1 : NBUF - 1;  // prefetch distance in tiles
+    static_assert(NBUF == 0 || (NBUF >= 2 && NBUF <= 4) || (WIDE && NBUF > 4), "ring of 2 to 4 buffers, or 0 for the rolled form");
+    constexpr int PF = (NBUF == 0) ? 1 : (WIDE ? NBUF - 3 : NBUF - 1);  // prefetch distance in tiles
     constexpr int NB = (NBUF == 0) ? 2 : NBUF;
     // A buffer holds the rows of a tile, (dE) the 2 x BY coefficient constants of its rows, and the row numbers of the
     // tile PF places further on, which ride along so that no load in the main loop returns into registers: the
@@ -318,7 +351,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     // (NBUF = 0) keeps one copy of the loop body where registers are short.
     auto buf_at = [&](int i) -> uint16_t * {
         if (NBUF == 0) return buf0 + (i & 1) * BUF;
-        if (STREAM) return buf0 + (i & 3) * BUF;
+        if (STREAM) return buf0 + (i % NB) * BUF;
         return i == 0 ? buf0 : (i == 1 ? buf1 : (i == 2 ? buf2 : buf3));
     };
 
@@ -382,6 +415,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         }
     }
     if (xb * XPB >= n_x) return;  // whole block past the end (the grid is sized for the unmasked N)
+    if (WIDE && n_y == 0) return;  // dE without a valid position
 
     const uint16_t *Xbase = (MODE == MODE_DE) ? a.E : a.H;
     const uint16_t *Ybase = (MODE == MODE_DE) ? a.H : a.E;
@@ -412,13 +446,22 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         }
     }
 
+    float op_early[XG];  // WIDE, FDH: score of the correct item, taken while the first tiles are on their way
+    // WIDE: read again where they are wanted behind the streaming loop, so that they need not outlive it
+    auto reload_x = [&](int g) {
+        const uint16_t *xp = Xbase + xrow[g] * D;
+        asm volatile("" : "+v"(xp));
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) xr[g][kk] = *reinterpret_cast<const uint4 *>(xp + kk * 16 + hi * 8);
+    };
+
     // ---- range of streamed tiles of this split
     const int64_t n_tiles = (n_y + BY - 1) / BY;
     const int64_t t_begin = n_tiles * split / splits;
     const int64_t t_end = n_tiles * (split + 1) / splits;
 
     f32x16 acc[XG][MODE == MODE_FWD ? 1 : MBH];
-    if (MODE != MODE_FWD) {
+    if (MODE != MODE_FWD && !WIDE) {
 #pragma unroll
         for (int g = 0; g < XG; ++g)
 #pragma unroll
@@ -1434,8 +1477,350 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         }
         return overflow != 0;
     };
-    bool again;
-    if constexpr (STREAM) again = run_stream();
+    // ---- Hidden size 256.  Accumulators and stationary rows of 32 positions take 192 registers, and with two wavefronts to a
+    // SIMD every operand read from LDS served one matrix instruction: the eight wavefronts of a block met at every barrier and
+    // waited for the same reads 41 % of the time (2.03 us a tile against 0.85 of matrix work).  Here a wavefront has a SIMD to
+    // itself: two row groups, so that an operand serves two matrix instructions, the accumulators in the 256 accumulation
+    // registers, and everything else in the other 256.  Tile t: its score product, then the second product of tile t - 1 with
+    // the softmax arithmetic of t in between; the 32 operands of the two are one sequence, read R ahead of their use.
+    // The matrix instructions are inline assembly, which alone keeps scores in vector and sums in accumulation registers.  The
+    // compiler does not know when their results are there: scores are first looked at behind three later matrix instructions
+    // (96 cycles, a result takes 48) and never live round the loop; the sums are left alone until settle().
+    auto run_stream_wide = [&]() {
+        constexpr bool WATCH = (MODE == MODE_FDH);
+        constexpr int R = XG == 2 ? 4 : 8, NP = 16, PIECES = 32;  // R divides PIECES: the ring carries on into the next tile
+        static_assert(!WIDE || (NP == 2 * MBH && KK == NP && NA == 8 && NT == 4 && NSB == 1 && PF >= 2), "hidden size 256");
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        typedef const u32x4 __attribute__((address_space(3))) *lds_u4;
+        typedef const f32x4 __attribute__((address_space(3))) *lds_f4;
+        f32x16 sv[XG];
+        u32x4 gp[XG][2], gn[XG][2];  // coefficients of the tile before, and of the tile at hand
+        u32x4 ring[R];
+        f32x4 cy[2], gy[2];          // DE: offsets and gradients of four streamed rows
+        float part[XG][2];           // FDH: running sums
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)buf0;  // a multiple of 1024, as are the buffers: no carry into the XORs
+        auto buffer = [&](int i) -> uint32_t { return lds0 + (uint32_t)(i * BUF * 2); };
+        // operand i of the sequence: pieces of the score product (i < 16), then of the second product; neighbours share their XOR
+        auto read_op = [&](int i, uint32_t b) -> u32x4 {
+            return *(lds_u4)(uintptr_t)(((b + (uint32_t)(a_base * 2)) ^ (uint32_t)(i / 2 * 32)) + (i & 1) * (NA * 32));
+        };
+        auto read_tr = [&](int i, uint32_t b) -> u32x4 {
+            const int k2 = i / 8, mb0 = (i % 8) / 2, ofs = k2 * 16 * D * 2 + (i & 1) * (NT * 64);
+            const s16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(uintptr_t)(((b + (uint32_t)(t_base0 * 2)) ^ (uint32_t)(mb0 * 64)) + ofs));
+            const s16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(uintptr_t)(((b + (uint32_t)(t_base1 * 2)) ^ (uint32_t)(mb0 * 64)) + ofs));
+            const s16x8 both = __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7);
+            u32x4 v;
+            __builtin_memcpy(&v, &both, 16);
+            return v;
+        };
+        auto mfma_score = [&](int i, int g, const u32x4 &a) {
+            u32x4 x;
+            __builtin_memcpy(&x, &xr[g][i / 2 + (i & 1) * NA], 16);
+            if (i == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(sv[g]) : "v"(a), "v"(x));
+            else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(sv[g]) : "v"(a), "v"(x));
+        };
+        auto mfma_second = [&](int i, int g, const u32x4 &a, const u32x4 (&p)[XG][2]) {
+            asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc[g][(i % 8) / 2 + (i & 1) * NT]) : "v"(a), "v"(p[g][i / 8]));
+        };
+        auto settle = [&]() {
+            asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+#pragma unroll
+            for (int g = 0; g < XG; ++g)
+#pragma unroll
+                for (int mb = 0; mb < MBH; ++mb) asm volatile("" : "+a"(acc[g][mb]));
+        };
+        auto hold_scores = [&]() {
+#pragma unroll
+            for (int g = 0; g < XG; ++g) asm volatile("" : "+v"(sv[g]));
+        };
+        auto settle_scores = [&]() {
+            asm volatile("s_nop 15" ::: "memory");
+            hold_scores();
+        };
+        auto load_quad = [&](uint32_t b, int qq) {
+            const uint32_t at = b + OFF_C * 2 + hi * 16 + qq * 32;
+            cy[qq % 2] = *(lds_f4)(uintptr_t)at;
+            gy[qq % 2] = *(lds_f4)(uintptr_t)(at + BY * 4);
+        };
+        // scores q, q + 1 of group g -> exponentials (and coefficients of dE), in place; rem: see softmax above
+        auto weigh = [&](int g, int q, bool masked, int rem) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float ofs = MODE == MODE_FDH ? -run_m[g] : (MODE == MODE_DH ? cx[g] : cy[(q / 4) % 2][q % 4 + h]);
+                float v = __builtin_amdgcn_exp2f(fmaf(sv[g][q + h], kLog2e, ofs));
+                if (MODE == MODE_DE) v *= gy[(q / 4) % 2][q % 4 + h];
+                if (masked && (q / 4) * 8 + q % 4 + h >= rem) v = 0.f;
+                sv[g][q + h] = v;
+            }
+        };
+        auto file = [&](int g, int q) {
+            if (MODE == MODE_FDH) {
+                part[g][0] += sv[g][q];
+                part[g][1] += sv[g][q + 1];
+            }
+            gn[g][q / 8][(q / 2) % 4] = pack2(sv[g][q], sv[g][q + 1]);
+        };
+        auto take_over = [&]() {
+#pragma unroll
+            for (int g = 0; g < XG; ++g)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) gp[g][h] = gn[g][h];
+        };
+        // A load group is as in issue_group, of a fixed size (row numbers are loaded, and not used, also where there is no list of
+        // them) and one instruction at a time, so that it can be dealt out over the slices of a tile: in one piece behind the
+        // barrier, when all wavefronts have theirs to issue, it held the matrix pipe up for half a microsecond a tile.  Beyond the
+        // range the last tile is loaded again, into a buffer that nobody reads.
+        constexpr int GROUP = LPW + (MODE == MODE_DE ? 1 : 0) + 1;
+        const int64_t t_last = t_end - 1;
+        const int32_t *const numbers = ind ? ind : reinterpret_cast<const int32_t *>(Ybase);
+        const uint32_t wave_u = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
+        const uint32_t id_limit = a.validate ? (uint32_t)a.V : 0xffffffffu;  // an id beyond is flagged by the preparation kernel; row 0 stands in
+        const uint32_t listed = (uint32_t)__builtin_amdgcn_readfirstlane(ind ? ~0 : 0);
+        auto lds_dst = [&](int at) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + (uint32_t)(at * BUF * 2))); };
+        auto load_rows = [&](int i, uint32_t row, uint32_t dst) {
+            load_to_lds_16(Ybytes + ((uint64_t)row * (uint32_t)(D * 2) + chunk_ofs[i]), dst + (wave_u + (uint32_t)(i * NW)) * 1024u);
+        };
+        auto load_const = [&](int64_t t, uint32_t dst) {
+            uint32_t y = (uint32_t)(t * BY) + (uint32_t)(lane % BY);
+            if (y > last_y) y = last_y;
+            load_to_lds_4(a.de_const + (int64_t)(lane / BY) * a.N + y, dst + OFF_C * 2);
+        };
+        auto load_numbers = [&](int64_t t, uint32_t dst) {
+            uint32_t y = (uint32_t)(t * BY) + (uint32_t)lane;
+            if (y > last_y) y = last_y;
+            load_to_lds_4(numbers + y, dst + OFF_I * 2);
+        };
+        auto clamp = [&](int64_t t) -> int64_t { return t < t_last ? t : t_last; };
+        const uint32_t my_row = (uint32_t)(tid / CPR);  // instruction i of this lane fetches row my_row + i * (NW * 64 / CPR)
+        auto row_at = [&](int i, int64_t t) -> uint32_t {
+            const uint32_t y = (uint32_t)(t * BY) + my_row + (uint32_t)(i * (NW * 64 / CPR));
+            return y < last_y ? y : last_y;
+        };
+        auto row_of = [&](int i, int64_t t, int32_t id) -> uint32_t {
+            const uint32_t r = MODE != MODE_DE && (uint32_t)id >= id_limit ? 0u : (uint32_t)id;
+            return (r & listed) | (row_at(i, t) & ~listed);  // not a branch in the middle of a tile
+        };
+        auto start_loads = [&]() {
+            uint32_t rows[PF][LPW];
+#pragma unroll
+            for (int j = 0; j < PF; ++j)
+#pragma unroll
+                for (int i = 0; i < LPW; ++i) {
+                    const uint32_t y = row_at(i, clamp(t_begin + j));
+                    rows[j][i] = row_of(i, clamp(t_begin + j), ind ? ind[y] : 0);
+                }
+#pragma unroll
+            for (int j = 0; j < PF; ++j) {
+                const uint32_t dst = lds_dst(j);
+#pragma unroll
+                for (int i = 0; i < LPW; ++i) load_rows(i, rows[j][i], dst);
+                if (MODE == MODE_DE) load_const(clamp(t_begin + j), dst);
+                load_numbers(clamp(t_begin + j + PF), dst);
+            }
+        };
+        auto first_landed = [&]() {
+            wait_vm<(PF - 1) * GROUP>();
+            barrier_keep_loads();
+        };
+        auto tile = [&](int64_t t, int at) {
+            const uint32_t cur = buffer(at), next = buffer((at + 1) % NB);
+            const uint32_t prev = t == t_begin ? cur : buffer((at + NB - 1) % NB);  // before the first tile: coefficients of zero
+            constexpr int NPAIR = 8 * XG, FIRST = 3, SLICES = NP * XG;
+            typedef const int32_t __attribute__((address_space(3))) *lds_i32;
+            const uint32_t dst = lds_dst((at + PF) % NB);
+            const int64_t t_load = clamp(t + PF);
+            int32_t ids[LPW];
+            // pair p of the scores is worked on behind slice_of(p) of the second product
+            constexpr auto slice_of = [](int p) constexpr { return FIRST + p * (SLICES - FIRST - 2) / NPAIR; };
+            constexpr auto pair_at = [slice_of](int sl) constexpr {  // the pair of a slice; -1: none
+                for (int p = 0; p < NPAIR; ++p)
+                    if (slice_of(p) == sl) return p;
+                return -1;
+            };
+            static_assert(SLICES - FIRST - 2 >= NPAIR, "at most one pair to a slice");
+            static_for<PIECES>([&](auto piece) __attribute__((always_inline)) {
+                constexpr int i = decltype(piece)::value;
+                if constexpr (i == PIECES - R) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    // ahead of the first read of tile t + 1
+                    wait_vm<(PF - 1) * GROUP>();  // tile t + 1 has landed: all but t + 2 .. t + PF
+                    asm volatile("s_barrier" ::: "memory");
+                }
+                static_for<XG>([&](auto group) __attribute__((always_inline)) {
+                    constexpr int g = decltype(group)::value, sl = (i - NP) * XG + g;  // sl: slice of the second product
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (i < NP) mfma_score(i, g, ring[i % R]);
+                    else mfma_second(i - NP, g, ring[i % R], gp);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (sl == FIRST) hold_scores();
+                    if constexpr (g == XG - 1) {
+                        constexpr int j = i + R;
+                        if constexpr (j < NP) ring[j % R] = read_op(j, cur);
+                        else if constexpr (j < PIECES) ring[j % R] = read_tr(j - NP, prev);
+                        else ring[j % R] = read_op(j - PIECES, next);
+                    }
+                    if constexpr (sl >= 0) {
+                        // both groups of four rows before the next four: they share the constants, of which two sets are held
+                        constexpr int p = pair_at(sl), pp = pair_at(sl - 1);
+                        if constexpr (p >= 0) weigh(p % XG, 2 * (p / XG), false, 0);
+                        if constexpr (pp >= 0) file(pp % XG, 2 * (pp / XG));
+                        if constexpr (MODE == MODE_DE && p >= 0 && p % (2 * XG) == 2 * XG - 1 && p / (2 * XG) + 2 < 4) load_quad(cur, p / (2 * XG) + 2);
+                    }
+                });
+                if constexpr (MODE == MODE_DE && i == NP - 4) {
+                    load_quad(cur, 0);
+                    load_quad(cur, 1);
+                }
+                // The loads of tile t + PF, beside the score product, into the buffer of tile t - 3: every wavefront has been past
+                // its last use since the barrier of t - 1.
+                if constexpr (i == 0) {
+#pragma unroll
+                    for (int k = 0; k < LPW; ++k) ids[k] = *(lds_i32)(uintptr_t)(cur + OFF_I * 2 + (my_row + (uint32_t)(k * (NW * 64 / CPR))) * 4u);
+                }
+                if constexpr (i >= 3 && i % 2 == 1 && (i - 3) / 2 < LPW) load_rows((i - 3) / 2, row_of((i - 3) / 2, t_load, ids[(i - 3) / 2]), dst);
+                if constexpr (i == 3 + 2 * LPW) {
+                    if (MODE == MODE_DE) load_const(t_load, dst);
+                    load_numbers(clamp(t + 2 * PF), dst);
+                }
+            });
+            __builtin_amdgcn_sched_barrier(0);
+            take_over();
+        };
+        auto all_scores = [&](uint32_t b) {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const u32x4 v = read_op(i, b);
+#pragma unroll
+                for (int g = 0; g < XG; ++g) mfma_score(i, g, v);
+            }
+            settle_scores();
+        };
+        auto all_second = [&](uint32_t b) {
+            asm volatile("s_nop 7" ::: "memory");  // coefficients written by vector instructions, read by a matrix instruction
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const u32x4 v = read_tr(i, b);
+#pragma unroll
+                for (int g = 0; g < XG; ++g) mfma_second(i, g, v, gp);
+            }
+        };
+        auto raise_to_max_of = [&](uint32_t b, int rows_here) {  // FDH: reference of the largest score so far
+            all_scores(b);
+            const int rem = rows_here - hi * 4;
+#pragma unroll
+            for (int g = 0; g < XG; ++g) {
+                float tm = -INFINITY;
+#pragma unroll
+                for (int q = 0; q < 16; ++q)
+                    if ((q / 4) * 8 + (q % 4) < rem) tm = fmaxf(tm, sv[g][q]);
+                tm *= kLog2e;
+                run_m[g] = fmaxf(run_m[g], fmaxf(tm, __shfl_xor(tm, 32, 64)));  // both halves of a position agree
+            }
+        };
+        auto rows_of = [&](int64_t t) -> int { return (n_y - t * BY < BY) ? (int)(n_y - t * BY) : BY; };
+        // FDH: an attempt takes the largest of the first 32 scores as its reference; if a sum leaves the float range, a second one
+        // first goes over the range for the largest of all.
+        auto attempt = [&](auto second_tag) __attribute__((always_inline)) -> bool {
+            constexpr bool SECOND = decltype(second_tag)::value;
+            if (WATCH && tid == 0) over_flag[0] = 0;  // visible behind the barrier that follows the first loads
+#pragma unroll
+            for (int g = 0; g < XG; ++g) {
+                part[g][0] = part[g][1] = 0.f;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) gp[g][h] = (u32x4)(0u);
+                // zero where they stay: a zero written any other way lives in vector registers first, and is copied
+#pragma unroll
+                for (int mb = 0; mb < MBH; ++mb) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %1, 0" : "=a"(acc[g][mb]) : "v"(gp[0][0]));
+            }
+            start_loads();
+            if (MODE == MODE_FDH && !SECOND && splits == 1) {
+#pragma unroll
+                for (int g = 0; g < XG; ++g) {
+                    float o = 0.f;
+                    if (x_ok[g]) o = half_row_dot<D>(xr[g], a.E + (int64_t)a.tgt[xrow[g]] * D, hi);
+                    op_early[g] = o + __shfl_xor(o, 32, 64);
+                }
+            }
+            first_landed();
+            if (MODE == MODE_FDH) {
+                if constexpr (!SECOND) {
+                    raise_to_max_of(lds0, rows_of(t_begin));
+                } else {
+#pragma unroll 1
+                    for (int64_t t = t_begin; t < t_end; ++t) {
+                        const int at = (int)((t - t_begin) % NB);
+                        raise_to_max_of(buffer(at), rows_of(t));
+                        uint32_t rows[LPW];
+#pragma unroll
+                        for (int i = 0; i < LPW; ++i) rows[i] = row_of(i, clamp(t + PF), reinterpret_cast<const int32_t *>(buf_at(at) + OFF_I)[my_row + i * (NW * 64 / CPR)]);
+                        const uint32_t dst = lds_dst((at + PF) % NB);
+#pragma unroll
+                        for (int i = 0; i < LPW; ++i) load_rows(i, rows[i], dst);
+                        load_numbers(clamp(t + 2 * PF), dst);
+                        wait_vm<(PF - 1) * GROUP>();
+                        barrier_keep_loads();
+                    }
+                    wait_vm<0>();
+                    __syncthreads();
+                    start_loads();
+                    first_landed();
+                }
+            }
+            if (t_begin < t_stop) {
+#pragma unroll
+                for (int i = 0; i < R; ++i) ring[i] = read_op(i, lds0);
+                int at = 0;
+                int64_t t = t_begin;
+#pragma unroll 1
+                do {
+                    tile(t, __builtin_amdgcn_readfirstlane(at));
+                    at = (at + 1) % NB;
+                    ++t;
+                } while (t < t_stop);
+                all_second(buffer((at + NB - 1) % NB));
+            }
+            if (tail_ragged) {  // the short last tile, by itself
+                const uint32_t b = buffer((int)((t_stop - t_begin) % NB));
+                all_scores(b);
+#pragma unroll
+                for (int q = 0; q < 16; q += 2) {
+                    if (MODE == MODE_DE && q % 4 == 0) load_quad(b, q / 4);
+#pragma unroll
+                    for (int g = 0; g < XG; ++g) {
+                        weigh(g, q, true, rows_of(t_stop) - hi * 4);
+                        file(g, q);
+                    }
+                }
+                take_over();
+                all_second(b);
+            }
+            if (WATCH && !SECOND) {  // a sum of exponentials that was beyond the limit once stays there
+                bool over = false;
+#pragma unroll
+                for (int g = 0; g < XG; ++g) over |= !(part[g][0] + part[g][1] < 1.0e30f);  // or NaN
+                if (__any(over) && lane == 0) over_flag[0] = 1;
+            }
+            settle();
+            wait_vm<0>();     // the loads beyond the range
+            __syncthreads();  // the tile buffers are free, the flag is in place
+            return WATCH && !SECOND && __builtin_amdgcn_readfirstlane(over_flag[0]) != 0;
+        };
+        if (attempt(std::false_type{})) {
+            if constexpr (WATCH) {
+#pragma unroll
+                for (int g = 0; g < XG; ++g) {
+                    run_m[g] = -INFINITY;
+                    reload_x(g);
+                }
+                attempt(std::true_type{});
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < XG; ++g) run_s[g] = part[g][0] + part[g][1];
+    };
+    bool again = false;
+    if constexpr (WIDE) run_stream_wide();
+    else if constexpr (STREAM) again = run_stream();
     else again = run_attempt(FastTag{});
     if (again) {
         if constexpr (MODE == MODE_FDH) {  // start over in the exact form
@@ -1518,8 +1903,12 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             }
             float op = 0.f;
             const uint16_t *erow = a.E + (x_ok[g] ? (int64_t)a.tgt[xrow[g]] : 0) * D;
-            if (x_ok[g]) op = half_row_dot<D>(xr[g], erow, hi);
-            op += __shfl_xor(op, 32, 64);
+            if (WIDE) {
+                op = op_early[g];
+            } else {
+                if (x_ok[g]) op = half_row_dot<D>(xr[g], erow, hi);
+                op += __shfl_xor(op, 32, 64);
+            }
             if (x_ok[g]) {
                 const float w = a.pos_weight_mode == 2 ? 0.f : (a.cnt ? 1.f - (float)a.cnt[xrow[g]] : 1.f);
                 const float o2 = op * kLog2e;
@@ -1565,6 +1954,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             }
             float op = 0.f;
             const uint16_t *erow = a.E + (x_ok[g] ? (int64_t)a.tgt[xrow[g]] : 0) * D;
+            if (WIDE) reload_x(g);
             if (x_ok[g]) op = half_row_dot<D>(xr[g], erow, hi);
             op += __shfl_xor(op, 32, 64);
             if (x_ok[g]) {
@@ -1956,9 +2346,9 @@ inline int de_split_cap(const TileArgs &a)
     int cap = (int)(a.N * 5e-4) < 8 ? 8 : (int)(a.N * 5e-4);
     if (a.d > 128) {
         // hidden size 256, one block of 256 candidates per compute unit: a short list gives few blocks, and the cap
-        // above left the chip idle.  Tile time tiles / s (2.1 us a tile) plus atomics s n_cols d / 327 G/s is least
-        // at the root (511 candidates, 24,576 positions: 16 splits 93 us)
-        const double best = sqrt((double)(a.N / 32) * 2100.0 * 327.0 / ((double)a.n_cols * a.d));
+        // above left the chip idle.  Tile time tiles / s (1 us a tile in blocks of 128 candidates) plus atomics
+        // s n_cols d / 327 G/s is least at the root (511 candidates, 24,576 positions: 16 splits 93 us)
+        const double best = sqrt((double)(a.N / 32) * 1000.0 * 327.0 / ((double)a.n_cols * a.d));
         if ((double)cap < best) cap = (int)best;
     }
     return cap;
@@ -2034,11 +2424,10 @@ hipError_t launch_bwd_kernel(TileArgs &a_dh, TileArgs &a_de, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Hidden size 256: microseconds of a tile in a block of eight wavefronts, and what a tile takes a block of four that has a
-// compute unit to itself, in those (one wavefront to a SIMD: nobody waits for the matrix pipe).  24,576 positions, us, blocks
-// of 256 / of 128: forward + dH against 511 candidates 56 / 42, 2048 candidates 130 / 93; 20,000 positions, 9000 items 453 / 308;
-// dE, 60,000 positions, 511 candidates 105 / 87, 8000 positions 48 / 42.
-constexpr double kTileUs = 2.07, kNarrowTile = 0.65;
+// Hidden size 256: microseconds of a tile in a block of 256 stationary rows, and what a tile takes a block of 128 (one row group
+// to a wavefront), in those; either has a compute unit to itself.  Forward + dH, us, blocks of 256 / of 128: 65,536 positions, 8192
+// candidates 481 / -, 32,768 positions - / 281; 20,480 positions, 9000 items - / 273.
+constexpr double kTileUs = 1.75, kNarrowTile = 0.56;
 
 template <int D>
 hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
@@ -2051,21 +2440,19 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
     constexpr int BY_F = (D <= 128) ? BY : 128;
     constexpr int MINB_F = (D <= 64) ? 3 : 2;
     // d = 256: every block streams the whole other operand from L2 (about 12 TB/s over the chip for direct-to-LDS
-    // loads), so the rows it keeps stationary decide the traffic: eight wavefronts per block, one block per compute
-    // unit.  The backward accumulators for all columns (d/2 registers) plus the stationary rows (d/4) leave little of
-    // the 256-register budget: operands are read two at a time there.
+    // loads), so the rows it keeps stationary decide the traffic: 256 of them per block, one block per compute unit.  The forward
+    // pass and gradient filtering do that with eight wavefronts of 256 registers (operands are read two at a time where they
+    // accumulate), the other passes with four of 512, two row groups each (run_stream_wide).
     constexpr int NW_L = (D <= 128) ? 4 : 8;
-    constexpr int DS_B = 1;
     constexpr int BY_B = BY;  // d = 256: tiles of 64 rows measured 3-6 % slower
-    constexpr int MINB = (D <= 128) ? 2 : 1;   // backward: 256 registers per wavefront
+    constexpr int MINB = (D <= 128) ? 2 : 1;   // backward: 256 registers per wavefront up to d = 128
     // LDS buffers in flight, 18 KiB each: three blocks per compute unit leave room for three of them, two blocks or
-    // one for four.  d = 256: two 66-KiB buffers in the forward pass; three buffers in the backward passes (measured:
-    // dE 5 % faster than with two, dH unchanged, four no better).
+    // one for four.  d = 256: two 66-KiB buffers in the forward pass; three of 16 KiB with filtering, six else.
     constexpr int NBUF_F = (D <= 64) ? 3 : (D <= 128 ? 4 : 2);
     constexpr int NBUF_B = (D <= 128) ? 4 : 3;
-    constexpr int NBUF_FDH = 4;  // d = 256: 2 % faster than three (the dE pass: 20 % slower)
+    constexpr int XG_L = (D <= 128) ? 1 : 2, NBUF_L = (D <= 128) ? 4 : 6;
     // Two groups of stationary rows per wavefront use each LDS operand for two matrix instructions; the backward
-    // accumulators leave room for that up to d = 64.
+    // accumulators leave room for that up to d = 64, and at d = 256 with a SIMD to a wavefront.
     constexpr int XG_F = 2;
     constexpr int XG_B = (D <= 64) ? 2 : 1;
     hipError_t e = hipSuccess;
@@ -2100,9 +2487,9 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
             }
         }
         if (!done && a.filter_log2 > -INFINITY) {
-            if constexpr (D > 128) e = launch_tile_kernel<D, MODE_DH, BY_B, NW_L, 1, MINB, NBUF_B, DS_B, true>(a, a.N, stream);
+            if constexpr (D > 128) e = launch_tile_kernel<D, MODE_DH, BY_B, NW_L, 1, MINB, NBUF_B, 1, true>(a, a.N, stream);
             else e = hipErrorInvalidValue;  // smaller hidden sizes filter in the fused launch
-        } else if (!done) e = launch_tile_kernel<D, MODE_DH, BY_B, NW_L, 1, MINB, NBUF_B, DS_B>(a, a.N, stream);
+        } else if (!done) e = launch_tile_kernel<D, MODE_DH, BY_B, 4, XG_L, MINB, NBUF_L>(a, a.N, stream);
         if constexpr (D > 128) {
             if (e == hipSuccess && a.tail_slots > 0) {  // rows of the split last round: at most half the chip's blocks
                 constexpr int PPB = 256 / (D / 8), XPB_L = NW_L * 32;
@@ -2131,7 +2518,7 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
         if constexpr (D > 128) {
             // Blocks of 128 rows, one to a compute unit, where that is the faster way to fill the chip: tiles of a share, and the
             // partial rows of the shares (written and read, at 5 TB/s), which need half the shares.
-            const int cus = resident_blocks(tile_kernel<D, MODE_FDH, BY_B, NW_L, 1, MINB, NBUF_FDH, DS_B, false>, NW_L * 64);
+            const int cus = resident_blocks(tile_kernel<D, MODE_FDH, BY_B, 4, XG_L, MINB, NBUF_L, 1, false>, 256);
             const int64_t xb = (a.N + 127) / 128;
             if (xb > 0 && xb <= cus) {
                 TileArgs w = a;
@@ -2142,12 +2529,12 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
                 auto cost = [&](int64_t n, double tile_us) { return tiles / n * tile_us + (n > 1 ? n * rows_us : 0.); };
                 if (cost(s, kTileUs * kNarrowTile) < cost(w.splits, kTileUs)) {
                     a.splits = (int)s;
-                    e = launch_tile_kernel<D, MODE_FDH, BY_B, 4, 1, 2, NBUF_FDH, DS_B>(a, a.N, stream, true);
+                    e = launch_tile_kernel<D, MODE_FDH, BY_B, 4, 1, 1, NBUF_L>(a, a.N, stream, true);
                     done = true;
                 }
             }
         }
-        if (!done) e = launch_tile_kernel<D, MODE_FDH, BY_B, NW_L, 1, MINB, NBUF_FDH, DS_B>(a, a.N, stream);
+        if (!done) e = launch_tile_kernel<D, MODE_FDH, BY_B, 4, XG_L, MINB, NBUF_L>(a, a.N, stream);
         if constexpr (D > 128) {
             if (e == hipSuccess && a.tail_slots > 0) {
                 constexpr int PPB = 256 / (D / 8), XPB_L = NW_L * 32;
@@ -2180,11 +2567,11 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
             if (wide(a.n_cols, false)) return launch_tile_kernel<D, MODE_DE, BY_B, 4, 2, MINB, NBUF_B>(a, a.n_cols, stream);
         }
         if (a.filter_log2 > -INFINITY) {
-            if constexpr (D > 128) return launch_tile_kernel<D, MODE_DE, BY_B, NW_L, 1, MINB, NBUF_B, DS_B, true>(a, a.n_cols, stream);
+            if constexpr (D > 128) return launch_tile_kernel<D, MODE_DE, BY_B, NW_L, 1, MINB, NBUF_B, 1, true>(a, a.n_cols, stream);
             else return hipErrorInvalidValue;
         }
         if constexpr (D > 128) {
-            const int cus = resident_blocks(tile_kernel<D, MODE_DE, BY_B, NW_L, 1, MINB, NBUF_B, DS_B, false>, NW_L * 64);
+            const int cus = resident_blocks(tile_kernel<D, MODE_DE, BY_B, 4, XG_L, MINB, NBUF_L, 1, false>, 256);
             TileArgs w = a;
             const int64_t wide_blocks = plan_tile_grid<MODE_DE>(w, a.n_cols, NW_L * 32, NW_L * 64, cus);
             const int64_t xb = (a.n_cols + 127) / 128, tiles = (a.N + BY_B - 1) / BY_B;
@@ -2193,10 +2580,10 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
             if (s > cap) s = cap;
             if (s >= 1 && (double)((tiles + s - 1) / s) * kNarrowTile < (double)((wide_blocks + cus - 1) / cus) * ((tiles + w.splits - 1) / w.splits)) {
                 a.splits = (int)s;
-                return launch_tile_kernel<D, MODE_DE, BY_B, 4, 1, 2, NBUF_B, DS_B>(a, a.n_cols, stream, true);
+                return launch_tile_kernel<D, MODE_DE, BY_B, 4, 1, 1, NBUF_L>(a, a.n_cols, stream, true);
             }
         }
-        return launch_tile_kernel<D, MODE_DE, BY_B, NW_L, 1, MINB, NBUF_B, DS_B>(a, a.n_cols, stream);
+        return launch_tile_kernel<D, MODE_DE, BY_B, 4, XG_L, MINB, NBUF_L>(a, a.n_cols, stream);
     default:
         return hipErrorInvalidValue;
     }
