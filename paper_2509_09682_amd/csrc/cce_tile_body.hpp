@@ -415,7 +415,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         }
     }
     if (xb * XPB >= n_x) return;  // whole block past the end (the grid is sized for the unmasked N)
-    if (WIDE && n_y == 0) return;  // dE without a valid position
+    if (STREAM && n_y == 0) return;  // dE without a valid position
 
     const uint16_t *Xbase = (MODE == MODE_DE) ? a.E : a.H;
     const uint16_t *Ybase = (MODE == MODE_DE) ? a.H : a.E;
@@ -556,11 +556,19 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         uint32_t dst_lds = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uintptr_t)(lds_ptr)dst_generic);
         asm volatile("" : "+s"(dst_lds));
         uint16_t __attribute__((address_space(3))) *dst = (uint16_t __attribute__((address_space(3))) *)(uintptr_t)dst_lds;
+        auto to_lds_16 = [&](const void *src, uint32_t at, uint16_t __attribute__((address_space(3))) *to) {
+            if (STREAM) load_to_lds_16(src, (uint32_t)__builtin_amdgcn_readfirstlane((int)at));
+            else __builtin_amdgcn_global_load_lds((global_cptr)src, (lds_ptr)to, 16, 0, 0);
+        };
+        auto to_lds_4 = [&](const void *src, uint32_t at, uint16_t __attribute__((address_space(3))) *to) {
+            if (STREAM) load_to_lds_4(src, (uint32_t)__builtin_amdgcn_readfirstlane((int)at));
+            else __builtin_amdgcn_global_load_lds((global_cptr)src, (lds_ptr)to, 4, 0, 0);
+        };
         if (small_table) {
 #pragma unroll
             for (int i = 0; i < LPW; ++i) {
                 const uint32_t ofs = (uint32_t)rows[i] * (uint32_t)(D * 2) + chunk_ofs[i];
-                __builtin_amdgcn_global_load_lds((global_cptr)(Ybytes + ofs), (lds_ptr)(dst + (wave + i * NW) * 512), 16, 0, 0);
+                to_lds_16(Ybytes + ofs, dst_lds + (wave + i * NW) * 1024, dst + (wave + i * NW) * 512);
             }
         } else {
 #pragma unroll
@@ -568,7 +576,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 uint32_t co = chunk_ofs[i];
                 asm volatile("" : "+v"(co));  // keeps the per-lane sum Ybytes + chunk_ofs from being carried (and spilled) as a 64-bit pair
                 const char *src = Ybytes + ((int64_t)rows[i] * (D * 2) + co);
-                __builtin_amdgcn_global_load_lds((global_cptr)src, (lds_ptr)(dst + (wave + i * NW) * 512), 16, 0, 0);
+                to_lds_16(src, dst_lds + (wave + i * NW) * 1024, dst + (wave + i * NW) * 512);
             }
         }
         if (MODE == MODE_DE) {  // wavefronts beyond CI repeat a load (same data, same place): group sizes stay uniform
@@ -579,14 +587,14 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             const uint32_t *src = a.de_const + (int64_t)(e / BY) * a.N + y;
             // upstream gradient straight from the caller's array, by row number, where the forward pass left the rest
             if (GSEP && a.g_separate && !a.g_stream_off && e / BY == 1) src = reinterpret_cast<const uint32_t *>(a.g) + rows[LPW];
-            __builtin_amdgcn_global_load_lds((global_cptr)src, (lds_ptr)(dst + OFF_C + inst * 128), 4, 0, 0);
+            to_lds_4(src, dst_lds + (OFF_C + inst * 128) * 2, dst + OFF_C + inst * 128);
         }
         if (ind) {
             const int inst = wave % NI;
             const int64_t t_ids = (t + PF) * BY < n_y ? (t + PF) * BY : n_y - 1;  // uniform
             uint32_t y = (uint32_t)t_ids + (uint32_t)(inst * 64 + lane);
             if (y > last_y) y = last_y;
-            __builtin_amdgcn_global_load_lds((global_cptr)(ind + y), (lds_ptr)(dst + OFF_I + inst * 128), 4, 0, 0);
+            to_lds_4(ind + y, dst_lds + (OFF_I + inst * 128) * 2, dst + OFF_I + inst * 128);
         }
     };
 
@@ -1221,6 +1229,81 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         }
         return overflow != 0;
     };
+    // A load group is as in issue_group, of a fixed size (row numbers are loaded, and not used, also where there is no list of
+    // them) and one instruction at a time, so that it can be dealt out over the slices of a tile: in one piece behind the
+    // barrier, when all wavefronts have theirs to issue, it held the matrix pipe up for half a microsecond a tile.  Beyond the
+    // range the last tile is loaded again, into a buffer that nobody reads.
+    constexpr int GROUP = LPW + (MODE == MODE_DE ? 1 : 0) + 1;
+    const int64_t t_last = t_end - 1;
+    const int32_t *const numbers = ind ? ind : reinterpret_cast<const int32_t *>(Ybase);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)buf0;
+    const uint32_t wave_u = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
+    const uint32_t id_limit = a.validate ? (uint32_t)a.V : 0xffffffffu;  // an id beyond is flagged by the preparation kernel; row 0 stands in
+    const uint32_t listed = (uint32_t)__builtin_amdgcn_readfirstlane(ind ? ~0 : 0);
+    auto lds_dst = [&](int at) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + (uint32_t)(at * BUF * 2))); };
+    auto load_rows = [&](int i, uint32_t row, uint32_t dst) {
+        load_to_lds_16(Ybytes + ((uint64_t)row * (uint32_t)(D * 2) + chunk_ofs[i]), dst + (wave_u + (uint32_t)(i * NW)) * 1024u);
+    };
+    // row: number of the row whose constant this lane fetches (used where the upstream gradient comes straight from the caller's array)
+    auto load_const = [&](int64_t t, uint32_t row, uint32_t dst) {  // wavefronts beyond CI repeat a load: same data, same place
+        const uint32_t inst = wave_u % CI, e = inst * 64 + lane;
+        uint32_t y = (uint32_t)(t * BY) + e % BY;
+        if (y > last_y) y = last_y;
+        const void *src = a.de_const + (int64_t)(e / BY) * a.N + y;
+        if (GSEP && a.g_separate && !a.g_stream_off && e / BY == 1) src = a.g + row;
+        load_to_lds_4(src, dst + (uint32_t)(OFF_C * 2) + inst * 256u);
+    };
+    auto load_numbers = [&](int64_t t, uint32_t dst) {
+        const uint32_t inst = wave_u % NI;
+        uint32_t y = (uint32_t)(t * BY) + inst * 64 + lane;
+        if (y > last_y) y = last_y;
+        load_to_lds_4(numbers + y, dst + (uint32_t)(OFF_I * 2) + inst * 256u);
+    };
+    auto clamp = [&](int64_t t) -> int64_t { return t < t_last ? t : t_last; };
+    const uint32_t my_row = (uint32_t)(tid / CPR);  // instruction i of this lane fetches row my_row + i * (NW * 64 / CPR)
+    auto row_at = [&](int i, int64_t t) -> uint32_t {
+        const uint32_t y = (uint32_t)(t * BY) + my_row + (uint32_t)(i * (NW * 64 / CPR));
+        return y < last_y ? y : last_y;
+    };
+    auto listed_or = [&](int32_t id, uint32_t y) -> uint32_t {  // the row of an id, or of the place y itself; not a branch in the middle of a tile
+        const uint32_t r = MODE != MODE_DE && (uint32_t)id >= id_limit ? 0u : (uint32_t)id;
+        return (r & listed) | (y & ~listed);
+    };
+    auto row_of = [&](int i, int64_t t, int32_t id) -> uint32_t { return listed_or(id, row_at(i, t)); };
+    const uint32_t const_slot = ((wave_u % CI) * 64 + lane) % BY;
+    auto const_at = [&](int64_t t) -> uint32_t {
+        const uint32_t y = (uint32_t)(t * BY) + const_slot;
+        return y < last_y ? y : last_y;
+    };
+    auto start_loads = [&]() {
+        uint32_t rows[PF][LPW + 1];
+#pragma unroll
+        for (int j = 0; j < PF; ++j)
+#pragma unroll
+            for (int i = 0; i < LPW; ++i) {
+                const uint32_t y = row_at(i, clamp(t_begin + j));
+                rows[j][i] = row_of(i, clamp(t_begin + j), ind ? ind[y] : 0);
+            }
+        if (GSEP) {
+#pragma unroll
+            for (int j = 0; j < PF; ++j) {
+                const uint32_t y = const_at(clamp(t_begin + j));
+                rows[j][LPW] = ind ? (uint32_t)ind[y] : y;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < PF; ++j) {
+            const uint32_t dst = lds_dst(j);
+#pragma unroll
+            for (int i = 0; i < LPW; ++i) load_rows(i, rows[j][i], dst);
+            if (MODE == MODE_DE) load_const(clamp(t_begin + j), GSEP ? rows[j][LPW] : 0u, dst);
+            load_numbers(clamp(t_begin + j + PF), dst);
+        }
+    };
+    auto first_landed = [&]() {
+        wait_vm<(PF - 1) * GROUP>();
+        barrier_keep_loads();
+    };
     // ---- STREAM: the tiles of the range as one unbroken sequence of sub-tiles (hidden sizes up to 128, passes with a second
     // product).  A phase is one sub-tile: its softmax arithmetic runs between the matrix instructions of the second product of
     // the sub-tile before it and, behind those, of the score product of the one after it, across tile borders.  LDS operands
@@ -1285,9 +1368,14 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
 #pragma unroll
             for (int q = 0; q < 16; ++q) v[q] = 0.f;
         };
-        auto phase = [&](const uint16_t *ptile, int pk, const uint16_t *tile, int k, const uint16_t *ntile, int nk, auto parity, auto with_signs, int tile_parity) {
+        auto phase = [&](const uint16_t *ptile, int pk, const uint16_t *tile, int k, const uint16_t *ntile, int nk, auto parity, auto with_signs, int tile_parity, auto with_loads, int64_t t, int at) {
             constexpr int c = decltype(parity)::value ? 1 : 0, n = c ^ 1;
-            constexpr bool SIGNS = decltype(with_signs)::value;
+            constexpr bool SIGNS = decltype(with_signs)::value, LOADS_HERE = decltype(with_loads)::value;
+            // the loads of tile t + PF, one behind every STEP-th slice, into the buffer of tile t - 1
+            constexpr int L0 = XG == 2 || KK > 4 ? 3 : 1, STEP = XG == 2 || KK > 4 ? 2 : 1;
+            const int64_t t_load = clamp(t + PF);
+            const uint32_t dst = lds_dst((at + PF) % NB);
+            int32_t ids[NR];
             uint4 op[KK], sy[2];
             if (SIGNS) {
 #pragma unroll
@@ -1335,6 +1423,19 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if (i < KK) op[i] = load_op(ntile, nk, i);
+                if (LOADS_HERE) {
+                    if (i == 0) {
+                        const int32_t *list = reinterpret_cast<const int32_t *>(tile + OFF_I);
+#pragma unroll
+                        for (int j = 0; j < LPW; ++j) ids[j] = list[my_row + (uint32_t)(j * (NW * 64 / CPR))];
+                        if (GSEP) ids[LPW] = list[const_slot];
+                    }
+                    if (i >= L0 && (i - L0) % STEP == 0 && (i - L0) / STEP < LPW) load_rows((i - L0) / STEP, row_of((i - L0) / STEP, t_load, ids[(i - L0) / STEP]), dst);
+                    if (i == L0 + STEP * LPW) {
+                        if (MODE == MODE_DE) load_const(t_load, GSEP ? (((uint32_t)ids[LPW] & listed) | (const_at(t_load) & ~listed)) : 0u, dst);
+                        load_numbers(clamp(t + 2 * PF), dst);
+                    }
+                }
 #pragma unroll
                 for (int j = 0; j < 2 * MBH; ++j) {  // pieces late in the list are read at the head of the phase that uses them
                     if (j * XG < TR_AHEAD && i == NS + j * XG - TR_AHEAD) load_tr1(tile, k, j);
@@ -1352,55 +1453,28 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             for (int p = 0; p < NPAIR; ++p)
                 if (FIRST + p * (NS - FIRST) / NPAIR + 1 >= NS) end_pair(p);
         };
-        int overflow = 0;
-        auto note_parts = [&](int parity) {
-            bool over = false;
-#pragma unroll
-            for (int g = 0; g < XG; ++g) over |= !((part[g][0] + part[g][1]) + (part[g][2] + part[g][3]) < 1.0e30f);  // or NaN
-            if (__any(over)) {
-                if (lane == 0) over_flag[parity] = 1;
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the barrier below does not wait for it
-            }
-        };
         // Tile t.  Ahead of its last phase, which reads the first operands of tile t + 1: wait for that tile, and start the loads
         // of tile t + 3 into the buffer of tile t - 1, whose last operands every wavefront has used in the first phase of t.
         auto step = [&](int64_t t, int at, auto signs) {
             // the first tile's predecessor has coefficients of zero: any finite rows do
             const uint16_t *const cur = buf_at(at), *const prev = t == t_begin ? cur : buf_at((at + 3) % 4), *const next = buf_at((at + 1) % 4);
             const int tile_parity = at & 1;
-            int seen = 0;
+            constexpr std::false_type no{};
+            constexpr std::true_type yes{};
 #pragma unroll
             for (int k = 0; k + 1 < NSB; ++k) {
-                if (k == 0) phase(prev, NSB - 1, cur, 0, cur, 1, std::false_type{}, signs, tile_parity);
-                else if (k % 2 == 0) phase(cur, k - 1, cur, k, cur, k + 1, std::false_type{}, signs, tile_parity);
-                else phase(cur, k - 1, cur, k, cur, k + 1, std::true_type{}, signs, tile_parity);
+                if (k == 0) phase(prev, NSB - 1, cur, 0, cur, 1, no, signs, tile_parity, no, t, at);
+                else if (k % 2 == 0) phase(cur, k - 1, cur, k, cur, k + 1, no, signs, tile_parity, no, t, at);
+                else phase(cur, k - 1, cur, k, cur, k + 1, yes, signs, tile_parity, no, t, at);
             }
-            if (t + 1 < t_end) {
-                wait_all_but<LPW>(t + 2 < t_end ? 1 : 0, group_extras);
-                if (WATCH) note_parts((int)((t - t_begin) & 1));
-                asm volatile("s_barrier" ::: "memory");
-                if (t + PF < t_end) {
-                    int32_t rows[NR];
-                    rows_from_lds(t + PF, cur, rows);
-                    issue_group(t + PF, rows, buf_at((at + 3) % 4));
-                }
-                if (WATCH) seen = over_flag[(int)((t - t_begin) & 1)];
-            }
+            wait_vm<GROUP>();  // tile t + 1 has landed: all but t + 2
+            asm volatile("s_barrier" ::: "memory");
             if constexpr (FOLD) fold_tile(next, tile_parity ^ 1);  // the offsets of tile t are in registers to the last one
-            phase(cur, NSB - 2, cur, NSB - 1, next, 0, std::true_type{}, signs, tile_parity);
-            if (WATCH) overflow |= __builtin_amdgcn_readfirstlane(seen);
+            phase(cur, NSB - 2, cur, NSB - 1, next, 0, yes, signs, tile_parity, yes, t, at);
         };
-        if (WATCH && tid < 2) over_flag[tid] = 0;  // visible behind the barrier that follows the first loads
-        if (t_begin < t_end) {
-            int32_t rows[PF][NR];
-#pragma unroll
-            for (int j = 0; j < PF; ++j)
-                if (t_begin + j < t_end) rows_from_global(t_begin + j, rows[j]);
-#pragma unroll
-            for (int j = 0; j < PF; ++j)
-                if (t_begin + j < t_end) issue_group(t_begin + j, rows[j], buf_at(j));
-        }
-        wait_for_next(t_begin - 1);
+        if (WATCH && tid == 0) over_flag[0] = 0;  // visible behind the barrier that follows the first loads
+        start_loads();
+        wait_vm<(PF - 1) * GROUP>();
         barrier_keep_loads();
         if (WATCH && t_begin < t_end) {  // reference: the largest score among the first 32 candidates
             const int64_t left = n_y - t_begin * BY;
@@ -1443,7 +1517,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                     step(t, __builtin_amdgcn_readfirstlane(at), std::false_type{});
                     at = (at + 1) % 4;
                     ++t;
-                } while (t < t_stop && !overflow && !negative);
+                } while (t < t_stop && !negative);
             }
             if constexpr (FOLD) {
 #pragma unroll 1
@@ -1460,22 +1534,13 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             if (WATCH) {
 #pragma unroll
                 for (int g = 0; g < XG; ++g) run_s[g] = (part[g][0] + part[g][1]) + (part[g][2] + part[g][3]);
-                note_overflow(0);
             }
         }
-        if (tail_ragged && !overflow) {
-            process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{}, Exact{});
-            if (WATCH) note_overflow(1);
-        }
-        __syncthreads();  // the tile buffers are free, the flags in place
-        if (WATCH) {
-            if (!overflow) overflow = __builtin_amdgcn_readfirstlane(over_flag[0] | over_flag[1]);
-            if (overflow) {  // loads of later tiles may still be in flight into the ring: let them land
-                wait_vm<0>();
-                __syncthreads();
-            }
-        }
-        return overflow != 0;
+        if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{}, Exact{});
+        if (WATCH) note_overflow(0);  // a sum that was beyond the limit once stays there
+        wait_vm<0>();     // the loads beyond the range
+        __syncthreads();  // the tile buffers are free, the flag is in place
+        return WATCH && __builtin_amdgcn_readfirstlane(over_flag[0]) != 0;
     };
     // ---- Hidden size 256.  Accumulators and stationary rows of 32 positions take 192 registers, and with two wavefronts to a
     // SIMD every operand read from LDS served one matrix instruction: the eight wavefronts of a block met at every barrier and
@@ -1498,7 +1563,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         u32x4 ring[R];
         f32x4 cy[2], gy[2];          // DE: offsets and gradients of four streamed rows
         float part[XG][2];           // FDH: running sums
-        const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)buf0;  // a multiple of 1024, as are the buffers: no carry into the XORs
+        // buf0 is a multiple of 1024, as are the buffers: no carry into the XORs
         auto buffer = [&](int i) -> uint32_t { return lds0 + (uint32_t)(i * BUF * 2); };
         // operand i of the sequence: pieces of the score product (i < 16), then of the second product; neighbours share their XOR
         auto read_op = [&](int i, uint32_t b) -> u32x4 {
@@ -1566,62 +1631,6 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
 #pragma unroll
                 for (int h = 0; h < 2; ++h) gp[g][h] = gn[g][h];
         };
-        // A load group is as in issue_group, of a fixed size (row numbers are loaded, and not used, also where there is no list of
-        // them) and one instruction at a time, so that it can be dealt out over the slices of a tile: in one piece behind the
-        // barrier, when all wavefronts have theirs to issue, it held the matrix pipe up for half a microsecond a tile.  Beyond the
-        // range the last tile is loaded again, into a buffer that nobody reads.
-        constexpr int GROUP = LPW + (MODE == MODE_DE ? 1 : 0) + 1;
-        const int64_t t_last = t_end - 1;
-        const int32_t *const numbers = ind ? ind : reinterpret_cast<const int32_t *>(Ybase);
-        const uint32_t wave_u = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
-        const uint32_t id_limit = a.validate ? (uint32_t)a.V : 0xffffffffu;  // an id beyond is flagged by the preparation kernel; row 0 stands in
-        const uint32_t listed = (uint32_t)__builtin_amdgcn_readfirstlane(ind ? ~0 : 0);
-        auto lds_dst = [&](int at) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + (uint32_t)(at * BUF * 2))); };
-        auto load_rows = [&](int i, uint32_t row, uint32_t dst) {
-            load_to_lds_16(Ybytes + ((uint64_t)row * (uint32_t)(D * 2) + chunk_ofs[i]), dst + (wave_u + (uint32_t)(i * NW)) * 1024u);
-        };
-        auto load_const = [&](int64_t t, uint32_t dst) {
-            uint32_t y = (uint32_t)(t * BY) + (uint32_t)(lane % BY);
-            if (y > last_y) y = last_y;
-            load_to_lds_4(a.de_const + (int64_t)(lane / BY) * a.N + y, dst + OFF_C * 2);
-        };
-        auto load_numbers = [&](int64_t t, uint32_t dst) {
-            uint32_t y = (uint32_t)(t * BY) + (uint32_t)lane;
-            if (y > last_y) y = last_y;
-            load_to_lds_4(numbers + y, dst + OFF_I * 2);
-        };
-        auto clamp = [&](int64_t t) -> int64_t { return t < t_last ? t : t_last; };
-        const uint32_t my_row = (uint32_t)(tid / CPR);  // instruction i of this lane fetches row my_row + i * (NW * 64 / CPR)
-        auto row_at = [&](int i, int64_t t) -> uint32_t {
-            const uint32_t y = (uint32_t)(t * BY) + my_row + (uint32_t)(i * (NW * 64 / CPR));
-            return y < last_y ? y : last_y;
-        };
-        auto row_of = [&](int i, int64_t t, int32_t id) -> uint32_t {
-            const uint32_t r = MODE != MODE_DE && (uint32_t)id >= id_limit ? 0u : (uint32_t)id;
-            return (r & listed) | (row_at(i, t) & ~listed);  // not a branch in the middle of a tile
-        };
-        auto start_loads = [&]() {
-            uint32_t rows[PF][LPW];
-#pragma unroll
-            for (int j = 0; j < PF; ++j)
-#pragma unroll
-                for (int i = 0; i < LPW; ++i) {
-                    const uint32_t y = row_at(i, clamp(t_begin + j));
-                    rows[j][i] = row_of(i, clamp(t_begin + j), ind ? ind[y] : 0);
-                }
-#pragma unroll
-            for (int j = 0; j < PF; ++j) {
-                const uint32_t dst = lds_dst(j);
-#pragma unroll
-                for (int i = 0; i < LPW; ++i) load_rows(i, rows[j][i], dst);
-                if (MODE == MODE_DE) load_const(clamp(t_begin + j), dst);
-                load_numbers(clamp(t_begin + j + PF), dst);
-            }
-        };
-        auto first_landed = [&]() {
-            wait_vm<(PF - 1) * GROUP>();
-            barrier_keep_loads();
-        };
         auto tile = [&](int64_t t, int at) {
             const uint32_t cur = buffer(at), next = buffer((at + 1) % NB);
             const uint32_t prev = t == t_begin ? cur : buffer((at + NB - 1) % NB);  // before the first tile: coefficients of zero
@@ -1679,7 +1688,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 }
                 if constexpr (i >= 3 && i % 2 == 1 && (i - 3) / 2 < LPW) load_rows((i - 3) / 2, row_of((i - 3) / 2, t_load, ids[(i - 3) / 2]), dst);
                 if constexpr (i == 3 + 2 * LPW) {
-                    if (MODE == MODE_DE) load_const(t_load, dst);
+                    if (MODE == MODE_DE) load_const(t_load, 0u, dst);
                     load_numbers(clamp(t + 2 * PF), dst);
                 }
             });
