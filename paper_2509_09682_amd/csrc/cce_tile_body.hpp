@@ -246,9 +246,9 @@ __device__ __forceinline__ void dh_scale_chunk(const TileArgs &a, int64_t chunk)
 // and keeps 1/DS of the output columns, which divides the accumulator registers by DS at the price of DS score products.
 // LDS needs of one tile-kernel configuration (the kernel wrappers declare the arrays, the body gets pointers).
 // STREAM: the unbroken pipeline of the passes with a second product (run_stream in tile_body), whose ring is one array.
-constexpr bool streams(int d, int mode, int by, int nbuf, int ds, bool filter)
+constexpr bool streams(int d, int mode, int by, int nbuf, int ds)
 {
-    return d <= 128 && by % 64 == 0 && mode != MODE_FWD && nbuf == 4 && ds == 1 && !filter;
+    return d <= 128 && by % 64 == 0 && mode != MODE_FWD && nbuf == 4 && ds == 1;
 }
 // The same for hidden size 256, a wavefront to a SIMD and all of its registers (run_stream_wide).
 constexpr bool streams_wide(int d, int mode, int by, int nw, int ds, bool filter)
@@ -258,7 +258,7 @@ constexpr bool streams_wide(int d, int mode, int by, int nw, int ds, bool filter
 template <int D, int MODE, int BY, int NW, int XG, int NBUF, int DS, bool FILTER>
 struct TileGeom {
     static constexpr bool WIDE = streams_wide(D, MODE, BY, NW, DS, FILTER);
-    static constexpr bool STREAM = streams(D, MODE, BY, NBUF, DS, FILTER) || WIDE;
+    static constexpr bool STREAM = streams(D, MODE, BY, NBUF, DS) || WIDE;
     static constexpr int TILE = BY * D;
     static constexpr int IDS = (BY < 64) ? 64 : BY;
     static constexpr int CONSTS = (MODE == MODE_DE) ? 2 * BY : 0;
@@ -1542,6 +1542,147 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         __syncthreads();  // the tile buffers are free, the flag is in place
         return WATCH && __builtin_amdgcn_readfirstlane(over_flag[0]) != 0;
     };
+    // ---- Gradient filtering up to d = 128, same ring and loads.  Late in training nearly every block is dropped (on a peaked
+    // softmax over 100,000 items 1.2 % are kept), so the pipeline is for those: while the matrix pipe has the scores of the
+    // next sub-tile, the vector units look for this one's largest probability; a kept one is finished on the spot.  The dH side
+    // needs no probabilities for the verdict, only the largest score, as a position's offset is one to a lane.
+    auto run_stream_filter = [&]() {
+        f32x16 sv[2][XG];
+        uint4 op[KK];
+        float4 cy[4];  // DE: exponent offsets of the streamed rows
+        auto load_op = [&](const uint16_t *tile, int sb, int kk) -> uint4 {
+            return *reinterpret_cast<const uint4 *>(lds_at(tile + sb * 32 * D, a_base, ((kk * 2) & SM) * 8, (kk / NA) * (NA * 16)));
+        };
+        auto const_at_row = [&](const uint16_t *tile, int sb, int qq) -> const float * {
+            return reinterpret_cast<const float *>(tile + OFF_C) + sb * 32 + qq * 8 + hi * 4;
+        };
+        auto score = [&](int kk, int g, f32x16 &v) {
+            if (kk == 0) {
+#pragma unroll
+                for (int q = 0; q < 16; ++q) v[q] = 0.f;
+            }
+            v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(op[kk]), as_bf16x8(xr[g][kk]), v, 0, 0, 0);
+        };
+        // sub-tile k of tile; next: the sub-tile whose scores are taken beside it; after: the one behind that, whose operands are read
+        auto phase = [&](const uint16_t *tile, int k, const uint16_t *ntile, int nk, const uint16_t *atile, int ak, auto parity, auto with_loads,
+                         int64_t t, int at) {
+            constexpr int c = decltype(parity)::value ? 1 : 0, n = c ^ 1;
+            constexpr bool LOADS_HERE = decltype(with_loads)::value;
+            const int64_t t_load = clamp(t + PF);
+            const uint32_t dst = lds_dst((at + PF) % NB);
+            int32_t ids[NR];
+            if (LOADS_HERE) {
+                const int32_t *list = reinterpret_cast<const int32_t *>(tile + OFF_I);
+#pragma unroll
+                for (int j = 0; j < LPW; ++j) ids[j] = list[my_row + (uint32_t)(j * (NW * 64 / CPR))];
+                if (GSEP) ids[LPW] = list[const_slot];
+            }
+            float first[XG], big[XG];
+            constexpr int QPS = 16 / KK, PER_G = 16 / QPS;  // scores worked on per slice; slices to a row group
+            // the first reader of a score tile is one that the compiler sees (see softmax above)
+#pragma unroll
+            for (int g = 0; g < XG; ++g) first[g] = MODE == MODE_DH ? sv[c][g][15] * kLog2e : 0.f;
+#pragma unroll
+            for (int i = 0; i < KK * XG; ++i) {
+                __builtin_amdgcn_sched_barrier(0);
+                score(i / XG, i % XG, sv[n][i % XG]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (i % XG == XG - 1) op[i / XG] = load_op(atile, ak, i / XG);
+                const int g = i / PER_G;
+#pragma unroll
+                for (int q = (i % PER_G) * QPS; q < (i % PER_G + 1) * QPS; q += 2) {
+                    if (MODE == MODE_DH) {
+                        big[g] = q == 0 ? max3_after(first[g], sv[c][g][0], sv[c][g][1], sv[c][g][1]) : max3(big[g], sv[c][g][q], sv[c][g][q + 1]);
+                    } else {
+                        const float4 o = cy[q / 4];
+                        const float l0 = fmaf(sv[c][g][q], kLog2e, q % 4 == 0 ? o.x : o.z), l1 = fmaf(sv[c][g][q + 1], kLog2e, q % 4 == 0 ? o.y : o.w);
+                        big[g] = q == 0 ? max3(l0, l1, l1) : max3(big[g], l0, l1);
+                        if (g == XG - 1 && q % 4 == 2) cy[q / 4] = *reinterpret_cast<const float4 *>(const_at_row(ntile, nk, q / 4));
+                    }
+                }
+                if (LOADS_HERE) {  // the loads of tile t + PF, into the buffer of tile t - 1
+                    constexpr int EACH = KK * XG > 4 ? 1 : 2;
+#pragma unroll
+                    for (int j = i * EACH; j < (i + 1) * EACH; ++j) {
+                        if (j < LPW) load_rows(j, row_of(j, t_load, ids[j]), dst);
+                        if (j == LPW && MODE == MODE_DE) load_const(t_load, GSEP ? listed_or(ids[LPW], const_at(t_load)) : 0u, dst);
+                        if (j == LPW + 1) load_numbers(clamp(t + 2 * PF), dst);
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int g = 0; g < XG; ++g) {
+                if (MODE == MODE_DH) big[g] = fmaf(big[g], kLog2e, cx[g]);
+                // stationary rows past the end hold a copy of row 0: they must not keep a block alive
+                if (!__any(x_ok[g] && big[g] >= a.filter_log2)) continue;
+                uint32_t gp[8];
+                s16x8 tr[2][MBH];
+                load_tr(tile, k, tr);
+#pragma unroll
+                for (int q = 0; q < 16; q += 2) {
+                    float2 o = make_float2(cx[g], cx[g]);
+                    if (MODE == MODE_DE) o = *reinterpret_cast<const float2 *>(const_at_row(tile, k, q / 4) + q % 4);
+                    float v0 = __builtin_amdgcn_exp2f(fmaf(sv[c][g][q], kLog2e, o.x)), v1 = __builtin_amdgcn_exp2f(fmaf(sv[c][g][q + 1], kLog2e, o.y));
+                    if (MODE == MODE_DE) {
+                        const float2 gq = *reinterpret_cast<const float2 *>(const_at_row(tile, k, q / 4) + BY + q % 4);
+                        v0 *= gq.x;
+                        v1 *= gq.y;
+                    }
+                    gp[q / 2] = pack2(v0, v1);
+                }
+#pragma unroll
+                for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+                    for (int mb = 0; mb < MBH; ++mb) {
+                        bf16x8 av;
+                        __builtin_memcpy(&av, &tr[k2][mb], 16);
+                        const uint4 bv = make_uint4(gp[k2 * 4 + 0], gp[k2 * 4 + 1], gp[k2 * 4 + 2], gp[k2 * 4 + 3]);
+                        acc[g][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, as_bf16x8(bv), acc[g][mb], 0, 0, 0);
+                    }
+            }
+        };
+        start_loads();
+        wait_vm<(PF - 1) * GROUP>();
+        barrier_keep_loads();
+        if (t_begin < t_stop) {
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) op[kk] = load_op(buf0, 0, kk);
+#pragma unroll
+            for (int i = 0; i < KK * XG; ++i) score(i / XG, i % XG, sv[0][i % XG]);
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) op[kk] = load_op(buf0, 1, kk);
+            if (MODE == MODE_DE) {
+#pragma unroll
+                for (int qq = 0; qq < 4; ++qq) cy[qq] = *reinterpret_cast<const float4 *>(const_at_row(buf0, 0, qq));
+            }
+            int at = 0;
+            int64_t t = t_begin;
+#pragma unroll 1
+            do {
+                const int at_u = __builtin_amdgcn_readfirstlane(at);
+                const uint16_t *const cur = buf_at(at_u), *const next = buf_at((at_u + 1) % NB);
+                constexpr std::false_type no{};
+                constexpr std::true_type yes{};
+#pragma unroll
+                for (int k = 0; k < NSB; ++k) {
+                    const uint16_t *const n1 = k + 1 < NSB ? cur : next, *const n2 = k + 2 < NSB ? cur : next;
+                    if (k == NSB - 2) {  // ahead of the first read of tile t + 1: it has landed (all but t + 2)
+                        wait_vm<GROUP>();
+                        asm volatile("s_barrier" ::: "memory");
+                    }
+                    if (k % 2 == 0 && k == NSB - 2) phase(cur, k, n1, (k + 1) % NSB, n2, (k + 2) % NSB, no, yes, t, at_u);
+                    else if (k % 2 == 0) phase(cur, k, n1, (k + 1) % NSB, n2, (k + 2) % NSB, no, no, t, at_u);
+                    else phase(cur, k, n1, (k + 1) % NSB, n2, (k + 2) % NSB, yes, no, t, at_u);
+                }
+                at = (at + 1) % NB;
+                ++t;
+            } while (t < t_stop);
+        }
+        if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{}, Exact{});
+        wait_vm<0>();     // the loads beyond the range
+        __syncthreads();  // the tile buffers are free
+    };
     // ---- Hidden size 256.  Accumulators and stationary rows of 32 positions take 192 registers, and with two wavefronts to a
     // SIMD every operand read from LDS served one matrix instruction: the eight wavefronts of a block met at every barrier and
     // waited for the same reads 41 % of the time (2.03 us a tile against 0.85 of matrix work).  Here a wavefront has a SIMD to
@@ -1829,6 +1970,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     };
     bool again = false;
     if constexpr (WIDE) run_stream_wide();
+    else if constexpr (STREAM && FILTER) run_stream_filter();
     else if constexpr (STREAM) again = run_stream();
     else again = run_attempt(FastTag{});
     if (again) {
@@ -2617,8 +2759,15 @@ hipError_t launch_bwd_for_d(TileArgs a_dh, TileArgs a_de, hipStream_t stream)
     };
     const bool wide_dh = wide(a_dh.N, a_dh.splits, true), wide_de = wide(a_de.n_cols, a_de.splits, false);
     hipError_t e;
-    if (a_dh.filter_log2 > -INFINITY) {  // gradient filtering: one group of stationary rows per wavefront, so that a
-        e = launch_bwd_kernel<D, 1, 1, true>(a_dh, a_de, stream);  // dropped block skips a whole second product
+    if (a_dh.filter_log2 > -INFINITY) {
+        if constexpr (XG_B == 2) {
+            if (wide_dh && wide_de) e = launch_bwd_kernel<D, 2, 2, true>(a_dh, a_de, stream);
+            else if (wide_dh) e = launch_bwd_kernel<D, 2, 1, true>(a_dh, a_de, stream);
+            else if (wide_de) e = launch_bwd_kernel<D, 1, 2, true>(a_dh, a_de, stream);
+            else e = launch_bwd_kernel<D, 1, 1, true>(a_dh, a_de, stream);
+        } else {
+            e = launch_bwd_kernel<D, 1, 1, true>(a_dh, a_de, stream);
+        }
     } else if constexpr (XG_B == 2) {
         if (wide_dh && wide_de) e = launch_bwd_kernel<D, 2, 2>(a_dh, a_de, stream);
         else if (wide_dh) e = launch_bwd_kernel<D, 2, 1>(a_dh, a_de, stream);

@@ -356,6 +356,37 @@ def test_gradient_filtering_of_the_full_catalogue_mode(d, V):
     assert e_dH <= TOL_BF16 and e_dE <= TOL_BF16, (e_dH, e_dE)
 
 
+@pytest.mark.parametrize("N,V", [(7700, 77_003), (7700, 3001), (700, 77_003)])
+def test_gradient_filtering_with_two_row_groups(N, V):
+    """d = 64: from 7680 positions (dH side) and 76,545 items (dE side) on a wavefront has two groups of stationary rows, each with
+    a verdict of its own.  Few of the positions are valid, which the choice of the kernel does not look at; the threshold as
+    in the test above, among the largest hundredth of the block maxima."""
+    import paper_2509_09682_amd as P
+    from workloads import bf16_bits_from_f32, f32_from_bf16_bits
+
+    w = make_workload(f"filter_wide_{N}_{V}", N, 1, 64, V, 0, "bf16", NEG_FULL, 5 + V, pad="bernoulli", pad_p=1 - 250 / N,
+                      g_kind="random", e_sigma=0.125, tgt_dist="zipf")
+    rng = np.random.default_rng(N)
+    H = 9.0 * f32_from_bf16_bits(w.E)[w.tgt] + 0.5 * rng.standard_normal((w.N, 64)).astype(np.float32)
+    w.H = bf16_bits_from_f32(H.astype(np.float32))
+    _, valid, p = O.run_workload_filtered(w, 1e-3)
+    nr, nc = p.shape
+    big = np.pad(p, ((0, -nr % 32), (0, -nc % 32))).reshape((nr + -nr % 32) // 32, 32, (nc + -nc % 32) // 32, 32).max(axis=(1, 3))
+    srt = np.sort(big.ravel())
+    cand = srt[int(0.99 * srt.size):-5] if srt.size > 2000 else srt[int(0.3 * srt.size):int(0.9 * srt.size)]
+    gaps = cand[1:] / cand[:-1]
+    k = int(np.argmax(gaps))
+    assert gaps[k] > 1.005
+    eps = float(np.sqrt(cand[k] * cand[k + 1]))
+    ref, valid, p = O.run_workload_filtered(w, eps)
+    out = _run(w, algo=P.CCE_ALGO_TILE, filter_eps=eps)
+    assert np.all(out["dH"][w.mask == 0] == 0)
+    e_dH, e_dE = tensor_rel(out["dH"][valid], ref.dH), tensor_rel(out["dE"], ref.dE)
+    assert e_dH <= TOL_BF16 and e_dE <= TOL_BF16, (e_dH, e_dE)
+    exact = O.run_workload(w)
+    assert tensor_rel(exact.dE, ref.dE) > 0 or tensor_rel(exact.dH[valid], ref.dH) > 0   # something was dropped
+
+
 @pytest.mark.parametrize("d,V,eps", [(64, 1500, 1e-3), (128, 700, 1e-4), (256, 900, 1e-2)])
 def test_gradient_filtering_against_the_unfiltered_definition(d, V, eps):
     """Evidence that does not lean on any block structure: only the paper's statement that values below the threshold
