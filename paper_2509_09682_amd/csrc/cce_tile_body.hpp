@@ -245,10 +245,10 @@ __device__ __forceinline__ void dh_scale_chunk(const TileArgs &a, int64_t chunk)
 // DS: wavefronts that share a group of stationary rows in the backward passes; each of them forms the full score tile
 // and keeps 1/DS of the output columns, which divides the accumulator registers by DS at the price of DS score products.
 // LDS needs of one tile-kernel configuration (the kernel wrappers declare the arrays, the body gets pointers).
-// STREAM: the unbroken pipeline of the passes with a second product (run_stream in tile_body), whose ring is one array.
+// STREAM: the unbroken pipelines (run_stream and run_stream_scores in tile_body), whose ring is one array.
 constexpr bool streams(int d, int mode, int by, int nbuf, int ds)
 {
-    return d <= 128 && by % 64 == 0 && mode != MODE_FWD && nbuf == 4 && ds == 1;
+    return d <= 128 && by % 64 == 0 && (nbuf == 4 || (mode == MODE_FWD && nbuf == 3)) && ds == 1;
 }
 // The same for hidden size 256, a wavefront to a SIMD and all of its registers (run_stream_wide).
 constexpr bool streams_wide(int d, int mode, int by, int nw, int ds, bool filter)
@@ -1546,7 +1546,9 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     // softmax over 100,000 items 1.2 % are kept), so the pipeline is for those: while the matrix pipe has the scores of the
     // next sub-tile, the vector units look for this one's largest probability; a kept one is finished on the spot.  The dH side
     // needs no probabilities for the verdict, only the largest score, as a position's offset is one to a lane.
-    auto run_stream_filter = [&]() {
+    // Forward pass: the same with the sum of exponentials in the place of the verdict, against a reference per position as in FDH.
+    auto run_stream_scores = [&]() -> bool {
+        float part[XG][4];
         f32x16 sv[2][XG];
         uint4 op[KK];
         float4 cy[4];  // DE: exponent offsets of the streamed rows
@@ -1591,7 +1593,10 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 const int g = i / PER_G;
 #pragma unroll
                 for (int q = (i % PER_G) * QPS; q < (i % PER_G + 1) * QPS; q += 2) {
-                    if (MODE == MODE_DH) {
+                    if (MODE == MODE_FWD) {
+                        part[g][q % 4] += __builtin_amdgcn_exp2f(fmaf(sv[c][g][q], kLog2e, -run_m[g]));
+                        part[g][q % 4 + 1] += __builtin_amdgcn_exp2f(fmaf(sv[c][g][q + 1], kLog2e, -run_m[g]));
+                    } else if (MODE == MODE_DH) {
                         big[g] = q == 0 ? max3_after(first[g], sv[c][g][0], sv[c][g][1], sv[c][g][1]) : max3(big[g], sv[c][g][q], sv[c][g][q + 1]);
                     } else {
                         const float4 o = cy[q / 4];
@@ -1611,6 +1616,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
+            if (MODE == MODE_FWD) return;
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
                 if (MODE == MODE_DH) big[g] = fmaf(big[g], kLog2e, cx[g]);
@@ -1642,9 +1648,21 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                     }
             }
         };
+        if (MODE == MODE_FWD && tid == 0) over_flag[0] = 0;  // visible behind the barrier that follows the first loads
         start_loads();
         wait_vm<(PF - 1) * GROUP>();
         barrier_keep_loads();
+        if (MODE == MODE_FWD && t_begin < t_end) {  // reference: the largest score among the first 32 candidates
+            const int64_t left = n_y - t_begin * BY;
+            float tmax[XG];
+            tile_max(buf0, 1, left < BY ? (int)left : BY, tmax);
+#pragma unroll
+            for (int g = 0; g < XG; ++g) {
+                run_m[g] = tmax[g];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) part[g][q] = 0.f;
+            }
+        }
         if (t_begin < t_stop) {
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) op[kk] = load_op(buf0, 0, kk);
@@ -1667,8 +1685,8 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
 #pragma unroll
                 for (int k = 0; k < NSB; ++k) {
                     const uint16_t *const n1 = k + 1 < NSB ? cur : next, *const n2 = k + 2 < NSB ? cur : next;
-                    if (k == NSB - 2) {  // ahead of the first read of tile t + 1: it has landed (all but t + 2)
-                        wait_vm<GROUP>();
+                    if (k == NSB - 2) {  // ahead of the first read of tile t + 1: it has landed
+                        wait_vm<(PF - 2) * GROUP>();
                         asm volatile("s_barrier" ::: "memory");
                     }
                     if (k % 2 == 0 && k == NSB - 2) phase(cur, k, n1, (k + 1) % NSB, n2, (k + 2) % NSB, no, yes, t, at_u);
@@ -1679,9 +1697,15 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 ++t;
             } while (t < t_stop);
         }
+        if (MODE == MODE_FWD && t_begin < t_stop) {
+#pragma unroll
+            for (int g = 0; g < XG; ++g) run_s[g] = (part[g][0] + part[g][1]) + (part[g][2] + part[g][3]);
+            note_overflow(0);  // ahead of the short tile, which may raise the reference
+        }
         if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{}, Exact{});
         wait_vm<0>();     // the loads beyond the range
-        __syncthreads();  // the tile buffers are free
+        __syncthreads();  // the tile buffers are free, the flag is in place
+        return MODE == MODE_FWD && __builtin_amdgcn_readfirstlane(over_flag[0]) != 0;
     };
     // ---- Hidden size 256.  Accumulators and stationary rows of 32 positions take 192 registers, and with two wavefronts to a
     // SIMD every operand read from LDS served one matrix instruction: the eight wavefronts of a block met at every barrier and
@@ -1970,10 +1994,18 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     };
     bool again = false;
     if constexpr (WIDE) run_stream_wide();
-    else if constexpr (STREAM && FILTER) run_stream_filter();
+    else if constexpr (STREAM && (FILTER || MODE == MODE_FWD)) again = run_stream_scores();
     else if constexpr (STREAM) again = run_stream();
     else again = run_attempt(FastTag{});
     if (again) {
+        if constexpr (MODE == MODE_FWD) {  // start over with the maximum kept up to date tile by tile
+#pragma unroll
+            for (int g = 0; g < XG; ++g) {
+                run_m[g] = -INFINITY;
+                run_s[g] = 0.f;
+            }
+            run_attempt(FastTag{});
+        }
         if constexpr (MODE == MODE_FDH) {  // start over in the exact form
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
