@@ -239,13 +239,14 @@ __device__ __forceinline__ void dh_scale_chunk(const TileArgs &a, int64_t chunk)
 
 // D: hidden size.  BY: streamed rows per LDS tile.  NW: wavefronts per block.  XG: groups of 32 stationary rows per
 // wavefront (XG = 2 reads every streamed operand from LDS once for two matrix instructions).  MINB: blocks per
-// compute unit the register budget is sized for.  NBUF: LDS tile buffers in the ring (2..4: separate arrays, main loop
-// unrolled NBUF times, NBUF - 1 tiles in flight; 0: two buffers in one array and a single copy of the loop body).
+// compute unit the register budget is sized for.  NBUF: LDS tile buffers in the ring (2..4: NBUF - 1 tiles in flight, in
+// separate arrays with the main loop unrolled NBUF times, or one array and a rolled loop where STREAM holds; 6: NBUF - 3 in
+// flight, hidden size 256 only; 0: two buffers in one array and a single copy of the loop body).
 // FILTER: gradient filtering of the backward passes (32 x 32 blocks of the softmax matrix below a threshold are skipped).
 // DS: wavefronts that share a group of stationary rows in the backward passes; each of them forms the full score tile
 // and keeps 1/DS of the output columns, which divides the accumulator registers by DS at the price of DS score products.
 // LDS needs of one tile-kernel configuration (the kernel wrappers declare the arrays, the body gets pointers).
-// STREAM: the unbroken pipelines (run_stream and run_stream_scores in tile_body), whose ring is one array.
+// STREAM: the unbroken pipelines (run_stream, run_stream_scores, run_stream_wide in tile_body), whose ring is one array.
 constexpr bool streams(int d, int mode, int by, int nbuf, int ds)
 {
     return d <= 128 && by % 64 == 0 && (nbuf == 4 || (mode == MODE_FWD && nbuf == 3)) && ds == 1;
@@ -346,7 +347,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     constexpr bool EPI_IN_TILES = (MODE == MODE_DE) && (NW == 4) && (TILE * 2 >= 2 * 32 * 33 * 4 + XPB * 8);
     static_assert(NW % 2 == 0, "wavefronts pair up on the tile buffers");
 
-    // buf0..buf3 are separate LDS arrays of the calling kernel: the compiler then sees that operand reads of one buffer
+    // Without STREAM buf0..buf3 are separate LDS arrays of the calling kernel: the compiler then sees that operand reads of one buffer
     // cannot touch the buffers that loads are in flight into, and does not wait for them; the single-array form
     // (NBUF = 0) keeps one copy of the loop body where registers are short.
     auto buf_at = [&](int i) -> uint16_t * {
