@@ -1177,8 +1177,9 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         if constexpr (STREAM) {  // the exact form, off the common path
 #pragma unroll 1
             for (int64_t t = t_begin; t < t_stop && !overflow; ++t) {
-                const int s = (int)((t - t_begin) & 3);
-                step(t, buf_at(s), buf_at(s + 3));
+                static_assert(WIDE || PF == NB - 1, "tile t + PF goes where tile t - 1 was");
+                const int s = (int)((t - t_begin) % NB);
+                step(t, buf_at(s), buf_at(s + PF));
             }
         } else if (NBUF == 4) {
             for (int64_t t = t_begin; t < t_stop; t += 4) {

@@ -107,3 +107,36 @@ def test_blocks_of_either_width_at_d256(N, K):
         E[int(w.neg[K - 1 if i > N // 2 else K - 2])] = 90.0 * H[i] / float(H[i].astype(np.float64) @ H[i].astype(np.float64))
     w = dataclasses.replace(w, H=bf16_bits_from_f32(H.reshape(w.H.shape)), E=bf16_bits_from_f32(E.reshape(w.E.shape)), in_dtype="bf16")
     check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), TOL_BF16)
+
+
+@pytest.mark.parametrize("fuse", [False, True])
+@pytest.mark.parametrize("tiles,rest", [(3, 0), (4, 1), (5, 17), (8, 0), (11, 31)])
+@pytest.mark.parametrize("d,N,mode", [(64, 25_000, "shared"), (64, 77_000, "full"), (128, 25_000, "full"), (128, 77_000, "shared")])
+def test_blocks_that_start_over_part_way_through_a_long_range(d, N, mode, tiles, rest, fuse):
+    """Ranges of three tiles (8192 / d candidates each) and more, so that the ring of tile buffers goes round in the form a block
+    falls back to when a score outgrows the largest of its first 32 candidates by 90 nats: in the third tile, in the last full one
+    and in the last candidate.  196 blocks of 128 positions and 300 of 256 (two row groups) take the candidates in one piece; few of
+    the positions are valid, which the launcher does not look at."""
+    import dataclasses
+
+    import numpy as np
+    from hip_harness import run_hip
+    from workloads import NEG_SHARED, bf16_bits_from_f32
+
+    by = 8192 // d
+    n = tiles * by + rest
+    full = mode == "full"
+    w = make_workload(f"over_{d}_{N}_{n}_{mode}", 1, N, d, n if full else 3000, 0 if full else n, "f32", NEG_FULL if full else NEG_SHARED,
+                      N + n, g_kind="random", neg_dist="uniform" if full else "uniform_distinct", pad="bernoulli", pad_p=1 - 300 / N,
+                      e_sigma=0.05, tgt_dist="zipf")
+    H, E = w.H.reshape(w.N, d).copy(), w.E.reshape(w.V, d).copy()
+    valid = np.flatnonzero(w.mask)
+    tgt = w.tgt.copy()
+    for i, k in zip(valid[[7, 150, -3]], (2 * by + 5, (tiles - 1) * by + 40, n - 1)):
+        item = k if full else int(w.neg[k])
+        E[item] = 90.0 * H[i] / float(H[i].astype(np.float64) @ H[i].astype(np.float64))
+        # nobody's target: with p next to 1 there, p - 1 is rounding (2^-9 of p in bf16) against a row of the same size, and the bar
+        # of a row against its own largest entry says nothing
+        tgt[tgt == item] = 0
+    w = dataclasses.replace(w, tgt=tgt, H=bf16_bits_from_f32(H.reshape(w.H.shape)), E=bf16_bits_from_f32(E.reshape(w.E.shape)), in_dtype="bf16")
+    check_against_oracle(w, run_hip(w, fuse_dH=fuse, reuse_prep=True), TOL_BF16)
