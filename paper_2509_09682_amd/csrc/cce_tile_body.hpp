@@ -1898,7 +1898,9 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         // first goes over the range for the largest of all.
         auto attempt = [&](auto second_tag) __attribute__((always_inline)) -> bool {
             constexpr bool SECOND = decltype(second_tag)::value;
-            if (WATCH && tid == 0) over_flag[0] = 0;  // visible behind the barrier that follows the first loads
+            // visible behind the barrier that follows the first loads; left alone by the second attempt, which a wavefront may begin
+            // before the others have read it
+            if (WATCH && !SECOND && tid == 0) over_flag[0] = 0;
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
                 part[g][0] = part[g][1] = 0.f;

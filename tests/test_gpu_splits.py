@@ -140,3 +140,24 @@ def test_blocks_that_start_over_part_way_through_a_long_range(d, N, mode, tiles,
         tgt[tgt == item] = 0
     w = dataclasses.replace(w, tgt=tgt, H=bf16_bits_from_f32(H.reshape(w.H.shape)), E=bf16_bits_from_f32(E.reshape(w.E.shape)), in_dtype="bf16")
     check_against_oracle(w, run_hip(w, fuse_dH=fuse, reuse_prep=True), TOL_BF16)
+
+
+@pytest.mark.parametrize("N,K", [(300, 70), (20_000, 65), (70_000, 96)])
+def test_every_block_starts_over_at_d256(N, K):
+    """d = 256, blocks of 128 positions with and without shares and blocks of 256 in whole and split rounds: every position has its
+    last candidate 90 nats up, so the wavefronts of every block that sees it agree on a second attempt."""
+    import dataclasses
+
+    import numpy as np
+    from hip_harness import run_hip
+    from workloads import NEG_SHARED, bf16_bits_from_f32
+
+    w = make_workload(f"all_over_{N}_{K}", 1, N, 256, 3000, K, "f32", NEG_SHARED, N + K, g_kind="random", neg_dist="uniform_distinct",
+                      e_sigma=0.05, h_sigma=0.3, tgt_dist="zipf")
+    u = np.random.default_rng(N).standard_normal(256).astype(np.float32)
+    u /= np.linalg.norm(u)
+    H, E, tgt = w.H.reshape(w.N, 256) + 3.0 * u, w.E.reshape(w.V, 256).copy(), w.tgt.copy()
+    E[int(w.neg[-1])] = 30.0 * u
+    tgt[tgt == w.neg[-1]] = int(w.neg[0])  # p - 1 with p next to 1 is rounding: see the test above
+    w = dataclasses.replace(w, tgt=tgt, H=bf16_bits_from_f32(H.reshape(w.H.shape)), E=bf16_bits_from_f32(E.reshape(w.E.shape)), in_dtype="bf16")
+    check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), TOL_BF16)
