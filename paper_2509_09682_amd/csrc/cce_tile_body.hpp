@@ -1814,6 +1814,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 return -1;
             };
             static_assert(SLICES - FIRST - 2 >= NPAIR, "at most one pair to a slice");
+            static_assert(FIRST * 32 >= 48, "a score is looked at behind FIRST later matrix instructions of 32 cycles");
             static_for<PIECES>([&](auto piece) __attribute__((always_inline)) {
                 constexpr int i = decltype(piece)::value;
                 if constexpr (i == PIECES - R) {
@@ -1872,7 +1873,10 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             settle_scores();
         };
         auto all_second = [&](uint32_t b) {
-            asm volatile("s_nop 7" ::: "memory");  // coefficients written by vector instructions, read by a matrix instruction
+            // coefficients written by vector instructions, read by a matrix instruction: written ahead of the wait, not between
+#pragma unroll
+            for (int g = 0; g < XG; ++g) asm volatile("" : "+v"(gp[g][0]), "+v"(gp[g][1]));
+            asm volatile("s_nop 1" ::: "memory");
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
                 const u32x4 v = read_tr(i, b);
