@@ -179,7 +179,7 @@ __device__ __forceinline__ float max3_after(float after, float x, float y, float
 // Direct-to-LDS loads that the compiler does not see as such: 16 or 4 bytes a lane from src to lds + 16 (4) * lane.  Shown one, it
 // protects the next transpose read with a wait for all loads in flight.  Waits and barriers are the caller's, as everywhere here;
 // there is no result register that could be written late.  m0 is the compiler's for its own loads of this kind only, and a kernel
-// uses one sort or the other.
+// uses one sort or the other (tests/test_wait_states.py looks: m0 is reserved and cannot be named as changed).
 __device__ __forceinline__ void load_to_lds_16(const void *src, uint32_t lds)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory");

@@ -144,4 +144,7 @@ def test_wait_states_of_the_tile_kernels(tmp_path):
         for name, blocks in parse(out.read_text().splitlines()).items():
             seen += any(i[4] and i[0].startswith("v_mfma") for b in blocks for i in b[1])
             assert not faults(blocks), name
+            # m0, which inline assembly cannot name as changed (the compiler reserves it): a kernel's own or the compiler's
+            uses = {i[4] for b in blocks for i in b[1] if re.search(r"\bm0\b|_lds_", i[3])}
+            assert len(uses) <= 1, name
     assert seen >= 4  # the kernels of hidden size 256 with matrix instructions in inline assembly
