@@ -1306,6 +1306,22 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         wait_vm<(PF - 1) * GROUP>();
         barrier_keep_loads();
     };
+    // The sum of exponentials of the pipelines below: a lane's sixteen of a sub-tile in four chains, which are joined onto the running
+    // sum when the next sub-tile begins.  Chains that run on over the range are as many instructions, and the steps no faster
+    // (204,800 positions, 4096 candidates, d = 256: 1266 and 1267 us), but lose more: one candidate with 4095 others 2^-12 to 2^-14 as large, error of lse
+    // 6.2e-6 with the chains of a sub-tile, 2.5e-5 with four and 5.0e-5 with two over the range.
+    float part[XG][4];
+    auto join_sums = [&](int g) { run_s[g] += (part[g][0] + part[g][1]) + (part[g][2] + part[g][3]); };
+    auto add_to_sums = [&](int g, int q, float v0, float v1) {  // exponentials q, q + 1 of a sub-tile
+        if (q == 0) join_sums(g);
+        part[g][q % 4] = q < 4 ? v0 : part[g][q % 4] + v0;
+        part[g][q % 4 + 1] = q < 4 ? v1 : part[g][q % 4 + 1] + v1;
+    };
+    auto clear_sums = [&](int g) {
+        run_s[g] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) part[g][q] = 0.f;
+    };
     // ---- STREAM: the tiles of the range as one unbroken sequence of sub-tiles (hidden sizes up to 128, passes with a second
     // product).  A phase is one sub-tile: its softmax arithmetic runs between the matrix instructions of the second product of
     // the sub-tile before it and, behind those, of the score product of the one after it, across tile borders.  LDS operands
@@ -1321,7 +1337,6 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         gp_t gp[2];
         s16x8 tr[2][MBH];
         float4 cy[4], gy[4];   // DE: exponent offsets and upstream gradients of the streamed rows
-        float part[XG][4];     // FDH: running sums
         // FOLD (dE with two row groups, where the registers of the gradients are short and their products an eighth of the
         // vector instructions): g 2^x = +-2^(x + log2 |g|).  A wavefront folds the gradients of a tile into the offsets once,
         // in LDS of its own.  From the first tile with a negative gradient on, signs are put on the packed coefficients, two at a time.
@@ -1398,10 +1413,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             auto end_pair = [&](int p) {
                 const int g = p / 8, q = 2 * (p % 8);
                 float v0 = w[2 * p], v1 = w[2 * p + 1];
-                if (MODE == MODE_FDH) {
-                    part[g][q % 4] += v0;
-                    part[g][q % 4 + 1] += v1;
-                }
+                if (MODE == MODE_FDH) add_to_sums(g, q, v0, v1);
                 if (MODE == MODE_DE && !FOLD) {
                     v0 *= (q % 4 == 0) ? gy[q / 4].x : gy[q / 4].z;
                     v1 *= (q % 4 == 0) ? gy[q / 4].y : gy[q / 4].w;
@@ -1492,8 +1504,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 zero(sv[0][g]);
 #pragma unroll
                 for (int q = 0; q < 8; ++q) gp[1][g][q] = 0u;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) part[g][q] = 0.f;
+                clear_sums(g);
             }
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
@@ -1535,7 +1546,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             for (int i = 0; i < NM_P; ++i) mfma_second(i, gp[1]);
             if (WATCH) {
 #pragma unroll
-                for (int g = 0; g < XG; ++g) run_s[g] = (part[g][0] + part[g][1]) + (part[g][2] + part[g][3]);
+                for (int g = 0; g < XG; ++g) join_sums(g);
             }
         }
         if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{}, Exact{});
@@ -1550,7 +1561,6 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     // needs no probabilities for the verdict, only the largest score, as a position's offset is one to a lane.
     // Forward pass: the same with the sum of exponentials in the place of the verdict, against a reference per position as in FDH.
     auto run_stream_scores = [&]() -> bool {
-        float part[XG][4];
         f32x16 sv[2][XG];
         uint4 op[KK];
         float4 cy[4];  // DE: exponent offsets of the streamed rows
@@ -1596,8 +1606,8 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
 #pragma unroll
                 for (int q = (i % PER_G) * QPS; q < (i % PER_G + 1) * QPS; q += 2) {
                     if (MODE == MODE_FWD) {
-                        part[g][q % 4] += __builtin_amdgcn_exp2f(fmaf(sv[c][g][q], kLog2e, -run_m[g]));
-                        part[g][q % 4 + 1] += __builtin_amdgcn_exp2f(fmaf(sv[c][g][q + 1], kLog2e, -run_m[g]));
+                        add_to_sums(g, q, __builtin_amdgcn_exp2f(fmaf(sv[c][g][q], kLog2e, -run_m[g])),
+                                    __builtin_amdgcn_exp2f(fmaf(sv[c][g][q + 1], kLog2e, -run_m[g])));
                     } else if (MODE == MODE_DH) {
                         big[g] = q == 0 ? max3_after(first[g], sv[c][g][0], sv[c][g][1], sv[c][g][1]) : max3(big[g], sv[c][g][q], sv[c][g][q + 1]);
                     } else {
@@ -1661,8 +1671,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
                 run_m[g] = tmax[g];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) part[g][q] = 0.f;
+                clear_sums(g);
             }
         }
         if (t_begin < t_stop) {
@@ -1701,7 +1710,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         }
         if (MODE == MODE_FWD && t_begin < t_stop) {
 #pragma unroll
-            for (int g = 0; g < XG; ++g) run_s[g] = (part[g][0] + part[g][1]) + (part[g][2] + part[g][3]);
+            for (int g = 0; g < XG; ++g) join_sums(g);
             note_overflow(0);  // ahead of the short tile, which may raise the reference
         }
         if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{}, Exact{});
@@ -1729,7 +1738,6 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         u32x4 gp[XG][2], gn[XG][2];  // coefficients of the tile before, and of the tile at hand
         u32x4 ring[R];
         f32x4 cy[2], gy[2];          // DE: offsets and gradients of four streamed rows
-        float part[XG][2];           // FDH: running sums
         // buf0 is a multiple of 1024, as are the buffers: no carry into the XORs
         auto buffer = [&](int i) -> uint32_t { return lds0 + (uint32_t)(i * BUF * 2); };
         // operand i of the sequence: pieces of the score product (i < 16), then of the second product; neighbours share their XOR
@@ -1786,10 +1794,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             }
         };
         auto file = [&](int g, int q) {
-            if (MODE == MODE_FDH) {
-                part[g][0] += sv[g][q];
-                part[g][1] += sv[g][q + 1];
-            }
+            if (MODE == MODE_FDH) add_to_sums(g, q, sv[g][q], sv[g][q + 1]);
             gn[g][q / 8][(q / 2) % 4] = pack2(sv[g][q], sv[g][q + 1]);
         };
         auto take_over = [&]() {
@@ -1907,7 +1912,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             if (WATCH && !SECOND && tid == 0) over_flag[0] = 0;
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
-                part[g][0] = part[g][1] = 0.f;
+                if (MODE == MODE_FDH) clear_sums(g);
 #pragma unroll
                 for (int h = 0; h < 2; ++h) gp[g][h] = (u32x4)(0u);
                 // zero where they stay: a zero written any other way lives in vector registers first, and is copied
@@ -1976,11 +1981,10 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 take_over();
                 all_second(b);
             }
-            if (WATCH && !SECOND) {  // a sum of exponentials that was beyond the limit once stays there
-                bool over = false;
+            if (WATCH) {
 #pragma unroll
-                for (int g = 0; g < XG; ++g) over |= !(part[g][0] + part[g][1] < 1.0e30f);  // or NaN
-                if (__any(over) && lane == 0) over_flag[0] = 1;
+                for (int g = 0; g < XG; ++g) join_sums(g);
+                if (!SECOND) note_overflow(0);  // a sum of exponentials that was beyond the limit once stays there
             }
             settle();
             wait_vm<0>();     // the loads beyond the range
@@ -1997,8 +2001,6 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 attempt(std::true_type{});
             }
         }
-#pragma unroll
-        for (int g = 0; g < XG; ++g) run_s[g] = part[g][0] + part[g][1];
     };
     bool again = false;
     if constexpr (WIDE) run_stream_wide();

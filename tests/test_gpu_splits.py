@@ -161,3 +161,30 @@ def test_every_block_starts_over_at_d256(N, K):
     tgt[tgt == w.neg[-1]] = int(w.neg[0])  # p - 1 with p next to 1 is rounding: see the test above
     w = dataclasses.replace(w, tgt=tgt, H=bf16_bits_from_f32(H.reshape(w.H.shape)), E=bf16_bits_from_f32(E.reshape(w.E.shape)), in_dtype="bf16")
     check_against_oracle(w, run_hip(w, fuse_dH=True, reuse_prep=True), TOL_BF16)
+
+
+@pytest.mark.parametrize("d,N,fuse", [(64, 41_000, False), (64, 77_000, False), (64, 41_000, True), (64, 77_000, True), (128, 41_000, False),
+                                      (128, 77_000, False), (128, 41_000, True), (256, 32_700, True), (256, 41_000, True)])
+def test_sum_of_exponentials_over_a_long_range(d, N, fuse):
+    """A peaked softmax over 4096 candidates taken in one piece: the first scores 0, the others all the same, some 2^-12 of it each.
+    Every sum they are added to lies between 1 and 2, so an addition loses up to 2^-24, the same at each one where the addends
+    are equal.  A lane has 128 sub-tiles of 32 candidates to add up (16 each, joined first, which loses next to nothing); its
+    exponentials are off by 2e-6 of themselves (|o| log2 e rounded at 16, the constant, the instruction)."""
+    import numpy as np
+    from hip_harness import run_hip
+    from workloads import bf16_bits_from_f32, f32_from_bf16_bits
+
+    V = 4096
+    w = make_workload(f"long_sum_{d}_{N}", 1, N, d, V, 0, "bf16", NEG_FULL, N, pad="bernoulli", pad_p=1 - 400 / N)
+    rng = np.random.default_rng(d)
+    H, E = np.zeros((N, d), np.float32), np.zeros((V, d), np.float32)
+    H[:, 0], H[:, 1] = rng.uniform(8.5, 10, N), rng.uniform(0, 1, N)
+    E[1:, 0], E[1:, 1] = -1.0, -(2.0 ** -6)
+    w.H, w.E = bf16_bits_from_f32(H), bf16_bits_from_f32(E)
+    H = f32_from_bf16_bits(w.H).astype(np.float64)
+    out = run_hip(w, fuse_dH=fuse, reuse_prep=True)
+    valid = w.mask != 0
+    tot = 1.0 + (V - 1) * np.exp(-(H[valid, 0] + H[valid, 1] * 2.0 ** -6))
+    err = np.abs(out["lse"][valid].astype(np.float64) - np.log(tot))
+    print(f"d {d} N {N} fuse {fuse}: error {err.max():.2e}, bound {np.min(128 * 2.0 ** -24 / tot + 2e-6):.2e}")
+    assert np.all(err <= 128 * 2.0 ** -24 / tot + 2e-6)
