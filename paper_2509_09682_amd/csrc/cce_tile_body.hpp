@@ -271,7 +271,7 @@ struct TileGeom {
     static constexpr int BUF1 = (NBUF >= 2 && !STREAM) ? BUF : 8;
     static constexpr int BUF2 = (NBUF >= 3 && !STREAM) ? BUF : 8;
     static constexpr int BUF3 = (NBUF >= 4 && !STREAM) ? BUF : 8;
-    static constexpr bool FOLD = STREAM && !WIDE && MODE == MODE_DE && XG == 2;  // per wavefront: offsets of a tile, sign words of two
+    static constexpr bool FOLD = STREAM && !WIDE && MODE == MODE_DE && XG == 2 && !FILTER;  // per wavefront: offsets of a tile, sign words of two
     static_assert(!FOLD || BY == 128, "a lane folds two rows of a tile");
     static constexpr int FOLD_FLOATS = FOLD ? 2 * BY : 0;
     static constexpr int EPI_OWN = (MODE == MODE_DE && !EPI_IN_TILES) ? EPI_BYTES / 4 : (FOLD ? NW * FOLD_FLOATS : 4);  // floats
@@ -306,8 +306,10 @@ __device__ __forceinline__ TailPlan tail_plan(int64_t n_xb, int slots)
     return p;
 }
 
-template <int D, int MODE, int BY, int NW, int XG, int NBUF, int DS, bool FILTER = false>
-__device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_id, uint16_t *const buf0, uint16_t *const buf1,
+// One block.  Returns whether it has to be done over with PLAIN (dE with two row groups, see FOLD in run_stream): a call of its own, since what
+// a second form would keep in registers across the first one costs that one 1 %.
+template <int D, int MODE, int BY, int NW, int XG, int NBUF, int DS, bool FILTER = false, bool PLAIN = false>
+__device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_id, uint16_t *const buf0, uint16_t *const buf1,
                                           uint16_t *const buf2, uint16_t *const buf3, float *const epi_own)
 {
     constexpr bool BWD_MODE = (MODE != MODE_FWD);
@@ -367,13 +369,13 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
     if (MODE == MODE_DE && block_id < a.pos_blocks) {  // leading blocks: scatter of the correct items
         static_assert(NW * 64 >= kPosChunk, "the scatter role needs 256 threads");
         pos_scatter_block<D>(a, block_id, reinterpret_cast<uint64_t *>(buf0), D <= 128 ? a.pos_parts : pos_parts(a.N));
-        return;
+        return false;
     }
     if (MODE == MODE_DE && a.scale_blocks > 0 && block_id >= a.scale_block0) {  // trailing blocks: dH = grad_loss * U
 #pragma unroll
         for (int j = 0; j < kScaleChunks; ++j)
             dh_scale_chunk<D>(a, ((block_id - a.scale_block0) * kScaleChunks + j) * (NW * 64) + tid);
-        return;
+        return false;
     }
     if (MODE == MODE_DH && block_id < a.pad_blocks) {  // leading blocks: dH rows of padded positions are zero
         const int64_t i = block_id * (NW * 64) + tid;
@@ -395,7 +397,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
                 }
             }
         }
-        return;
+        return false;
     }
     const int64_t bid = block_id - (MODE == MODE_DE ? a.pos_blocks : (MODE == MODE_DH ? a.pad_blocks : 0));
     const int64_t n_pos = a.n_valid_ptr ? (int64_t)*a.n_valid_ptr : a.N;
@@ -412,11 +414,11 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             splits = tp.splits;
             part_rows = tp.tail * XPB;
             part_x0 = tp.whole * XPB;
-            if (bid >= tp.whole + tp.tail * tp.splits) return;
+            if (bid >= tp.whole + tp.tail * tp.splits) return false;
         }
     }
-    if (xb * XPB >= n_x) return;  // whole block past the end (the grid is sized for the unmasked N)
-    if (STREAM && n_y == 0) return;  // dE without a valid position
+    if (xb * XPB >= n_x) return false;  // whole block past the end (the grid is sized for the unmasked N)
+    if (STREAM && n_y == 0) return false;  // dE without a valid position
 
     const uint16_t *Xbase = (MODE == MODE_DE) ? a.E : a.H;
     const uint16_t *Ybase = (MODE == MODE_DE) ? a.H : a.E;
@@ -1306,6 +1308,32 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         wait_vm<(PF - 1) * GROUP>();
         barrier_keep_loads();
     };
+    // Off the common path: the tiles of the range one by one, with the loads of tile t + PF in one piece.
+    auto run_plain = [&](auto work) {
+        start_loads();
+        first_landed();
+#pragma unroll 1
+        for (int64_t t = t_begin; t < t_stop; ++t) {
+            const int at = (int)((t - t_begin) % NB);
+            const int32_t *list = reinterpret_cast<const int32_t *>(buf_at(at) + OFF_I);
+            const int64_t t_load = clamp(t + PF);
+            const uint32_t dst = lds_dst((at + PF) % NB);
+            int32_t ids[NR];
+#pragma unroll
+            for (int i = 0; i < LPW; ++i) ids[i] = list[my_row + (uint32_t)(i * (NW * 64 / CPR))];
+            if (GSEP) ids[LPW] = list[const_slot];
+#pragma unroll
+            for (int i = 0; i < LPW; ++i) load_rows(i, row_of(i, t_load, ids[i]), dst);
+            if (MODE == MODE_DE) load_const(t_load, GSEP ? listed_or(ids[LPW], const_at(t_load)) : 0u, dst);
+            load_numbers(clamp(t + 2 * PF), dst);
+            work(t, buf_at(at));
+            wait_vm<(PF - 1) * GROUP>();
+            barrier_keep_loads();
+        }
+        if (tail_ragged) work(t_stop, buf_at((int)((t_stop - t_begin) % NB)));
+        wait_vm<0>();     // the loads beyond the range
+        __syncthreads();  // the tile buffers are free
+    };
     // The sum of exponentials of the pipelines below: a lane's sixteen of a sub-tile in four chains, which are joined onto the running
     // sum when the next sub-tile begins.  Chains that run on over the range are as many instructions, and the steps no faster
     // (204,800 positions, 4096 candidates, d = 256: 1266 and 1267 us), but lose more: one candidate with 4095 others 2^-12 to 2^-14 as large, error of lse
@@ -1340,13 +1368,18 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         // FOLD (dE with two row groups, where the registers of the gradients are short and their products an eighth of the
         // vector instructions): g 2^x = +-2^(x + log2 |g|).  A wavefront folds the gradients of a tile into the offsets once,
         // in LDS of its own.  From the first tile with a negative gradient on, signs are put on the packed coefficients, two at a time.
+        // An exponential ends at 2^-126, the product of gradient and probability at the 2^-133 of a bf16 coefficient: a range with a
+        // gradient below 2^-80, where probabilities of 2^-46 and above would be lost, is repeated by run_plain, which multiplies.
         constexpr bool FOLD = G::FOLD;
+        uint32_t smallest = 0u;  // bits of log2 |g|, for negative ones the larger the smaller; those of -inf for 0 and what the logarithm takes for 0
         bool negative = false;  // wave-uniform, and the same in every wavefront of the block
         float *const folded = epi_own + wave * G::FOLD_FLOATS;
         auto fold_tile = [&](const uint16_t *tile, int parity) {  // the signs of two tiles: those of one are read while the next one is folded
             const float2 c = reinterpret_cast<const float2 *>(tile + OFF_C)[lane];  // rows 2 lane, 2 lane + 1
             const float2 g = reinterpret_cast<const float2 *>(tile + OFF_C)[BY / 2 + lane];
-            reinterpret_cast<float2 *>(folded)[lane] = make_float2(c.x + __builtin_amdgcn_logf(fabsf(g.x)), c.y + __builtin_amdgcn_logf(fabsf(g.y)));
+            const float lx = __builtin_amdgcn_logf(fabsf(g.x)), ly = __builtin_amdgcn_logf(fabsf(g.y));
+            reinterpret_cast<float2 *>(folded)[lane] = make_float2(c.x + lx, c.y + ly);
+            smallest = max(smallest, max(__float_as_uint(lx), __float_as_uint(ly)));
             // in the order a lane of the streaming loop wants them: sub-tile, half, eight words
             const int at = (lane >> 4) * 16 + ((lane >> 1) & 1) * 8 + ((lane >> 2) & 3) * 2 + (lane & 1);
             const uint32_t signs = (__float_as_uint(g.x) >> 31 << 15) | (__float_as_uint(g.y) & 0x80000000u);
@@ -1553,6 +1586,22 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         if (WATCH) note_overflow(0);  // a sum that was beyond the limit once stays there
         wait_vm<0>();     // the loads beyond the range
         __syncthreads();  // the tile buffers are free, the flag is in place
+        if constexpr (FOLD) {
+            if (!__any(smallest > 0xc2a00000u)) return false;  // -80; all wavefronts alike
+            int *const flag = reinterpret_cast<int *>(epi_own);
+            if (tid == 0) flag[0] = 0;
+            __syncthreads();
+            const int64_t y_end = t_end * BY < n_y ? t_end * BY : n_y;
+            bool tiny = false;
+            for (int64_t y = t_begin * BY + tid; y < y_end; y += NW * 64) {
+                const bool direct = GSEP && a.g_separate && !a.g_stream_off;
+                const float g = fabsf(direct ? a.g[ind ? (int64_t)ind[y] : y] : __uint_as_float(a.de_const[a.N + y]));
+                tiny |= g != 0.f && g < 0x1p-80f;
+            }
+            if (__any(tiny) && lane == 0) flag[0] = 1;
+            __syncthreads();
+            return __builtin_amdgcn_readfirstlane(flag[0]) != 0;
+        }
         return WATCH && __builtin_amdgcn_readfirstlane(over_flag[0]) != 0;
     };
     // ---- Gradient filtering up to d = 128, same ring and loads.  Late in training nearly every block is dropped (on a peaked
@@ -2003,11 +2052,29 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
         }
     };
     bool again = false;
-    if constexpr (WIDE) run_stream_wide();
+    if constexpr (PLAIN) {
+        run_plain([&](int64_t t, const uint16_t *tile) {
+            const int rows_here = (n_y - t * BY < BY) ? (int)(n_y - t * BY) : BY;
+#pragma unroll 1
+            for (int sb = 0; sb < NSB; ++sb) {
+                uint4 op[KK];
+                f32x16 sv[XG];
+                gp_t gp;
+                s16x8 tr[2][MBH];
+                bool kept;
+                load_ops(tile, sb, op);
+                mfma_scores(op, sv);
+                softmax(tile, sb, sv, gp, rows_here, Ragged{}, kept, Exact{});
+                load_tr(tile, sb, tr);
+                second(tr, gp);
+            }
+        });
+    } else if constexpr (WIDE) run_stream_wide();
     else if constexpr (STREAM && (FILTER || MODE == MODE_FWD)) again = run_stream_scores();
     else if constexpr (STREAM) again = run_stream();
     else again = run_attempt(FastTag{});
     if (again) {
+        if constexpr (MODE == MODE_DE) return true;
         if constexpr (MODE == MODE_FWD) {  // start over with the maximum kept up to date tile by tile
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
@@ -2205,6 +2272,7 @@ __device__ __forceinline__ void tile_body(const TileArgs a, const int64_t block_
             }
         }
     }
+    return false;
 }
 
 template <int D, int MODE, int BY, int NW, int XG, int MINB, int NBUF, int DS, bool FILTER>
@@ -2216,7 +2284,10 @@ __global__ __launch_bounds__(NW * 64, MINB) void tile_kernel(TileArgs a)
     __shared__ __attribute__((aligned(1024))) uint16_t buf2[G::BUF2];
     __shared__ __attribute__((aligned(1024))) uint16_t buf3[G::BUF3];
     __shared__ __attribute__((aligned(16))) float epi_own[G::EPI_OWN];
-    tile_body<D, MODE, BY, NW, XG, NBUF, DS, FILTER>(a, (int64_t)blockIdx.x, buf0, buf1, buf2, buf3, epi_own);
+    const bool over = tile_body<D, MODE, BY, NW, XG, NBUF, DS, FILTER>(a, (int64_t)blockIdx.x, buf0, buf1, buf2, buf3, epi_own);
+    if constexpr (G::FOLD) {
+        if (over) tile_body<D, MODE, BY, NW, XG, NBUF, DS, FILTER, true>(a, (int64_t)blockIdx.x, buf0, buf1, buf2, buf3, epi_own);
+    }
 }
 
 // The dH and the dE pass of one backward call in a single launch: with few positions neither pass fills the chip on
@@ -2239,10 +2310,14 @@ __global__ __launch_bounds__(256, 2) void tile_bwd_kernel(TileArgs a_dh, TileArg
     // grid order: the dE role (correct-item scatter, then its tiles) ahead of the dH role (zeroing of padded rows, then
     // its tiles); measured faster on c2 than tiles first
     const int64_t b = (int64_t)blockIdx.x;
-    if (b < de_blocks)
-        tile_body<D, MODE_DE, BY, 4, XG_DE, NBUF, 1, FILTER>(a_de, b, buf0, buf1, buf2, buf3, epi_own);
-    else
+    if (b < de_blocks) {
+        const bool over = tile_body<D, MODE_DE, BY, 4, XG_DE, NBUF, 1, FILTER>(a_de, b, buf0, buf1, buf2, buf3, epi_own);
+        if constexpr (GE::FOLD) {
+            if (over) tile_body<D, MODE_DE, BY, 4, XG_DE, NBUF, 1, FILTER, true>(a_de, b, buf0, buf1, buf2, buf3, epi_own);
+        }
+    } else {
         tile_body<D, MODE_DH, BY, 4, XG_DH, NBUF, 1, FILTER>(a_dh, b - de_blocks, buf0, buf1, buf2, buf3, epi_own);
+    }
 }
 
 // Per valid position, ahead of a fused backward launch that does not reuse the forward call's constants: the coefficient of the correct item g (w p+ - 1) for the

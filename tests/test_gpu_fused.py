@@ -273,3 +273,47 @@ def test_signs_and_zeros_of_the_upstream_gradient(first_negative):
         w.g[first_negative::3] *= -1
     # rows of dE are sums over positions whose gradients span 2^40: the largest ones decide, as in any sum of few terms
     check_against_oracle(w, _run(w), TOL_BF16, row_tol=TOL_BF16)
+
+
+@pytest.mark.parametrize("where", ["everywhere", "late", "short_last_tile"])
+@pytest.mark.parametrize("shift", [-110, -90, 100])
+def test_upstream_gradients_near_the_ends_of_the_float_range(shift, where):
+    """As above, gradients of 2^-110: times a probability of 2^-17 a bf16 coefficient still holds them, an exponential of the folded
+    offset does not.  In all positions (some negative), from a late tile on, or in the short last tile alone (15 full ones before it);
+    2^-90 and 2^100 the folded form takes or has to hand over without loss.  dE of items that are nobody's target, to the bf16
+    rounding of the coefficients (2^-9; of one below 2^-126 fewer bits are left, 2^-7 of 2^-127 at most)."""
+    from hip_harness import run_hip
+    import paper_2509_09682_amd as P
+
+    w = make_workload("ends", 1957, 1, 64, 77_003, 0, "bf16", NEG_FULL, 77, g_kind="random", e_sigma=0.1, tgt_dist="zipf")
+    at = {"everywhere": 0, "late": 1700, "short_last_tile": 1920}[where]
+    w.g[:] = np.abs(w.g) * np.float32(2.0) ** shift
+    w.g[:at] = 0
+    if where == "everywhere":
+        w.g[40::5] *= -1
+    ref = O.run_workload(w, g=w.g.astype(np.float64))
+    rows = np.setdiff1d(np.arange(w.V), np.unique(w.tgt))
+    for out in (_run(w), run_hip(w, algo=P.CCE_ALGO_TILE)):
+        err = np.linalg.norm(out["dE"][rows] - ref.dE[rows]) / np.linalg.norm(ref.dE[rows])
+        print(f"2^{shift} {where}: dE {err:.2e}")
+        assert err <= (2.0 ** -7 if shift < -100 else 2.0 ** -9)
+
+
+@pytest.mark.parametrize("at,value", [(3, np.nan), (1900, np.inf), (700, -np.inf), (1950, np.nan)])
+def test_upstream_gradients_that_are_no_numbers(at, value):
+    """As above, one gradient that is infinite or NaN, in a full tile or the short last one: every row of dE has a term of it, of
+    the sign of the hidden state where it is infinite, and no row of dH but its own."""
+    from hip_harness import run_hip
+    from workloads import f32_from_bf16_bits
+    import paper_2509_09682_amd as P
+
+    w = make_workload("no_numbers", 1957, 1, 64, 77_003, 0, "bf16", NEG_FULL, 77, g_kind="random", e_sigma=0.1, tgt_dist="zipf")
+    w.g[:] = np.abs(w.g)
+    ref = O.run_workload(w, g=w.g.astype(np.float64))
+    w.g[at] = value
+    others = np.setdiff1d(np.arange(w.N), [at])
+    rows = np.setdiff1d(np.arange(w.V), w.tgt[at])
+    want = value * np.sign(f32_from_bf16_bits(w.H).reshape(w.N, 64)[at])
+    for out in (_run(w), run_hip(w, algo=P.CCE_ALGO_TILE)):
+        assert np.array_equal(out["dE"][rows], np.broadcast_to(want, (rows.size, 64)).astype(np.float32), equal_nan=True)
+        assert not np.isfinite(out["dH"][at]).any() and tensor_rel(out["dH"][others], ref.dH[others]) <= TOL_BF16
