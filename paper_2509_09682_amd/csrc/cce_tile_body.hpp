@@ -1047,27 +1047,30 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     // value), and the block starts over in the exact form: the largest score of every tile is taken first (a score
     // product of its own), sums and accumulators are rescaled when it grows, and no exponent is ever positive.
     int *const over_flag = reinterpret_cast<int *>(epi_own);
+    auto scores_of = [&](const uint16_t *tile, int sb, f32x16 (&sv)[XG]) {
+#pragma unroll
+        for (int g = 0; g < XG; ++g)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) sv[g][q] = 0.f;
+        const uint16_t *arow = tile + sb * 32 * D;
+#pragma unroll
+        for (int kk = 0; kk < KK; kk += 2) {  // two operands at a time: registers are short at large hidden sizes
+            const uint4 o0 = *reinterpret_cast<const uint4 *>(lds_at(arow, a_base, ((kk * 2) & SM) * 8, (kk / NA) * (NA * 16)));
+            const uint4 o1 = *reinterpret_cast<const uint4 *>(lds_at(arow, a_base, (((kk + 1) * 2) & SM) * 8, ((kk + 1) / NA) * (NA * 16)));
+#pragma unroll
+            for (int g = 0; g < XG; ++g) {
+                sv[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(o0), as_bf16x8(xr[g][kk]), sv[g], 0, 0, 0);
+                sv[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(o1), as_bf16x8(xr[g][kk + 1]), sv[g], 0, 0, 0);
+            }
+        }
+    };
     auto tile_max = [&](const uint16_t *tile, int nsub, int rows_here, float (&tmax)[XG]) {
 #pragma unroll
         for (int g = 0; g < XG; ++g) tmax[g] = -INFINITY;
 #pragma unroll 1
         for (int sb = 0; sb < nsub; ++sb) {
             f32x16 sv[XG];
-#pragma unroll
-            for (int g = 0; g < XG; ++g)
-#pragma unroll
-                for (int q = 0; q < 16; ++q) sv[g][q] = 0.f;
-            const uint16_t *arow = tile + sb * 32 * D;
-#pragma unroll
-            for (int kk = 0; kk < KK; kk += 2) {  // two operands at a time: registers are short at large hidden sizes
-                const uint4 o0 = *reinterpret_cast<const uint4 *>(lds_at(arow, a_base, ((kk * 2) & SM) * 8, (kk / NA) * (NA * 16)));
-                const uint4 o1 = *reinterpret_cast<const uint4 *>(lds_at(arow, a_base, (((kk + 1) * 2) & SM) * 8, ((kk + 1) / NA) * (NA * 16)));
-#pragma unroll
-                for (int g = 0; g < XG; ++g) {
-                    sv[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(o0), as_bf16x8(xr[g][kk]), sv[g], 0, 0, 0);
-                    sv[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(o1), as_bf16x8(xr[g][kk + 1]), sv[g], 0, 0, 0);
-                }
-            }
+            scores_of(tile, sb, sv);
             const int rem = rows_here - sb * 32 - hi * 4;
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
@@ -1335,15 +1338,16 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         __syncthreads();  // the tile buffers are free
     };
     // The sum of exponentials of the pipelines below: a lane's sixteen of a sub-tile in four chains, which are joined onto the running
-    // sum when the next sub-tile begins.  Chains that run on over the range are as many instructions, and the steps no faster
+    // sum when the next sub-tile begins (forward pass alone, which looks at the sum behind every tile: at once).  Chains that run on over the range are as many instructions, and the steps no faster
     // (204,800 positions, 4096 candidates, d = 256: 1266 and 1267 us), but lose more: one candidate with 4095 others 2^-12 to 2^-14 as large, error of lse
     // 6.2e-6 with the chains of a sub-tile, 2.5e-5 with four and 5.0e-5 with two over the range.
     float part[XG][4];
     auto join_sums = [&](int g) { run_s[g] += (part[g][0] + part[g][1]) + (part[g][2] + part[g][3]); };
     auto add_to_sums = [&](int g, int q, float v0, float v1) {  // exponentials q, q + 1 of a sub-tile
-        if (q == 0) join_sums(g);
+        if (MODE != MODE_FWD && q == 0) join_sums(g);
         part[g][q % 4] = q < 4 ? v0 : part[g][q % 4] + v0;
         part[g][q % 4 + 1] = q < 4 ? v1 : part[g][q % 4 + 1] + v1;
+        if (MODE == MODE_FWD && q == 14) join_sums(g);
     };
     auto clear_sums = [&](int g) {
         run_s[g] = 0.f;
@@ -1608,8 +1612,11 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     // softmax over 100,000 items 1.2 % are kept), so the pipeline is for those: while the matrix pipe has the scores of the
     // next sub-tile, the vector units look for this one's largest probability; a kept one is finished on the spot.  The dH side
     // needs no probabilities for the verdict, only the largest score, as a position's offset is one to a lane.
-    // Forward pass: the same with the sum of exponentials in the place of the verdict, against a reference per position as in FDH.
-    auto run_stream_scores = [&]() -> bool {
+    // Forward pass: the same with the sum of exponentials in the place of the verdict, against a reference per position as in FDH.  A
+    // tile behind which a sum is beyond 1e30 (its buffer is not loaded into before every wavefront has begun the next one) is taken
+    // again with the maximum kept up to date, by the wavefronts that see it: 51,200 positions, 1024 candidates, a late score 90
+    // nats up in every position, us, block started over / tile taken again: d = 64 32.3 / 19.5, d = 128 46.9 / 25.7.
+    auto run_stream_scores = [&]() {
         f32x16 sv[2][XG];
         uint4 op[KK];
         float4 cy[4];  // DE: exponent offsets of the streamed rows
@@ -1709,7 +1716,6 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                     }
             }
         };
-        if (MODE == MODE_FWD && tid == 0) over_flag[0] = 0;  // visible behind the barrier that follows the first loads
         start_loads();
         wait_vm<(PF - 1) * GROUP>();
         barrier_keep_loads();
@@ -1720,7 +1726,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
                 run_m[g] = tmax[g];
-                clear_sums(g);
+                run_s[g] = 0.f;
             }
         }
         if (t_begin < t_stop) {
@@ -1742,6 +1748,9 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 const uint16_t *const cur = buf_at(at_u), *const next = buf_at((at_u + 1) % NB);
                 constexpr std::false_type no{};
                 constexpr std::true_type yes{};
+                float s0[XG];
+#pragma unroll
+                for (int g = 0; g < XG; ++g) s0[g] = run_s[g];
 #pragma unroll
                 for (int k = 0; k < NSB; ++k) {
                     const uint16_t *const n1 = k + 1 < NSB ? cur : next, *const n2 = k + 2 < NSB ? cur : next;
@@ -1753,19 +1762,30 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                     else if (k % 2 == 0) phase(cur, k, n1, (k + 1) % NSB, n2, (k + 2) % NSB, no, no, t, at_u);
                     else phase(cur, k, n1, (k + 1) % NSB, n2, (k + 2) % NSB, yes, no, t, at_u);
                 }
+                if (MODE == MODE_FWD) {
+                    bool over = false;
+#pragma unroll
+                    for (int g = 0; g < XG; ++g) over |= !(run_s[g] < 1.0e30f);  // or NaN
+                    if (__any(over)) {
+#pragma unroll
+                        for (int g = 0; g < XG; ++g) run_s[g] = s0[g];
+#pragma unroll 1
+                        for (int k = 0; k < NSB; ++k) {
+                            f32x16 again[XG];
+                            gp_t unused;
+                            bool kept;
+                            scores_of(cur, k, again);
+                            softmax(cur, k, again, unused, BY, Full{}, kept, Exact{});
+                        }
+                    }
+                }
                 at = (at + 1) % NB;
                 ++t;
             } while (t < t_stop);
         }
-        if (MODE == MODE_FWD && t_begin < t_stop) {
-#pragma unroll
-            for (int g = 0; g < XG; ++g) join_sums(g);
-            note_overflow(0);  // ahead of the short tile, which may raise the reference
-        }
         if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{}, Exact{});
         wait_vm<0>();     // the loads beyond the range
-        __syncthreads();  // the tile buffers are free, the flag is in place
-        return MODE == MODE_FWD && __builtin_amdgcn_readfirstlane(over_flag[0]) != 0;
+        __syncthreads();  // the tile buffers are free
     };
     // ---- Hidden size 256.  Accumulators and stationary rows of 32 positions take 192 registers, and with two wavefronts to a
     // SIMD every operand read from LDS served one matrix instruction: the eight wavefronts of a block met at every barrier and
@@ -2070,19 +2090,11 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             }
         });
     } else if constexpr (WIDE) run_stream_wide();
-    else if constexpr (STREAM && (FILTER || MODE == MODE_FWD)) again = run_stream_scores();
+    else if constexpr (STREAM && (FILTER || MODE == MODE_FWD)) run_stream_scores();
     else if constexpr (STREAM) again = run_stream();
     else again = run_attempt(FastTag{});
     if (again) {
         if constexpr (MODE == MODE_DE) return true;
-        if constexpr (MODE == MODE_FWD) {  // start over with the maximum kept up to date tile by tile
-#pragma unroll
-            for (int g = 0; g < XG; ++g) {
-                run_m[g] = -INFINITY;
-                run_s[g] = 0.f;
-            }
-            run_attempt(FastTag{});
-        }
         if constexpr (MODE == MODE_FDH) {  // start over in the exact form
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
