@@ -56,14 +56,6 @@ enum { MODE_FWD = 0, MODE_DH = 1, MODE_DE = 2, MODE_FDH = 3 };
 // Compile-time tags: a full streamed tile, or the short last tile whose missing rows are masked.
 struct Full { static constexpr bool value = false; };
 struct Ragged { static constexpr bool value = true; };
-// Forward softmax of a tile: with the running maximum kept up to date (Exact), or against the maximum as it stood when
-// the tile began (Lazy: no maximum, no rescaling; the caller repeats the tile exactly if a sum overflowed).
-struct Exact { static constexpr bool lazy = false; };
-struct Lazy { static constexpr bool lazy = true; };
-// The two forms of an attempt at a block's streamed range in the fused forward + dH pass (see the FDH notes in tile_body).
-struct FastTag { static constexpr bool exact = false; };
-struct ExactTag { static constexpr bool exact = true; };
-
 __device__ __forceinline__ uint32_t pack2(float lo, float hi)
 {
     f32x2 v = {lo, hi};
@@ -239,38 +231,35 @@ __device__ __forceinline__ void dh_scale_chunk(const TileArgs &a, int64_t chunk)
 
 // D: hidden size.  BY: streamed rows per LDS tile.  NW: wavefronts per block.  XG: groups of 32 stationary rows per
 // wavefront (XG = 2 reads every streamed operand from LDS once for two matrix instructions).  MINB: blocks per
-// compute unit the register budget is sized for.  NBUF: LDS tile buffers in the ring (2..4: NBUF - 1 tiles in flight, in
+// compute unit the register budget is sized for.  NBUF: LDS tile buffers in the ring (2 or 3: NBUF - 1 tiles in flight, in
 // separate arrays with the main loop unrolled NBUF times, or one array and a rolled loop where STREAM holds; 6: NBUF - 3 in
-// flight, hidden size 256 only; 0: two buffers in one array and a single copy of the loop body).
+// flight, hidden size 256 only).
 // FILTER: gradient filtering of the backward passes (32 x 32 blocks of the softmax matrix below a threshold are skipped).
-// DS: wavefronts that share a group of stationary rows in the backward passes; each of them forms the full score tile
-// and keeps 1/DS of the output columns, which divides the accumulator registers by DS at the price of DS score products.
 // LDS needs of one tile-kernel configuration (the kernel wrappers declare the arrays, the body gets pointers).
 // STREAM: the unbroken pipelines (run_stream, run_stream_scores, run_stream_wide in tile_body), whose ring is one array.
-constexpr bool streams(int d, int mode, int by, int nbuf, int ds)
+constexpr bool streams(int d, int by)
 {
-    return d <= 128 && by % 64 == 0 && (nbuf == 4 || (mode == MODE_FWD && nbuf == 3)) && ds == 1;
+    return d <= 128 && by % 64 == 0;
 }
 // The same for hidden size 256, a wavefront to a SIMD and all of its registers (run_stream_wide).
-constexpr bool streams_wide(int d, int mode, int by, int nw, int ds, bool filter)
+constexpr bool streams_wide(int d, int mode, int by, int nw, bool filter)
 {
-    return d == 256 && by == 32 && nw == 4 && mode != MODE_FWD && ds == 1 && !filter;
+    return d == 256 && by == 32 && nw == 4 && mode != MODE_FWD && !filter;
 }
-template <int D, int MODE, int BY, int NW, int XG, int NBUF, int DS, bool FILTER>
+template <int D, int MODE, int BY, int NW, int XG, int NBUF, bool FILTER>
 struct TileGeom {
-    static constexpr bool WIDE = streams_wide(D, MODE, BY, NW, DS, FILTER);
-    static constexpr bool STREAM = streams(D, MODE, BY, NBUF, DS) || WIDE;
+    static constexpr bool WIDE = streams_wide(D, MODE, BY, NW, FILTER);
+    static constexpr bool STREAM = streams(D, BY) || WIDE;
     static constexpr int TILE = BY * D;
     static constexpr int IDS = (BY < 64) ? 64 : BY;
     static constexpr int CONSTS = (MODE == MODE_DE) ? 2 * BY : 0;
     static constexpr int BUF = ((TILE + 2 * CONSTS + 2 * IDS + 511) / 512) * 512;  // 16-bit elements per buffer
-    static constexpr int XPB = (NW / DS) * XG * 32;
+    static constexpr int XPB = NW * XG * 32;
     static constexpr int EPI_BYTES = NW * 32 * 33 * 4 + XPB * 8;
     static constexpr bool EPI_IN_TILES = (MODE == MODE_DE) && (NW == 4) && (TILE * 2 >= 2 * 32 * 33 * 4 + XPB * 8);
-    static constexpr int BUF0 = (NBUF == 0) ? 2 * BUF : (STREAM ? NBUF * BUF : BUF);
-    static constexpr int BUF1 = (NBUF >= 2 && !STREAM) ? BUF : 8;
+    static constexpr int BUF0 = STREAM ? NBUF * BUF : BUF;
+    static constexpr int BUF1 = STREAM ? 8 : BUF;
     static constexpr int BUF2 = (NBUF >= 3 && !STREAM) ? BUF : 8;
-    static constexpr int BUF3 = (NBUF >= 4 && !STREAM) ? BUF : 8;
     static constexpr bool FOLD = STREAM && !WIDE && MODE == MODE_DE && XG == 2 && !FILTER;  // per wavefront: offsets of a tile, sign words of two
     static_assert(!FOLD || BY == 128, "a lane folds two rows of a tile");
     static constexpr int FOLD_FLOATS = FOLD ? 2 * BY : 0;
@@ -308,15 +297,15 @@ __device__ __forceinline__ TailPlan tail_plan(int64_t n_xb, int slots)
 
 // One block.  Returns whether it has to be done over with PLAIN (dE with two row groups, see FOLD in run_stream): a call of its own, since what
 // a second form would keep in registers across the first one costs that one 1 %.
-template <int D, int MODE, int BY, int NW, int XG, int NBUF, int DS, bool FILTER = false, bool PLAIN = false>
+template <int D, int MODE, int BY, int NW, int XG, int NBUF, bool FILTER = false, bool PLAIN = false>
 __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_id, uint16_t *const buf0, uint16_t *const buf1,
-                                          uint16_t *const buf2, uint16_t *const buf3, float *const epi_own)
+                                          uint16_t *const buf2, float *const epi_own)
 {
     constexpr bool BWD_MODE = (MODE != MODE_FWD);
     // The pipelined sub-tile loop alternates between two register sets; above d = 128 only the forward pass with one
     // group of stationary rows has the registers for it (the operands of a whole sub-tile are d/4 registers).
     constexpr bool SWP = (BY % 64 == 0) && (D <= 128 || (MODE == MODE_FWD && XG == 1));
-    typedef TileGeom<D, MODE, BY, NW, XG, NBUF, DS, FILTER> G;
+    typedef TileGeom<D, MODE, BY, NW, XG, NBUF, FILTER> G;
     constexpr bool STREAM = G::STREAM, WIDE = G::WIDE;
     constexpr int KK = D / 16;             // k-steps of the score product
     constexpr int MB = D / 32;             // 32-row output blocks of the second product
@@ -324,16 +313,14 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     constexpr int SM = (CPR == 8) ? 7 : 15;  // chunk-index bits that the LDS swizzle permutes
     constexpr int NA = (KK < (SM + 1) / 2) ? KK : (SM + 1) / 2;  // distinct swizzled offsets of the operand reads
     constexpr int NT = (MB < (SM + 1) / 4) ? MB : (SM + 1) / 4;  // ... and of the transpose reads
-    constexpr int XPB = (NW / DS) * XG * 32;  // stationary rows per block
-    constexpr int MBH = MB / DS;           // output blocks of the second product that this wavefront accumulates
-    static_assert(DS == 1 || (MODE != MODE_FWD && DS == 2 && NW % 2 == 0 && MBH % 4 == 0), "column split: backward passes, two ways, whole swizzle periods");
+    constexpr int XPB = NW * XG * 32;      // stationary rows per block
     constexpr int TILE = BY * D;           // elements per LDS tile
     constexpr int LOADS = BY * CPR / 64;   // 1-KiB direct-to-LDS load instructions per tile
     static_assert(LOADS % NW == 0, "tile loads must split evenly over the wavefronts");
     constexpr int LPW = LOADS / NW;
-    static_assert(NBUF == 0 || (NBUF >= 2 && NBUF <= 4) || (WIDE && NBUF > 4), "ring of 2 to 4 buffers, or 0 for the rolled form");
-    constexpr int PF = (NBUF == 0) ? 1 : (WIDE ? NBUF - 3 : NBUF - 1);  // prefetch distance in tiles
-    constexpr int NB = (NBUF == 0) ? 2 : NBUF;
+    static_assert(NBUF == 2 || NBUF == 3 || STREAM, "separate buffers: two or three");
+    constexpr int PF = WIDE ? NBUF - 3 : NBUF - 1;  // prefetch distance in tiles
+    constexpr int NB = NBUF;
     // A buffer holds the rows of a tile, (dE) the 2 x BY coefficient constants of its rows, and the row numbers of the
     // tile PF places further on, which ride along so that no load in the main loop returns into registers: the
     // outstanding-load count of a wavefront is then made of whole groups of known size.
@@ -349,13 +336,11 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     constexpr bool EPI_IN_TILES = (MODE == MODE_DE) && (NW == 4) && (TILE * 2 >= 2 * 32 * 33 * 4 + XPB * 8);
     static_assert(NW % 2 == 0, "wavefronts pair up on the tile buffers");
 
-    // Without STREAM buf0..buf3 are separate LDS arrays of the calling kernel: the compiler then sees that operand reads of one buffer
-    // cannot touch the buffers that loads are in flight into, and does not wait for them; the single-array form
-    // (NBUF = 0) keeps one copy of the loop body where registers are short.
+    // Without STREAM buf0..buf2 are separate LDS arrays of the calling kernel: the compiler then sees that operand reads of one buffer
+    // cannot touch the buffers that loads are in flight into, and does not wait for them.
     auto buf_at = [&](int i) -> uint16_t * {
-        if (NBUF == 0) return buf0 + (i & 1) * BUF;
         if (STREAM) return buf0 + (i % NB) * BUF;
-        return i == 0 ? buf0 : (i == 1 ? buf1 : (i == 2 ? buf2 : buf3));
+        return i == 0 ? buf0 : (i == 1 ? buf1 : buf2);
     };
 
     const int tid = threadIdx.x;
@@ -363,8 +348,6 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     const int wave = tid >> 6;
     const int lo = lane & 31;
     const int hi = lane >> 5;
-    const int xgrp = wave / DS;   // group(s) of stationary rows of this wavefront
-    const int half = wave % DS;   // its share of the output columns
 
     if (MODE == MODE_DE && block_id < a.pos_blocks) {  // leading blocks: scatter of the correct items
         static_assert(NW * 64 >= kPosChunk, "the scatter role needs 256 threads");
@@ -430,7 +413,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     float cx[XG];  // DH: -lse * log2(e) of the lane's position
 #pragma unroll
     for (int g = 0; g < XG; ++g) {
-        const int64_t x = xb * XPB + (xgrp * XG + g) * 32 + lo;
+        const int64_t x = xb * XPB + (wave * XG + g) * 32 + lo;
         x_ok[g] = x < n_x;
         xrow[g] = (MODE == MODE_DE) ? item_row(a, x_ok[g] ? x : 0) : pos_row(a, x_ok[g] ? x : 0);
         const uint16_t *xp = Xbase + xrow[g] * D;
@@ -441,7 +424,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             cx[g] = -a.lse_in[xrow[g]] * kLog2e;
             // The dE pass wants g * exp(o - lse) = g * 2^(o log2e - lse log2e) for every position it streams: the
             // offset and g are filed here under the compacted index, where that pass finds them in order.
-            if (a.write_consts && split == 0 && hi == 0 && half == 0 && x_ok[g]) {
+            if (a.write_consts && split == 0 && hi == 0 && x_ok[g]) {
                 const float gg = a.g ? a.g[xrow[g]] : 1.f;
                 a.de_const[x] = __float_as_uint(cx[g]);
                 a.de_const[a.N + x] = __float_as_uint(gg);
@@ -463,12 +446,12 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     const int64_t t_begin = n_tiles * split / splits;
     const int64_t t_end = n_tiles * (split + 1) / splits;
 
-    f32x16 acc[XG][MODE == MODE_FWD ? 1 : MBH];
+    f32x16 acc[XG][MODE == MODE_FWD ? 1 : MB];
     if (MODE != MODE_FWD && !WIDE) {
 #pragma unroll
         for (int g = 0; g < XG; ++g)
 #pragma unroll
-            for (int mb = 0; mb < MBH; ++mb)
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int q = 0; q < 16; ++q) acc[g][mb][q] = 0.f;
     }
@@ -606,7 +589,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     // operand read is (kk*2) ^ hi ^ swz(row), that of a transpose read (mb*4) ^ (cb*2 + tb/2) ^ swz(row), and the
     // row part of the offset has no bits in common with the chunk part.  Where registers are short (LEAN) the XOR is
     // redone at every read instead of being kept in a register per constant.
-    constexpr bool LEAN = (D >= 256 && DS == 1 && (BWD_MODE || XG == 2)) || (D == 128 && BWD_MODE);
+    constexpr bool LEAN = (D >= 256 && (BWD_MODE || XG == 2)) || (D == 128 && BWD_MODE);
     const int a_base = lo * D + ((hi ^ swz<CPR>(lo)) * 8);  // operand reads of the score product: row lo, chunk kk*2 + hi
     const int j16 = lane & 15, ta = j16 >> 2, tb = j16 & 3, cb = (lane >> 4) & 1;
     // transpose reads of the second product: rows hi*4 + ta and 8 below (whose swizzle differs in bit 1), chunk
@@ -648,23 +631,10 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 sv[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(op[kk]), as_bf16x8(xr[g][kk]), sv[g], 0, 0, 0);
     };
     // accumulator register q of lane (lo, hi) holds streamed row y = sb*32 + (q/4)*8 + hi*4 + q%4
-    auto softmax = [&](const uint16_t *tile, int sb, f32x16 (&sv)[XG], gp_t &gp, int rows_here, auto ragged_tag, bool &kept,
-                       auto max_tag) {
+    auto softmax = [&](const uint16_t *tile, int sb, f32x16 (&sv)[XG], gp_t &gp, int rows_here, auto ragged_tag, bool &kept) {
         constexpr bool RAGGED = decltype(ragged_tag)::value;
-        constexpr bool LAZY = decltype(max_tag)::lazy;
         const int rem = rows_here - sb * 32 - hi * 4;  // register q is a real row iff (q/4)*8 + q%4 < rem
-        if (MODE == MODE_FWD && LAZY) {
-            // Any reference keeps the sum of exponentials exact as long as nothing overflows; the one in hand saves the
-            // maximum chain and the rescaling (a fifth of the vector instructions of the forward pass).
-#pragma unroll
-            for (int g = 0; g < XG; ++g) {
-                const float ref = -run_m[g];
-                float part[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int q = 0; q < 16; ++q) part[q & 3] += __builtin_amdgcn_exp2f(fmaf(sv[g][q], kLog2e, ref));
-                run_s[g] += (part[0] + part[1]) + (part[2] + part[3]);
-            }
-        } else if (MODE == MODE_FWD) {
+        if (MODE == MODE_FWD) {
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
                 if (RAGGED) {  // rows past the end do not take part
@@ -795,12 +765,12 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         }
     };
     // out^T[t, x] += sum_y Y[y, t] * G^T[y, x]; the A operand is read transposed from the row-major tile
-    auto load_tr = [&](const uint16_t *tile, int sb, s16x8 (&tr)[2][MBH]) {
+    auto load_tr = [&](const uint16_t *tile, int sb, s16x8 (&tr)[2][MB]) {
 #pragma unroll
         for (int k2 = 0; k2 < 2; ++k2) {
-            const uint16_t *tbase = tile + (sb * 32 + k2 * 16) * D + half * (MBH * 32);  // this wavefront's columns
+            const uint16_t *tbase = tile + (sb * 32 + k2 * 16) * D;
 #pragma unroll
-            for (int mb = 0; mb < MBH; ++mb) {
+            for (int mb = 0; mb < MB; ++mb) {
                 const int col = (mb / NT) * (NT * 32);
                 const s16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(lds_at(tbase, t_base0, ((mb * 4) & SM) * 8, col)));
                 const s16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(lds_at(tbase, t_base1, ((mb * 4) & SM) * 8, col)));
@@ -808,11 +778,11 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             }
         }
     };
-    auto second = [&](const s16x8 (&tr)[2][MBH], const gp_t &gp) {
+    auto second = [&](const s16x8 (&tr)[2][MB], const gp_t &gp) {
 #pragma unroll
         for (int k2 = 0; k2 < 2; ++k2)
 #pragma unroll
-            for (int mb = 0; mb < MBH; ++mb) {
+            for (int mb = 0; mb < MB; ++mb) {
                 bf16x8 av;
                 __builtin_memcpy(&av, &tr[k2][mb], 16);
 #pragma unroll
@@ -834,10 +804,10 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     // The short last tile of the streamed range takes a separate copy of the code (RAGGED), so that full tiles have
     // no branch or select in this loop.
     constexpr int NM_S = KK * XG;                 // matrix instructions of a score product
-    constexpr int NM_P = BWD ? 2 * MBH * XG : 0;  // ... of a second product
-    constexpr int N_TR = 4 * MBH;                 // transpose reads of a second product
+    constexpr int NM_P = BWD ? 2 * MB * XG : 0;  // ... of a second product
+    constexpr int N_TR = 4 * MB;                 // transpose reads of a second product
     constexpr int VALU_C = XG * (MODE == MODE_FWD ? 56 : (MODE == MODE_DH ? 42 : 58));  // vector instructions of a softmax (FDH: 58)
-    auto process_tile = [&](int64_t t, const uint16_t *tile, auto ragged_tag, auto max_tag) {
+    auto process_tile = [&](int64_t t, const uint16_t *tile, auto ragged_tag) {
         // rows of this tile that exist; only the last tile of the streamed range can be short
         const int rows_here = (n_y - t * BY < BY) ? (int)(n_y - t * BY) : BY;
         if constexpr (SWP) {
@@ -845,7 +815,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             uint4 op[2][KK];
             f32x16 sv[2][XG];
             gp_t gp[2];
-            s16x8 tr[2][MBH];
+            s16x8 tr[2][MB];
             bool kept[2] = {true, true};  // gradient filtering: whether the sub-tile of either register set survived
             // Forward: operands two sub-tiles ahead (nothing else covers their latency).  Backward: one ahead, and the
             // second product of the previous sub-tile goes to the matrix pipe before the score product that needs them.
@@ -862,7 +832,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 if (k + OPD < NSB) load_ops(tile, k + OPD, op[opl]);
                 if (BWD && k > 0 && kept[n]) second(tr, gp[n]);
                 if (k + 1 < NSB) mfma_scores(op[opn], sv[n]);
-                softmax(tile, k, sv[c], gp[c], rows_here, ragged_tag, kept[c], max_tag);
+                softmax(tile, k, sv[c], gp[c], rows_here, ragged_tag, kept[c]);
                 if (BWD && kept[c]) load_tr(tile, k, tr);
                 // ---- issue order of this phase
                 const int n_mfma = ((BWD && k > 0) ? NM_P : 0) + (k + 1 < NSB ? NM_S : 0);
@@ -894,119 +864,74 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 second(tr, gp[(NSB - 1) & 1]);
                 __builtin_amdgcn_sched_group_barrier(0x008, NM_P, 0);
             }
-        } else {
-            // Large hidden sizes, backward passes: no room for a second sub-tile in flight, the other wavefront of the
+        } else if constexpr (FILTER) {
+            // Hidden size 256 with gradient filtering: no room for a second sub-tile in flight, the other wavefront of the
             // SIMD fills the gaps.  What must not happen is one LDS read per matrix instruction with the read issued just ahead of
             // it, as the compiler orders them: LDS latency is several times the 32 cycles of a matrix instruction.
-            // Operands are therefore read in batches of four into two alternating register sets, and every batch is
-            // requested one batch of matrix instructions ahead of its use.
-            constexpr int BS = (DS == 1 && BWD) ? 2 : 4;  // operands per batch: two where all output columns are held
-            // operand batches in flight: three in the dH pass (measured 2 % faster at d = 256), two elsewhere (in the dE
-            // pass the third costs spilled registers and 7 %)
-            constexpr int RD = (DS == 1 && (MODE == MODE_DH || MODE == MODE_FDH)) ? 3 : 2;
-            constexpr int NB_S = KK / BS;         // batches of the score product
-            constexpr int NB_P = 2 * MBH / BS;    // batches of the second product
-            static_assert(KK % BS == 0 && MBH % BS == 0, "whole operand batches");
+            // Operands are therefore read in batches of two into alternating register sets, and every batch is
+            // requested ahead of the batches of matrix instructions before its own.  The two reads of a batch are the ones whose
+            // swizzled offsets agree (pieces kk and kk + NA; output blocks mb and mb + NT), so that one XOR serves both and the rest of
+            // the address is an immediate: a third of the vector instructions of a step were such XORs.
+            static_assert(FILTER && LEAN && XG == 1 && KK == 2 * NA && MB == 2 * NT, "hidden size 256");
+            // operand batches in flight: three in the dH pass (measured 2 % faster), two in the dE pass (where the third costs
+            // spilled registers and 7 %)
+            constexpr int RD = (MODE == MODE_DH) ? 3 : 2;
 #pragma unroll 1
             for (int sb = 0; sb < NSB; ++sb) {
                 f32x16 sv[XG];
                 gp_t gp;
-                uint4 ob[RD][BS];
+                uint4 ob[RD][2];
+                s16x8 tb[RD][2];
                 const uint16_t *arow = tile + sb * 32 * D;
-                // PAIRED (register-lean addressing): the two reads of a batch are the ones whose swizzled offsets agree
-                // (pieces kk and kk + NA; output blocks mb and mb + NT), so that one XOR serves both and the rest of the
-                // address is an immediate: a third of the vector instructions of a step were such XORs.
-                constexpr bool PAIRED = LEAN && BS == 2 && KK == 2 * NA && MBH == 2 * NT;
-                auto s_piece = [&](int b, int i) { return PAIRED ? b + i * NA : b * BS + i; };
-                auto p_block = [&](int b, int i) { return PAIRED ? (b % (MBH / BS)) + i * NT : (b % (MBH / BS)) * BS + i; };
-                auto read_batch = [&](int b, uint4 (&dst)[BS]) {
-                    if constexpr (PAIRED) {
-                        const uint16_t *q = lds_at(arow, a_base, ((b * 2) & SM) * 8, 0);
-                        dst[0] = *reinterpret_cast<const uint4 *>(q);
-                        dst[1] = *reinterpret_cast<const uint4 *>(q + NA * 16);
-                        return;
-                    }
+                auto read_batch = [&](int b, uint4 (&dst)[2]) {
+                    const uint16_t *q = lds_at(arow, a_base, ((b * 2) & SM) * 8, 0);
+                    dst[0] = *reinterpret_cast<const uint4 *>(q);
+                    dst[1] = *reinterpret_cast<const uint4 *>(q + NA * 16);
+                };
+                auto read_tr_batch = [&](int b, s16x8 (&dst)[2]) {
+                    const uint16_t *tbase = tile + (sb * 32 + b / NT * 16) * D;
+                    const uint16_t *q0 = lds_at(tbase, t_base0, ((b % NT * 4) & SM) * 8, 0);
+                    const uint16_t *q1 = lds_at(tbase, t_base1, ((b % NT * 4) & SM) * 8, 0);
 #pragma unroll
-                    for (int i = 0; i < BS; ++i) {
-                        const int kk = b * BS + i;
-                        dst[i] = *reinterpret_cast<const uint4 *>(lds_at(arow, a_base, ((kk * 2) & SM) * 8, (kk / NA) * (NA * 16)));
+                    for (int i = 0; i < 2; ++i) {
+                        const s16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(q0 + i * (NT * 32)));
+                        const s16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(q1 + i * (NT * 32)));
+                        dst[i] = __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7);
                     }
                 };
 #pragma unroll
-                for (int g = 0; g < XG; ++g)
+                for (int q = 0; q < 16; ++q) sv[0][q] = 0.f;
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) sv[g][q] = 0.f;
+                for (int b = 0; b < RD; ++b) read_batch(b, ob[b]);
 #pragma unroll
-                for (int b = 0; b < RD && b < NB_S; ++b) read_batch(b, ob[b]);
-#pragma unroll
-                for (int b = 0; b < NB_S; ++b) {
+                for (int b = 0; b < NA; ++b) {
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int i = 0; i < BS; ++i)
-#pragma unroll
-                        for (int g = 0; g < XG; ++g)
-                            sv[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ob[b % RD][i]), as_bf16x8(xr[g][s_piece(b, i)]), sv[g], 0, 0, 0);
+                    for (int i = 0; i < 2; ++i)
+                        sv[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ob[b % RD][i]), as_bf16x8(xr[0][b + i * NA]), sv[0], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (b + RD < NB_S) read_batch(b + RD, ob[b % RD]);
+                    if (b + RD < NA) read_batch(b + RD, ob[b % RD]);
                 }
-                if (BWD) {
-                    // transpose reads of the first two batches go out before the softmax arithmetic and land under it
-                    s16x8 tb[RD][BS];
-                    auto read_tr_batch = [&](int b, s16x8 (&dst)[BS]) {
-                        const int k2 = b / (MBH / BS);
-                        const uint16_t *tbase = tile + (sb * 32 + k2 * 16) * D + half * (MBH * 32);
-                        if constexpr (PAIRED) {
-                            const int mb0 = b % (MBH / BS);
-                            const uint16_t *q0 = lds_at(tbase, t_base0, ((mb0 * 4) & SM) * 8, 0);
-                            const uint16_t *q1 = lds_at(tbase, t_base1, ((mb0 * 4) & SM) * 8, 0);
+                bool kept = true;  // the transpose reads wait for the verdict on the block
+                softmax(tile, sb, sv, gp, rows_here, ragged_tag, kept);
+                if (!kept) continue;
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                            for (int i = 0; i < BS; ++i) {
-                                const s16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(q0 + i * (NT * 32)));
-                                const s16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(q1 + i * (NT * 32)));
-                                dst[i] = __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7);
-                            }
-                            return;
-                        }
+                for (int b = 0; b < RD; ++b) read_tr_batch(b, tb[b]);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int i = 0; i < BS; ++i) {
-                            const int mb = (b % (MBH / BS)) * BS + i;
-                            const int col = (mb / NT) * (NT * 32);
-                            const s16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(lds_at(tbase, t_base0, ((mb * 4) & SM) * 8, col)));
-                            const s16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(lds_at(tbase, t_base1, ((mb * 4) & SM) * 8, col)));
-                            dst[i] = __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7);
-                        }
-                    };
-                    bool kept = true;
-                    if (FILTER) {  // the reads wait for the verdict on the block
-                        softmax(tile, sb, sv, gp, rows_here, ragged_tag, kept, max_tag);
-                        if (!kept) continue;
+                for (int b = 0; b < 2 * NT; ++b) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    const uint4 bv = make_uint4(gp[0][b / NT * 4 + 0], gp[0][b / NT * 4 + 1], gp[0][b / NT * 4 + 2], gp[0][b / NT * 4 + 3]);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const int mb = b % NT + i * NT;
+                        bf16x8 av;
+                        __builtin_memcpy(&av, &tb[b % RD][i], 16);
+                        acc[0][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, as_bf16x8(bv), acc[0][mb], 0, 0, 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int b = 0; b < RD && b < NB_P; ++b) read_tr_batch(b, tb[b]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (!FILTER) softmax(tile, sb, sv, gp, rows_here, ragged_tag, kept, max_tag);
-#pragma unroll
-                    for (int b = 0; b < NB_P; ++b) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        const int k2 = b / (MBH / BS);
-#pragma unroll
-                        for (int i = 0; i < BS; ++i) {
-                            const int mb = p_block(b, i);
-                            bf16x8 av;
-                            __builtin_memcpy(&av, &tb[b % RD][i], 16);
-#pragma unroll
-                            for (int g = 0; g < XG; ++g) {
-                                const uint4 bv = make_uint4(gp[g][k2 * 4 + 0], gp[g][k2 * 4 + 1], gp[g][k2 * 4 + 2], gp[g][k2 * 4 + 3]);
-                                acc[g][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, as_bf16x8(bv), acc[g][mb], 0, 0, 0);
-                            }
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (b + RD < NB_P) read_tr_batch(b + RD, tb[b % RD]);
-                    }
-                } else {
-                    bool kept = true;
-                    softmax(tile, sb, sv, gp, rows_here, ragged_tag, kept, max_tag);
+                    if (b + RD < 2 * NT) read_tr_batch(b + RD, tb[b % RD]);
                 }
             }
         }
@@ -1024,28 +949,17 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         for (int k = 2; k <= PF; ++k) younger += (t + k < t_end) ? 1 : 0;
         wait_all_but<LPW>(younger, group_extras);
     };
-    // Keeps the arithmetic of a tile in front of the wait that follows it: without a use at this point the compiler
-    // sinks the whole softmax update below the wait, into the next step, where no matrix work is left to overlap it.
-    auto pin_results = [&]() {
-        if (MODE == MODE_FWD) {
-#pragma unroll
-            for (int g = 0; g < XG; ++g) asm volatile("" : "+v"(run_m[g]), "+v"(run_s[g]));
-        }
-        if (MODE == MODE_FDH) {
-#pragma unroll
-            for (int g = 0; g < XG; ++g) asm volatile("" : "+v"(run_s[g]));
-        }
-    };
     // ---- FDH: forward sum and hidden-state gradient in one pass (an online softmax, Alg. 1, carried through Eq. 6 left).
     // The probabilities of the second product are taken against a reference m per position instead of the final
     // log-sum-exp: acc = sum_j 2^(o_j log2e - m) E_j, run_s = sum_j 2^(o_j log2e - m), and the epilogue divides.  Any m
-    // gives the same result as long as nothing leaves the float range, so the fast attempt takes m = the largest score
-    // among the first 32 candidates of the block's range and never looks at a maximum again (no maximum chain, no
-    // rescaling, no branch inside the software-pipelined loop).  Scores that outgrow that reference by more than about
-    // 69 nats push a sum beyond 1e30: the wavefront that sees it raises a flag in LDS, every wavefront of the block reads
-    // the flag of the previous tile during a step (two flags, by tile parity, so that all of them read the same
-    // value), and the block starts over in the exact form: the largest score of every tile is taken first (a score
-    // product of its own), sums and accumulators are rescaled when it grows, and no exponent is ever positive.
+    // gives the same result as long as nothing leaves the float range, so the pipelines take m = the largest score
+    // among the first 32 candidates of the block's range and never look at a maximum again (no maximum chain, no
+    // rescaling, no branch).  Scores that outgrow that reference by more than about 69 nats push a sum beyond 1e30, where it stays:
+    // at the end of the range a wavefront that sees one raises a flag in LDS, and the block starts over.  Up to 128 columns in
+    // the exact form: the largest score of every tile is taken first (a score product of its own), sums and accumulators are
+    // rescaled when it grows, and no exponent is ever positive; at 256 against the largest score of the whole range.  The first attempt
+    // is spent by then: in every position the last candidate 90 nats up, us a call, plain / starting over: 51,200 positions, 1024
+    // candidates, d = 64 25 / 49, d = 128 41 / 86; 65,536 positions, 8192 candidates, d = 256 436 / 1138.
     int *const over_flag = reinterpret_cast<int *>(epi_own);
     auto scores_of = [&](const uint16_t *tile, int sb, f32x16 (&sv)[XG]) {
 #pragma unroll
@@ -1099,68 +1013,37 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 run_m[g] = mn;
                 run_s[g] *= sc;
 #pragma unroll
-                for (int mb = 0; mb < (MODE == MODE_FWD ? 1 : MBH); ++mb)
+                for (int mb = 0; mb < (MODE == MODE_FWD ? 1 : MB); ++mb)
 #pragma unroll
                     for (int q = 0; q < 16; ++q) acc[g][mb][q] *= sc;
             }
         }
     };
-    auto note_overflow = [&](int parity) {
+    auto note_overflow = [&]() {
         bool over = false;
 #pragma unroll
         for (int g = 0; g < XG; ++g) over |= !(run_s[g] < 1.0e30f);  // or NaN
-        if (__any(over) && lane == 0) over_flag[parity] = 1;
+        if (__any(over) && lane == 0) over_flag[0] = 1;
     };
-    // One attempt at the streamed range: prologue loads, the ring of steps, the short last tile.  Returns whether the
-    // block has to start over (FDH, fast form only; the value is the same in every wavefront of the block).
-    auto run_attempt = [&](auto form) -> bool {
-        constexpr bool EXACT = decltype(form)::exact;
-        constexpr bool WATCH = (MODE == MODE_FDH) && !EXACT;  // the fast form watches for sums that leave the float range
-        int overflow = 0;  // wave-uniform
+    // The range tile by tile: prologue loads, the ring of steps, the short last tile.  Hidden size 256 forward alone and with gradient
+    // filtering; elsewhere what the pipelines below hand over.  work(tile number, tile, Full or Ragged).
+    auto run_ring = [&](auto work) {
         auto step = [&](int64_t t, const uint16_t *cur, uint16_t *nxt) {
             if (t + PF < t_end) {
                 int32_t rows[NR];
                 rows_from_lds(t + PF, cur, rows);
                 issue_group(t + PF, rows, nxt);
             }
-            if (MODE == MODE_FDH && EXACT) raise_reference(cur, BY);
-            // The flag that the previous step may have raised (every wavefront of the block reads it between the same
-            // two barriers, so all of them see the same value); the read lands under the work on this tile.
-            int seen = 0;
-            if (WATCH && t != t_begin) seen = over_flag[(int)((t - t_begin - 1) & 1)];
-            // d = 256: few tiles per block and a kernel at the edge of its register budget; measured slower there
-            if (MODE == MODE_FWD && D <= 128 && t != t_begin) {  // the first tile has no maximum to lean on
-                float m0[XG], s0[XG];
-                bool over = false;
+            work(t, cur, Full{});
+            // Keeps the arithmetic of a tile in front of the wait that follows it: without a use at this point the compiler
+            // sinks the whole softmax update below the wait, into the next step, where no matrix work is left to overlap it.
+            if (MODE == MODE_FWD || MODE == MODE_FDH) {
 #pragma unroll
-                for (int g = 0; g < XG; ++g) {
-                    m0[g] = run_m[g];
-                    s0[g] = run_s[g];
-                }
-                process_tile(t, cur, Full{}, Lazy{});
-#pragma unroll
-                for (int g = 0; g < XG; ++g) over |= !(run_s[g] < 1.0e30f);  // near overflow (or NaN): the merges of
-                                                                                  // half-waves and of split runs add up to 16 such sums
-                if (__any(over)) {
-#pragma unroll
-                    for (int g = 0; g < XG; ++g) {
-                        run_m[g] = m0[g];
-                        run_s[g] = s0[g];
-                    }
-                    process_tile(t, cur, Full{}, Exact{});
-                }
-            } else {
-                process_tile(t, cur, Full{}, Exact{});
-            }
-            pin_results();
-            if (WATCH) {
-                note_overflow((int)((t - t_begin) & 1));
-                overflow |= __builtin_amdgcn_readfirstlane(seen);
+                for (int g = 0; g < XG; ++g) asm volatile("" : "+v"(run_m[g]), "+v"(run_s[g]));
             }
             wait_for_next(t);
             barrier_keep_loads();
         };
-        if (WATCH && tid < 2) over_flag[tid] = 0;  // visible behind the barrier that follows the first loads
         if (t_begin < t_end) {
             int32_t rows[PF][NR];
 #pragma unroll
@@ -1172,69 +1055,32 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         }
         wait_for_next(t_begin - 1);
         barrier_keep_loads();
-        if (WATCH && t_begin < t_end) {  // reference of the fast form: the largest score among the first 32 candidates
-            const int64_t left = n_y - t_begin * BY;
-            float tmax[XG];
-            tile_max(buf_at(0), 1, left < BY ? (int)left : BY, tmax);
-#pragma unroll
-            for (int g = 0; g < XG; ++g) run_m[g] = tmax[g];
-        }
-        if constexpr (STREAM) {  // the exact form, off the common path
+        if constexpr (STREAM) {
+            static_assert(PF == NB - 1, "tile t + PF goes where tile t - 1 was");
 #pragma unroll 1
-            for (int64_t t = t_begin; t < t_stop && !overflow; ++t) {
-                static_assert(WIDE || PF == NB - 1, "tile t + PF goes where tile t - 1 was");
+            for (int64_t t = t_begin; t < t_stop; ++t) {
                 const int s = (int)((t - t_begin) % NB);
                 step(t, buf_at(s), buf_at(s + PF));
-            }
-        } else if (NBUF == 4) {
-            for (int64_t t = t_begin; t < t_stop; t += 4) {
-                step(t, buf0, buf3);
-                if (t + 1 >= t_stop || overflow) break;
-                step(t + 1, buf1, buf0);
-                if (t + 2 >= t_stop || overflow) break;
-                step(t + 2, buf2, buf1);
-                if (t + 3 >= t_stop || overflow) break;
-                step(t + 3, buf3, buf2);
-                if (overflow) break;
             }
         } else if (NBUF == 3) {
             for (int64_t t = t_begin; t < t_stop; t += 3) {
                 step(t, buf0, buf2);
-                if (t + 1 >= t_stop || overflow) break;
+                if (t + 1 >= t_stop) break;
                 step(t + 1, buf1, buf0);
-                if (t + 2 >= t_stop || overflow) break;
+                if (t + 2 >= t_stop) break;
                 step(t + 2, buf2, buf1);
-                if (overflow) break;
-            }
-        } else if (NBUF == 2) {
-            for (int64_t t = t_begin; t < t_stop; t += 2) {
-                step(t, buf0, buf1);
-                if (t + 1 >= t_stop || overflow) break;
-                step(t + 1, buf1, buf0);
-                if (overflow) break;
             }
         } else {
-            for (int64_t t = t_begin; t < t_stop && !overflow; ++t) {
-                const int s = (int)((t - t_begin) & 1);
-                step(t, buf_at(s), buf_at(s ^ 1));
+            for (int64_t t = t_begin; t < t_stop; t += 2) {
+                step(t, buf0, buf1);
+                if (t + 1 >= t_stop) break;
+                step(t + 1, buf1, buf0);
             }
         }
-        if (tail_ragged && !overflow) {  // its group was issued with the others, and the last wait above was for all loads
-            const uint16_t *last = buf_at((int)((t_stop - t_begin) % NB));
-            if (MODE == MODE_FDH && EXACT) raise_reference(last, (int)(n_y - t_stop * BY));
-            process_tile(t_stop, last, Ragged{}, Exact{});
-            if (WATCH) note_overflow(0);
+        if (tail_ragged) {  // its group was issued with the others, and the last wait above was for all loads
+            work(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{});
             __syncthreads();  // the dE epilogue reuses the tile buffers
         }
-        if (WATCH) {
-            // the flags of the last step and of the short tile have not been read yet (the last barrier is behind us)
-            if (!overflow) overflow = __builtin_amdgcn_readfirstlane(over_flag[0] | over_flag[1]);
-            if (overflow) {  // loads of later tiles may still be in flight into the ring: let them land
-                wait_vm<0>();
-                __syncthreads();
-            }
-        }
-        return overflow != 0;
     };
     // A load group is as in issue_group, of a fixed size (row numbers are loaded, and not used, also where there is no list of
     // them) and one instruction at a time, so that it can be dealt out over the slices of a tile: in one piece behind the
@@ -1311,32 +1157,6 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         wait_vm<(PF - 1) * GROUP>();
         barrier_keep_loads();
     };
-    // Off the common path: the tiles of the range one by one, with the loads of tile t + PF in one piece.
-    auto run_plain = [&](auto work) {
-        start_loads();
-        first_landed();
-#pragma unroll 1
-        for (int64_t t = t_begin; t < t_stop; ++t) {
-            const int at = (int)((t - t_begin) % NB);
-            const int32_t *list = reinterpret_cast<const int32_t *>(buf_at(at) + OFF_I);
-            const int64_t t_load = clamp(t + PF);
-            const uint32_t dst = lds_dst((at + PF) % NB);
-            int32_t ids[NR];
-#pragma unroll
-            for (int i = 0; i < LPW; ++i) ids[i] = list[my_row + (uint32_t)(i * (NW * 64 / CPR))];
-            if (GSEP) ids[LPW] = list[const_slot];
-#pragma unroll
-            for (int i = 0; i < LPW; ++i) load_rows(i, row_of(i, t_load, ids[i]), dst);
-            if (MODE == MODE_DE) load_const(t_load, GSEP ? listed_or(ids[LPW], const_at(t_load)) : 0u, dst);
-            load_numbers(clamp(t + 2 * PF), dst);
-            work(t, buf_at(at));
-            wait_vm<(PF - 1) * GROUP>();
-            barrier_keep_loads();
-        }
-        if (tail_ragged) work(t_stop, buf_at((int)((t_stop - t_begin) % NB)));
-        wait_vm<0>();     // the loads beyond the range
-        __syncthreads();  // the tile buffers are free
-    };
     // The sum of exponentials of the pipelines below: a lane's sixteen of a sub-tile in four chains, which are joined onto the running
     // sum when the next sub-tile begins (forward pass alone, which looks at the sum behind every tile: at once).  Chains that run on over the range are as many instructions, and the steps no faster
     // (204,800 positions, 4096 candidates, d = 256: 1266 and 1267 us), but lose more: one candidate with 4095 others 2^-12 to 2^-14 as large, error of lse
@@ -1367,7 +1187,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         constexpr bool WATCH = (MODE == MODE_FDH);
         f32x16 sv[2][XG];
         gp_t gp[2];
-        s16x8 tr[2][MBH];
+        s16x8 tr[2][MB];
         float4 cy[4], gy[4];   // DE: exponent offsets and upstream gradients of the streamed rows
         // FOLD (dE with two row groups, where the registers of the gradients are short and their products an eighth of the
         // vector instructions): g 2^x = +-2^(x + log2 |g|).  A wavefront folds the gradients of a tile into the offsets once,
@@ -1402,8 +1222,8 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         auto load_op = [&](const uint16_t *tile, int sb, int kk) -> uint4 {
             return *reinterpret_cast<const uint4 *>(lds_at(tile + sb * 32 * D, a_base, ((kk * 2) & SM) * 8, (kk / NA) * (NA * 16)));
         };
-        auto load_tr1 = [&](const uint16_t *tile, int sb, int j) {  // j: k2 * MBH + mb
-            const int k2 = j / MBH, mb = j % MBH;
+        auto load_tr1 = [&](const uint16_t *tile, int sb, int j) {  // j: k2 * MB + mb
+            const int k2 = j / MB, mb = j % MB;
             const uint16_t *tbase = tile + (sb * 32 + k2 * 16) * D;
             const int col = (mb / NT) * (NT * 32);
             const s16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(lds_at(tbase, t_base0, ((mb * 4) & SM) * 8, col)));
@@ -1411,7 +1231,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             tr[k2][mb] = __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7);
         };
         auto mfma_second = [&](int i, const gp_t &p) {  // piece by piece of the transposed operand, the row groups inside
-            const int g = i % XG, k2 = i / XG / MBH, mb = (i / XG) % MBH;
+            const int g = i % XG, k2 = i / XG / MB, mb = (i / XG) % MB;
             bf16x8 av;
             __builtin_memcpy(&av, &tr[k2][mb], 16);
             const uint4 bv = make_uint4(p[g][k2 * 4 + 0], p[g][k2 * 4 + 1], p[g][k2 * 4 + 2], p[g][k2 * 4 + 3]);
@@ -1488,7 +1308,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                     }
                 }
 #pragma unroll
-                for (int j = 0; j < 2 * MBH; ++j) {  // pieces late in the list are read at the head of the phase that uses them
+                for (int j = 0; j < 2 * MB; ++j) {  // pieces late in the list are read at the head of the phase that uses them
                     if (j * XG < TR_AHEAD && i == NS + j * XG - TR_AHEAD) load_tr1(tile, k, j);
                     if (j * XG >= TR_AHEAD && i == j * XG - TR_AHEAD) load_tr1(ptile, pk, j);
                 }
@@ -1551,7 +1371,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                     sv[0][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(o), as_bf16x8(xr[g][kk]), sv[0][g], 0, 0, 0);
             }
 #pragma unroll
-            for (int j = 0; j < 2 * MBH; ++j)
+            for (int j = 0; j < 2 * MB; ++j)
                 if (j * XG < TR_AHEAD) load_tr1(buf0, 0, j);
             if (MODE == MODE_DE) {
                 if constexpr (FOLD) fold_tile(buf0, 0);
@@ -1577,7 +1397,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 }
             }
 #pragma unroll
-            for (int j = 0; j < 2 * MBH; ++j)
+            for (int j = 0; j < 2 * MB; ++j)
                 if (j * XG >= TR_AHEAD) load_tr1(buf_at(at + 3), NSB - 1, j);
 #pragma unroll
             for (int i = 0; i < NM_P; ++i) mfma_second(i, gp[1]);
@@ -1586,8 +1406,8 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 for (int g = 0; g < XG; ++g) join_sums(g);
             }
         }
-        if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{}, Exact{});
-        if (WATCH) note_overflow(0);  // a sum that was beyond the limit once stays there
+        if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{});
+        if (WATCH) note_overflow();  // a sum that was beyond the limit once stays there
         wait_vm<0>();     // the loads beyond the range
         __syncthreads();  // the tile buffers are free, the flag is in place
         if constexpr (FOLD) {
@@ -1691,7 +1511,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 // stationary rows past the end hold a copy of row 0: they must not keep a block alive
                 if (!__any(x_ok[g] && big[g] >= a.filter_log2)) continue;
                 uint32_t gp[8];
-                s16x8 tr[2][MBH];
+                s16x8 tr[2][MB];
                 load_tr(tile, k, tr);
 #pragma unroll
                 for (int q = 0; q < 16; q += 2) {
@@ -1708,7 +1528,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
 #pragma unroll
                 for (int k2 = 0; k2 < 2; ++k2)
 #pragma unroll
-                    for (int mb = 0; mb < MBH; ++mb) {
+                    for (int mb = 0; mb < MB; ++mb) {
                         bf16x8 av;
                         __builtin_memcpy(&av, &tr[k2][mb], 16);
                         const uint4 bv = make_uint4(gp[k2 * 4 + 0], gp[k2 * 4 + 1], gp[k2 * 4 + 2], gp[k2 * 4 + 3]);
@@ -1775,7 +1595,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                             gp_t unused;
                             bool kept;
                             scores_of(cur, k, again);
-                            softmax(cur, k, again, unused, BY, Full{}, kept, Exact{});
+                            softmax(cur, k, again, unused, BY, Full{}, kept);
                         }
                     }
                 }
@@ -1783,7 +1603,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 ++t;
             } while (t < t_stop);
         }
-        if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{}, Exact{});
+        if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{});
         wait_vm<0>();     // the loads beyond the range
         __syncthreads();  // the tile buffers are free
     };
@@ -1799,7 +1619,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     auto run_stream_wide = [&]() {
         constexpr bool WATCH = (MODE == MODE_FDH);
         constexpr int R = XG == 2 ? 4 : 8, NP = 16, PIECES = 32;  // R divides PIECES: the ring carries on into the next tile
-        static_assert(!WIDE || (NP == 2 * MBH && KK == NP && NA == 8 && NT == 4 && NSB == 1 && PF >= 2), "hidden size 256");
+        static_assert(!WIDE || (NP == 2 * MB && KK == NP && NA == 8 && NT == 4 && NSB == 1 && PF >= 2), "hidden size 256");
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
         typedef const u32x4 __attribute__((address_space(3))) *lds_u4;
         typedef const f32x4 __attribute__((address_space(3))) *lds_f4;
@@ -1836,7 +1656,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
 #pragma unroll
             for (int g = 0; g < XG; ++g)
 #pragma unroll
-                for (int mb = 0; mb < MBH; ++mb) asm volatile("" : "+a"(acc[g][mb]));
+                for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+a"(acc[g][mb]));
         };
         auto hold_scores = [&]() {
 #pragma unroll
@@ -1986,7 +1806,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 for (int h = 0; h < 2; ++h) gp[g][h] = (u32x4)(0u);
                 // zero where they stay: a zero written any other way lives in vector registers first, and is copied
 #pragma unroll
-                for (int mb = 0; mb < MBH; ++mb) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %1, 0" : "=a"(acc[g][mb]) : "v"(gp[0][0]));
+                for (int mb = 0; mb < MB; ++mb) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %1, 0" : "=a"(acc[g][mb]) : "v"(gp[0][0]));
             }
             start_loads();
             if (MODE == MODE_FDH && !SECOND && splits == 1) {
@@ -2053,7 +1873,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             if (WATCH) {
 #pragma unroll
                 for (int g = 0; g < XG; ++g) join_sums(g);
-                if (!SECOND) note_overflow(0);  // a sum of exponentials that was beyond the limit once stays there
+                if (!SECOND) note_overflow();  // a sum of exponentials that was beyond the limit once stays there
             }
             settle();
             wait_vm<0>();     // the loads beyond the range
@@ -2071,44 +1891,48 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             }
         }
     };
-    bool again = false;
     if constexpr (PLAIN) {
-        run_plain([&](int64_t t, const uint16_t *tile) {
+        run_ring([&](int64_t t, const uint16_t *tile, auto) {
             const int rows_here = (n_y - t * BY < BY) ? (int)(n_y - t * BY) : BY;
 #pragma unroll 1
             for (int sb = 0; sb < NSB; ++sb) {
                 uint4 op[KK];
                 f32x16 sv[XG];
                 gp_t gp;
-                s16x8 tr[2][MBH];
+                s16x8 tr[2][MB];
                 bool kept;
                 load_ops(tile, sb, op);
                 mfma_scores(op, sv);
-                softmax(tile, sb, sv, gp, rows_here, Ragged{}, kept, Exact{});
+                softmax(tile, sb, sv, gp, rows_here, Ragged{}, kept);
                 load_tr(tile, sb, tr);
                 second(tr, gp);
             }
         });
-    } else if constexpr (WIDE) run_stream_wide();
-    else if constexpr (STREAM && (FILTER || MODE == MODE_FWD)) run_stream_scores();
-    else if constexpr (STREAM) again = run_stream();
-    else again = run_attempt(FastTag{});
-    if (again) {
-        if constexpr (MODE == MODE_DE) return true;
-        if constexpr (MODE == MODE_FDH) {  // start over in the exact form
+    } else if constexpr (WIDE) {
+        run_stream_wide();
+    } else if constexpr (STREAM && (FILTER || MODE == MODE_FWD)) {
+        run_stream_scores();
+    } else if constexpr (STREAM && MODE == MODE_FDH) {
+        if (run_stream()) {  // start over in the exact form
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
                 run_m[g] = -INFINITY;
                 run_s[g] = 0.f;
 #pragma unroll
-                for (int mb = 0; mb < MBH; ++mb)
+                for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                     for (int q = 0; q < 16; ++q) acc[g][mb][q] = 0.f;
             }
-            run_attempt(ExactTag{});
+            run_ring([&](int64_t t, const uint16_t *tile, auto ragged_tag) {
+                raise_reference(tile, decltype(ragged_tag)::value ? (int)(n_y - t * BY) : BY);
+                process_tile(t, tile, ragged_tag);
+            });
         }
+    } else if constexpr (STREAM) {
+        if (run_stream()) return true;
+    } else {
+        run_ring([&](int64_t t, const uint16_t *tile, auto ragged_tag) { process_tile(t, tile, ragged_tag); });
     }
-
 
     // =====================================================================================================  epilogues
     if (MODE == MODE_FWD) {
@@ -2124,7 +1948,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                     rm = M;
                 }
             }
-            const int64_t x = xb * XPB + (xgrp * XG + g) * 32 + lo;
+            const int64_t x = xb * XPB + (wave * XG + g) * 32 + lo;
             if (a.splits > 1) {
                 if (x_ok[g] && hi == 0) {
                     a.part_m[(int64_t)split * a.N + x] = rm;
@@ -2153,22 +1977,22 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     } else if (MODE == MODE_FDH) {
 #pragma unroll
         for (int g = 0; g < XG; ++g) {
-            const int64_t x = xb * XPB + (xgrp * XG + g) * 32 + lo;
+            const int64_t x = xb * XPB + (wave * XG + g) * 32 + lo;
             const float rm = run_m[g];
             const float rs = run_s[g] + __shfl_xor(run_s[g], 32, 64);  // the two halves share the reference
             if (splits > 1) {  // partial (reference, sum, rows) of this part of the candidate range; the merge finishes
                 if (x_ok[g]) {
                     const int64_t slot = (int64_t)split * part_rows + (x - part_x0);
-                    if (hi == 0 && half == 0) {
+                    if (hi == 0) {
                         a.part_m[slot] = rm;
                         a.part_s[slot] = rs;
                     }
                     float *dst = a.part_dH + slot * D;
 #pragma unroll
-                    for (int mb = 0; mb < MBH; ++mb)
+                    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                         for (int qq = 0; qq < 4; ++qq)
-                            *reinterpret_cast<float4 *>(dst + (half * MBH + mb) * 32 + qq * 8 + hi * 4) = make_float4(
+                            *reinterpret_cast<float4 *>(dst + mb * 32 + qq * 8 + hi * 4) = make_float4(
                                 acc[g][mb][qq * 4], acc[g][mb][qq * 4 + 1], acc[g][mb][qq * 4 + 2], acc[g][mb][qq * 4 + 3]);
                 }
                 continue;
@@ -2190,17 +2014,17 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 const float l = (M + __builtin_amdgcn_logf(tot)) * kLn2;
                 const float inv = e1 / tot;        // 2^(reference) / sum of all live exponentials
                 const float cpos = e2 / tot - 1.f;  // coefficient of the correct item, w p+ - 1
-                if (hi == 0 && half == 0) {
+                if (hi == 0) {
                     a.lse[xrow[g]] = l;
                     a.loss[xrow[g]] = l - op;
                     a.coef[xrow[g]] = cpos;
                     a.de_const[x] = __float_as_uint(-l * kLog2e);
                 }
 #pragma unroll
-                for (int mb = 0; mb < MBH; ++mb)
+                for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                     for (int qq = 0; qq < 4; ++qq) {
-                        const int col = (half * MBH + mb) * 32 + qq * 8 + hi * 4;
+                        const int col = mb * 32 + qq * 8 + hi * 4;
                         const uint2 ev = *reinterpret_cast<const uint2 *>(erow + col);
                         *reinterpret_cast<float4 *>(a.U + xrow[g] * D + col) =
                             make_float4(fmaf(cpos, bf16_lo(ev.x), acc[g][mb][qq * 4 + 0] * inv), fmaf(cpos, bf16_hi(ev.x), acc[g][mb][qq * 4 + 1] * inv),
@@ -2211,15 +2035,15 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     } else if (MODE == MODE_DH) {
 #pragma unroll
         for (int g = 0; g < XG; ++g) {
-            const int64_t x = xb * XPB + (xgrp * XG + g) * 32 + lo;
+            const int64_t x = xb * XPB + (wave * XG + g) * 32 + lo;
             if (splits > 1) {
                 if (x_ok[g]) {
                     float *dst = a.part_dH + ((int64_t)split * part_rows + (x - part_x0)) * D;
 #pragma unroll
-                    for (int mb = 0; mb < MBH; ++mb)
+                    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                         for (int qq = 0; qq < 4; ++qq)
-                            *reinterpret_cast<float4 *>(dst + (half * MBH + mb) * 32 + qq * 8 + hi * 4) = make_float4(
+                            *reinterpret_cast<float4 *>(dst + mb * 32 + qq * 8 + hi * 4) = make_float4(
                                 acc[g][mb][qq * 4], acc[g][mb][qq * 4 + 1], acc[g][mb][qq * 4 + 2], acc[g][mb][qq * 4 + 3]);
                 }
                 continue;
@@ -2234,12 +2058,12 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 const float pp = __builtin_amdgcn_exp2f(fmaf(op, kLog2e, cx[g]));
                 const float cpos = w * pp - 1.f;  // coefficient of the correct item before the upstream gradient
                 const float gg = a.g ? a.g[xrow[g]] : 1.f;
-                if (a.write_consts && hi == 0 && half == 0) a.coef[xrow[g]] = gg * cpos;
+                if (a.write_consts && hi == 0) a.coef[xrow[g]] = gg * cpos;
 #pragma unroll
-                for (int mb = 0; mb < MBH; ++mb)
+                for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                     for (int qq = 0; qq < 4; ++qq) {
-                        const int col = (half * MBH + mb) * 32 + qq * 8 + hi * 4;
+                        const int col = mb * 32 + qq * 8 + hi * 4;
                         const uint2 ev = *reinterpret_cast<const uint2 *>(erow + col);
                         const float v0 = gg * fmaf(cpos, bf16_lo(ev.x), acc[g][mb][qq * 4 + 0]);
                         const float v1 = gg * fmaf(cpos, bf16_hi(ev.x), acc[g][mb][qq * 4 + 1]);
@@ -2264,21 +2088,21 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         int64_t *xrow_s = EPI_IN_TILES ? reinterpret_cast<int64_t *>(reinterpret_cast<float *>(buf0) + 2 * (32 * 33))
                                        : reinterpret_cast<int64_t *>(epi_own + NW * (32 * 33));
 #pragma unroll
-        for (int g = 0; g < XG; ++g) xrow_s[(xgrp * XG + g) * 32 + lo] = x_ok[g] ? xrow[g] : -1;  // both half-waves agree
+        for (int g = 0; g < XG; ++g) xrow_s[(wave * XG + g) * 32 + lo] = x_ok[g] ? xrow[g] : -1;  // both half-waves agree
         __syncthreads();
 #pragma unroll
         for (int g = 0; g < XG; ++g) {
 #pragma unroll
-            for (int mb = 0; mb < MBH; ++mb) {
+            for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
                 for (int q = 0; q < 16; ++q) tbuf[lo * 33 + (q / 4) * 8 + hi * 4 + (q % 4)] = acc[g][mb][q];
                 __syncthreads();
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int xl = r * 2 + hi;
-                    const int64_t row = xrow_s[(xgrp * XG + g) * 32 + xl];
+                    const int64_t row = xrow_s[(wave * XG + g) * 32 + xl];
                     const float v = tbuf[xl * 33 + lo];
-                    if (row >= 0) unsafeAtomicAdd(a.dE + row * D + (half * MBH + mb) * 32 + lo, v);
+                    if (row >= 0) unsafeAtomicAdd(a.dE + row * D + mb * 32 + lo, v);
                 }
                 __syncthreads();
             }
@@ -2287,18 +2111,17 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     return false;
 }
 
-template <int D, int MODE, int BY, int NW, int XG, int MINB, int NBUF, int DS, bool FILTER>
+template <int D, int MODE, int BY, int NW, int XG, int MINB, int NBUF, bool FILTER>
 __global__ __launch_bounds__(NW * 64, MINB) void tile_kernel(TileArgs a)
 {
-    typedef TileGeom<D, MODE, BY, NW, XG, NBUF, DS, FILTER> G;
+    typedef TileGeom<D, MODE, BY, NW, XG, NBUF, FILTER> G;
     __shared__ __attribute__((aligned(1024))) uint16_t buf0[G::BUF0];
     __shared__ __attribute__((aligned(1024))) uint16_t buf1[G::BUF1];
     __shared__ __attribute__((aligned(1024))) uint16_t buf2[G::BUF2];
-    __shared__ __attribute__((aligned(1024))) uint16_t buf3[G::BUF3];
     __shared__ __attribute__((aligned(16))) float epi_own[G::EPI_OWN];
-    const bool over = tile_body<D, MODE, BY, NW, XG, NBUF, DS, FILTER>(a, (int64_t)blockIdx.x, buf0, buf1, buf2, buf3, epi_own);
+    const bool over = tile_body<D, MODE, BY, NW, XG, NBUF, FILTER>(a, (int64_t)blockIdx.x, buf0, buf1, buf2, epi_own);
     if constexpr (G::FOLD) {
-        if (over) tile_body<D, MODE, BY, NW, XG, NBUF, DS, FILTER, true>(a, (int64_t)blockIdx.x, buf0, buf1, buf2, buf3, epi_own);
+        if (over) tile_body<D, MODE, BY, NW, XG, NBUF, FILTER, true>(a, (int64_t)blockIdx.x, buf0, buf1, buf2, epi_own);
     }
 }
 
@@ -2310,25 +2133,24 @@ __global__ __launch_bounds__(NW * 64, MINB) void tile_kernel(TileArgs a)
 template <int D, int BY, int XG_DH, int XG_DE, int NBUF, bool FILTER>
 __global__ __launch_bounds__(256, 2) void tile_bwd_kernel(TileArgs a_dh, TileArgs a_de, int64_t de_blocks)
 {
-    typedef TileGeom<D, MODE_DH, BY, 4, XG_DH, NBUF, 1, FILTER> GH;
-    typedef TileGeom<D, MODE_DE, BY, 4, XG_DE, NBUF, 1, FILTER> GE;
+    typedef TileGeom<D, MODE_DH, BY, 4, XG_DH, NBUF, FILTER> GH;
+    typedef TileGeom<D, MODE_DE, BY, 4, XG_DE, NBUF, FILTER> GE;
     constexpr int B0 = GH::BUF0 > GE::BUF0 ? GH::BUF0 : GE::BUF0, B1 = GH::BUF1 > GE::BUF1 ? GH::BUF1 : GE::BUF1;
-    constexpr int B2 = GH::BUF2 > GE::BUF2 ? GH::BUF2 : GE::BUF2, B3 = GH::BUF3 > GE::BUF3 ? GH::BUF3 : GE::BUF3;
+    constexpr int B2 = GH::BUF2 > GE::BUF2 ? GH::BUF2 : GE::BUF2;
     __shared__ __attribute__((aligned(1024))) uint16_t buf0[B0];
     __shared__ __attribute__((aligned(1024))) uint16_t buf1[B1];
     __shared__ __attribute__((aligned(1024))) uint16_t buf2[B2];
-    __shared__ __attribute__((aligned(1024))) uint16_t buf3[B3];
     __shared__ __attribute__((aligned(16))) float epi_own[GE::EPI_OWN];
     // grid order: the dE role (correct-item scatter, then its tiles) ahead of the dH role (zeroing of padded rows, then
     // its tiles); measured faster on c2 than tiles first
     const int64_t b = (int64_t)blockIdx.x;
     if (b < de_blocks) {
-        const bool over = tile_body<D, MODE_DE, BY, 4, XG_DE, NBUF, 1, FILTER>(a_de, b, buf0, buf1, buf2, buf3, epi_own);
+        const bool over = tile_body<D, MODE_DE, BY, 4, XG_DE, NBUF, FILTER>(a_de, b, buf0, buf1, buf2, epi_own);
         if constexpr (GE::FOLD) {
-            if (over) tile_body<D, MODE_DE, BY, 4, XG_DE, NBUF, 1, FILTER, true>(a_de, b, buf0, buf1, buf2, buf3, epi_own);
+            if (over) tile_body<D, MODE_DE, BY, 4, XG_DE, NBUF, FILTER, true>(a_de, b, buf0, buf1, buf2, epi_own);
         }
     } else {
-        tile_body<D, MODE_DH, BY, 4, XG_DH, NBUF, 1, FILTER>(a_dh, b - de_blocks, buf0, buf1, buf2, buf3, epi_own);
+        tile_body<D, MODE_DH, BY, 4, XG_DH, NBUF, FILTER>(a_dh, b - de_blocks, buf0, buf1, buf2, epi_own);
     }
 }
 
@@ -2673,11 +2495,11 @@ int64_t plan_tile_grid(TileArgs &a, int64_t n_x, int xpb, int threads, int slots
     return blocks;
 }
 
-template <int D, int MODE, int BY, int NW, int XG, int MINB, int NBUF, int DS = 1, bool FILTER = false>
+template <int D, int MODE, int BY, int NW, int XG, int MINB, int NBUF, bool FILTER = false>
 hipError_t launch_tile_kernel(TileArgs &a, int64_t n_x, hipStream_t stream, bool as_given = false)
 {
-    const int slots = resident_blocks(tile_kernel<D, MODE, BY, NW, XG, MINB, NBUF, DS, FILTER>, NW * 64);
-    constexpr int XPB = (NW / DS) * XG * 32;
+    const int slots = resident_blocks(tile_kernel<D, MODE, BY, NW, XG, MINB, NBUF, FILTER>, NW * 64);
+    constexpr int XPB = NW * XG * 32;
     int64_t blocks = plan_tile_grid<MODE>(a, n_x, XPB, NW * 64, slots, false, as_given);
     if (blocks == 0) return hipSuccess;
     a.tail_slots = 0;
@@ -2686,7 +2508,7 @@ hipError_t launch_tile_kernel(TileArgs &a, int64_t n_x, hipStream_t stream, bool
         blocks += slots;
     }
     ProfScope prof(MODE == MODE_FWD ? PROF_TILE_FWD : (MODE == MODE_DH ? PROF_TILE_DH : (MODE == MODE_DE ? PROF_TILE_DE : PROF_TILE_FDH)), stream);
-    hipLaunchKernelGGL((tile_kernel<D, MODE, BY, NW, XG, MINB, NBUF, DS, FILTER>), dim3((unsigned)blocks), dim3(NW * 64), 0, stream, a);
+    hipLaunchKernelGGL((tile_kernel<D, MODE, BY, NW, XG, MINB, NBUF, FILTER>), dim3((unsigned)blocks), dim3(NW * 64), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -2758,35 +2580,26 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
             e = hipGetLastError();
         }
         return e;
-    case TILE_PASS_DH: {
-        bool done = false;
-        if constexpr (XG_B == 2) {
-            if (wide(a.N, true)) {
-                e = launch_tile_kernel<D, MODE_DH, BY_B, 4, 2, MINB, NBUF_B>(a, a.N, stream);
-                done = true;
-            }
-        }
-        if (!done && a.filter_log2 > -INFINITY) {
-            if constexpr (D > 128) e = launch_tile_kernel<D, MODE_DH, BY_B, NW_L, 1, MINB, NBUF_B, 1, true>(a, a.N, stream);
-            else e = hipErrorInvalidValue;  // smaller hidden sizes filter in the fused launch
-        } else if (!done) e = launch_tile_kernel<D, MODE_DH, BY_B, 4, XG_L, MINB, NBUF_L>(a, a.N, stream);
+    case TILE_PASS_DH:  // hidden sizes up to 128: in the fused launch
         if constexpr (D > 128) {
+            constexpr int PPB = 256 / (D / 8), XPB_L = NW_L * 32;
+            if (a.filter_log2 > -INFINITY) e = launch_tile_kernel<D, MODE_DH, BY_B, NW_L, 1, MINB, NBUF_B, true>(a, a.N, stream);
+            else e = launch_tile_kernel<D, MODE_DH, BY_B, 4, XG_L, MINB, NBUF_L>(a, a.N, stream);
             if (e == hipSuccess && a.tail_slots > 0) {  // rows of the split last round: at most half the chip's blocks
-                constexpr int PPB = 256 / (D / 8), XPB_L = NW_L * 32;
                 const int64_t rows = (int64_t)(a.tail_slots / 2) * XPB_L;
                 ProfScope prof(PROF_DH_MERGE, stream);
                 hipLaunchKernelGGL((dh_merge_kernel<D, XPB_L>), dim3((unsigned)((rows + PPB - 1) / PPB)), dim3(256), 0, stream, a);
                 e = hipGetLastError();
             }
+            if (e == hipSuccess && a.splits > 1) {
+                ProfScope prof(PROF_DH_MERGE, stream);
+                hipLaunchKernelGGL((dh_merge_kernel<D>), dim3((unsigned)((a.N + PPB - 1) / PPB)), dim3(256), 0, stream, a);
+                e = hipGetLastError();
+            }
+            return e;
+        } else {
+            return hipErrorInvalidValue;
         }
-        if (e == hipSuccess && a.splits > 1) {
-            constexpr int PPB = 256 / (D / 8);
-            ProfScope prof(PROF_DH_MERGE, stream);
-            hipLaunchKernelGGL((dh_merge_kernel<D>), dim3((unsigned)((a.N + PPB - 1) / PPB)), dim3(256), 0, stream, a);
-            e = hipGetLastError();
-        }
-        return e;
-    }
     case TILE_PASS_FDH: {  // the dH pass's shapes: same stationary rows, same splits, same last-round plan
         bool done = false;
         if constexpr (XG_B == 2) {
@@ -2798,7 +2611,7 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
         if constexpr (D > 128) {
             // Blocks of 128 rows, one to a compute unit, where that is the faster way to fill the chip: tiles of a share, and the
             // partial rows of the shares (written and read, at 5 TB/s), which need half the shares.
-            const int cus = resident_blocks(tile_kernel<D, MODE_FDH, BY_B, 4, XG_L, MINB, NBUF_L, 1, false>, 256);
+            const int cus = resident_blocks(tile_kernel<D, MODE_FDH, BY_B, 4, XG_L, MINB, NBUF_L, false>, 256);
             const int64_t xb = (a.N + 127) / 128;
             if (xb > 0 && xb <= cus) {
                 TileArgs w = a;
@@ -2847,11 +2660,11 @@ hipError_t launch_for_d(int pass, TileArgs a, hipStream_t stream)
             if (wide(a.n_cols, false)) return launch_tile_kernel<D, MODE_DE, BY_B, 4, 2, MINB, NBUF_B>(a, a.n_cols, stream);
         }
         if (a.filter_log2 > -INFINITY) {
-            if constexpr (D > 128) return launch_tile_kernel<D, MODE_DE, BY_B, NW_L, 1, MINB, NBUF_B, 1, true>(a, a.n_cols, stream);
+            if constexpr (D > 128) return launch_tile_kernel<D, MODE_DE, BY_B, NW_L, 1, MINB, NBUF_B, true>(a, a.n_cols, stream);
             else return hipErrorInvalidValue;
         }
         if constexpr (D > 128) {
-            const int cus = resident_blocks(tile_kernel<D, MODE_DE, BY_B, 4, XG_L, MINB, NBUF_L, 1, false>, 256);
+            const int cus = resident_blocks(tile_kernel<D, MODE_DE, BY_B, 4, XG_L, MINB, NBUF_L, false>, 256);
             TileArgs w = a;
             const int64_t wide_blocks = plan_tile_grid<MODE_DE>(w, a.n_cols, NW_L * 32, NW_L * 64, cus);
             const int64_t xb = (a.n_cols + 127) / 128, tiles = (a.N + BY_B - 1) / BY_B;
