@@ -1435,7 +1435,8 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     // Forward pass: the same with the sum of exponentials in the place of the verdict, against a reference per position as in FDH.  A
     // tile behind which a sum is beyond 1e30 (its buffer is not loaded into before every wavefront has begun the next one) is taken
     // again with the maximum kept up to date, by the wavefronts that see it: 51,200 positions, 1024 candidates, a late score 90
-    // nats up in every position, us, block started over / tile taken again: d = 64 32.3 / 19.5, d = 128 46.9 / 25.7.
+    // nats up in every position, us, block started over / tile taken again: d = 64 32.3 / 19.3, d = 128
+    // 46.9 / 24.8; the look at the sum costs plain inputs 0.3 % (12,800 positions, 100,000 items, d = 64 232 / 233).
     auto run_stream_scores = [&]() {
         f32x16 sv[2][XG];
         uint4 op[KK];
@@ -1562,13 +1563,13 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             }
             int at = 0;
             int64_t t = t_begin;
-#pragma unroll 1
-            do {
+            int left = __builtin_amdgcn_readfirstlane((int)(t_stop - t_begin));
+            float s0[XG];
+            auto tile_at = [&]() -> bool {  // forward pass: whether a sum has gone beyond 1e30 (or is NaN)
                 const int at_u = __builtin_amdgcn_readfirstlane(at);
                 const uint16_t *const cur = buf_at(at_u), *const next = buf_at((at_u + 1) % NB);
                 constexpr std::false_type no{};
                 constexpr std::true_type yes{};
-                float s0[XG];
 #pragma unroll
                 for (int g = 0; g < XG; ++g) s0[g] = run_s[g];
 #pragma unroll
@@ -1582,26 +1583,32 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                     else if (k % 2 == 0) phase(cur, k, n1, (k + 1) % NSB, n2, (k + 2) % NSB, no, no, t, at_u);
                     else phase(cur, k, n1, (k + 1) % NSB, n2, (k + 2) % NSB, yes, no, t, at_u);
                 }
-                if (MODE == MODE_FWD) {
-                    bool over = false;
-#pragma unroll
-                    for (int g = 0; g < XG; ++g) over |= !(run_s[g] < 1.0e30f);  // or NaN
-                    if (__any(over)) {
-#pragma unroll
-                        for (int g = 0; g < XG; ++g) run_s[g] = s0[g];
-#pragma unroll 1
-                        for (int k = 0; k < NSB; ++k) {
-                            f32x16 again[XG];
-                            gp_t unused;
-                            bool kept;
-                            scores_of(cur, k, again);
-                            softmax(cur, k, again, unused, BY, Full{}, kept);
-                        }
-                    }
-                }
                 at = (at + 1) % NB;
                 ++t;
-            } while (t < t_stop);
+                --left;
+                if (MODE != MODE_FWD) return false;
+                return __any(!(run_s[0] + (XG == 2 ? run_s[XG - 1] : 0.f) < 1.0e30f));
+            };
+#pragma unroll 1
+            do {
+                bool over;
+#pragma unroll 1
+                do over = tile_at();
+                while ((left > 0) & !over);  // one branch a tile
+                if (MODE == MODE_FWD && over) {
+                    const uint16_t *const tile = buf_at(at + NB - 1);
+#pragma unroll
+                    for (int g = 0; g < XG; ++g) run_s[g] = s0[g];
+#pragma unroll 1
+                    for (int k = 0; k < NSB; ++k) {
+                        f32x16 again[XG];
+                        gp_t unused;
+                        bool kept;
+                        scores_of(tile, k, again);
+                        softmax(tile, k, again, unused, BY, Full{}, kept);
+                    }
+                }
+            } while (MODE == MODE_FWD && left > 0);
         }
         if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{});
         wait_vm<0>();     // the loads beyond the range
