@@ -356,11 +356,12 @@ def test_gradient_filtering_of_the_full_catalogue_mode(d, V):
     assert e_dH <= TOL_BF16 and e_dE <= TOL_BF16, (e_dH, e_dE)
 
 
-@pytest.mark.parametrize("N,V", [(7700, 77_003), (7700, 3001), (700, 77_003)])
+@pytest.mark.parametrize("N,V", [(7700, 77_003), (7700, 3001), (7700, 4099), (700, 77_003)])
 def test_gradient_filtering_with_two_row_groups(N, V):
-    """d = 64: from 7680 positions (dH side) and 76,545 items (dE side) on a wavefront has two groups of stationary rows, each with
-    a verdict of its own.  Few of the positions are valid, which the choice of the kernel does not look at; the threshold as
-    in the test above, among the largest hundredth of the block maxima."""
+    """d = 64, two groups of stationary rows to a wavefront, each with a verdict of its own: on the dE side from 76,545 items on, on the
+    dH side where blocks of 256 positions times shares of the items (one for every two tiles of 128, 16 at most) come to 480.
+    Both; neither (31 x 12); dH alone (31 x 16); dE alone.  Few of the positions are valid, which the choice of the kernel does
+    not look at; the threshold as in the test above, among the largest hundredth of the block maxima."""
     import paper_2509_09682_amd as P
     from workloads import bf16_bits_from_f32, f32_from_bf16_bits
 
