@@ -1192,8 +1192,10 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         // FOLD (dE with two row groups, where the registers of the gradients are short and their products an eighth of the
         // vector instructions): g 2^x = +-2^(x + log2 |g|).  A wavefront folds the gradients of a tile into the offsets once,
         // in LDS of its own.  From the first tile with a negative gradient on, signs are put on the packed coefficients, two at a time.
+        // A rounding more in the exponent: a coefficient is off by 6.4e-7 to 1.3e-6 of itself, rms, with gradients N(0,1) to 1e-6,
+        // instead of 5.2e-7; rounded to bf16 it is off by 1.66e-3 either way.
         // An exponential ends at 2^-126, the product of gradient and probability at the 2^-133 of a bf16 coefficient: a range with a
-        // gradient below 2^-80, where probabilities of 2^-46 and above would be lost, is repeated by run_plain, which multiplies.
+        // gradient below 2^-80, where probabilities of 2^-46 and above would be lost, is done over with PLAIN, which multiplies.
         constexpr bool FOLD = G::FOLD;
         uint32_t smallest = 0u;  // bits of log2 |g|, for negative ones the larger the smaller; those of -inf for 0 and what the logarithm takes for 0
         bool negative = false;  // wave-uniform, and the same in every wavefront of the block
@@ -2454,9 +2456,9 @@ inline int de_split_cap(const TileArgs &a)
     // time of the pass (4 n_cols d N flop at ~1 PFLOP/s against ~300 G atomics/s) => splits <= 3e-4 N
     int cap = (int)(a.N * 5e-4) < 8 ? 8 : (int)(a.N * 5e-4);
     if (a.d > 128) {
-        // hidden size 256, one block of 256 candidates per compute unit: a short list gives few blocks, and the cap
-        // above left the chip idle.  Tile time tiles / s (1 us a tile in blocks of 128 candidates) plus atomics
-        // s n_cols d / 327 G/s is least at the root (511 candidates, 24,576 positions: 16 splits 93 us)
+        // hidden size 256, one block per compute unit: a short list gives few blocks, and the cap above left the chip idle.
+        // Tile time tiles / s (1 us a tile in blocks of 128 candidates) plus atomics s n_cols d / 327 G/s is least at the root.
+        // 511 candidates, 24,576 positions, us: 8 shares 93, 16 57, 24 50, 32 50, 43 (the root) 53, 50 57, 64 63.
         const double best = sqrt((double)(a.N / 32) * 1000.0 * 327.0 / ((double)a.n_cols * a.d));
         if ((double)cap < best) cap = (int)best;
     }

@@ -84,8 +84,9 @@ def test_fused_last_round_of_position_blocks_splits_the_candidates(batch, pad):
 
 @pytest.mark.parametrize("d,mode", [(64, NEG_FULL), (128, NEG_SHARED), (256, NEG_FULL)])
 def test_fused_scores_that_outgrow_the_reference_by_hundreds_of_nats(d, mode):
-    """The fast form takes its reference from the first 32 candidates; here the scores climb (or fall) by several
-    hundred nats along the candidate index, so blocks overflow and start over in the exact form."""
+    """The pass takes its reference from the first 32 candidates of a share; here the scores climb (or fall) by several hundred
+    nats along the candidate index, and the shares, of two tiles or so, meet again in the merge (within one the scores climb by
+    51 nats at most; blocks that start over: test_gpu_splits.py)."""
     from workloads import bf16_bits_from_f32
 
     V, K = 3000, 1500

@@ -629,9 +629,9 @@ def test_last_round_of_position_blocks_splits_the_candidates(batch, pad):
 
 @pytest.mark.parametrize("d,mode", [(64, NEG_FULL), (128, NEG_SHARED), (256, NEG_FULL)])
 def test_scores_that_outgrow_the_running_maximum_by_hundreds_of_nats(d, mode):
-    """The forward pass sums a tile's exponentials against the maximum it knew when the tile began and repeats the tile
-    exactly when that overflowed.  Here the scores of a position climb (or fall) by several hundred nats along the
-    candidate index, far beyond the range of a float exponential relative to a stale maximum."""
+    """The forward pass sums exponentials against the largest of the first 32 scores of a share.  Here the scores of a position climb
+    (or fall) by several hundred nats along the candidate index, far beyond the range of a float exponential; within a share, of
+    two tiles or so, by 51 nats at most (tiles that are taken again: test_gpu_splits.py)."""
     from workloads import bf16_bits_from_f32
 
     V, K = 3000, 1500
