@@ -955,11 +955,13 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     // gives the same result as long as nothing leaves the float range, so the pipelines take m = the largest score
     // among the first 32 candidates of the block's range and never look at a maximum again (no maximum chain, no
     // rescaling, no branch).  Scores that outgrow that reference by more than about 69 nats push a sum beyond 1e30, where it stays:
-    // at the end of the range a wavefront that sees one raises a flag in LDS, and the block starts over.  Up to 128 columns in
-    // the exact form: the largest score of every tile is taken first (a score product of its own), sums and accumulators are
-    // rescaled when it grows, and no exponent is ever positive; at 256 against the largest score of the whole range.  The first attempt
-    // is spent by then: in every position the last candidate 90 nats up, us a call, plain / starting over: 51,200 positions, 1024
-    // candidates, d = 64 25 / 49, d = 128 41 / 86; 65,536 positions, 8192 candidates, d = 256 436 / 1138.
+    // a wavefront that sees one, behind a few tiles of the range and at its end (watched_tiles), raises a flag in LDS, and the block
+    // starts over.  Up to 128 columns in the exact form: the largest score of every tile is taken first (a score product of its
+    // own), sums and accumulators are rescaled when it grows, and no exponent is ever positive; at 256 against the largest score of
+    // the tiles seen, then of the whole range.  A candidate 90 nats above the rest in every position, the 201st / the last but one, us a
+    // step, looked for at the end alone and as here: 204,800 positions, 4096 candidates, d = 256 2278 / 2299 and 1444 / 2304;
+    // 204,800 positions, 10,000 items, d = 64 1570 / 1612 and 1159 / 1598; plain inputs 1232 and 1229, 620 and 620 (12,800
+    // positions, 100,000 items).
     int *const over_flag = reinterpret_cast<int *>(epi_own);
     auto scores_of = [&](const uint16_t *tile, int sb, f32x16 (&sv)[XG]) {
 #pragma unroll
@@ -1023,7 +1025,35 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         bool over = false;
 #pragma unroll
         for (int g = 0; g < XG; ++g) over |= !(run_s[g] < 1.0e30f);  // or NaN
-        if (__any(over) && lane == 0) over_flag[0] = 1;
+        if (__any(over)) {
+            if (lane == 0) over_flag[0] = 1;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // ahead of the next barrier
+        }
+    };
+    // The full tiles of an attempt, one() each.  Behind tile 2, 7, 16, 33, ... a wavefront whose sum is too large raises the flag, and
+    // behind the tile after that all of them look: the barrier of that tile lies between, and another one before the flag can be
+    // raised again.  Spans that double: a start-over costs at most about as much again as there was to see, and 128 tiles
+    // are looked at six times.  Returns whether the block starts over.
+    auto watched_tiles = [&](bool watch, auto one) -> bool {
+        int left = __builtin_amdgcn_readfirstlane((int)(t_stop - t_begin)), span = watch ? 2 : left;
+        bool look = false, over = false;
+#pragma unroll 1
+        do {
+            int n = look ? 1 : span;
+            if (n > left) n = left;
+            left -= n;
+#pragma unroll 1
+            do one();
+            while (--n > 0);
+            if (look) {
+                over = __builtin_amdgcn_readfirstlane(over_flag[0]) != 0;
+                span *= 2;
+            } else {
+                note_overflow();
+            }
+            look = !look;
+        } while ((left > 0) & !over);
+        return over;
     };
     // The range tile by tile: prologue loads, the ring of steps, the short last tile.  Hidden size 256 forward alone and with gradient
     // filtering; elsewhere what the pipelines below hand over.  work(tile number, tile, Full or Ragged).
@@ -1356,6 +1386,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
 #pragma unroll
             for (int g = 0; g < XG; ++g) run_m[g] = tmax[g];
         }
+        bool over = false;
         if (t_begin < t_stop) {
             // first scores; the sub-tile before the first one has coefficients of zero
 #pragma unroll
@@ -1383,7 +1414,13 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             int at = 0;
             int64_t t = t_begin;
             // one copy of the tile and one way out: the state carried round is most of the register file
-            if (!negative) {
+            if constexpr (WATCH) {
+                over = watched_tiles(true, [&]() __attribute__((always_inline)) {
+                    step(t, __builtin_amdgcn_readfirstlane(at), std::false_type{});
+                    at = (at + 1) % 4;
+                    ++t;
+                });
+            } else if (!negative) {
 #pragma unroll 1
                 do {
                     step(t, __builtin_amdgcn_readfirstlane(at), std::false_type{});
@@ -1408,7 +1445,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                 for (int g = 0; g < XG; ++g) join_sums(g);
             }
         }
-        if (tail_ragged) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{});
+        if (tail_ragged && !over) process_tile(t_stop, buf_at((int)((t_stop - t_begin) % NB)), Ragged{});
         if (WATCH) note_overflow();  // a sum that was beyond the limit once stays there
         wait_vm<0>();     // the loads beyond the range
         __syncthreads();  // the tile buffers are free, the flag is in place
@@ -1801,12 +1838,16 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             }
         };
         auto rows_of = [&](int64_t t) -> int { return (n_y - t * BY < BY) ? (int)(n_y - t * BY) : BY; };
-        // FDH: an attempt takes the largest of the first 32 scores as its reference; if a sum leaves the float range, a second one
-        // first goes over the range for the largest of all.
+        // FDH: the first attempt takes the largest of the first 32 scores as its reference; if a sum leaves the float range, the next
+        // one first goes over the tiles seen so far for the largest of them, and one that fails again (or whose first was noticed at
+        // the end) over the whole range.
+        int64_t seen = t_begin;  // the reference of a further attempt is the largest score ahead of this tile
         auto attempt = [&](auto second_tag) __attribute__((always_inline)) -> bool {
             constexpr bool SECOND = decltype(second_tag)::value;
-            // visible behind the barrier that follows the first loads; left alone by the second attempt, which a wavefront may begin
-            // before the others have read it
+            const int64_t upto = seen;
+            const bool last = SECOND && upto >= t_end;  // nothing can outgrow the reference any more (NaN stays what it is)
+            // visible behind the barrier that follows the first loads; a further attempt, which a wavefront may begin before the others
+            // have read the flag, clears it behind its first pass
             if (WATCH && !SECOND && tid == 0) over_flag[0] = 0;
 #pragma unroll
             for (int g = 0; g < XG; ++g) {
@@ -1832,7 +1873,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                     raise_to_max_of(lds0, rows_of(t_begin));
                 } else {
 #pragma unroll 1
-                    for (int64_t t = t_begin; t < t_end; ++t) {
+                    for (int64_t t = t_begin; t < upto; ++t) {
                         const int at = (int)((t - t_begin) % NB);
                         raise_to_max_of(buffer(at), rows_of(t));
                         uint32_t rows[LPW];
@@ -1847,24 +1888,35 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                     }
                     wait_vm<0>();
                     __syncthreads();
+                    if (tid == 0) over_flag[0] = 0;
                     start_loads();
                     first_landed();
                 }
             }
+            bool over = false;
+            seen = t_end;
             if (t_begin < t_stop) {
 #pragma unroll
                 for (int i = 0; i < R; ++i) ring[i] = read_op(i, lds0);
                 int at = 0;
                 int64_t t = t_begin;
-#pragma unroll 1
-                do {
+                auto one = [&]() __attribute__((always_inline)) {
                     tile(t, __builtin_amdgcn_readfirstlane(at));
                     at = (at + 1) % NB;
                     ++t;
-                } while (t < t_stop);
+                };
+                if constexpr (WATCH) {
+                    over = watched_tiles(!last, one);
+                    // not where the range is through: there a wavefront may have looked behind another's last word
+                    if (!SECOND && over && t < t_stop) seen = t;
+                } else {
+#pragma unroll 1
+                    do one();
+                    while (t < t_stop);
+                }
                 all_second(buffer((at + NB - 1) % NB));
             }
-            if (tail_ragged) {  // the short last tile, by itself
+            if (tail_ragged && !over) {  // the short last tile, by itself
                 const uint32_t b = buffer((int)((t_stop - t_begin) % NB));
                 all_scores(b);
 #pragma unroll
@@ -1882,21 +1934,23 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
             if (WATCH) {
 #pragma unroll
                 for (int g = 0; g < XG; ++g) join_sums(g);
-                if (!SECOND) note_overflow();  // a sum of exponentials that was beyond the limit once stays there
+                note_overflow();  // a sum of exponentials that was beyond the limit once stays there
             }
             settle();
             wait_vm<0>();     // the loads beyond the range
             __syncthreads();  // the tile buffers are free, the flag is in place
-            return WATCH && !SECOND && __builtin_amdgcn_readfirstlane(over_flag[0]) != 0;
+            return WATCH && !last && __builtin_amdgcn_readfirstlane(over_flag[0]) != 0;
         };
         if (attempt(std::false_type{})) {
             if constexpr (WATCH) {
+#pragma unroll 1
+                do {
 #pragma unroll
-                for (int g = 0; g < XG; ++g) {
-                    run_m[g] = -INFINITY;
-                    reload_x(g);
-                }
-                attempt(std::true_type{});
+                    for (int g = 0; g < XG; ++g) {
+                        run_m[g] = -INFINITY;
+                        reload_x(g);
+                    }
+                } while (attempt(std::true_type{}));
             }
         }
     };
