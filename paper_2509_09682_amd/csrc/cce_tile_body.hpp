@@ -1225,17 +1225,19 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         // A rounding more in the exponent: a coefficient is off by 6.4e-7 to 1.3e-6 of itself, rms, with gradients N(0,1) to 1e-6,
         // instead of 5.2e-7; rounded to bf16 it is off by 1.66e-3 either way.
         // An exponential ends at 2^-126, the product of gradient and probability at the 2^-133 of a bf16 coefficient: a range with a
-        // gradient below 2^-80, where probabilities of 2^-46 and above would be lost, is done over with PLAIN, which multiplies.
+        // gradient below 2^-80, where probabilities of 2^-46 and above would be lost, is left when that is folded, and done over with PLAIN,
+        // which multiplies.
         constexpr bool FOLD = G::FOLD;
-        uint32_t smallest = 0u;  // bits of log2 |g|, for negative ones the larger the smaller; those of -inf for 0 and what the logarithm takes for 0
-        bool negative = false;  // wave-uniform, and the same in every wavefront of the block
+        bool negative = false, tiny = false;  // wave-uniform, and the same in every wavefront of the block
         float *const folded = epi_own + wave * G::FOLD_FLOATS;
         auto fold_tile = [&](const uint16_t *tile, int parity) {  // the signs of two tiles: those of one are read while the next one is folded
             const float2 c = reinterpret_cast<const float2 *>(tile + OFF_C)[lane];  // rows 2 lane, 2 lane + 1
             const float2 g = reinterpret_cast<const float2 *>(tile + OFF_C)[BY / 2 + lane];
             const float lx = __builtin_amdgcn_logf(fabsf(g.x)), ly = __builtin_amdgcn_logf(fabsf(g.y));
             reinterpret_cast<float2 *>(folded)[lane] = make_float2(c.x + lx, c.y + ly);
-            smallest = max(smallest, max(__float_as_uint(lx), __float_as_uint(ly)));
+            // twice the bits of |g| less two: zero is the largest
+            const uint32_t bx = (__float_as_uint(g.x) << 1) - 2u, by = (__float_as_uint(g.y) << 1) - 2u;
+            tiny |= __any(min(bx, by) < (0x17800000u << 1) - 2u);  // 2^-80
             // in the order a lane of the streaming loop wants them: sub-tile, half, eight words
             const int at = (lane >> 4) * 16 + ((lane >> 1) & 1) * 8 + ((lane >> 2) & 3) * 2 + (lane & 1);
             const uint32_t signs = (__float_as_uint(g.x) >> 31 << 15) | (__float_as_uint(g.y) & 0x80000000u);
@@ -1426,11 +1428,11 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
                     step(t, __builtin_amdgcn_readfirstlane(at), std::false_type{});
                     at = (at + 1) % 4;
                     ++t;
-                } while (t < t_stop && !negative);
+                } while (t < t_stop && !negative && !tiny);
             }
             if constexpr (FOLD) {
 #pragma unroll 1
-                for (; t < t_stop; ++t) {
+                for (; t < t_stop && !tiny; ++t) {
                     step(t, __builtin_amdgcn_readfirstlane(at), std::true_type{});
                     at = (at + 1) % 4;
                 }
@@ -1449,22 +1451,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
         if (WATCH) note_overflow();  // a sum that was beyond the limit once stays there
         wait_vm<0>();     // the loads beyond the range
         __syncthreads();  // the tile buffers are free, the flag is in place
-        if constexpr (FOLD) {
-            if (!__any(smallest > 0xc2a00000u)) return false;  // -80; all wavefronts alike
-            int *const flag = reinterpret_cast<int *>(epi_own);
-            if (tid == 0) flag[0] = 0;
-            __syncthreads();
-            const int64_t y_end = t_end * BY < n_y ? t_end * BY : n_y;
-            bool tiny = false;
-            for (int64_t y = t_begin * BY + tid; y < y_end; y += NW * 64) {
-                const bool direct = GSEP && a.g_separate && !a.g_stream_off;
-                const float g = fabsf(direct ? a.g[ind ? (int64_t)ind[y] : y] : __uint_as_float(a.de_const[a.N + y]));
-                tiny |= g != 0.f && g < 0x1p-80f;
-            }
-            if (__any(tiny) && lane == 0) flag[0] = 1;
-            __syncthreads();
-            return __builtin_amdgcn_readfirstlane(flag[0]) != 0;
-        }
+        if constexpr (FOLD) return tiny;
         return WATCH && __builtin_amdgcn_readfirstlane(over_flag[0]) != 0;
     };
     // ---- Gradient filtering up to d = 128, same ring and loads.  Late in training nearly every block is dropped (on a peaked
