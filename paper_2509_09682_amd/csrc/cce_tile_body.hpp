@@ -1033,7 +1033,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs a, const int64_t block_
     // The full tiles of an attempt, one() each.  Behind tile 2, 7, 16, 33, ... a wavefront whose sum is too large raises the flag, and
     // behind the tile after that all of them look: the barrier of that tile lies between, and another one before the flag can be
     // raised again.  Spans that double: a start-over costs at most about as much again as there was to see, and 128 tiles
-    // are looked at six times.  Returns whether the block starts over.
+    // are looked at five times.  Returns whether the block starts over.
     auto watched_tiles = [&](bool watch, auto one) -> bool {
         int left = __builtin_amdgcn_readfirstlane((int)(t_stop - t_begin)), span = watch ? 2 : left;
         bool look = false, over = false;
